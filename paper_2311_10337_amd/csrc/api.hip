@@ -188,11 +188,12 @@ ce_status stage_write_rows(Bufs &b, const ce_result *out, hipStream_t s) {
 }
 
 // Workspace: a few persistent arrays, then a phase area holding
-//   X  skeleton and Boruvka state (live until the MSF is sorted), at its start
+//   X  skeleton and first Boruvka minima (live until the MSF is sorted), at its start
+//   T  the rest of the Boruvka tree, right behind X (from Boruvka on)
 //   Y  sorted MSF, dendrogram and row placement (live from the MSF sort on), at its end
-// Scratch A (grouping, skeleton, Boruvka) follows X and may overlap Y; scratch
-// M (MSF sort) lies between X and Y; scratch B (dendrogram, condensing) starts
-// at the phase area and overlaps X.
+// Scratch A (grouping, skeleton) follows X, scratch T (Boruvka) follows T; both
+// may overlap Y. Scratch M (MSF sort) lies between T and Y; scratch B
+// (dendrogram, condensing) starts at the phase area and overlaps X and T.
 // nnz >= 0: a hypergraph with nnz memberships (its skeleton has at most nnz rows)
 static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discrete, int64_t nnz) {
   const int64_t slots = nnz >= 0 ? (nnz > 0 ? nnz : 1) : 2 * n;
@@ -210,20 +211,22 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   b.skel_key = ws.alloc<uint64_t>(slots);
   b.skel_tail = ws.alloc<uint32_t>(slots);
   b.skel_tid = ws.alloc<uint32_t>(slots);
-  b.best = ws.alloc<uint64_t>(n);
   b.msf_flag = ws.alloc<uint8_t>(slots);
+  b.best = ws.alloc<uint64_t>(n);
   const size_t xbytes = ws.off - base;
+  ws.alloc<uint64_t>(n);  // best of the tree's inner nodes, right behind
+  b.bpar = ws.alloc<uint32_t>(2 * n);
+  const size_t tbytes = ws.off - base - xbytes;
   Ws y;
   y.alloc<uint64_t>(n);
   y.alloc<uint64_t>(n);
   for (int k = 0; k < 5; k++) y.alloc<uint32_t>(n);
   y.alloc<uint32_t>(G + 1);
   const size_t ybytes = y.off;
-  size_t scr_a = stage_boruvka_scratch(n, slots);
-  size_t x = nnz >= 0 ? stage_hyper_skeleton_scratch(n, nnz) : stage_sort_skeleton_scratch(n);
+  size_t scr_a = nnz >= 0 ? stage_hyper_skeleton_scratch(n, nnz) : stage_sort_skeleton_scratch(n);
+  size_t x = nnz >= 0 ? 0 : stage_causal_skeleton_scratch(n);
   if (x > scr_a) scr_a = x;
-  x = nnz >= 0 ? 0 : stage_causal_skeleton_scratch(n);
-  if (x > scr_a) scr_a = x;
+  const size_t scr_t = stage_boruvka_scratch(n, slots);
   const size_t scr_m = stage_msf_sort_scratch(n);
   size_t scr_b = stage_dendrogram_scratch(n);
   x = stage_graph_rows_scratch(n, G);
@@ -232,7 +235,8 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   if (x > scr_b) scr_b = x;
   auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
   size_t phase = xbytes + al(scr_a);
-  if (xbytes + al(scr_m) + ybytes > phase) phase = xbytes + al(scr_m) + ybytes;
+  if (xbytes + tbytes + al(scr_t) > phase) phase = xbytes + tbytes + al(scr_t);
+  if (xbytes + tbytes + al(scr_m) + ybytes > phase) phase = xbytes + tbytes + al(scr_m) + ybytes;
   if (al(scr_b) + ybytes > phase) phase = al(scr_b) + ybytes;
   ws.off = base + phase - ybytes;
   b.msf_key = ws.alloc<uint64_t>(n);
@@ -246,8 +250,10 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   char *pb = ws.base ? ws.base + base : nullptr;
   b.scratch_a = pb ? pb + xbytes : nullptr;
   b.scratch_a_bytes = phase - xbytes;
-  b.scratch_m = b.scratch_a;
-  b.scratch_m_bytes = phase - xbytes - ybytes;
+  b.scratch_t = pb ? pb + xbytes + tbytes : nullptr;
+  b.scratch_t_bytes = phase - xbytes - tbytes;
+  b.scratch_m = b.scratch_t;
+  b.scratch_m_bytes = phase - xbytes - tbytes - ybytes;
   b.scratch_b = pb;
   b.scratch_b_bytes = phase - ybytes;
 }
@@ -597,9 +603,11 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
     CE_LAUNCH(k_header_trivial, dim3(grid_for(G + 1, B, 1024)), dim3(B), 0, s, b.hdr, G, hout);
     CE_HIP(hipGetLastError());
   } else {
-    Ws wa, wm, wb;
+    Ws wa, wt, wm, wb;
     wa.base = b.scratch_a;
     wa.cap = b.scratch_a_bytes;
+    wt.base = b.scratch_t;
+    wt.cap = b.scratch_t_bytes;
     wm.base = b.scratch_m;
     wm.cap = b.scratch_m_bytes;
     wb.base = b.scratch_b;
@@ -607,7 +615,7 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
     if (hy) CE_TRY(stage_hyper_skeleton(hy->members, hy->offsets, c.t, nnz, b, wa, s));
     else if (c.causal) CE_TRY(stage_causal_skeleton(c.src, c.dst, c.t, b, wa, s));
     else CE_TRY(stage_sort_skeleton(c.src, c.dst, c.t, b, wa, s));
-    CE_TRY(stage_boruvka(b, wa, s));
+    CE_TRY(stage_boruvka(b, wt, s));
     CE_TRY(stage_msf_sort(b, wm, s));
     if (max_dt >= 0) CE_TRY(stage_time_filter(b, max_dt, s));
     CE_TRY(stage_dendrogram(b, wb, s));

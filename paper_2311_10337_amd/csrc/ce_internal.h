@@ -338,6 +338,53 @@ __device__ inline void tile_positions(const bool (&keep)[CT], uint32_t (&pos)[CT
   __syncthreads();  // s_cnt / s_base may be reused by a later call
 }
 
+// List kernels (a pass that compacts a list): workgroups of LBK threads, up to
+// LCT elements per thread and tile, one counter update per tile. All
+// workgroups update one address, which takes about 15 ns each, so the tiles
+// are cut so that a list of up to LBK * LCT * 512 elements has at most 512.
+constexpr int LBK = 512, LCT = 8;
+__device__ inline int list_items(int64_t n) {
+  const int64_t per = (n + (int64_t)LBK * 512 - 1) / ((int64_t)LBK * 512);
+  return per < 1 ? 1 : (per > LCT ? LCT : (int)per);
+}
+// tile_positions for workgroups of LBK threads
+__device__ inline void list_positions(const bool (&keep)[LCT], uint32_t (&pos)[LCT], unsigned long long *counter) {
+  constexpr int W = LBK / 64;
+  static_assert(LCT * W == 64, "one wave scans the (k, wave) counts");
+  __shared__ uint32_t s_cnt[LCT * W];
+  __shared__ uint32_t s_base;
+  const uint32_t lane = wave_lane(), w = threadIdx.x >> 6;
+  uint64_t mask[LCT];
+#pragma unroll
+  for (int k = 0; k < LCT; k++) {
+    mask[k] = __ballot(keep[k]);
+    if (lane == 0) s_cnt[k * W + w] = (uint32_t)__popcll(mask[k]);
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    uint32_t x = s_cnt[threadIdx.x], inc = x;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      uint32_t y = __shfl_up(inc, d, 64);
+      if (threadIdx.x >= (uint32_t)d) inc += y;
+    }
+    uint32_t tot = __shfl(inc, 63, 64);
+    s_cnt[threadIdx.x] = inc - x;
+    if (threadIdx.x == 0) s_base = tot ? (uint32_t)atomicAdd(counter, (unsigned long long)tot) : 0u;
+  }
+  __syncthreads();
+  const uint64_t below = lanes_below(lane);
+#pragma unroll
+  for (int k = 0; k < LCT; k++) pos[k] = s_base + s_cnt[k * W + w] + (uint32_t)__popcll(mask[k] & below);
+  __syncthreads();  // s_cnt / s_base may be reused by a later call
+}
+
+// workgroups of a list kernel over up to n elements (ce_tuning.list_grid counts 128-thread units)
+inline unsigned list_blocks(int64_t n) {
+  const int64_t cap = tuning().list_grid / 4;
+  return grid_for(n, LBK, cap < 1 ? 1 : cap);
+}
+
 __device__ inline void tile_append(const bool (&keep)[CT], const uint32_t (&vals)[CT], uint32_t *out,
                                    unsigned long long *counter) {
   uint32_t pos[CT];
@@ -409,7 +456,9 @@ struct Bufs {
   uint64_t *skel_key = nullptr; // [slots] slot 2h+s: key of the skeleton edge whose head is rank h
   uint32_t *skel_tail = nullptr;// [slots] tail rank of that edge or NONE
   uint32_t *skel_tid = nullptr; // [slots] input id of that tail (flat: the head rank)
-  uint64_t *best = nullptr;     // [n] Boruvka: minimum key leaving each component
+  uint64_t *best = nullptr;     // [2n] Boruvka tree: minimum key leaving each node (the last array of X; the
+                                // second half lies in the tree's own region)
+  uint32_t *bpar = nullptr;     // [2n] Boruvka tree: parent of each node
   uint8_t *msf_flag = nullptr;  // [slots]
   uint64_t *msf_key = nullptr;  // [n] sorted MSF keys
   uint64_t *msf_val = nullptr;  // [n] tail rank | head rank << 32; the head's id is in the key
@@ -417,8 +466,8 @@ struct Bufs {
   // scratch arenas: A for grouping, skeleton and Boruvka (it may overlap the
   // MSF/dendrogram arrays, which are not live yet), M for sorting the MSF, B
   // for the dendrogram and condensing (it overlaps the dead skeleton arrays)
-  char *scratch_a = nullptr, *scratch_m = nullptr, *scratch_b = nullptr;
-  size_t scratch_a_bytes = 0, scratch_m_bytes = 0, scratch_b_bytes = 0;
+  char *scratch_a = nullptr, *scratch_t = nullptr, *scratch_m = nullptr, *scratch_b = nullptr;
+  size_t scratch_a_bytes = 0, scratch_t_bytes = 0, scratch_m_bytes = 0, scratch_b_bytes = 0;
 };
 
 // host pinned staging for small readbacks (per thread)

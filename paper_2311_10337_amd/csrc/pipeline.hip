@@ -194,12 +194,6 @@ __global__ __launch_bounds__(B) void k_skel_keys(uint32_t *skel_tail, const uint
 __global__ __launch_bounds__(B) void k_fill_u64(uint64_t *p, int64_t n, uint64_t v) {
   for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) p[i] = v;
 }
-__global__ __launch_bounds__(B) void k_fill_u8(uint8_t *p, int64_t n, uint8_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) p[i] = v;
-}
-__global__ __launch_bounds__(B) void k_rankof(const uint32_t *perm, int64_t n, uint32_t *rankof) {
-  for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) rankof[perm[r]] = (uint32_t)r;
-}
 
 // slot of the (unique) edge with key k: its head is rank rankof[head id]; of
 // the two slots of that head, the one holding k
@@ -210,50 +204,61 @@ __device__ inline uint32_t slot_of_key(uint64_t k, int idbits, const uint32_t *r
 }
 
 // ---------------------------------------------------------------- Boruvka
-// Round 1 runs on records (best[] was seeded while emitting the skeleton).
-// Each later round runs on a CONTRACTED graph: components carry dense ids
-// 0..C-1 and the live edges are records (key, endpoint ids, slot), so the
-// per-round arrays shrink with C and stay cache resident after round 1.
+// Every component that ever exists is a node: the records are nodes 0..n-1,
+// and each round gives the components it forms the next free ids. best[x] is
+// the minimum key leaving node x, bpar[x] the node of the component x merged
+// into (x itself while it is a component of its own). Together they are the
+// Boruvka tree: at most 2n nodes, parents after children, as deep as there
+// were rounds.
 //
-// Every count that steers the rounds (live edges E, components C, the phase of
-// a filter split) lives in the call's control block, and every round kernel
-// reads it when it starts. The host enqueues a fixed number of rounds, enough
-// for any input of n records (live components at least halve per round); the
-// rounds after the forest is complete find E = 0 and return at once. The last
-// block of a round's final kernel advances the state (a ticket counter tells
-// it that every other block is done).
+// Round 1 runs on records (best[] was seeded while emitting the skeleton).
+// Each later round runs on a contracted graph: live edges are records (key,
+// endpoint nodes, slot), and the nodes of a round are a contiguous range
+// [LO, HI), so its passes shrink with the components.
+//
+// One round is one slot of five kernels:
+//   k_bv_min       minimum key per node over the live edges
+//   k_bv_hook      every edge that is its endpoint's minimum hooks it
+//   k_bv_compress  every node to the root of its hooks; roots get new ids
+//   k_bv_link      bpar of every node = the new id of its root
+//   k_contract     edges between different components, renamed
+// preceded by k_bv_ctl, one workgroup that advances the state (live edges E,
+// the node range, a filter split) from the counters of the slot before it.
+// (With the state advanced by the last workgroup of the contraction, found by
+// a ticket, and one counter update per 256-edge tile, 4096 workgroups queued
+// at two addresses for about 15 ns each: a round of 1e6 edges took 145 us in
+// its contraction alone, now 12. A 1e6-record call went from 7.5 to 4.65 ms, a
+// 2e5-record call from 2.74 to 2.04 ms, 5e7 records from 89.6 to 84.4 ms.)
+// Every kernel reads the state when it starts; the
+// host enqueues a fixed number of slots, and those after the forest is
+// complete return at once.
 
 // Boruvka state, words H_BV + k of the control block
 enum : int {
-  BV_E = 0,        // live edges of the current list
-  BV_C = 1,        // components (ids 0..C-1)
-  BV_PHASE = 2,    // 0 plain rounds, 1 light rounds of a filter split
-  BV_IN = 3,       // the list: edge buffer 0 or 1, or 2 = the skeleton rows themselves
-  BV_OFF = 4,      // its first entry in that buffer
-  BV_HB = 5,       // buffer holding the heavy edges of a split at its back
-  BV_EH = 6,       // heavy edges
-  BV_SPLIT = 7,    // this round starts with a split at BV_PIVOT
-  BV_PIVOT = 8,
-  BV_FIRSTL = 9,   // first light round (the root map starts as the identity)
-  BV_HEAVY = 10,   // the light edges are gone: contract the heavy ones next
-  BV_SEEDED = 11,  // the minima of this round were seeded while the skeleton was emitted
-  BV_SPLITDONE = 12,  // at most one split per call (it bounds the rounds)
-  // gates: the live counts of the kernels of one phase, 0 while they have nothing to do
-  BV_EN = 13, BV_CN = 14, BV_EL = 15, BV_CL = 16, BV_CG = 17, BV_EHG = 18,
-  BV_TICKET = 19,  // last-block ticket, then two list counters
-  BV_CNT1 = 20, BV_CNT2 = 21,
+  BV_ACT = 0,      // what this slot does: 0 nothing, 1 a round, 2 a filter split, 3 the heavy edges of the split
+  BV_E = 1,        // live edges of the current list
+  BV_IN = 2,       // the list: edge buffer 0 or 1, or 2 = the skeleton rows themselves
+  BV_OFF = 3,      // its first entry in that buffer
+  BV_LO = 4,       // nodes of this round: [LO, HI)
+  BV_HI = 5,
+  BV_NB = 6,       // next free node id (a counter while a round runs)
+  BV_MARK = 7,     // the range holds merged nodes too (marked NONE in rootc)
+  BV_LIGHT = 8,    // rounds run on the light edges of a split
+  BV_SPLITDONE = 9,  // at most one split per call (it bounds the slots)
+  BV_PIVOT = 10,
+  BV_SLO = 11,     // LO at the split
+  BV_HB = 12,      // buffer holding the heavy edges at its back
+  BV_EH = 13,      // heavy edges
+  BV_CNT1 = 14, BV_CNT2 = 15,  // list counters
   BV_WORDS = 24
 };
+enum : int { ACT_NONE = 0, ACT_ROUND = 1, ACT_SPLIT = 2, ACT_HEAVY = 3 };
 
 struct EdgeLists {
   uint64_t *key[3];
   uint32_t *u[3], *v[3], *s[3];  // s[2] == nullptr: the slot of a skeleton row is its index
   int64_t cap;                   // entries of buffers 0 and 1
 };
-
-__device__ inline uint64_t ld_coherent(const uint64_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // the live list of the current round
 struct Live {
@@ -271,37 +276,31 @@ __device__ inline int out_buffer(const uint64_t *bv) {
   return in == 2 ? 0 : 1 - in;
 }
 
-// gates from the state (run by the block that last changed it)
-__device__ inline void bv_publish(uint64_t *bv) {
-  const bool light = bv[BV_PHASE] == 1, live = bv[BV_E] > 0;
-  bv[BV_EN] = light ? 0 : bv[BV_E];
-  bv[BV_CN] = (!light && live) ? bv[BV_C] : 0;
-  bv[BV_EL] = light ? bv[BV_E] : 0;
-  bv[BV_CL] = (light && live) ? bv[BV_C] : 0;
-  bv[BV_CG] = live ? bv[BV_C] : 0;
-  bv[BV_EHG] = bv[BV_HEAVY] ? bv[BV_EH] : 0;
-}
-
-// true in exactly one block, the last to arrive; all blocks must call it
-__device__ inline bool last_block(uint64_t *ticket) {
-  __shared__ bool last;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    const unsigned long long t = atomicAdd((unsigned long long *)ticket, 1ull);
-    last = t == (unsigned long long)(gridDim.x - 1);
+// Before the first round: the state, record ranks by id, no forest edge yet.
+// Flat skeletons start as the live list (rows, counted on the device) of a
+// round over the records, so their hooks start empty.
+__global__ __launch_bounds__(B) void k_bv_start(const uint32_t *perm, int64_t n, int64_t slots, bool flat,
+                                                const uint64_t *rows, uint32_t *rankof, uint8_t *msf_flag,
+                                                uint32_t *bpar, uint64_t *bv) {
+  const int64_t step = (int64_t)gridDim.x * B, i0 = (int64_t)blockIdx.x * B + threadIdx.x;
+  for (int64_t r = i0; r < n; r += step) {
+    rankof[perm[r]] = (uint32_t)r;
+    if (flat) bpar[r] = (uint32_t)r;
   }
-  __syncthreads();
-  if (last) __threadfence();
-  return last;
+  for (int64_t e = i0; e < (slots + 3) / 4; e += step) ((uint32_t *)msf_flag)[e] = 0u;  // regions are 256-byte aligned
+  if (blockIdx.x == 0 && threadIdx.x < BV_WORDS) {
+    const int k = threadIdx.x;
+    bv[k] = k == BV_ACT ? ACT_ROUND : k == BV_E ? (flat ? *rows : 0) : k == BV_IN ? 2 : (k == BV_HI || k == BV_NB)
+                                                                                          ? (uint64_t)n : 0;
+  }
 }
 
 // first round, on records: hook each record onto the record across its
 // minimum edge; of a mutual pair the smaller id stays; the hooking edge joins
-// the forest. flags[c] = 1 for roots that have an edge (they get dense ids).
+// the forest.
 __global__ __launch_bounds__(B) void k_bv_hook_first(int64_t n, const uint64_t *best, const uint64_t *skel_key,
                                                      const uint32_t *skel_tail, const uint32_t *rankof, int idbits,
-                                                     uint32_t *hook, uint8_t *msf_flag, uint32_t *flags) {
+                                                     uint32_t *bpar, uint8_t *msf_flag) {
   for (int64_t c = (int64_t)blockIdx.x * B + threadIdx.x; c < n; c += (int64_t)gridDim.x * B) {
     uint32_t to = (uint32_t)c;
     const uint64_t bk = best[c];
@@ -318,183 +317,215 @@ __global__ __launch_bounds__(B) void k_bv_hook_first(int64_t n, const uint64_t *
         msf_flag[e] = 1;
       }
     }
-    hook[c] = to;
-    flags[c] = (to == (uint32_t)c && bk != NONE64) ? 1u : 0u;
+    bpar[c] = to;
   }
 }
 
-// later rounds, on the contracted graph
-__global__ __launch_bounds__(B) void k_bv_hook(EdgeLists L, const uint64_t *bv, const uint64_t *best,
-                                               const uint32_t *bidx, uint32_t *hook, uint8_t *msf_flag,
-                                               uint32_t *flags) {
+// Later rounds, per edge: an edge that is its endpoint's minimum hooks it.
+// Copies of one line-graph edge carry equal keys (hypergraphs): the
+// compare-and-swap lets one of them in.
+__device__ inline bool bv_hook_edge(uint64_t k, uint32_t u, uint32_t v, const uint64_t *best, uint32_t *bpar) {
+  const bool pu = best[u] == k, pv = best[v] == k;
+  bool won = false;
+  if (pu && !(pv && u < v)) won |= atomicCAS(&bpar[u], u, v) == u;
+  if (pv && !(pu && v < u)) won |= atomicCAS(&bpar[v], v, u) == v;
+  return won;
+}
+__global__ __launch_bounds__(B) void k_bv_hook(EdgeLists L, const uint64_t *bv, const uint64_t *best, uint32_t *bpar,
+                                               uint8_t *msf_flag) {
+  if (bv[BV_ACT] != ACT_ROUND) return;
   const Live lv = live_list(L, bv);
-  const int64_t C = (int64_t)bv[BV_C];
-  if (lv.E == 0) return;
-  for (int64_t c = (int64_t)blockIdx.x * B + threadIdx.x; c < C; c += (int64_t)gridDim.x * B) {
-    uint32_t to = (uint32_t)c;
-    const uint64_t bk = best[c];
-    if (bk != NONE64) {
-      const uint32_t i = bidx[c];
-      const uint32_t o = lv.u[i] == (uint32_t)c ? lv.v[i] : lv.u[i];
-      if (!(best[o] == bk && (uint32_t)c < o)) {
-        to = o;
-        msf_flag[lv.s ? lv.s[i] : i] = 1;
-      }
-    }
-    hook[c] = to;
-    flags[c] = (to == (uint32_t)c && bk != NONE64) ? 1u : 0u;
-  }
+  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < lv.E; i += (int64_t)gridDim.x * B)
+    if (bv_hook_edge(lv.key[i], lv.u[i], lv.v[i], best, bpar)) msf_flag[lv.s ? lv.s[i] : i] = 1;
 }
 
-// Every component to its final root, in two passes. The first walks from
-// every component and halves the path it follows (each store moves a link to
-// a grandparent), so long hook chains shrink as in pointer jumping. Walks only
-// ever store ancestors, so a stale link seen by another walk is still an
-// ancestor and every walk ends at the root (hooks form a forest: keys are
-// unique, and of a mutual pair only one side hooks). But a halving store can
-// land after the owner of that entry stored its root, and put a lower
-// ancestor back; so the second pass walks again, read only, and each
-// component stores its own root alone. A walk longer than any forest allows
-// marks the call failed and stops.
+// The root of node c's hooks. The walk halves the path it follows (each store
+// moves a link to a grandparent), so long hook chains shrink as in pointer
+// jumping; a stale link is still an ancestor, so every walk ends at the root
+// (hooks form a forest: keys are unique, and of a mutual pair only one side
+// hooks). The root goes to an array of its own, which no halving store
+// touches. A walk longer than any forest allows marks the call failed.
 constexpr uint32_t MAX_WALK = 1u << 26;
-__global__ __launch_bounds__(B) void k_bv_compress(Cnt C, uint32_t *hook, uint64_t *hdr) {
-  const int64_t nc = C.get();
-  for (int64_t c = (int64_t)blockIdx.x * B + threadIdx.x; c < nc; c += (int64_t)gridDim.x * B) {
-    uint32_t x = hook[c];
-    if (x == (uint32_t)c) continue;
-    for (uint32_t steps = 0;; steps++) {
-      const uint32_t p = __hip_atomic_load(&hook[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (p == x) break;
-      const uint32_t gp = __hip_atomic_load(&hook[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (gp != p) __hip_atomic_store(&hook[x], gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      x = gp;
-      if (steps > MAX_WALK) {
-        atomicOr((unsigned long long *)&hdr[H_STATUS], 16ull);
-        break;
-      }
+__device__ inline uint32_t bv_root(uint32_t *bpar, uint32_t c, uint64_t *hdr) {
+  uint32_t x = __hip_atomic_load(&bpar[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (x == c) return c;
+  for (uint32_t steps = 0;; steps++) {
+    const uint32_t p = __hip_atomic_load(&bpar[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (p == x) return x;
+    const uint32_t gp = __hip_atomic_load(&bpar[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (gp != p) __hip_atomic_store(&bpar[x], gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    x = gp;
+    if (steps > MAX_WALK) {
+      atomicOr((unsigned long long *)&hdr[H_STATUS], 16ull);
+      return x;
     }
   }
 }
-__global__ __launch_bounds__(B) void k_bv_roots(Cnt C, uint32_t *hook, uint64_t *hdr) {
-  const int64_t nc = C.get();
-  for (int64_t c = (int64_t)blockIdx.x * B + threadIdx.x; c < nc; c += (int64_t)gridDim.x * B) {
-    uint32_t x = __hip_atomic_load(&hook[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (x == (uint32_t)c) continue;
-    for (uint32_t steps = 0;; steps++) {
-      const uint32_t p = __hip_atomic_load(&hook[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (p == x) break;
-      x = p;
-      if (steps > MAX_WALK) {
-        atomicOr((unsigned long long *)&hdr[H_STATUS], 16ull);
-        break;
-      }
-    }
-    __hip_atomic_store(&hook[c], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
 
-// dense id of every component's final root (contraction reads one id per
-// endpoint); the minima of the next round start empty
-__global__ __launch_bounds__(B) void k_final_ids(Cnt C, const uint32_t *hook, const uint32_t *newid, uint32_t *fin,
-                                                 uint64_t *best) {
-  const int64_t nc = C.get();
-  const int64_t cn = nc > 0 ? (int64_t)newid[nc] : 0;
-  for (int64_t c = (int64_t)blockIdx.x * B + threadIdx.x; c < nc; c += (int64_t)gridDim.x * B) {
-    fin[c] = newid[hook[c]];
-    if (c < cn) best[c] = NONE64;
+// rootc[c - LO] = the root of node c, or for a root the new node's id; NONE for
+// a node without edges and (after the heavy edges of a split, when the range
+// holds nodes merged in earlier rounds) for a merged one.
+__global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_t *best, uint32_t *bpar,
+                                                     uint32_t *rootc, uint64_t *hdr) {
+  const uint64_t act = bv[BV_ACT];
+  if (act == ACT_HEAVY) {  // mark the range of the next round: NONE for merged nodes
+    const int64_t lo = (int64_t)bv[BV_SLO], hi = (int64_t)bv[BV_NB];
+    for (int64_t c = lo + (int64_t)blockIdx.x * LBK + threadIdx.x; c < hi; c += (int64_t)gridDim.x * LBK)
+      rootc[c - lo] = bpar[c] == (uint32_t)c ? 0u : NONE32;
+    return;
   }
-}
-
-// first contraction: skeleton slots between different final roots, endpoints renamed to dense ids
-__global__ __launch_bounds__(B) void k_contract_first(int64_t n, const uint64_t *skel_key, const uint32_t *skel_tail,
-                                                      const uint32_t *fin, const uint32_t *newid, EdgeLists L,
-                                                      uint64_t *bv) {
-  const int64_t n2 = 2 * n;
-  unsigned long long *cnt = (unsigned long long *)&bv[BV_CNT1];
-  const int ct = tile_items(n2);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < n2; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t pos[CT], nu[CT], nv[CT];
-    uint64_t kk[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(n2, tile, B * ct);
+  if (act != ACT_ROUND) return;
+  const int64_t lo = (int64_t)bv[BV_LO], nc = (int64_t)bv[BV_HI] - lo;
+  const bool marked = bv[BV_MARK] != 0;
+  const int ct = list_items(nc);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nc; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nc, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t e = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
       keep[k] = false;
-      kk[k] = NONE64;
-      nu[k] = nv[k] = 0;
-      if (e >= end) continue;
-      kk[k] = skel_key[e];
-      if (kk[k] == NONE64) continue;
-      const uint32_t fu = fin[skel_tail[e]], fv = fin[e >> 1];
-      if (fu == fv) continue;
-      keep[k] = true;
-      nu[k] = fu;
-      nv[k] = fv;
+      if (i >= end) continue;
+      const uint32_t c = (uint32_t)(lo + i);
+      if (marked && rootc[i] == NONE32) continue;
+      uint32_t r = NONE32;
+      if (best[c] != NONE64) {
+        r = bv_root(bpar, c, hdr);
+        keep[k] = r == c;
+      }
+      if (!keep[k]) rootc[i] = r;
     }
-    tile_positions(keep, pos, cnt);
+    list_positions(keep, pos, (unsigned long long *)&bv[BV_NB]);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) rootc[base + (int64_t)k * LBK] = pos[k];
+  }
+}
+
+// node c -> the new node of its component; new nodes start without a minimum
+__device__ inline void bv_link(uint32_t c, uint32_t rc, int64_t lo, const uint32_t *rootc, uint32_t *bpar) {
+  if (rc == NONE32) return;
+  bpar[c] = bpar[c] == c ? rc : rootc[rc - lo];
+}
+__global__ __launch_bounds__(B) void k_bv_link(const uint64_t *bv, const uint32_t *rootc, uint32_t *bpar,
+                                               uint64_t *best) {
+  if (bv[BV_ACT] != ACT_ROUND) return;
+  const int64_t lo = (int64_t)bv[BV_LO], hi = (int64_t)bv[BV_HI], nb = (int64_t)bv[BV_NB];
+  const int64_t step = (int64_t)gridDim.x * B, i0 = (int64_t)blockIdx.x * B + threadIdx.x;
+  for (int64_t c = lo + i0; c < hi; c += step) bv_link((uint32_t)c, rootc[c - lo], lo, rootc, bpar);
+  for (int64_t x = hi + i0; x < nb; x += step) {
+    best[x] = NONE64;
+    bpar[x] = (uint32_t)x;
+  }
+}
+
+// first contraction: skeleton slots between different components, endpoints renamed to nodes
+__global__ __launch_bounds__(LBK) void k_contract_first(int64_t n, const uint64_t *skel_key, const uint32_t *skel_tail,
+                                                        const uint32_t *bpar, EdgeLists L, uint64_t *bv) {
+  const int64_t n2 = 2 * n;
+  const int ct = list_items(n2);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < n2; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT], nu[LCT], nv[LCT];
+    uint64_t kk[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(n2, tile, LBK * ct);
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      const int64_t e = base + (int64_t)k * LBK;
+      keep[k] = false;
+      kk[k] = e < end ? skel_key[e] : NONE64;
+      nu[k] = nv[k] = 0;
+      if (kk[k] == NONE64) continue;
+      nu[k] = bpar[skel_tail[e]];
+      nv[k] = bpar[e >> 1];
+      keep[k] = nu[k] != nv[k];
+    }
+    list_positions(keep, pos, (unsigned long long *)&bv[BV_CNT1]);
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
       if (!keep[k]) continue;
       const uint32_t p = pos[k];
       L.key[0][p] = kk[k];
       L.u[0][p] = nu[k];
       L.v[0][p] = nv[k];
-      L.s[0][p] = (uint32_t)(base + (int64_t)k * B);
-    }
-  }
-  if (last_block(&bv[BV_TICKET])) {
-    if (threadIdx.x == 0) {
-      bv[BV_E] = ld_coherent(&bv[BV_CNT1]);
-      bv[BV_C] = newid[n];
-      bv[BV_IN] = 0;
-      bv[BV_OFF] = 0;
-      bv[BV_PHASE] = 0;
-      bv[BV_SEEDED] = 0;
-      bv[BV_CNT1] = 0;
-      bv[BV_TICKET] = 0;
-      bv_publish(bv);
+      L.s[0][p] = (uint32_t)(base + (int64_t)k * LBK);
     }
   }
 }
 
-// Contraction of the live list (gated count E) with the map f: edges between
-// different f-images go to the front of the output buffer, renamed. The last
-// block advances the state: `mode` 0 = plain round (new ids from the scan),
-// 1 = light round (ids stay), 2 = the heavy edges after the light phase.
-__global__ __launch_bounds__(B) void k_contract(EdgeLists L, uint64_t *bv, const uint64_t *gate,
-                                                const uint32_t *fmap, const uint32_t *newid, int mode) {
-  const int64_t E = (int64_t)*gate;
-  if (E == 0) return;  // uniform: every block returns, and the state does not change
-  const int in = mode == 2 ? (int)bv[BV_HB] : (int)bv[BV_IN];
-  const int64_t off = mode == 2 ? L.cap - (int64_t)bv[BV_EH] : (int64_t)bv[BV_OFF];
-  const int ob = mode == 2 ? 1 - in : out_buffer(bv);
+// A round's contraction: edges between different components go to the front
+// of the output buffer, renamed. The heavy edges of a split, parked since,
+// climb to their current components. A split: the live edges with key below
+// the pivot go to the front of the output buffer, the others to its back,
+// counted down from cap (light and heavy together are E <= cap entries, so
+// later contractions of the light part, which only shrink it, never reach the
+// heavy part).
+__global__ __launch_bounds__(LBK) void k_contract(EdgeLists L, uint64_t *bv, const uint32_t *bpar) {
+  const uint64_t act = bv[BV_ACT];
+  if (act == ACT_NONE) return;
+  const bool heavy = act == ACT_HEAVY;
+  const int in = heavy ? (int)bv[BV_HB] : (int)bv[BV_IN], ob = heavy ? 1 - in : out_buffer(bv);
+  const int64_t E = heavy ? (int64_t)bv[BV_EH] : (int64_t)bv[BV_E];
+  const int64_t off = heavy ? L.cap - E : (int64_t)bv[BV_OFF];
   const uint64_t *key = L.key[in] + off;
   const uint32_t *eu = L.u[in] + off, *ev = L.v[in] + off;
   const uint32_t *es = L.s[in] ? L.s[in] + off : nullptr;
-  unsigned long long *cnt = (unsigned long long *)&bv[BV_CNT1];
-  const int ct = tile_items(E);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < E; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t pos[CT], nu[CT], nv[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(E, tile, B * ct);
+  unsigned long long *cnt = (unsigned long long *)&bv[BV_CNT1], *cnt2 = (unsigned long long *)&bv[BV_CNT2];
+  const int ct = list_items(E);
+  if (act == ACT_SPLIT) {
+    const uint64_t pivot = bv[BV_PIVOT];
+    for (int64_t tile = blockIdx.x; tile * (LBK * ct) < E; tile += gridDim.x) {
+      bool lt[LCT], ge[LCT];
+      uint32_t pl[LCT], ph[LCT];
+      uint64_t kk[LCT];
+      const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(E, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t i = base + (int64_t)k * B;
+      for (int k = 0; k < LCT; k++) {
+        const int64_t i = base + (int64_t)k * LBK;
+        kk[k] = i < end ? key[i] : 0;
+        lt[k] = i < end && kk[k] < pivot;
+        ge[k] = i < end && kk[k] >= pivot;
+      }
+      list_positions(lt, pl, cnt);
+      list_positions(ge, ph, cnt2);
+#pragma unroll
+      for (int k = 0; k < LCT; k++) {
+        if (!lt[k] && !ge[k]) continue;
+        const int64_t i = base + (int64_t)k * LBK;
+        const int64_t p = lt[k] ? (int64_t)pl[k] : L.cap - 1 - (int64_t)ph[k];
+        L.key[ob][p] = kk[k];
+        L.u[ob][p] = eu[i];
+        L.v[ob][p] = ev[i];
+        L.s[ob][p] = es ? es[i] : (uint32_t)i;
+      }
+    }
+    return;
+  }
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < E; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT], nu[LCT], nv[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(E, tile, LBK * ct);
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
       keep[k] = false;
       nu[k] = nv[k] = 0;
       if (i >= end) continue;
-      const uint32_t fu = fmap[eu[i]], fv = fmap[ev[i]];
-      if (fu == fv) continue;
-      keep[k] = true;
+      uint32_t fu = bpar[eu[i]], fv = bpar[ev[i]];
+      if (heavy) {  // up to the top: as many steps as light rounds at most
+        for (uint32_t p = bpar[fu]; p != fu; p = bpar[fu]) fu = p;
+        for (uint32_t p = bpar[fv]; p != fv; p = bpar[fv]) fv = p;
+      }
+      keep[k] = fu != fv;
       nu[k] = fu;
       nv[k] = fv;
     }
-    tile_positions(keep, pos, cnt);
+    list_positions(keep, pos, cnt);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
+    for (int k = 0; k < LCT; k++) {
       if (!keep[k]) continue;
-      const int64_t i = base + (int64_t)k * B;
+      const int64_t i = base + (int64_t)k * LBK;
       const uint32_t p = pos[k];
       L.key[ob][p] = key[i];
       L.u[ob][p] = nu[k];
@@ -502,44 +533,69 @@ __global__ __launch_bounds__(B) void k_contract(EdgeLists L, uint64_t *bv, const
       L.s[ob][p] = es ? es[i] : (uint32_t)i;
     }
   }
-  if (last_block(&bv[BV_TICKET])) {
-    if (threadIdx.x == 0) {
-      const uint64_t c = ld_coherent(&bv[BV_CNT1]);
-      if (mode == 0) bv[BV_C] = newid[bv[BV_C]];
-      bv[BV_E] = c;
-      bv[BV_IN] = (uint64_t)ob;
-      bv[BV_OFF] = 0;
-      bv[BV_SEEDED] = 0;
-      if (mode == 1) {
-        bv[BV_FIRSTL] = 0;
-        if (c == 0) bv[BV_HEAVY] = 1;  // light edges used up: the heavy ones are contracted next
-      }
-      if (mode == 2) {
-        bv[BV_PHASE] = 0;
-        bv[BV_HEAVY] = 0;
-      }
-      bv[BV_CNT1] = 0;
-      bv[BV_TICKET] = 0;
-      bv_publish(bv);
-    }
-  }
 }
 
-// Filter split (Filter-Kruskal applied to Borůvka). A round may start with a
-// split when live edges are at least `split_min` and more than twice the
-// components: the pivot is the key of rank ~C*S/E among S evenly spaced
+// Advances the state past the slot before this one and decides what this one
+// does; one workgroup, so no other writes the words it reads.
+//
+// Filter split (Filter-Kruskal applied to Boruvka): a slot splits the list
+// when live edges are at least `split_min` and more than twice the
+// components; the pivot is the key of rank ~C*S/E among S evenly spaced
 // samples of the list (sorted in LDS), so about one light edge per component.
 constexpr int SPLIT_SAMPLES = 256;
-__global__ __launch_bounds__(SPLIT_SAMPLES) void k_split_prep(EdgeLists L, uint64_t *bv, int64_t split_min) {
+__global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t *bv, int64_t split_min) {
   __shared__ uint64_t sk[SPLIT_SAMPLES];
-  const Live lv = live_list(L, bv);
-  const int64_t C = (int64_t)bv[BV_C];
-  const bool go = bv[BV_PHASE] == 0 && bv[BV_SEEDED] == 0 && bv[BV_SPLITDONE] == 0 && lv.E >= split_min &&
-                  lv.E > 2 * C;
-  if (!go) {
-    if (threadIdx.x == 0) bv[BV_SPLIT] = 0;
-    return;
+  __shared__ int s_split;
+  if (threadIdx.x == 0) {
+    const uint64_t act = bv[BV_ACT], c1 = bv[BV_CNT1], c2 = bv[BV_CNT2], ob = (uint64_t)out_buffer(bv);
+    uint64_t E = bv[BV_E], lo = bv[BV_LO], hi = bv[BV_HI], light = bv[BV_LIGHT];
+    if (act == ACT_ROUND) {
+      E = c1;
+      bv[BV_IN] = ob;
+      bv[BV_OFF] = 0;
+      bv[BV_MARK] = 0;
+      lo = hi;
+      hi = bv[BV_NB];
+    } else if (act == ACT_SPLIT) {
+      bv[BV_IN] = ob;
+      bv[BV_SPLITDONE] = 1;
+      if (c1 > 0) {  // light rounds first
+        light = 1;
+        E = c1;
+        bv[BV_OFF] = 0;
+        bv[BV_HB] = ob;
+        bv[BV_EH] = c2;
+        bv[BV_SLO] = lo;
+      } else {  // no light edge: the heavy ones are the whole list
+        E = c2;
+        bv[BV_OFF] = (uint64_t)L.cap - c2;
+      }
+    } else if (act == ACT_HEAVY) {
+      E = c1;
+      bv[BV_IN] = 1 - bv[BV_HB];
+      bv[BV_OFF] = 0;
+      bv[BV_MARK] = 1;
+      light = 0;
+      lo = bv[BV_SLO];
+      hi = bv[BV_NB];
+    }
+    uint64_t next = E > 0 ? ACT_ROUND : ACT_NONE;
+    if (light && E == 0) next = ACT_HEAVY;  // light edges used up: the heavy ones are contracted next
+    const bool split = next == ACT_ROUND && !light && act == ACT_ROUND && !bv[BV_SPLITDONE] &&
+                       (int64_t)E >= split_min && E > 2 * (hi - lo);
+    bv[BV_ACT] = split ? (uint64_t)ACT_SPLIT : next;
+    bv[BV_E] = E;
+    bv[BV_LO] = lo;
+    bv[BV_HI] = hi;
+    bv[BV_LIGHT] = light;
+    bv[BV_CNT1] = 0;
+    bv[BV_CNT2] = 0;
+    s_split = split;
   }
+  __threadfence_block();
+  __syncthreads();
+  if (!s_split) return;
+  const Live lv = live_list(L, bv);
   const int i = threadIdx.x;
   sk[i] = lv.key[(int64_t)((unsigned __int128)i * (uint64_t)lv.E / SPLIT_SAMPLES)];
   __syncthreads();
@@ -555,106 +611,29 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_split_prep(EdgeLists L, uint6
     }
   }
   if (i == 0) {
-    int64_t q = (int64_t)((unsigned __int128)SPLIT_SAMPLES * (uint64_t)C / (uint64_t)lv.E);
+    const uint64_t C = bv[BV_HI] - bv[BV_LO];
+    int64_t q = (int64_t)((unsigned __int128)SPLIT_SAMPLES * C / (uint64_t)lv.E);
     if (q > SPLIT_SAMPLES - 1) q = SPLIT_SAMPLES - 1;
     bv[BV_PIVOT] = sk[q];
-    bv[BV_SPLIT] = 1;
-    bv[BV_CNT1] = 0;
-    bv[BV_CNT2] = 0;
   }
 }
 
-// The live edges with key below the pivot go to the front of the output
-// buffer, the others to its back, counted down from cap. Light and heavy
-// together are E <= cap entries, so later contractions of the light part,
-// which only shrink it, never reach the heavy part.
-__global__ __launch_bounds__(B) void k_split(EdgeLists L, uint64_t *bv) {
-  if (bv[BV_SPLIT] == 0) return;
-  const Live lv = live_list(L, bv);
-  const uint64_t pivot = bv[BV_PIVOT];
-  const int ob = out_buffer(bv);
-  const int64_t cap = L.cap;
-  unsigned long long *nlight = (unsigned long long *)&bv[BV_CNT1];
-  unsigned long long *nheavy = (unsigned long long *)&bv[BV_CNT2];
-  const int ct = tile_items(lv.E);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < lv.E; tile += gridDim.x) {
-    bool lt[CT], ge[CT];
-    uint32_t pl[CT], ph[CT];
-    uint64_t kk[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(lv.E, tile, B * ct);
-#pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t i = base + (int64_t)k * B;
-      kk[k] = i < end ? lv.key[i] : 0;
-      lt[k] = i < end && kk[k] < pivot;
-      ge[k] = i < end && kk[k] >= pivot;
-    }
-    tile_positions(lt, pl, nlight);
-    tile_positions(ge, ph, nheavy);
-#pragma unroll
-    for (int k = 0; k < CT; k++) {
-      if (!lt[k] && !ge[k]) continue;
-      const int64_t i = base + (int64_t)k * B;
-      const int64_t p = lt[k] ? (int64_t)pl[k] : cap - 1 - (int64_t)ph[k];
-      L.key[ob][p] = kk[k];
-      L.u[ob][p] = lv.u[i];
-      L.v[ob][p] = lv.v[i];
-      L.s[ob][p] = lv.s ? lv.s[i] : (uint32_t)i;
-    }
-  }
-  if (last_block(&bv[BV_TICKET])) {
-    if (threadIdx.x == 0) {
-      const uint64_t el = ld_coherent(&bv[BV_CNT1]), eh = ld_coherent(&bv[BV_CNT2]);
-      bv[BV_IN] = (uint64_t)ob;
-      if (el > 0) {  // light rounds first; ids stay, the root map starts as the identity
-        bv[BV_PHASE] = 1;
-        bv[BV_FIRSTL] = 1;
-        bv[BV_HB] = (uint64_t)ob;
-        bv[BV_EH] = eh;
-        bv[BV_E] = el;
-        bv[BV_OFF] = 0;
-      } else {  // no light edge: the heavy ones are the whole list
-        bv[BV_E] = eh;
-        bv[BV_OFF] = (uint64_t)(cap - (int64_t)eh);
-      }
-      bv[BV_SPLIT] = 0;
-      bv[BV_SPLITDONE] = 1;
-      bv[BV_CNT1] = 0;
-      bv[BV_CNT2] = 0;
-      bv[BV_TICKET] = 0;
-      bv_publish(bv);
-    }
-  }
-}
-
-// light rounds: the root (in this round's hooks) of every component of the
-// split; the minima of the next round start empty
-__global__ __launch_bounds__(B) void k_compose_roots(Cnt C, const uint64_t *bv, const uint32_t *hook,
-                                                     uint32_t *rootof, uint64_t *best) {
-  const int64_t nc = C.get();
-  const bool first = bv[BV_FIRSTL] != 0;
-  for (int64_t c = (int64_t)blockIdx.x * B + threadIdx.x; c < nc; c += (int64_t)gridDim.x * B) {
-    rootof[c] = hook[first ? (uint32_t)c : rootof[c]];
-    best[c] = NONE64;
-  }
-}
-
-// per component, the minimum key over its live edges. A tile of up to 4096 edges
-// first takes per-component minima in an LDS hash (late rounds send most
-// edges to a few big components), then one atomicMin per component per tile.
-constexpr int MHS = 512;
-__global__ __launch_bounds__(B) void k_bv_min(EdgeLists L, const uint64_t *bv, uint64_t *best) {
-  if (bv[BV_SEEDED]) return;  // seeded while the skeleton was emitted
+// per node, the minimum key over its live edges. A tile of up to LBK * CT edges
+// first takes per-node minima in an LDS hash (late rounds send most edges to
+// a few big components), then one atomicMin per node per tile.
+constexpr int MHS = 1024;
+__global__ __launch_bounds__(LBK) void k_bv_min(EdgeLists L, const uint64_t *bv, uint64_t *best) {
+  if (bv[BV_ACT] != ACT_ROUND) return;
   const Live lv = live_list(L, bv);
   __shared__ uint32_t hk[MHS];
   __shared__ unsigned long long hv[MHS];
-  const int ct = tile_items(lv.E);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < lv.E; tile += gridDim.x) {
-    for (int i = threadIdx.x; i < MHS; i += B) { hk[i] = NONE32; hv[i] = NONE64; }
+  const int ct = list_items(lv.E);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < lv.E; tile += gridDim.x) {
+    for (int i = threadIdx.x; i < MHS; i += LBK) { hk[i] = NONE32; hv[i] = NONE64; }
     __syncthreads();
-    const int64_t tbase = tile * (B * ct);
+    const int64_t tbase = tile * (LBK * ct);
     for (int k = 0; k < ct; k++) {
-      const int64_t i = tbase + (int64_t)k * B + threadIdx.x;
+      const int64_t i = tbase + (int64_t)k * LBK + threadIdx.x;
       const bool act = i < lv.E;
       const unsigned long long kv = act ? lv.key[i] : NONE64;
       const uint32_t cu = act ? lv.u[i] : 0u, cv = act ? lv.v[i] : 0u;
@@ -667,7 +646,7 @@ __global__ __launch_bounds__(B) void k_bv_min(EdgeLists L, const uint64_t *bv, u
           if ((int)wave_lane() == leader) kmin = v;
         });
         if (upd) {
-          uint32_t sl = (c * 2654435761u) >> 23;  // 9 bits
+          uint32_t sl = (c * 2654435761u) >> 22;  // 10 bits
           bool placed = false;
           for (int probe = 0; probe < HASH_PROBES && !placed; probe++) {
             uint32_t old = atomicCAS(&hk[sl], NONE32, c);
@@ -683,7 +662,7 @@ __global__ __launch_bounds__(B) void k_bv_min(EdgeLists L, const uint64_t *bv, u
       }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < MHS; i += B) {
+    for (int i = threadIdx.x; i < MHS; i += LBK) {
       const uint32_t c = hk[i];
       if (c == NONE32) continue;
       const unsigned long long v = hv[i];
@@ -693,35 +672,77 @@ __global__ __launch_bounds__(B) void k_bv_min(EdgeLists L, const uint64_t *bv, u
   }
 }
 
-// the edge index holding each component's minimum (keys are unique)
-__global__ __launch_bounds__(B) void k_bv_pick(EdgeLists L, const uint64_t *bv, const uint64_t *best,
-                                               uint32_t *bidx) {
-  const Live lv = live_list(L, bv);
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < lv.E; i += (int64_t)gridDim.x * B) {
-    const uint64_t k = lv.key[i];
-    const uint32_t a = lv.u[i], b = lv.v[i];
-    if (best[a] == k) bidx[a] = (uint32_t)i;
-    if (best[b] == k) bidx[b] = (uint32_t)i;
+// The rounds left after the enqueued slots of a small call, in one workgroup:
+// the same five steps with barriers between them. Components at least halve
+// per round, so 32 rounds end any call; past them the call fails.
+constexpr int BTB = 1024;
+__global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint64_t *best, uint32_t *bpar,
+                                                 uint32_t *rootc, uint8_t *msf_flag, uint64_t *hdr) {
+  if (bv[BV_ACT] != ACT_ROUND) return;
+  __shared__ uint32_t s_nb, s_cnt;
+  Live lv = live_list(L, bv);
+  int ob = out_buffer(bv);
+  int64_t lo = (int64_t)bv[BV_LO], hi = (int64_t)bv[BV_HI];
+  if (threadIdx.x == 0) s_nb = (uint32_t)hi;
+  const int tid = threadIdx.x;
+  for (int round = 0; lv.E > 0 && round < 40; round++) {
+    if (tid == 0) s_cnt = 0;
+    for (int64_t i = tid; i < lv.E; i += BTB) {
+      const unsigned long long k = lv.key[i];
+      const uint32_t u = lv.u[i], v = lv.v[i];
+      if (k < best[u]) atomicMin((unsigned long long *)&best[u], k);
+      if (k < best[v]) atomicMin((unsigned long long *)&best[v], k);
+    }
+    __syncthreads();
+    for (int64_t i = tid; i < lv.E; i += BTB)
+      if (bv_hook_edge(lv.key[i], lv.u[i], lv.v[i], best, bpar)) msf_flag[lv.s ? lv.s[i] : i] = 1;
+    __syncthreads();
+    for (int64_t c = lo + tid; c < hi; c += BTB) {
+      uint32_t r = NONE32;
+      if (best[c] != NONE64) {
+        r = bv_root(bpar, (uint32_t)c, hdr);
+        if (r == (uint32_t)c) r = atomicAdd(&s_nb, 1u);
+      }
+      rootc[c - lo] = r;
+    }
+    __syncthreads();
+    const int64_t nb = s_nb;
+    for (int64_t c = lo + tid; c < hi; c += BTB) bv_link((uint32_t)c, rootc[c - lo], lo, rootc, bpar);
+    for (int64_t x = hi + tid; x < nb; x += BTB) {
+      best[x] = NONE64;
+      bpar[x] = (uint32_t)x;
+    }
+    __syncthreads();
+    for (int64_t i = tid; i < lv.E; i += BTB) {
+      const uint32_t fu = bpar[lv.u[i]], fv = bpar[lv.v[i]];
+      if (fu == fv) continue;
+      const uint32_t p = atomicAdd(&s_cnt, 1u);
+      L.key[ob][p] = lv.key[i];
+      L.u[ob][p] = fu;
+      L.v[ob][p] = fv;
+      L.s[ob][p] = lv.s ? lv.s[i] : (uint32_t)i;
+    }
+    __syncthreads();
+    lv = Live{L.key[ob], L.u[ob], L.v[ob], L.s[ob], (int64_t)s_cnt};
+    ob = 1 - ob;
+    lo = hi;
+    hi = nb;
+    __syncthreads();
+  }
+  if (tid == 0 && lv.E == 0) {
+    bv[BV_E] = 0;
+    bv[BV_ACT] = ACT_NONE;
+    bv[BV_NB] = (uint64_t)hi;
   }
 }
 
-// state of a flat skeleton's first round: the rows themselves are the live
-// list (S rows, counted on the device), records are the components, and the
-// minima were seeded during emission
-__global__ void k_bv_flat_init(uint64_t *bv, const uint64_t *rows, int64_t n) {
-  if (threadIdx.x != 0) return;
-  for (int k = 0; k < BV_WORDS; k++) bv[k] = 0;
-  bv[BV_E] = *rows;
-  bv[BV_C] = (uint64_t)n;
-  bv[BV_IN] = 2;
-  bv[BV_SEEDED] = 1;
-  bv_publish(bv);
-}
-
-// after the last enqueued round every live edge must be gone (the round bound
-// guarantees it); if not, the call fails instead of returning a partial forest
+// after the last enqueued slot every live edge must be gone (the slot bound
+// guarantees it); if not, the call fails instead of returning a partial
+// forest. Also clears the forest's row count for the listing that follows.
 __global__ void k_bv_check(const uint64_t *bv, uint64_t *hdr) {
-  if (threadIdx.x == 0 && (bv[BV_E] != 0 || bv[BV_HEAVY] != 0)) hdr[H_STATUS] |= 32;
+  if (threadIdx.x != 0) return;
+  if (bv[BV_ACT] != ACT_NONE) hdr[H_STATUS] |= 32;
+  hdr[H_M] = 0;
 }
 
 __global__ __launch_bounds__(B) void k_msf_list(const uint8_t *flag, int64_t n2, uint32_t *out,
@@ -762,8 +783,6 @@ __global__ __launch_bounds__(B) void k_msf_gather(const uint32_t *list, Cnt mc, 
     oval[i] = (uint64_t)skel_tail[e] | ((uint64_t)(e >> 1) << 32);
   }
 }
-
-__global__ void k_set_u64(uint64_t *p, uint64_t v) { *p = v; }
 
 // a forest has at most n - 1 rows; more means the call failed (and the rows
 // are dropped, so that later kernels stay in bounds)
@@ -1029,19 +1048,14 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
 
 size_t stage_boruvka_scratch(int64_t n, int64_t slots) {
   Ws w;
-  w.alloc<uint32_t>(n);      // hook
-  w.alloc<uint32_t>(n);      // bidx
-  w.alloc<uint32_t>(n + 1);  // root flags
-  w.alloc<uint32_t>(n + 1);  // dense ids
-  w.alloc<uint32_t>(n);      // final ids
-  w.alloc<uint32_t>(n);      // root map of a split
+  w.alloc<uint32_t>(n);          // roots of a round's nodes
   for (int k = 0; k < 2; k++) {  // edge lists (key, u, v, slot), ping-pong
     w.alloc<uint64_t>(slots);
     w.alloc<uint32_t>(slots);
     w.alloc<uint32_t>(slots);
     w.alloc<uint32_t>(slots);
   }
-  return w.off + scan_ws_bytes(n + 1) + 4096;
+  return w.off + 4096;
 }
 
 // The filter split runs when the live edges number at least 2^20 and more
@@ -1049,26 +1063,28 @@ size_t stage_boruvka_scratch(int64_t n, int64_t slots) {
 // CE_SPLIT_MIN_EDGES) overrides the 2^20 or turns the split off.
 static int64_t split_min_edges() { return tuning().split_min_edges; }
 
-// Rounds the host enqueues after the first: in every round the components
-// that still have live edges at least halve, so bits(n) + 1 rounds end a run
-// of plain rounds. With the (single) split, plain rounds before it and the
-// light rounds together halve the components at least once per round, and so
-// do the light rounds and the plain rounds after them: 2 (bits(n) + 1) + 1
-// rounds cover both.
+// Slots the host enqueues after the first round: in every round the
+// components that still have live edges at least halve, so bits(n) + 1 rounds
+// end a run of plain rounds. With the (single) split, plain rounds before it
+// and the light rounds together halve the components at least once per
+// round, and so do the light rounds and the plain rounds after them:
+// 2 (bits(n) + 1) + 1 rounds cover both, and two more slots split and
+// contract the heavy edges.
 int boruvka_rounds(int64_t n, bool split_possible) {
   const int r = bits_for((uint64_t)n) + 1;
-  return split_possible ? 2 * r + 1 : r;
+  return split_possible ? 2 * r + 3 : r;
 }
+
+// Up to this many skeleton slots, a call without a split enqueues fewer slots
+// and leaves the rest to one workgroup: an idle slot costs six launches of
+// about 2 us, a round of one workgroup about 10 us plus 0.5 us per 1024 edges
+// and step. Larger calls enqueue the full bound.
+constexpr int64_t TAIL_SLOTS = int64_t(1) << 20;
 
 ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   const int64_t n = b.n, n2 = b.slots;
   size_t m0 = ws.mark();
-  uint32_t *hook = ws.alloc<uint32_t>(n);
-  uint32_t *bidx = ws.alloc<uint32_t>(n);
-  uint32_t *flags = ws.alloc<uint32_t>(n + 1);
-  uint32_t *newid = ws.alloc<uint32_t>(n + 1);
-  uint32_t *fin = ws.alloc<uint32_t>(n);
-  uint32_t *rootof = ws.alloc<uint32_t>(n);
+  uint32_t *rootc = ws.alloc<uint32_t>(n);
   EdgeLists L;
   for (int k = 0; k < 2; k++) {
     L.key[k] = ws.alloc<uint64_t>(n2);
@@ -1082,68 +1098,53 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   L.v[2] = b.skel_tid;
   L.s[2] = nullptr;
   L.cap = n2;
-  uint64_t *bv = b.hdr + H_BV;
-  uint32_t *rankof = b.rankof;  // kept for writing the per-record outputs in input order
-  CE_LAUNCH(k_rankof, dim3(grid_for(n, B)), dim3(B), 0, s, b.perm, n, rankof);
-  uint64_t *best = b.best;  // seeded for the first round while the skeleton was emitted
-  CE_LAUNCH(k_fill_u8, dim3(grid_for(n2, B)), dim3(B), 0, s, b.msf_flag, n2, (uint8_t)0);
-  const unsigned gN = grid_cap(n, B), gE = grid_cap(n2, B), tE = grid_cap(n2, B, tuning().list_grid);
-  if (b.flat) {
-    // causal and hypergraph skeleton rows can share a head, so every round,
-    // the first included, runs on the edge-list form with records as
-    // components; the first reads the skeleton rows in place (slot = row)
-    CE_LAUNCH(k_bv_flat_init, dim3(1), dim3(64), 0, s, bv, &b.hdr[H_C7], n);
-  } else {
-    // first round on records, then its contraction into list 0
-    CE_LAUNCH(k_bv_hook_first, dim3(gN), dim3(B), 0, s, n, best, b.skel_key, b.skel_tail, rankof, b.idbits, hook,
-              b.msf_flag, flags);
-    CE_LAUNCH(k_bv_compress, dim3(gN), dim3(B), 0, s, Cnt(n), hook, b.hdr);
-    CE_LAUNCH(k_bv_roots, dim3(gN), dim3(B), 0, s, Cnt(n), hook, b.hdr);
-    CE_HIP(hipGetLastError());
-    CE_TRY(scan_exclusive_u32(flags, newid, Cnt(n), ws, s));
-    CE_LAUNCH(k_final_ids, dim3(gN), dim3(B), 0, s, Cnt(n), hook, newid, fin, best);
-    CE_LAUNCH(k_contract_first, dim3(tE), dim3(B), 0, s, n, b.skel_key, b.skel_tail, fin, newid, L, bv);
-    CE_HIP(hipGetLastError());
-  }
+  uint64_t *bv = b.hdr + H_BV, *best = b.best;
+  uint32_t *bpar = b.bpar;
+  const unsigned gN = grid_cap(n, B), gE = grid_cap(n2, B), lN = list_blocks(n), lE = list_blocks(n2);
+  CE_LAUNCH(k_bv_start, dim3(grid_cap(n2 > n ? n2 : n, B)), dim3(B), 0, s, b.perm, n, n2, b.flat, &b.hdr[H_C7],
+            b.rankof, b.msf_flag, bpar, bv);
+  // first round (its minima were seeded while the skeleton was emitted). Causal and hypergraph skeleton rows can
+  // share a head, so theirs runs on the edge-list form, with the skeleton rows in place as the list (slot = row).
+  if (b.flat)
+    CE_LAUNCH(k_bv_hook, dim3(gE), dim3(B), 0, s, L, bv, best, bpar, b.msf_flag);
+  else
+    CE_LAUNCH(k_bv_hook_first, dim3(gN), dim3(B), 0, s, n, best, b.skel_key, b.skel_tail, b.rankof, b.idbits, bpar,
+              b.msf_flag);
+  CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
+  CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
+  if (b.flat)
+    CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar);
+  else
+    CE_LAUNCH(k_contract_first, dim3(lE), dim3(LBK), 0, s, n, b.skel_key, b.skel_tail, bpar, L, bv);
+  CE_HIP(hipGetLastError());
   // Filter split. When live edges far outnumber components, most of them run
   // between components that later rounds merge anyway, and every round would
-  // scan them again. So the list is split at a pivot key: Borůvka runs on the
+  // scan them again. So the list is split at a pivot key: Boruvka runs on the
   // light edges (key below the pivot) alone until none is left, then the heavy
   // ones are contracted once and rounds go on with the survivors. Keys are
   // unique, so the forest is the same: a light edge outside the light forest
   // is the largest on a cycle of light edges, and contracting the light forest
-  // keeps every heavy edge's cycles. During the light phase components keep
-  // the ids they had at the split (no renumbering) and rootof maps each of
-  // them to its current root; the heavy edges wait at the back of the buffer
-  // the split wrote.
+  // keeps every heavy edge's cycles. The heavy edges wait, with the nodes they
+  // had at the split, at the back of the buffer the split wrote.
   const int64_t split_min = split_min_edges();
   const bool split_possible = n2 >= split_min;
-  const int rounds = boruvka_rounds(n, split_possible);
-  const Cnt CG(&bv[BV_CG], n), CN(&bv[BV_CN], n), CL(&bv[BV_CL], n);
-  for (int r = 0; r < rounds; r++) {
-    if (split_possible) {
-      CE_LAUNCH(k_split_prep, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
-      CE_LAUNCH(k_split, dim3(tE), dim3(B), 0, s, L, bv);
-    }
-    CE_LAUNCH(k_bv_min, dim3(tE), dim3(B), 0, s, L, bv, best);
-    CE_LAUNCH(k_bv_pick, dim3(gE), dim3(B), 0, s, L, bv, best, bidx);
-    CE_LAUNCH(k_bv_hook, dim3(gN), dim3(B), 0, s, L, bv, best, bidx, hook, b.msf_flag, flags);
-    CE_LAUNCH(k_bv_compress, dim3(gN), dim3(B), 0, s, CG, hook, b.hdr);
-    CE_LAUNCH(k_bv_roots, dim3(gN), dim3(B), 0, s, CG, hook, b.hdr);
-    CE_HIP(hipGetLastError());
-    if (split_possible) {
-      // light round: ids stay; the edges' endpoints are this round's roots, hook gives their new ones
-      CE_LAUNCH(k_compose_roots, dim3(gN), dim3(B), 0, s, CL, bv, hook, rootof, best);
-      CE_LAUNCH(k_contract, dim3(tE), dim3(B), 0, s, L, bv, &bv[BV_EL], hook, newid, 1);
-    }
-    // plain round: dense ids for the surviving roots, then the contraction
-    CE_TRY(scan_exclusive_u32(flags, newid, CN, ws, s));
-    CE_LAUNCH(k_final_ids, dim3(gN), dim3(B), 0, s, CN, hook, newid, fin, best);
-    CE_LAUNCH(k_contract, dim3(tE), dim3(B), 0, s, L, bv, &bv[BV_EN], fin, newid, 0);
-    if (split_possible)  // after the light phase: the heavy edges between different current roots
-      CE_LAUNCH(k_contract, dim3(tE), dim3(B), 0, s, L, bv, &bv[BV_EHG], rootof, newid, 2);
+  const bool tail = !split_possible && n2 <= TAIL_SLOTS;
+  int slots = boruvka_rounds(n, split_possible);
+  if (tail) {
+    const int few = n2 <= 8192 ? 0 : bits_for((uint64_t)n) / 2 + 1;
+    if (few < slots) slots = few;
+  }
+  for (int r = 0; r < slots; r++) {
+    CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
+    CE_LAUNCH(k_bv_min, dim3(lE), dim3(LBK), 0, s, L, bv, best);
+    CE_LAUNCH(k_bv_hook, dim3(gE), dim3(B), 0, s, L, bv, best, bpar, b.msf_flag);
+    CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
+    CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
+    CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar);
     CE_HIP(hipGetLastError());
   }
+  CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
+  if (tail) CE_LAUNCH(k_bv_tail, dim3(1), dim3(BTB), 0, s, L, bv, best, bpar, rootc, b.msf_flag, b.hdr);
   CE_LAUNCH(k_bv_check, dim3(1), dim3(64), 0, s, bv, b.hdr);
   CE_HIP(hipGetLastError());
   ws.release(m0);
@@ -1166,7 +1167,6 @@ size_t stage_msf_sort_scratch(int64_t n) {
   Ws w;
   w.alloc<uint64_t>(n);
   w.alloc<uint64_t>(n);
-  w.alloc<uint32_t>(n);
   return w.off + radix_ws_bytes(n) + 4096;
 }
 
@@ -1177,9 +1177,8 @@ ce_status stage_msf_sort(Bufs &b, Ws &ws, hipStream_t s) {
   size_t m0 = ws.mark();
   uint64_t *key_alt = ws.alloc<uint64_t>(n);
   uint64_t *val_alt = ws.alloc<uint64_t>(n);
-  uint32_t *list = ws.alloc<uint32_t>(n);
+  uint32_t *list = b.kc_u;  // not live yet
   CE_WS_CHECK(ws);
-  CE_LAUNCH(k_set_u64, dim3(1), dim3(1), 0, s, &b.hdr[H_M], (uint64_t)0);
   CE_LAUNCH(k_msf_list, dim3(grid_cap(n2, B, tuning().list_grid)), dim3(B), 0, s, b.msf_flag, n2, list,
             (unsigned long long *)&b.hdr[H_M]);
   CE_LAUNCH(k_check_rows, dim3(1), dim3(64), 0, s, b.hdr, n);
