@@ -105,11 +105,11 @@ typedef struct {
   uint32_t struct_size;           /* = sizeof(ce_tuning) */
   int32_t radix_keys_per_thread;  /* keys per thread of the radix sorts: 4 (sorts of up to 2^24 keys), 8
                                      (default) or 16 */
-  int32_t list_grid;              /* workgroups of the passes over live lists (compaction, Boruvka minima,
-                                     pointer jumping), 256..65536 (default 4096): with the list length it sets
-                                     the items per thread, up to 16 */
-  int32_t krt_level_bits;         /* dendrogram: the most bits one global level takes, 1..12 (default: a rule
-                                     of the row count) */
+  int32_t list_grid;              /* size of the passes over live lists (compaction, Boruvka minima, pointer
+                                     jumping), 256..65536 (default 4096): their workgroups, a quarter of it
+                                     where those are of 512 threads */
+  int32_t krt_level_bits;         /* taken (0..12) and reported, without effect: the dendrogram has no level
+                                     width to choose */
   int64_t split_min_edges;        /* Boruvka's filter split runs from this many live edges (default 2^20);
                                      < 0: never */
 } ce_tuning;
@@ -145,8 +145,7 @@ typedef struct {
 
 /* The launch choices a call of n records over num_vertices vertices with
  * these params (NULL: none given) would take, after every source of
- * ce_tuning's fields; 0 in out->krt_level_bits is the built-in rule, -1 in
- * out->split_min_edges is no split. Pure host function; out->struct_size
+ * ce_tuning's fields; -1 in out->split_min_edges is no split. Pure host function; out->struct_size
  * must be set. Errors: CE_EINVAL. */
 ce_status ce_resolve_tuning(int64_t n, int64_t num_vertices, const ce_params *params, ce_tuning *out);
 #define CE_MAX_THRESHOLDS 64

@@ -1,12 +1,11 @@
 """Autotuner for the launch choices of a call (``ce_tuning``).
 
-The knobs are the ones the kernels leave open: the dendrogram's largest level
-width (``krt_level_bits``: sub-intervals run one after another, each over
-m / 2^k rows), the row count from which Boruvka splits its edge list at a
-pivot key (``split_min_edges``), the workgroups of the passes over live lists
-(``list_grid``, which with a list's length sets its items per thread, i.e. the
-compaction tile), and the keys per thread of every radix sort
-(``radix_keys_per_thread``, the sort tile). None of them changes an output.
+The knobs are the ones the kernels leave open: the row count from which
+Boruvka splits its edge list at a pivot key (``split_min_edges``), the size of
+the passes over live lists (``list_grid``), and the keys per thread of every
+radix sort (``radix_keys_per_thread``, the sort tile). None of them changes an
+output. (``krt_level_bits`` is read and written with the others, but has no
+effect any more, so it is not swept.)
 
 A sweep is coordinate descent over the knobs in that order, starting from the
 built-in choices: each candidate is timed as the median wall time of ``reps``
@@ -36,7 +35,6 @@ from typing import Callable, Dict, Optional, Tuple
 from . import tuned
 
 CANDIDATES: Dict[str, Tuple[int, ...]] = {
-    "krt_level_bits": (3, 4, 5, 6, 7, 8, 9, 10, 11, 12),
     "split_min_edges": (1 << 18, 1 << 22, -1),
     "list_grid": (1024, 2048, 8192, 16384),
     "radix_keys_per_thread": (4, 16),
@@ -111,7 +109,7 @@ def sweep(run: Callable[[], object], digest: Callable[[object], tuple], reps: in
     best, best_ms = {}, base_ms
     trials = [({}, base_ms)]
     for knob in order:
-        for v in candidates[knob]:
+        for v in candidates.get(knob, ()):
             k = dict(best)
             k[knob] = v
             ms, d = measure(k)

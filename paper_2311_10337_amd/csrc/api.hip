@@ -59,15 +59,6 @@ namespace {
 
 constexpr int B = 256;
 
-__global__ __launch_bounds__(B) void k_iota32(uint32_t *p, Cnt nc) {
-  const int64_t n = nc.get();
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) p[i] = (uint32_t)i;
-}
-__global__ __launch_bounds__(B) void k_zero32(uint32_t *p, Cnt nc) {
-  const int64_t n = nc.get();
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) p[i] = 0u;
-}
-
 // graph of each MSF row (the graph of its tail record)
 __global__ __launch_bounds__(B) void k_rowg(const uint64_t *msf_val, const uint32_t *grank, Cnt mc, uint32_t *rowg,
                                             uint32_t *key) {
@@ -146,6 +137,7 @@ __global__ void k_trivial(const int64_t *eoff, int64_t G, const uint64_t *hdr, c
 }  // namespace
 
 size_t stage_graph_rows_scratch(int64_t n, int64_t G) {
+  if (G == 1) return 0;
   Ws w;
   for (int k = 0; k < 4; k++) w.alloc<uint32_t>(n);
   return w.off + radix_ws_bytes(n) + 4096;
@@ -157,23 +149,22 @@ size_t stage_graph_rows_scratch(int64_t n, int64_t G) {
 ce_status stage_graph_rows(Bufs &b, Ws &ws, hipStream_t s) {
   const int64_t G = b.G, mb = b.n > 1 ? b.n - 1 : 1;
   const Cnt m(&b.hdr[H_M], mb);
+  if (G == 1) {
+    CE_LAUNCH(k_moff_one, dim3(1), dim3(64), 0, s, b.moff, &b.hdr[H_M]);
+    CE_HIP(hipGetLastError());
+    return CE_OK;
+  }
   size_t m0 = ws.mark();
   uint32_t *key = ws.alloc<uint32_t>(mb), *val = ws.alloc<uint32_t>(mb);
   uint32_t *key2 = ws.alloc<uint32_t>(mb), *val2 = ws.alloc<uint32_t>(mb);
   CE_WS_CHECK(ws);
-  if (G == 1) {
-    CE_LAUNCH(k_zero32, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.rowg, m);
-    CE_LAUNCH(k_iota32, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.rowpos, m);
-    CE_LAUNCH(k_moff_one, dim3(1), dim3(64), 0, s, b.moff, &b.hdr[H_M]);
-  } else {
-    CE_LAUNCH(k_rowg, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_val, b.grank, m, b.rowg, key);
-    CE_HIP(hipGetLastError());
-    bool alt = false;
-    CE_TRY((radix_sort_pairs<uint32_t, uint32_t>(key, val, key2, val2, m, 0, bits_for((uint64_t)(G - 1)), true,
-                                                 &alt, ws, s)));
-    CE_LAUNCH(k_rowpos, dim3(grid_cap(mb, B)), dim3(B), 0, s, alt ? val2 : val, m, b.rowpos);
-    CE_TRY(segment_bounds_u32(alt ? key2 : key, m, G, b.moff, s));
-  }
+  CE_LAUNCH(k_rowg, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_val, b.grank, m, b.rowg, key);
+  CE_HIP(hipGetLastError());
+  bool alt = false;
+  CE_TRY((radix_sort_pairs<uint32_t, uint32_t>(key, val, key2, val2, m, 0, bits_for((uint64_t)(G - 1)), true, &alt, ws,
+                                               s)));
+  CE_LAUNCH(k_rowpos, dim3(grid_cap(mb, B)), dim3(B), 0, s, alt ? val2 : val, m, b.rowpos);
+  CE_TRY(segment_bounds_u32(alt ? key2 : key, m, G, b.moff, s));
   CE_HIP(hipGetLastError());
   ws.release(m0);
   return CE_OK;
@@ -192,8 +183,8 @@ ce_status stage_write_rows(Bufs &b, const ce_result *out, hipStream_t s) {
 //   T  the rest of the Boruvka tree, right behind X (from Boruvka on)
 //   Y  sorted MSF, dendrogram and row placement (live from the MSF sort on), at its end
 // Scratch A (grouping, skeleton) follows X, scratch T (Boruvka) follows T; both
-// may overlap Y. Scratch M (MSF sort) lies between T and Y; scratch B
-// (dendrogram, condensing) starts at the phase area and overlaps X and T.
+// may overlap Y. Scratch M (MSF sort, dendrogram) lies between T and Y; scratch
+// B (condensing) starts at the phase area and overlaps X and T.
 // nnz >= 0: a hypergraph with nnz memberships (its skeleton has at most nnz rows)
 static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discrete, int64_t nnz) {
   const int64_t slots = nnz >= 0 ? (nnz > 0 ? nnz : 1) : 2 * n;
@@ -204,7 +195,7 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   b.eoff = ws.alloc<int64_t>(G + 1);
   b.voff = ws.alloc<int64_t>(G + 1);
   b.perm = ws.alloc<uint32_t>(n);
-  b.grank = ws.alloc<uint32_t>(n);
+  if (G > 1) b.grank = ws.alloc<uint32_t>(n);
   b.rankof = ws.alloc<uint32_t>(n);
   const size_t base = ws.off;
   b.ts = ws.alloc<uint64_t>(n);
@@ -220,17 +211,18 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   Ws y;
   y.alloc<uint64_t>(n);
   y.alloc<uint64_t>(n);
-  for (int k = 0; k < 5; k++) y.alloc<uint32_t>(n);
+  for (int k = 0; k < (G > 1 ? 5 : 3); k++) y.alloc<uint32_t>(n);
+  y.alloc<uint32_t>(2 * n);
   y.alloc<uint32_t>(G + 1);
   const size_t ybytes = y.off;
   size_t scr_a = nnz >= 0 ? stage_hyper_skeleton_scratch(n, nnz) : stage_sort_skeleton_scratch(n);
   size_t x = nnz >= 0 ? 0 : stage_causal_skeleton_scratch(n);
   if (x > scr_a) scr_a = x;
   const size_t scr_t = stage_boruvka_scratch(n, slots);
-  const size_t scr_m = stage_msf_sort_scratch(n);
-  size_t scr_b = stage_dendrogram_scratch(n);
-  x = stage_graph_rows_scratch(n, G);
-  if (x > scr_b) scr_b = x;
+  size_t scr_m = stage_msf_sort_scratch(n);
+  x = stage_dendrogram_scratch(n, slots);
+  if (x > scr_m) scr_m = x;
+  size_t scr_b = stage_graph_rows_scratch(n, G);
   x = stage_condense_scratch(n, M, G, discrete);
   if (x > scr_b) scr_b = x;
   auto al = [](size_t v) { return (v + 255) & ~size_t(255); };
@@ -244,8 +236,11 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   b.kc_u = ws.alloc<uint32_t>(n);
   b.kc_v = ws.alloc<uint32_t>(n);
   b.ksize = ws.alloc<uint32_t>(n);
-  b.rowg = ws.alloc<uint32_t>(n);
-  b.rowpos = ws.alloc<uint32_t>(n);
+  if (G > 1) {
+    b.rowg = ws.alloc<uint32_t>(n);
+    b.rowpos = ws.alloc<uint32_t>(n);
+  }
+  b.kpar = ws.alloc<uint32_t>(2 * n);
   b.moff = ws.alloc<uint32_t>(G + 1);
   char *pb = ws.base ? ws.base + base : nullptr;
   b.scratch_a = pb ? pb + xbytes : nullptr;
@@ -617,8 +612,9 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
     else CE_TRY(stage_sort_skeleton(c.src, c.dst, c.t, b, wa, s));
     CE_TRY(stage_boruvka(b, wt, s));
     CE_TRY(stage_msf_sort(b, wm, s));
+    CE_TRY(stage_dendrogram_find(b, wm, s));
     if (max_dt >= 0) CE_TRY(stage_time_filter(b, max_dt, s));
-    CE_TRY(stage_dendrogram(b, wb, s));
+    CE_TRY(stage_dendrogram(b, max_dt >= 0, wm, s));
     CE_TRY(stage_graph_rows(b, wb, s));
     CE_TRY(stage_write_rows(b, out, s));
     CE_TRY(stage_condense(b, out, wb, s, hout));

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(B) void k_causal_entries(const uint4 *vals, const u
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) {
     const uint4 v = vals[r];
     perm[r] = v.x;
-    grank[r] = v.w;
+    if (grank) grank[r] = v.w;
     const uint32_t run = fx[r] + f[r] - 1;
     const int64_t g0 = start[run], g1 = start[run + 1];
     const int64_t pin = 2 * g0 + (r - g0), pout = 2 * g0 + (g1 - g0) + (r - g0);
@@ -237,7 +237,7 @@ size_t stage_causal_skeleton_scratch(int64_t n) {
   if (p3 > x) x = p3;
   x += w.off;
   const size_t rk = r0 + stage_rank_weights_scratch(n2);
-  return (x > rk ? x : rk) + 4096;
+  return (x > rk ? x : rk) + 1024;
 }
 
 ce_status stage_causal_skeleton(const int32_t *src, const int32_t *dst, const int64_t *t, Bufs &b, Ws &ws,

@@ -159,8 +159,12 @@ enum : int {
   H_KEYW = 13,   // key layout of the flat skeletons: wshift | hshift << 8 | keybits << 16
   H_NEOM = 14,   // rows of the excess-of-mass tree (cluster rows + virtual nodes)
   H_BV = 16,     // Boruvka state (24 words)
+  H_BV_NLEV = 40,  // levels of the Boruvka tree (rounds that made nodes)
   H_LOOP = 64,   // per-round counters of bounded loops
-  kHdrWords = 256
+  H_LOOP_END = 256,
+  H_LEV = 256,   // H_LEV + l: first node id after level l (level 0: the records)
+  H_LPOS = 352,  // H_LPOS + l: first chain-ordered row after the chains of level l
+  kHdrWords = 448
 };
 
 // The ce_status of a call from its error bits (H_STATUS).
@@ -211,6 +215,10 @@ __host__ __device__ inline uint32_t graph_of(const int64_t *eoff, int64_t G, int
   }
   return (uint32_t)lo;
 }
+
+// graph of record or row i, output position of row i (null for one graph)
+__device__ inline uint32_t graph_at(const uint32_t *g, int64_t i) { return g ? g[i] : 0u; }
+__device__ inline uint32_t pos_at(const uint32_t *pos, int64_t i) { return pos ? pos[i] : (uint32_t)i; }
 
 // lambda(w) = floor(2^63 / max(2w, 1)) for w >= 0
 __host__ __device__ inline uint64_t lambda_of(int64_t w) {
@@ -427,6 +435,7 @@ struct Bufs {
   // records [eoff[g], eoff[g+1]) and vertices [voff[g], voff[g+1]) (device copies)
   int64_t G = 1;
   const int64_t *eoff = nullptr, *voff = nullptr;
+  // (one graph has none of these three: every graph index is 0, every row stays in place)
   uint32_t *grank = nullptr;    // [n] graph of each record, by rank
   uint32_t *rowg = nullptr;     // [n] graph of each MSF row
   uint32_t *rowpos = nullptr;   // [n] output position of each MSF row (graphs in order, rows in key order)
@@ -463,9 +472,10 @@ struct Bufs {
   uint64_t *msf_key = nullptr;  // [n] sorted MSF keys
   uint64_t *msf_val = nullptr;  // [n] tail rank | head rank << 32; the head's id is in the key
   uint32_t *kc_u = nullptr, *kc_v = nullptr, *ksize = nullptr; // [n] dendrogram children (internal labels) and size
+  uint32_t *kpar = nullptr;     // [2n] dendrogram parent of each record and row, NONE without one
   // scratch arenas: A for grouping, skeleton and Boruvka (it may overlap the
-  // MSF/dendrogram arrays, which are not live yet), M for sorting the MSF, B
-  // for the dendrogram and condensing (it overlaps the dead skeleton arrays)
+  // MSF/dendrogram arrays, which are not live yet), T for Boruvka, M for sorting
+  // the MSF and the dendrogram, B for condensing (it overlaps the dead skeleton arrays)
   char *scratch_a = nullptr, *scratch_t = nullptr, *scratch_m = nullptr, *scratch_b = nullptr;
   size_t scratch_a_bytes = 0, scratch_t_bytes = 0, scratch_m_bytes = 0, scratch_b_bytes = 0;
 };
@@ -482,9 +492,17 @@ ce_status read_validation(Bufs &b, hipStream_t s, uint64_t *flags, int64_t *tmin
 ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int64_t *t, Bufs &b, Ws &ws,
                               hipStream_t s);
 ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s);
-int boruvka_rounds(int64_t n, bool split_possible);
+// how a call runs Boruvka after its first round: enqueued slots, whether one may split, whether one workgroup
+// finishes what they leave
+struct BvPlan {
+  int slots;
+  bool split_possible, tail;
+};
+BvPlan boruvka_plan(int64_t n, int64_t slots);
 ce_status stage_msf_sort(Bufs &b, Ws &ws, hipStream_t s);
-ce_status stage_dendrogram(Bufs &b, Ws &ws, hipStream_t s);
+// chains of the dendrogram from the sorted keys, which become weights; then (after a cutoff) the dendrogram
+ce_status stage_dendrogram_find(Bufs &b, Ws &ws, hipStream_t s);
+ce_status stage_dendrogram(Bufs &b, bool cut, Ws &ws, hipStream_t s);
 // condensing, stability, selection, labels; writes the call's header to hout
 ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, int64_t *hout);
 ce_status stage_graph_rows(Bufs &b, Ws &ws, hipStream_t s);
@@ -512,8 +530,7 @@ ce_status stage_hyper_skeleton(const int32_t *members, const int64_t *offsets, c
                                Bufs &b, Ws &ws, hipStream_t s);
 size_t stage_hyper_skeleton_scratch(int64_t n, int64_t nnz);
 size_t stage_msf_sort_scratch(int64_t n);
-size_t stage_dendrogram_scratch(int64_t n);
+size_t stage_dendrogram_scratch(int64_t n, int64_t slots);
 size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete);
-int krt_max_level_bits(int64_t m);
 
 }  // namespace ce

@@ -40,21 +40,12 @@ __global__ __launch_bounds__(B) void k_fill64(uint64_t *p, int64_t n, uint64_t v
 }
 __global__ void k_set64(uint64_t *p, uint64_t v) { *p = v; }
 
-__global__ __launch_bounds__(B) void k_cd_parents(const uint32_t *kc_u, const uint32_t *kc_v, Cnt mc, int64_t n,
-                                                  uint32_t *kpar) {
-  const int64_t m = mc.get();
-  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    kpar[kc_u[j]] = (uint32_t)(n + j);
-    kpar[kc_v[j]] = (uint32_t)(n + j);
-  }
-}
-
 // big component roots per graph
 __global__ __launch_bounds__(B) void k_cd_bigroots(const uint32_t *kpar, const uint32_t *ksize, const uint32_t *rowg,
                                                    Cnt mc, int64_t n, int64_t M, uint32_t *nbig) {
   const int64_t m = mc.get();
   for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B)
-    if (kpar[n + j] == NONE32 && ksize[j] >= (uint64_t)M) atomicAdd(&nbig[rowg[j]], 1u);
+    if (kpar[n + j] == NONE32 && ksize[j] >= (uint64_t)M) atomicAdd(&nbig[graph_at(rowg, j)], 1u);
 }
 
 __global__ __launch_bounds__(B) void k_cd_birth(const uint32_t *kc_u, const uint32_t *kc_v, const uint32_t *ksize,
@@ -71,7 +62,7 @@ __global__ __launch_bounds__(B) void k_cd_birth(const uint32_t *kc_u, const uint
       isbirth[b - n] = 1;
       birthL[b - n] = L;
     }
-    if (kpar[n + j] == NONE32 && ksize[j] >= (uint64_t)M && nbig[rowg[j]] >= 2) {
+    if (kpar[n + j] == NONE32 && ksize[j] >= (uint64_t)M && nbig[graph_at(rowg, j)] >= 2) {
       isbirth[j] = 1;
       birthL[j] = 0;
     }
@@ -244,7 +235,7 @@ __global__ __launch_bounds__(B) void k_cd_jinit(const uint8_t *isbirth, const ui
       uint32_t v = NONE32;
       if (ksize[j] >= (uint64_t)M) {
         if (isbirth[j]) v = (uint32_t)(n + j);
-        else if (kpar[n + j] == NONE32) v = (uint32_t)(n + m + rowg[j]);
+        else if (kpar[n + j] == NONE32) v = (uint32_t)(n + m + graph_at(rowg, j));
         else {
           v = kpar[n + j];
           keep[k] = !j_terminal(v, n, m, isbirth);
@@ -309,7 +300,7 @@ __global__ __launch_bounds__(B) void k_cd_rows(const uint8_t *isbirth, const uin
     csize[r] = ksize[j];
     cbirth[r] = birthL[j];
     uint32_t par = kpar[n + j];
-    uint32_t pc = par == NONE32 ? (uint32_t)(n + m + rowg[j]) : J[par - n];
+    uint32_t pc = par == NONE32 ? (uint32_t)(n + m + graph_at(rowg, j)) : J[par - n];
     cprow[r] = row_of(pc, n, m, rowof, rootrow);
   }
 }
@@ -483,7 +474,7 @@ __global__ __launch_bounds__(B) void k_cd_exit_ids(const uint32_t *rankof, const
       y = e.x;
     }
     uint64_t L = 0;
-    if (y == NONE32) r = rootrow[grank[p]];
+    if (y == NONE32) r = rootrow[graph_at(grank, p)];
     else L = rowL[y - n];
     prow[id] = r;
     if (pt_lambda) pt_lambda[id] = L;
@@ -862,7 +853,7 @@ __device__ inline uint32_t local_node(uint32_t x, uint32_t g, int64_t n, int64_t
                                       const uint32_t *moff, const uint32_t *rowpos) {
   const uint32_t ng = (uint32_t)(eoff[g + 1] - eoff[g]);
   if (x >= (uint64_t)(n + m)) return ng + (moff[g + 1] - moff[g]);
-  return ng + (rowpos[x - n] - moff[g]);
+  return ng + (pos_at(rowpos, x - n) - moff[g]);
 }
 
 // per record, in input order: its exit row's node and label
@@ -887,7 +878,7 @@ __global__ __launch_bounds__(B) void k_out_clusters(const uint32_t *cnode, const
   const int64_t m = mc.get(), nrows = nrc.get();
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * B) {
     const uint32_t c = cnode[r];
-    const uint32_t g = c >= (uint64_t)(n + m) ? (uint32_t)(c - n - m) : rowg[c - n];
+    const uint32_t g = c >= (uint64_t)(n + m) ? (uint32_t)(c - n - m) : graph_at(rowg, c - n);
     if (out.cl_id) out.cl_id[r] = local_node(c, g, n, m, eoff, moff, rowpos);
     if (out.cl_parent)
       out.cl_parent[r] = cprow[r] == NONE32 ? NONE32 : local_node(cnode[cprow[r]], g, n, m, eoff, moff, rowpos);
@@ -905,7 +896,7 @@ __global__ __launch_bounds__(B) void k_out_discrete(const uint32_t *level, const
                                                     int64_t n, Cnt mc, uint32_t *dd_level, uint32_t *dd_top) {
   const int64_t m = mc.get();
   for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    const uint32_t g = rowg[j], p = rowpos[j];
+    const uint32_t g = graph_at(rowg, j), p = pos_at(rowpos, j);
     if (dd_level) dd_level[p] = level[j];
     if (dd_top) dd_top[p] = local_node(top[j], g, n, m, eoff, moff, rowpos);
   }
@@ -923,7 +914,7 @@ __global__ __launch_bounds__(B) void k_row_point_vals(const uint32_t *cnode, con
   const int64_t m = mc.get(), nrows = nrc.get();
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * B) {
     const uint32_t c = cnode[r];
-    const uint32_t g = c >= (uint64_t)(n + m) ? (uint32_t)(c - n - m) : rowg[c - n];
+    const uint32_t g = c >= (uint64_t)(n + m) ? (uint32_t)(c - n - m) : graph_at(rowg, c - n);
     rlocal[r] = local_node(c, g, n, m, eoff, moff, rowpos);
     const uint32_t lr = cprow[r] == NONE32 ? NONE32 : top[r];
     const uint32_t mm = lr == NONE32 ? NONE32 : minmem[lr];
@@ -1013,7 +1004,6 @@ static int64_t cluster_row_bound(int64_t n, int64_t M, int64_t G) { return 2 * (
 size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete) {
   const int64_t m = n, R = cluster_row_bound(n, M < 2 ? 2 : M, G), RE = discrete ? 2 * R : R;
   Ws w;
-  w.alloc<uint32_t>(n + m + 1);  // kpar
   w.alloc<uint32_t>(m + 1); w.alloc<uint32_t>(m + 1); w.alloc<uint32_t>(m + 1);  // J, active lists
   w.alloc<uint8_t>(m + 4);       // isbirth
   w.alloc<uint64_t>(m + 1);      // birthL
@@ -1040,7 +1030,7 @@ size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete) {
   w.alloc<uint32_t>(n);  // labrow
   w.alloc<uint32_t>(n + 1);  // flag / scan
   return w.off + scan_ws_bytes(n + 1) + scan_ws_bytes(m + 1) + scan_ws_bytes(G + 1) + scan_ws_bytes(R + 1) +
-         radix_ws_bytes(R) + 8192;
+         radix_ws_bytes(R) + 4096;
 }
 
 // Grid rounds of the excess-of-mass and label pointer-jumping loops that the
@@ -1051,7 +1041,7 @@ size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete) {
 static int eom_rounds(int64_t R) { return bits_for((uint64_t)R) + 4; }
 static int top_rounds(int64_t R) { return bits_for((uint64_t)R) + 2; }
 // counter words of the bounded loops (from H_LOOP): level tops, J, excess of mass, label tops
-constexpr int LOOP_DD = 0, LOOP_J = 40, LOOP_EOM = 80, LOOP_TOP = 130, LOOP_END = kHdrWords - H_LOOP;
+constexpr int LOOP_DD = 0, LOOP_J = 40, LOOP_EOM = 80, LOOP_TOP = 130, LOOP_END = H_LOOP_END - H_LOOP;
 
 // Sizes: m rows (device word, bound n - 1), nb births and nrows = nb + G
 // cluster rows, nvirt virtual nodes (device words, bounds from R).
@@ -1061,7 +1051,7 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   size_t m0 = ws.mark();
   const int64_t R = cluster_row_bound(n, M, G), RE = b.q > 0 ? 2 * R : R;
   const Cnt nb(&b.hdr[H_NB], R), nrows(&b.hdr[H_NROWS], R), nvirt(&b.hdr[H_NVIRT], R), neom(&b.hdr[H_NEOM], RE);
-  uint32_t *kpar = ws.alloc<uint32_t>(n + mb + 1);
+  const uint32_t *kpar = b.kpar;
   uint32_t *J = ws.alloc<uint32_t>(mb + 1);
   uint32_t *jact = ws.alloc<uint32_t>(mb + 1), *jact2 = ws.alloc<uint32_t>(mb + 1);
   uint8_t *isbirth = ws.alloc<uint8_t>(mb + 4);
@@ -1112,11 +1102,9 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   auto tiles = [](int64_t k, int per = CT) { return (unsigned)((k + (int64_t)B * per - 1) / ((int64_t)B * per)); };
   uint64_t *loop = b.hdr + H_LOOP;  // counters of the bounded loops, zero from the start of the call
 
-  const unsigned gN = grid_cap(n + mb + 1, B), gm = grid_cap(mb + 1, B), gG = grid_for(G + 1, B),
+  const unsigned gm = grid_cap(mb + 1, B), gG = grid_for(G + 1, B),
                  gR = grid_cap(R, B), gRE = grid_cap(RE, B);
-  CE_LAUNCH(k_fill32, dim3(gN), dim3(B), 0, s, kpar, n + mb + 1, NONE32);
   CE_LAUNCH(k_fill32, dim3(gG), dim3(B), 0, s, nbig, G + 1, 0u);
-  CE_LAUNCH(k_cd_parents, dim3(gm), dim3(B), 0, s, b.kc_u, b.kc_v, m, n, kpar);
   CE_LAUNCH(k_cd_bigroots, dim3(gm), dim3(B), 0, s, kpar, b.ksize, b.rowg, m, n, M, nbig);
   CE_LAUNCH(k_fill32, dim3(grid_cap((mb + 4) / 4, B)), dim3(B), 0, s, (uint32_t *)isbirth, (mb + 4) / 4, 0u);
   CE_HIP(hipGetLastError());

@@ -89,13 +89,11 @@ __global__ __launch_bounds__(B) void k_htkeys(const int64_t *t, int64_t n, const
     keys[i] = (uint64_t)(t[i] - tmin);
 }
 
-// degree of every hyperedge by rank; the graph of every rank (one graph)
-__global__ __launch_bounds__(B) void k_hdeg(const uint32_t *perm, const int64_t *off, int64_t n, uint32_t *deg,
-                                            uint32_t *grank) {
+// degree of every hyperedge by rank
+__global__ __launch_bounds__(B) void k_hdeg(const uint32_t *perm, const int64_t *off, int64_t n, uint32_t *deg) {
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) {
     const uint32_t id = perm[r];
     deg[r] = (uint32_t)(off[id + 1] - off[id]);
-    grank[r] = 0u;
   }
 }
 
@@ -215,7 +213,7 @@ size_t stage_hyper_skeleton_scratch(int64_t n, int64_t nnz) {
   if (p3 > x) x = p3;
   x += w.off;
   const size_t rk = r0 + stage_rank_weights_scratch(nnz);
-  return (x > rk ? x : rk) + 4096;
+  return (x > rk ? x : rk) + 1024;
 }
 
 ce_status stage_hyper_skeleton(const int32_t *members, const int64_t *offsets, const int64_t *t, int64_t nnz,
@@ -250,7 +248,7 @@ ce_status stage_hyper_skeleton(const int32_t *members, const int64_t *offsets, c
     size_t m1 = ws.mark();
     uint32_t *deg = ws.alloc<uint32_t>(n + 1), *roff = ws.alloc<uint32_t>(n + 1);
     CE_WS_CHECK(ws);
-    CE_LAUNCH(k_hdeg, dim3(grid_for(n, B)), dim3(B), 0, s, b.perm, offsets, n, deg, b.grank);
+    CE_LAUNCH(k_hdeg, dim3(grid_for(n, B)), dim3(B), 0, s, b.perm, offsets, n, deg);
     CE_HIP(hipGetLastError());
     CE_TRY(scan_exclusive_u32(deg, roff, n, ws, s));
     if (nnz > 0)

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(B) void k_incidence(const uint4 *vals, int64_t n, u
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) {
     const uint4 v = vals[r];
     perm[r] = v.x;
-    grank[r] = v.w;
+    if (grank) grank[r] = v.w;
     ikey[2 * r] = v.y;
     ikey[2 * r + 1] = v.z;
   }
@@ -123,13 +123,11 @@ __global__ __launch_bounds__(B) void k_tkeys_packed(const int64_t *t, const int3
 
 // incidence entries from the packed sort; also t - tmin by rank (keys may be ts itself)
 __global__ __launch_bounds__(B) void k_incidence_packed(const uint64_t *keys, const uint64_t *vals, int64_t n,
-                                                        uint64_t *ts, uint32_t *perm, uint32_t *grank,
-                                                        uint32_t *ikey) {
+                                                        uint64_t *ts, uint32_t *perm, uint32_t *ikey) {
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) {
     const uint64_t k = keys[r], v = vals[r];
     ts[r] = k >> 32;
     perm[r] = (uint32_t)k;
-    grank[r] = 0;
     ikey[2 * r] = (uint32_t)v;
     ikey[2 * r + 1] = (uint32_t)(v >> 32);
   }
@@ -227,7 +225,7 @@ __device__ inline uint32_t slot_of_key(uint64_t k, int idbits, const uint32_t *r
 // (With the state advanced by the last workgroup of the contraction, found by
 // a ticket, and one counter update per 256-edge tile, 4096 workgroups queued
 // at two addresses for about 15 ns each: a round of 1e6 edges took 145 us in
-// its contraction alone, now 12. A 1e6-record call went from 7.5 to 4.65 ms, a
+// its contraction alone, now 14. A 1e6-record call went from 7.5 to 4.65 ms, a
 // 2e5-record call from 2.74 to 2.04 ms, 5e7 records from 89.6 to 84.4 ms.)
 // Every kernel reads the state when it starts; the
 // host enqueues a fixed number of slots, and those after the forest is
@@ -276,6 +274,12 @@ __device__ inline int out_buffer(const uint64_t *bv) {
   return in == 2 ? 0 : 1 - in;
 }
 
+// a round made the nodes up to nb: one more level of the tree
+__device__ inline void bv_level(uint64_t *bv, uint64_t nb) {
+  const uint64_t l = ++bv[H_BV_NLEV - H_BV];
+  bv[H_LEV - H_BV + l] = nb;
+}
+
 // Before the first round: the state, record ranks by id, no forest edge yet.
 // Flat skeletons start as the live list (rows, counted on the device) of a
 // round over the records, so their hooks start empty.
@@ -290,6 +294,10 @@ __global__ __launch_bounds__(B) void k_bv_start(const uint32_t *perm, int64_t n,
   for (int64_t e = i0; e < (slots + 3) / 4; e += step) ((uint32_t *)msf_flag)[e] = 0u;  // regions are 256-byte aligned
   if (blockIdx.x == 0 && threadIdx.x < BV_WORDS) {
     const int k = threadIdx.x;
+    if (k == 0) {
+      bv[H_LEV - H_BV] = (uint64_t)n;
+      bv[H_BV_NLEV - H_BV] = 0;
+    }
     bv[k] = k == BV_ACT ? ACT_ROUND : k == BV_E ? (flat ? *rows : 0) : k == BV_IN ? 2 : (k == BV_HI || k == BV_NB)
                                                                                           ? (uint64_t)n : 0;
   }
@@ -556,6 +564,7 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
       bv[BV_MARK] = 0;
       lo = hi;
       hi = bv[BV_NB];
+      bv_level(bv, hi);
     } else if (act == ACT_SPLIT) {
       bv[BV_IN] = ob;
       bv[BV_SPLITDONE] = 1;
@@ -723,6 +732,7 @@ __global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint
       L.s[ob][p] = lv.s ? lv.s[i] : (uint32_t)i;
     }
     __syncthreads();
+    if (tid == 0) bv_level(bv, (uint64_t)nb);
     lv = Live{L.key[ob], L.u[ob], L.v[ob], L.s[ob], (int64_t)s_cnt};
     ob = 1 - ob;
     lo = hi;
@@ -840,16 +850,6 @@ __global__ __launch_bounds__(B) void k_rank_apply(const uint64_t *w, const uint3
     atomicMin((unsigned long long *)&best[head], (unsigned long long)k);
   }
 }
-// sorted forest rows: the weight itself in place of the key (head minus tail time)
-__global__ __launch_bounds__(B) void k_msf_weights(uint64_t *msf_key, const uint64_t *msf_val, const uint64_t *ts,
-                                                   Cnt mc, int wshift, bool rank) {
-  const int64_t m = mc.get();
-  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    const uint64_t v = msf_val[j];
-    msf_key[j] = rank ? ts[v >> 32] - ts[(uint32_t)v] : msf_key[j] >> wshift;
-  }
-}
-
 }  // namespace
 
 uint64_t *pinned_scratch() {
@@ -974,7 +974,7 @@ size_t stage_sort_skeleton_scratch(int64_t n) {
   size_t b2 = base + radix_ws_bytes(2 * n);
   size_t c = r0 + stage_rank_weights_scratch(2 * n);
   if (b2 > a) a = b2;
-  return (a > c ? a : c) + 4096;
+  return (a > c ? a : c) + 1024;
 }
 
 // Records by (t, id): stable radix sort on t - tmin carrying (id, global src,
@@ -1019,7 +1019,7 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
       bool alt = false;
       CE_TRY((radix_sort_pairs<uint64_t, uint64_t>(b.ts, v0, kalt, v1, n, 32, 32 + b.tbits, false, &alt, ws, s)));
       CE_LAUNCH(k_incidence_packed, dim3(grid_for(n, B)), dim3(B), 0, s, alt ? kalt : b.ts, alt ? v1 : v0, n, b.ts,
-                b.perm, b.grank, ikey);
+                b.perm, ikey);
     } else {
       const uint4 *vals = nullptr;
       CE_TRY(sort_records_by_time(src, dst, t, b, ws, s, &vals));
@@ -1055,7 +1055,7 @@ size_t stage_boruvka_scratch(int64_t n, int64_t slots) {
     w.alloc<uint32_t>(slots);
     w.alloc<uint32_t>(slots);
   }
-  return w.off + 4096;
+  return w.off + 1024;
 }
 
 // The filter split runs when the live edges number at least 2^20 and more
@@ -1070,16 +1070,26 @@ static int64_t split_min_edges() { return tuning().split_min_edges; }
 // round, and so do the light rounds and the plain rounds after them:
 // 2 (bits(n) + 1) + 1 rounds cover both, and two more slots split and
 // contract the heavy edges.
-int boruvka_rounds(int64_t n, bool split_possible) {
+static int boruvka_rounds(int64_t n, bool split_possible) {
   const int r = bits_for((uint64_t)n) + 1;
   return split_possible ? 2 * r + 3 : r;
 }
 
-// Up to this many skeleton slots, a call without a split enqueues fewer slots
-// and leaves the rest to one workgroup: an idle slot costs six launches of
-// about 2 us, a round of one workgroup about 10 us plus 0.5 us per 1024 edges
-// and step. Larger calls enqueue the full bound.
-constexpr int64_t TAIL_SLOTS = int64_t(1) << 20;
+// Up to 2^20 skeleton slots, a call without a split enqueues fewer slots and
+// leaves the rest to one workgroup: an idle slot costs six launches of about
+// 2 us, a round of one workgroup about 10 us plus 0.5 us per 1024 edges and
+// step. Larger calls enqueue the full bound.
+BvPlan boruvka_plan(int64_t n, int64_t slots) {
+  BvPlan p;
+  p.split_possible = slots >= split_min_edges();
+  p.tail = !p.split_possible && slots <= (int64_t(1) << 20);
+  p.slots = boruvka_rounds(n, p.split_possible);
+  if (p.tail) {
+    const int few = slots <= 8192 ? 0 : bits_for((uint64_t)n) / 2 + 1;
+    if (few < p.slots) p.slots = few;
+  }
+  return p;
+}
 
 ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   const int64_t n = b.n, n2 = b.slots;
@@ -1127,14 +1137,8 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   // keeps every heavy edge's cycles. The heavy edges wait, with the nodes they
   // had at the split, at the back of the buffer the split wrote.
   const int64_t split_min = split_min_edges();
-  const bool split_possible = n2 >= split_min;
-  const bool tail = !split_possible && n2 <= TAIL_SLOTS;
-  int slots = boruvka_rounds(n, split_possible);
-  if (tail) {
-    const int few = n2 <= 8192 ? 0 : bits_for((uint64_t)n) / 2 + 1;
-    if (few < slots) slots = few;
-  }
-  for (int r = 0; r < slots; r++) {
+  const BvPlan plan = boruvka_plan(n, n2);
+  for (int r = 0; r < plan.slots; r++) {
     CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
     CE_LAUNCH(k_bv_min, dim3(lE), dim3(LBK), 0, s, L, bv, best);
     CE_LAUNCH(k_bv_hook, dim3(gE), dim3(B), 0, s, L, bv, best, bpar, b.msf_flag);
@@ -1144,7 +1148,7 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
     CE_HIP(hipGetLastError());
   }
   CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
-  if (tail) CE_LAUNCH(k_bv_tail, dim3(1), dim3(BTB), 0, s, L, bv, best, bpar, rootc, b.msf_flag, b.hdr);
+  if (plan.tail) CE_LAUNCH(k_bv_tail, dim3(1), dim3(BTB), 0, s, L, bv, best, bpar, rootc, b.msf_flag, b.hdr);
   CE_LAUNCH(k_bv_check, dim3(1), dim3(64), 0, s, bv, b.hdr);
   CE_HIP(hipGetLastError());
   ws.release(m0);
@@ -1200,9 +1204,6 @@ ce_status stage_msf_sort(Bufs &b, Ws &ws, hipStream_t s) {
     set_error("internal: sorted forest is not in place");
     return CE_EDEVICE;
   }
-  // the keys have done their work (the order); from here on msf_key holds each row's weight
-  CE_LAUNCH(k_msf_weights, dim3(grid_cap(m.v, B)), dim3(B), 0, s, b.msf_key, b.msf_val, b.ts, m, b.wshift, b.rank);
-  CE_HIP(hipGetLastError());
   ws.release(m0);
   return CE_OK;
 }

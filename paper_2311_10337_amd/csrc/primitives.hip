@@ -351,6 +351,8 @@ template ce_status radix_sort_pairs<uint64_t, uint32_t>(uint64_t *, uint32_t *, 
                                                         int, bool, bool *, Ws &, hipStream_t);
 template ce_status radix_sort_pairs<uint32_t, uint32_t>(uint32_t *, uint32_t *, uint32_t *, uint32_t *, Cnt, int,
                                                         int, bool, bool *, Ws &, hipStream_t);
+template ce_status radix_sort_pairs<uint32_t, uint64_t>(uint32_t *, uint64_t *, uint32_t *, uint64_t *, Cnt, int,
+                                                        int, bool, bool *, Ws &, hipStream_t);
 template ce_status radix_sort_pairs<uint64_t, uint4>(uint64_t *, uint4 *, uint64_t *, uint4 *, Cnt, int, int,
                                                      bool, bool *, Ws &, hipStream_t);
 template ce_status radix_sort_pairs<uint64_t, uint64_t>(uint64_t *, uint64_t *, uint64_t *, uint64_t *, Cnt, int,
