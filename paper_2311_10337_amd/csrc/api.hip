@@ -59,12 +59,12 @@ namespace {
 
 constexpr int B = 256;
 
-// graph of each MSF row (the graph of its tail record)
-__global__ __launch_bounds__(B) void k_rowg(const uint64_t *msf_val, const uint32_t *grank, Cnt mc, uint32_t *rowg,
-                                            uint32_t *key) {
+// graph of each MSF row (the graph of its tail record; the offsets stay in the caches)
+__global__ __launch_bounds__(B) void k_rowg(const uint64_t *msf_val, const int64_t *eoff, int64_t G, Cnt mc,
+                                            uint32_t *rowg, uint32_t *key) {
   const int64_t m = mc.get();
   for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    const uint32_t g = grank[(uint32_t)msf_val[j]];
+    const uint32_t g = graph_of(eoff, G, (uint32_t)msf_val[j]);
     rowg[j] = g;
     key[j] = g;
   }
@@ -81,29 +81,24 @@ __global__ __launch_bounds__(B) void k_rowpos(const uint32_t *sorted_j, Cnt mc, 
     rowpos[sorted_j[p]] = (uint32_t)p;
 }
 
-// A record that is a child of row j joins at row j, so it is one of that row's
-// two endpoints: its input id comes from the row itself (no gathers). Row j is
-// written at its position in the batch, with its graph's local ids.
-__global__ __launch_bounds__(B) void k_rows(const uint64_t *msf_w, const uint64_t *msf_val, const uint32_t *perm,
-                                            const uint32_t *kc_u,
+// Row j is written at its position in the batch, with its graph's local ids.
+__global__ __launch_bounds__(B) void k_rows(const uint64_t *msf_w, const uint64_t *msf_val, const uint32_t *kc_u,
                                             const uint32_t *kc_v, const uint32_t *ksize, const uint32_t *rowg,
                                             const uint32_t *rowpos, const uint32_t *moff, const int64_t *eoff,
                                             Cnt mc, int64_t n, bool one, ce_result out) {
   const int64_t m = mc.get();
   for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
     const uint64_t v = msf_val[j];
-    const uint32_t tr = (uint32_t)v;
     const int64_t w = (int64_t)msf_w[j];
     // one graph: rows stay in place and local ids are the internal ones
     const uint32_t g = one ? 0u : rowg[j], p = one ? (uint32_t)j : rowpos[j], m0 = one ? 0u : moff[g];
     const uint32_t e0 = one ? 0u : (uint32_t)eoff[g], ng = one ? (uint32_t)n : (uint32_t)(eoff[g + 1] - eoff[g]);
-    const uint32_t tid = perm[tr] - e0, hid = perm[v >> 32] - e0;
-    if (out.msf_tail) out.msf_tail[p] = tid;
-    if (out.msf_head) out.msf_head[p] = hid;
+    if (out.msf_tail) out.msf_tail[p] = (uint32_t)v - e0;
+    if (out.msf_head) out.msf_head[p] = (uint32_t)(v >> 32) - e0;
     if (out.msf_w) out.msf_w[p] = w;
     const uint32_t a = kc_u[j], b = kc_v[j];
-    const uint32_t fa = a < (uint64_t)n ? (a == tr ? tid : hid) : (one ? a : ng + (rowpos[a - n] - m0));
-    const uint32_t fb = b < (uint64_t)n ? (b == tr ? tid : hid) : (one ? b : ng + (rowpos[b - n] - m0));
+    const uint32_t fa = one ? a : a < (uint64_t)n ? a - e0 : ng + (rowpos[a - n] - m0);
+    const uint32_t fb = one ? b : b < (uint64_t)n ? b - e0 : ng + (rowpos[b - n] - m0);
     if (out.sl_left) out.sl_left[p] = fa < fb ? fa : fb;
     if (out.sl_right) out.sl_right[p] = fa < fb ? fb : fa;
     if (out.sl_w) out.sl_w[p] = w;
@@ -158,7 +153,7 @@ ce_status stage_graph_rows(Bufs &b, Ws &ws, hipStream_t s) {
   uint32_t *key = ws.alloc<uint32_t>(mb), *val = ws.alloc<uint32_t>(mb);
   uint32_t *key2 = ws.alloc<uint32_t>(mb), *val2 = ws.alloc<uint32_t>(mb);
   CE_WS_CHECK(ws);
-  CE_LAUNCH(k_rowg, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_val, b.grank, m, b.rowg, key);
+  CE_LAUNCH(k_rowg, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_val, b.eoff, G, m, b.rowg, key);
   CE_HIP(hipGetLastError());
   bool alt = false;
   CE_TRY((radix_sort_pairs<uint32_t, uint32_t>(key, val, key2, val2, m, 0, bits_for((uint64_t)(G - 1)), true, &alt, ws,
@@ -172,7 +167,7 @@ ce_status stage_graph_rows(Bufs &b, Ws &ws, hipStream_t s) {
 
 ce_status stage_write_rows(Bufs &b, const ce_result *out, hipStream_t s) {
   const int64_t mb = b.n > 1 ? b.n - 1 : 1;
-  CE_LAUNCH(k_rows, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_key, b.msf_val, b.perm, b.kc_u, b.kc_v, b.ksize,
+  CE_LAUNCH(k_rows, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_key, b.msf_val, b.kc_u, b.kc_v, b.ksize,
             b.rowg, b.rowpos, b.moff, b.eoff, Cnt(&b.hdr[H_M], mb), b.n, b.G == 1, *out);
   CE_HIP(hipGetLastError());
   return CE_OK;
@@ -195,8 +190,6 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   b.eoff = ws.alloc<int64_t>(G + 1);
   b.voff = ws.alloc<int64_t>(G + 1);
   b.perm = ws.alloc<uint32_t>(n);
-  if (G > 1) b.grank = ws.alloc<uint32_t>(n);
-  b.rankof = ws.alloc<uint32_t>(n);
   const size_t base = ws.off;
   b.ts = ws.alloc<uint64_t>(n);
   b.skel_key = ws.alloc<uint64_t>(slots);
@@ -219,9 +212,7 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   size_t x = nnz >= 0 ? 0 : stage_causal_skeleton_scratch(n);
   if (x > scr_a) scr_a = x;
   const size_t scr_t = stage_boruvka_scratch(n, slots);
-  size_t scr_m = stage_msf_sort_scratch(n);
-  x = stage_dendrogram_scratch(n, slots);
-  if (x > scr_m) scr_m = x;
+  const size_t scr_m = stage_dendrogram_scratch(n, slots);
   size_t scr_b = stage_graph_rows_scratch(n, G);
   x = stage_condense_scratch(n, M, G, discrete);
   if (x > scr_b) scr_b = x;
@@ -233,6 +224,7 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
   ws.off = base + phase - ybytes;
   b.msf_key = ws.alloc<uint64_t>(n);
   b.msf_val = ws.alloc<uint64_t>(n);
+  b.kpar = ws.alloc<uint32_t>(2 * n);  // (the rows' half and the three arrays behind it: see carve in dendrogram.hip)
   b.kc_u = ws.alloc<uint32_t>(n);
   b.kc_v = ws.alloc<uint32_t>(n);
   b.ksize = ws.alloc<uint32_t>(n);
@@ -240,7 +232,6 @@ static void layout(Bufs &b, Ws &ws, int64_t n, int64_t M, int64_t G, bool discre
     b.rowg = ws.alloc<uint32_t>(n);
     b.rowpos = ws.alloc<uint32_t>(n);
   }
-  b.kpar = ws.alloc<uint32_t>(2 * n);
   b.moff = ws.alloc<uint32_t>(G + 1);
   char *pb = ws.base ? ws.base + base : nullptr;
   b.scratch_a = pb ? pb + xbytes : nullptr;
@@ -532,6 +523,7 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
   b.V = V;
   b.M = c.M;
   b.G = G;
+  b.t = c.t;
   int64_t *hout = sync ? b.outhdr : hdr_out;
   // offsets and thresholds reach the device without host staging (a call may be captured in a graph)
   if (c.eoff_d) {
@@ -611,8 +603,7 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
     else if (c.causal) CE_TRY(stage_causal_skeleton(c.src, c.dst, c.t, b, wa, s));
     else CE_TRY(stage_sort_skeleton(c.src, c.dst, c.t, b, wa, s));
     CE_TRY(stage_boruvka(b, wt, s));
-    CE_TRY(stage_msf_sort(b, wm, s));
-    CE_TRY(stage_dendrogram_find(b, wm, s));
+    CE_TRY(stage_rows(b, wm, s));
     if (max_dt >= 0) CE_TRY(stage_time_filter(b, max_dt, s));
     CE_TRY(stage_dendrogram(b, max_dt >= 0, wm, s));
     CE_TRY(stage_graph_rows(b, wb, s));

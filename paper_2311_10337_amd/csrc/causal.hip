@@ -47,11 +47,10 @@ __global__ __launch_bounds__(B) void k_run_starts(const uint32_t *f, const uint3
 // side 1 = in-entry (at the head vertex), 0 = out-entry (at the tail vertex)
 __global__ __launch_bounds__(B) void k_causal_entries(const uint4 *vals, const uint32_t *f, const uint32_t *fx,
                                                       const uint32_t *start, int64_t n, uint32_t *perm,
-                                                      uint32_t *grank, uint32_t *ikey, uint32_t *ival) {
+                                                      uint32_t *ikey, uint32_t *ival) {
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) {
     const uint4 v = vals[r];
     perm[r] = v.x;
-    if (grank) grank[r] = v.w;
     const uint32_t run = fx[r] + f[r] - 1;
     const int64_t g0 = start[run], g1 = start[run + 1];
     const int64_t pin = 2 * g0 + (r - g0), pout = 2 * g0 + (g1 - g0) + (r - g0);
@@ -262,7 +261,7 @@ ce_status stage_causal_skeleton(const int32_t *src, const int32_t *dst, const in
     CE_HIP(hipGetLastError());
     CE_TRY(scan_exclusive_u32(f, fx, n, ws, s));
     CE_LAUNCH(k_run_starts, dim3(grid_for(n, B)), dim3(B), 0, s, f, fx, n, start);
-    CE_LAUNCH(k_causal_entries, dim3(grid_for(n, B)), dim3(B), 0, s, vals, f, fx, start, n, b.perm, b.grank, ikey,
+    CE_LAUNCH(k_causal_entries, dim3(grid_for(n, B)), dim3(B), 0, s, vals, f, fx, start, n, b.perm, ikey,
               ival);
     CE_HIP(hipGetLastError());
     ws.release(m1);

@@ -216,7 +216,7 @@ __host__ __device__ inline uint32_t graph_of(const int64_t *eoff, int64_t G, int
   return (uint32_t)lo;
 }
 
-// graph of record or row i, output position of row i (null for one graph)
+// graph and output position of row i (null for one graph)
 __device__ inline uint32_t graph_at(const uint32_t *g, int64_t i) { return g ? g[i] : 0u; }
 __device__ inline uint32_t pos_at(const uint32_t *pos, int64_t i) { return pos ? pos[i] : (uint32_t)i; }
 
@@ -427,16 +427,16 @@ namespace ce {
 
 // ---------------------------------------------------------------- pipeline
 // Device buffers of one clustering call, carved from the workspace.
-// Internal record ids are RANKS in the record order (t, id): rank r is the
-// r-th record by time; perm[r] is its input id.
+// Up to the forest, records go by their RANKS in the record order (t, id):
+// rank r is the r-th record by time; perm[r] is its input id. From the sorted
+// rows on they go by input id.
 struct Bufs {
   int64_t n = 0, V = 0, M = 0;
   // batch of G independent graphs packed as a disjoint union: graph g owns
   // records [eoff[g], eoff[g+1]) and vertices [voff[g], voff[g+1]) (device copies)
   int64_t G = 1;
   const int64_t *eoff = nullptr, *voff = nullptr;
-  // (one graph has none of these three: every graph index is 0, every row stays in place)
-  uint32_t *grank = nullptr;    // [n] graph of each record, by rank
+  // (one graph has neither of these two: every graph index is 0, every row stays in place)
   uint32_t *rowg = nullptr;     // [n] graph of each MSF row
   uint32_t *rowpos = nullptr;   // [n] output position of each MSF row (graphs in order, rows in key order)
   uint32_t *moff = nullptr;     // [G+1] first output row of each graph
@@ -455,24 +455,24 @@ struct Bufs {
   // discrete dendrogram (Alg. 5): q thresholds on the device, 0 = exact
   const int64_t *thr = nullptr;
   int q = 0;
-  int64_t tmin = 0;
+  const int64_t *t = nullptr;   // the input times
   // persistent
   uint64_t *hdr = nullptr;      // [kHdrWords] the call's control block (H_* words)
   int64_t *outhdr = nullptr;    // [CE_HDR_WORDS(G)] the call's header (read back by synchronous calls)
   uint64_t *ts = nullptr;       // [n] t - tmin by rank
   uint32_t *perm = nullptr;     // [n] rank -> input id
-  uint32_t *rankof = nullptr;   // [n] input id -> rank (from the MSF stage on)
   uint64_t *skel_key = nullptr; // [slots] slot 2h+s: key of the skeleton edge whose head is rank h
   uint32_t *skel_tail = nullptr;// [slots] tail rank of that edge or NONE
   uint32_t *skel_tid = nullptr; // [slots] input id of that tail (flat: the head rank)
   uint64_t *best = nullptr;     // [2n] Boruvka tree: minimum key leaving each node (the last array of X; the
                                 // second half lies in the tree's own region)
   uint32_t *bpar = nullptr;     // [2n] Boruvka tree: parent of each node
-  uint8_t *msf_flag = nullptr;  // [slots]
+  uint8_t *msf_flag = nullptr;  // [slots] nonzero: a forest edge (MSF_* bits)
   uint64_t *msf_key = nullptr;  // [n] sorted MSF keys
-  uint64_t *msf_val = nullptr;  // [n] tail rank | head rank << 32; the head's id is in the key
-  uint32_t *kc_u = nullptr, *kc_v = nullptr, *ksize = nullptr; // [n] dendrogram children (internal labels) and size
-  uint32_t *kpar = nullptr;     // [2n] dendrogram parent of each record and row, NONE without one
+  uint64_t *msf_val = nullptr;  // [n] tail id | head id << 32
+  // the dendrogram: node x < n is the record with input id x, node n + j row j
+  uint32_t *kpar = nullptr;     // [2n] parent of each node, NONE without one
+  uint32_t *kc_u = nullptr, *kc_v = nullptr, *ksize = nullptr; // [n] children and size of each row
   // scratch arenas: A for grouping, skeleton and Boruvka (it may overlap the
   // MSF/dendrogram arrays, which are not live yet), T for Boruvka, M for sorting
   // the MSF and the dendrogram, B for condensing (it overlaps the dead skeleton arrays)
@@ -483,6 +483,9 @@ struct Bufs {
 // host pinned staging for small readbacks (per thread)
 uint64_t *pinned_scratch();
 ce_status read_u64(const uint64_t *dev, uint64_t *host_out, int count, hipStream_t s);
+
+// msf_flag: an edge of the forest; one of the first round on records, chosen by its head, by its tail
+enum : uint8_t { MSF_EDGE = 1, MSF_FIRST = 2, MSF_HEAD = 4, MSF_TAIL = 8 };
 
 // Stages. Sizes that depend on the data (forest rows, births, list lengths)
 // are device words of the control block; the stages enqueue work only.
@@ -499,9 +502,9 @@ struct BvPlan {
   bool split_possible, tail;
 };
 BvPlan boruvka_plan(int64_t n, int64_t slots);
-ce_status stage_msf_sort(Bufs &b, Ws &ws, hipStream_t s);
-// chains of the dendrogram from the sorted keys, which become weights; then (after a cutoff) the dendrogram
-ce_status stage_dendrogram_find(Bufs &b, Ws &ws, hipStream_t s);
+// the forest's rows sorted by key, with their weights and the chains of the dendrogram; then (after a cutoff) the
+// dendrogram itself
+ce_status stage_rows(Bufs &b, Ws &ws, hipStream_t s);
 ce_status stage_dendrogram(Bufs &b, bool cut, Ws &ws, hipStream_t s);
 // condensing, stability, selection, labels; writes the call's header to hout
 ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, int64_t *hout);
@@ -529,7 +532,6 @@ ce_status stage_hyper_validate(const int32_t *members, const int64_t *offsets, c
 ce_status stage_hyper_skeleton(const int32_t *members, const int64_t *offsets, const int64_t *t, int64_t nnz,
                                Bufs &b, Ws &ws, hipStream_t s);
 size_t stage_hyper_skeleton_scratch(int64_t n, int64_t nnz);
-size_t stage_msf_sort_scratch(int64_t n);
 size_t stage_dendrogram_scratch(int64_t n, int64_t slots);
 size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete);
 

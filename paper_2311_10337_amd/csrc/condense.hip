@@ -2,7 +2,7 @@
 // stability, excess-of-mass selection and labels (Alg. 1 steps 4-5, with the
 // HDBSCAN semantics of Campello et al. 2013 to which the paper defers).
 //
-// Node space: records are ranks [0,n), row j of the sorted MSF is node n+j,
+// Node space: records are input ids [0,n), row j of the sorted MSF is node n+j,
 // the virtual root is n+m. A node is "big" if its size >= M.
 //  - birth nodes: both children of a row whose two children are big; and the
 //    big component roots of a graph when it has at least two of them. A
@@ -457,14 +457,13 @@ __global__ __launch_bounds__(B) void k_cd_walk_words(const uint32_t *kpar, const
 // subtrees (fewer than M records, so fewer than M steps) to the first big
 // row y; it leaves the cluster of y at lambda_y, or its graph's root at 0 when
 // no big row is above it. Writes the exit cluster row and the exit lambda.
-__global__ __launch_bounds__(B) void k_cd_exit_ids(const uint32_t *rankof, const uint32_t *kpar, const uint2 *wk,
-                                                   const uint64_t *rowL, const uint32_t *grank,
-                                                   const uint32_t *rootrow, int64_t n, int64_t M, uint32_t *prow,
-                                                   const uint64_t *hdr, uint64_t *pt_lambda) {
+__global__ __launch_bounds__(B) void k_cd_exit_ids(const uint32_t *kpar, const uint2 *wk, const uint64_t *rowL,
+                                                   const int64_t *eoff, int64_t G, const uint32_t *rootrow, int64_t n,
+                                                   int64_t M, uint32_t *prow, const uint64_t *hdr,
+                                                   uint64_t *pt_lambda) {
   if (hdr[H_STATUS] != 0) pt_lambda = nullptr;  // a data error: no output is written
   for (int64_t id = (int64_t)blockIdx.x * B + threadIdx.x; id < n; id += (int64_t)gridDim.x * B) {
-    const uint32_t p = rankof[id];
-    uint32_t y = kpar[p], r = NONE32;
+    uint32_t y = kpar[id], r = NONE32;
     while (y != NONE32) {
       const uint2 e = wk[y - n];
       if (e.y >= (uint64_t)M) {
@@ -474,7 +473,7 @@ __global__ __launch_bounds__(B) void k_cd_exit_ids(const uint32_t *rankof, const
       y = e.x;
     }
     uint64_t L = 0;
-    if (y == NONE32) r = rootrow[graph_at(grank, p)];
+    if (y == NONE32) r = rootrow[G > 1 ? graph_of(eoff, G, id) : 0u];
     else L = rowL[y - n];
     prow[id] = r;
     if (pt_lambda) pt_lambda[id] = L;
@@ -1162,7 +1161,7 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   uint32_t *prow = labrow;
   uint2 *wk = (uint2 *)exl;  // m <= n words of 8 bytes
   CE_LAUNCH(k_cd_walk_words, dim3(gm), dim3(B), 0, s, kpar, b.ksize, J, rowmap, rootrow, n, m, M, wk);
-  CE_LAUNCH(k_cd_exit_ids, dim3(grid_cap(n, B)), dim3(B), 0, s, b.rankof, kpar, wk, rowL, b.grank, rootrow, n, M,
+  CE_LAUNCH(k_cd_exit_ids, dim3(grid_cap(n, B)), dim3(B), 0, s, kpar, wk, rowL, b.eoff, G, rootrow, n, M,
             prow, b.hdr, out->pt_lambda);
   CE_LAUNCH(k_cd_acc_children, dim3((unsigned)((R + B - 1) / B)), dim3(B), 0, s, csize, cbirth, cprow, nrows, acc);
   CE_LAUNCH(k_cd_stab, dim3(gR), dim3(B), 0, s, acc, csize, cbirth, nrows, shi, slo);

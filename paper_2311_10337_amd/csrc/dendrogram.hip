@@ -1,4 +1,5 @@
-// Stage A7: exact single-linkage dendrogram from the sorted MSF (Alg. 1 step 3).
+// Stages A6-A7: the sorted MSF and its exact single-linkage dendrogram (Alg. 1
+// steps 2 and 3).
 //
 // The paper builds the dendrogram with a union-find pass over the sorted MST
 // edges and calls that pass an expensive serial operation (Sec. 3). Here it is
@@ -25,10 +26,11 @@
 // A row with e > best(S) for every S below the top ends in the top's chain.
 //
 // Steps: find every row's chain and chooser (two climbs of a few steps, for
-// most rows one), sort the rows by chain (stable, rows are in order), add up
+// most rows one, made before the rows are sorted by key), sort the rows by
+// chain (stable, rows are in order), add up
 // chain sizes level by level (a chooser's chain is of an earlier round), one
 // prefix sum over all rows, and write every row's node. All of it is gathers
-// over the rows and a handful of streaming passes: 15.6 ms at 5e7 rows, the
+// over the rows and a handful of streaming passes: 12.7 ms at 5e7 rows, the
 // parents included, where interval halving with a union-find took 35.0 ms
 // (768 dependent steps of two 20 us launches, a reset, an LDS stage, and a
 // scatter for the parents); 0.2 ms against 0.55 at 7e4 rows.
@@ -48,41 +50,109 @@ __global__ __launch_bounds__(B) void k_dn_init(uint32_t *kpar, int64_t n, uint32
   }
 }
 
-// Per sorted row: the node where its ends meet, who chose it, its chain, and
-// its weight in place of its key (the keys have done their work: the order).
-// up[S] = the row best(S) of an inner node, kpar = that of a record; mate[S] =
-// the second chooser of a chain's first row. Bound by the random reads of the
-// climbs (two parents and two minima for a row chosen in the first round).
-__global__ __launch_bounds__(B) void k_dn_find(uint64_t *msf_key, const uint64_t *msf_val, const uint64_t *ts,
-                                               const uint64_t *best, const uint32_t *bpar, int64_t n, Cnt mc,
-                                               int wshift, bool rank, uint32_t *chain, uint64_t *pick, uint32_t *kpar,
-                                               uint32_t *up, uint32_t *mate, uint64_t *hdr) {
-  const int64_t m = mc.get();
-  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    const uint64_t key = msf_key[j], v = msf_val[j];
-    uint32_t x = (uint32_t)v, y = (uint32_t)(v >> 32), cx = x, cy = y;
-    msf_key[j] = rank ? ts[y] - ts[x] : key >> wshift;
-    // parents have larger ids than their children, so the smaller end climbs
-    int steps = 0;
-    while (x != y && steps < 512) {
-      if (x < y) { cx = x; x = bpar[x]; }
-      else { cy = y; y = bpar[y]; }
-      steps++;
+__global__ __launch_bounds__(LBK) void k_msf_list(const uint8_t *flag, int64_t n2, uint32_t *out,
+                                                  unsigned long long *cnt) {
+  const int ct = list_items(n2);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < n2; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(n2, tile, LBK * ct);
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      const int64_t e = base + (int64_t)k * LBK;
+      keep[k] = e < end && flag[e];
     }
-    const bool px = best[cx] == key, py = best[cy] == key;
+    list_positions(keep, pos, cnt);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) out[pos[k]] = (uint32_t)(base + (int64_t)k * LBK);
+  }
+}
+
+// a forest has at most n - 1 rows; more means the call failed (and the rows
+// are dropped, so that later kernels stay in bounds)
+__global__ void k_check_rows(uint64_t *hdr, int64_t n) {
+  if (threadIdx.x == 0 && (int64_t)hdr[H_M] > (n > 1 ? n - 1 : 0)) {
+    hdr[H_STATUS] |= 64;
+    hdr[H_M] = 0;
+  }
+}
+
+// Per forest edge, in slot order: its key, and in one 16-byte record its ends'
+// input ids, its chain (with bit 31 when both sides chose it) and who chose
+// it (a record by its input id); mate[S] = the second chooser of a chain's
+// first row. The climbs go from the two ends to the node where they meet and
+// on to the chain; an edge of the first round, three in four, says who chose
+// it, and its ends meet at the parent of its head, which is the next in line.
+// Bound by the reads that are not: the tails' ids and the chains' minima.
+// 3.2 ms at 5e7 rows (made after the sort, the climbs took 9.5).
+constexpr uint32_t MUTUAL = 0x80000000u;
+__global__ __launch_bounds__(B) void k_dn_gather(const uint32_t *list, Cnt mc, const uint8_t *flag,
+                                                 const uint64_t *skel_key, const uint32_t *skel_tail,
+                                                 const uint32_t *skel_head, bool flat, const uint32_t *perm,
+                                                 const uint64_t *best, const uint32_t *bpar, int64_t n, uint64_t *okey,
+                                                 uint4 *rec, uint32_t *mate, uint64_t *hdr) {
+  const int64_t m = mc.get();
+  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < m; i += (int64_t)gridDim.x * B) {
+    const uint32_t e = list[i], f = flag[e];
+    const uint64_t key = skel_key[e];
+    uint32_t x = skel_tail[e], y = flat ? skel_head[e] : e >> 1, cx = x, cy = y;
+    const uint32_t tid = perm[x], hid = perm[y];
+    okey[i] = key;
+    bool px, py;
+    if (f & MSF_FIRST) {
+      px = (f & MSF_TAIL) != 0;
+      py = (f & MSF_HEAD) != 0;
+      x = y = bpar[y];
+      cx = tid;
+      cy = hid;
+    } else {
+      // parents have larger ids than their children, so the smaller end climbs
+      for (int steps = 0; x != y && steps < 512; steps++) {
+        if (x < y) { cx = x; x = bpar[x]; }
+        else { cy = y; y = bpar[y]; }
+      }
+      px = best[cx] == key;
+      py = best[cy] == key;
+      cx = cx < (uint64_t)n ? perm[cx] : cx;
+      cy = cy < (uint64_t)n ? perm[cy] : cy;
+    }
     if (x != y || x < (uint64_t)n || (!px && !py)) {  // (cannot happen: the forest is a spanning one) stay in bounds
       atomicOr((unsigned long long *)&hdr[H_STATUS], 32ull);
-      chain[j] = 0;
-      pick[j] = (uint64_t)j;
+      rec[i] = make_uint4(tid, hid, 0u, tid);
       continue;
     }
     uint32_t S = x;
     for (int k = 0; k < 512 && key > best[S]; k++) S = bpar[S];
-    if (px) { if (cx < (uint64_t)n) kpar[cx] = (uint32_t)(n + j); else up[cx - n] = (uint32_t)j; }
-    if (py) { if (cy < (uint64_t)n) kpar[cy] = (uint32_t)(n + j); else up[cy - n] = (uint32_t)j; }
     if (px && py) mate[S - n] = cy;
-    chain[j] = (uint32_t)(S - n);
-    pick[j] = (uint64_t)j | ((uint64_t)(px ? cx : cy) << 32);
+    rec[i] = make_uint4(tid, hid, (uint32_t)(S - n) | (px && py ? MUTUAL : 0u), px ? cx : cy);
+  }
+}
+
+__device__ inline void set_parent(uint32_t x, uint32_t j, int64_t n, uint32_t *kpar, uint32_t *up) {
+  if (x < (uint64_t)n) kpar[x] = (uint32_t)(n + j);
+  else up[x - n] = j;
+}
+
+// Per sorted row: its ends, chain and chooser from the record of its edge, its
+// weight in place of its key (the keys have done their work: the order).
+// up[S] = the row best(S) of an inner node, kpar = that of a record. Bound by
+// one random 16-byte read and one random 4-byte write a row: 3.9 ms at 5e7.
+__global__ __launch_bounds__(B) void k_dn_rows(const uint32_t *idx, const uint4 *rec, Cnt mc, const int64_t *t,
+                                               int wshift, bool rank, int64_t n, const uint32_t *mate,
+                                               uint64_t *msf_key, uint64_t *msf_val, uint32_t *chain, uint64_t *pick,
+                                               uint32_t *kpar, uint32_t *up) {
+  const int64_t m = mc.get();
+  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
+    const uint4 r = rec[idx[j]];
+    msf_val[j] = (uint64_t)r.x | ((uint64_t)r.y << 32);
+    msf_key[j] = rank ? (uint64_t)(t[r.y] - t[r.x]) : msf_key[j] >> wshift;
+    const uint32_t S = r.z & ~MUTUAL;
+    chain[j] = S;
+    pick[j] = (uint64_t)j | ((uint64_t)r.w << 32);
+    set_parent(r.w, (uint32_t)j, n, kpar, up);
+    if (r.z & MUTUAL)  // two records chose each other, or two inner nodes
+      set_parent(r.w < (uint64_t)n ? r.x ^ r.y ^ r.w : mate[S], (uint32_t)j, n, kpar, up);
   }
 }
 
@@ -229,11 +299,14 @@ __global__ __launch_bounds__(B) void k_dn_trim(uint32_t *kpar, int64_t n, Cnt mc
 }
 
 // Buffers of the two steps below, at the same places in both; a forest has at
-// most mb rows and mb inner nodes. Half of them lie where the skeleton arrays
-// were (dead once the rows are sorted), the others in scratch.
+// most mb rows and mb inner nodes. Three lie where the skeleton arrays were
+// (dead once the edges are gathered), the edges' records in the second half
+// of kpar and the three arrays behind it (written last), the others in scratch.
 struct Chains {
-  uint32_t *up, *mate, *key, *key_alt;
-  uint64_t *pick, *pick_alt;
+  uint32_t *up, *key, *key_alt;     // skeleton arrays
+  uint32_t *mate, *idx, *idx_alt;   // idx and idx_alt are pick_alt's bytes
+  uint64_t *pick, *pick_alt, *mkey_alt;  // mkey_alt is pick's
+  uint4 *rec;
 };
 int64_t row_bound(int64_t n, int64_t slots) { return slots < n ? slots : n; }
 ce_status carve(const Bufs &b, Ws &ws, Chains &c) {
@@ -242,11 +315,15 @@ ce_status carve(const Bufs &b, Ws &ws, Chains &c) {
   x.base = (char *)b.skel_key;
   x.cap = (size_t)((char *)b.best - (char *)b.skel_key);
   c.up = x.alloc<uint32_t>(mb);
-  c.mate = x.alloc<uint32_t>(mb);
   c.key = x.alloc<uint32_t>(mb);
   c.key_alt = x.alloc<uint32_t>(mb);
-  c.pick = ws.alloc<uint64_t>(mb);
+  c.mate = ws.alloc<uint32_t>(mb);
   c.pick_alt = ws.alloc<uint64_t>(mb);
+  c.idx = (uint32_t *)c.pick_alt;
+  c.idx_alt = c.idx + mb;
+  c.pick = c.mkey_alt = ws.alloc<uint64_t>(mb);
+  // 16 bytes for each of at most n - 1 rows from the next 16-byte boundary: kpar's half and three arrays of n words
+  c.rec = (uint4 *)(((uintptr_t)(b.kpar + b.n) + 15) & ~(uintptr_t)15);
   CE_WS_CHECK(x);
   CE_WS_CHECK(ws);
   return CE_OK;
@@ -257,21 +334,42 @@ ce_status carve(const Bufs &b, Ws &ws, Chains &c) {
 size_t stage_dendrogram_scratch(int64_t n, int64_t slots) {
   const int64_t mb = row_bound(n, slots);
   Ws w;
+  w.alloc<uint32_t>(mb);
   w.alloc<uint64_t>(mb);
   w.alloc<uint64_t>(mb);
   const size_t sort = radix_ws_bytes(mb), scan = scan_ws_bytes(mb + 1);
   return w.off + (sort > scan ? sort : scan) + 1024;
 }
 
-// Every row's chain, from the keys; then the rows' weights take the keys' place.
-ce_status stage_dendrogram_find(Bufs &b, Ws &ws, hipStream_t s) {
-  const int64_t n = b.n, mb = row_bound(n, b.slots);
+// The forest's rows (m on the device, at most n - 1) sorted by key: weights in
+// msf_key, ends in msf_val, and every row's chain.
+ce_status stage_rows(Bufs &b, Ws &ws, hipStream_t s) {
+  const int64_t n = b.n, n2 = b.slots, mb = row_bound(n, n2);
   size_t m0 = ws.mark();
   Chains c;
   CE_TRY(carve(b, ws, c));
+  uint32_t *list = (uint32_t *)b.msf_val;  // written after the list is read
+  CE_LAUNCH(k_msf_list, dim3(list_blocks(n2)), dim3(LBK), 0, s, b.msf_flag, n2, list,
+            (unsigned long long *)&b.hdr[H_M]);
+  CE_LAUNCH(k_check_rows, dim3(1), dim3(64), 0, s, b.hdr, n);
+  const Cnt m(&b.hdr[H_M], mb);
+  // gather into the key buffer from which an odd or even number of radix
+  // passes ends in msf_key, so no copy follows the sort
+  const int passes = b.keybits > 8 ? (b.keybits + 7) / 8 : 1;
+  uint64_t *gk = (passes & 1) ? c.mkey_alt : b.msf_key, *ok = (passes & 1) ? b.msf_key : c.mkey_alt;
+  const unsigned g = grid_cap(mb, B);
+  CE_LAUNCH(k_dn_gather, dim3(g), dim3(B), 0, s, list, m, b.msf_flag, b.skel_key, b.skel_tail, b.skel_tid, b.flat,
+            b.perm, b.best, b.bpar, n, gk, c.rec, c.mate, b.hdr);
+  CE_HIP(hipGetLastError());
+  bool alt = false;
+  CE_TRY((radix_sort_pairs<uint64_t, uint32_t>(gk, c.idx, ok, c.idx_alt, m, 0, b.keybits, true, &alt, ws, s)));
+  if ((alt ? ok : gk) != b.msf_key) {  // (not reached: the pass count is as computed)
+    set_error("internal: sorted forest is not in place");
+    return CE_EDEVICE;
+  }
   CE_LAUNCH(k_dn_init, dim3(grid_cap(n, B)), dim3(B), 0, s, b.kpar, n, c.up, mb);
-  CE_LAUNCH(k_dn_find, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_key, b.msf_val, b.ts, b.best, b.bpar, n,
-            Cnt(&b.hdr[H_M], mb), b.wshift, b.rank, c.key, c.pick, b.kpar, c.up, c.mate, b.hdr);
+  CE_LAUNCH(k_dn_rows, dim3(g), dim3(B), 0, s, alt ? c.idx_alt : c.idx, c.rec, m, b.t, b.wshift, b.rank, n, c.mate,
+            b.msf_key, b.msf_val, c.key, c.pick, b.kpar, c.up);
   CE_HIP(hipGetLastError());
   ws.release(m0);
   return CE_OK;
