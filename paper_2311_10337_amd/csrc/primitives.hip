@@ -4,7 +4,9 @@
 // each 256-thread block owns a 2048-key tile; the scatter pass ranks keys
 // stably inside the tile with 8 ballots per 64-key chunk (lanes with equal
 // digits form a peer mask), stages the tile in LDS in digit order and then
-// writes it out in runs of consecutive addresses.
+// writes it out in runs of consecutive addresses. Up to 4096 pairs are sorted
+// by one workgroup in one launch; up to 96 tiles a pass is two launches
+// (counts, scatter), beyond three.
 #include "ce_internal.h"
 
 namespace ce {
@@ -170,6 +172,10 @@ constexpr int RB = 256;              // block
 constexpr int RW = RB / 64;          // waves per block
 // keys per thread (IPT): 4, 8 or 16 (a tuning choice); a tile is RB * IPT keys
 
+// Digit counts per tile. Up to RS_FEW tiles, tile-major: a scatter workgroup
+// adds up the rows before its own itself, 256 digits at a time. Beyond,
+// digit-major, and k_rs_digits turns each digit's row into tile offsets.
+constexpr int RS_FEW = 96;
 template <class K, int IPT>
 __global__ __launch_bounds__(RB) void k_rs_hist(const K *keys, Cnt nc, int shift, uint32_t *hist,
                                                 int nblocks) {
@@ -190,8 +196,44 @@ __global__ __launch_bounds__(RB) void k_rs_hist(const K *keys, Cnt nc, int shift
     uint32_t c = 0;
 #pragma unroll
     for (int q = 0; q < RW; q++) c += cnt[q][d];
-    hist[(int64_t)d * nblocks + blockIdx.x] = c;
+    hist[nblocks <= RS_FEW ? (int64_t)blockIdx.x * 256 + d : (int64_t)d * nblocks + blockIdx.x] = c;
   }
+}
+
+// one workgroup per digit: its counts become offsets inside the digit, their sum goes to total[digit]
+constexpr int DB = 1024;
+__global__ __launch_bounds__(DB) void k_rs_digits(uint32_t *hist, int nblocks, uint32_t *total) {
+  __shared__ uint32_t lw[DB / 64];
+  uint32_t *row = hist + (int64_t)blockIdx.x * nblocks;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t run = 0;
+  for (int64_t b0 = 0; b0 < nblocks; b0 += DB * 4) {
+    uint32_t v[4], acc = 0;
+    const int64_t i0 = b0 + threadIdx.x * 4;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      v[k] = i0 + k < nblocks ? row[i0 + k] : 0u;
+      acc += v[k];
+    }
+    const uint32_t inc = wave_incl_scan(acc, lane);
+    if (lane == 63) lw[w] = inc;
+    __syncthreads();
+    uint32_t before = 0, tot = 0;
+#pragma unroll
+    for (int q = 0; q < DB / 64; q++) {
+      if (q < w) before += lw[q];
+      tot += lw[q];
+    }
+    __syncthreads();
+    uint32_t at = run + before + inc - acc;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+      if (i0 + k < nblocks) row[i0 + k] = at;
+      at += v[k];
+    }
+    run += tot;
+  }
+  if (threadIdx.x == 0) total[blockIdx.x] = run;
 }
 
 template <class V>
@@ -201,17 +243,34 @@ __device__ inline uint4 iota_value<uint4>(int64_t i) { return make_uint4((uint32
 
 template <class K, class V, int IPT>
 __global__ __launch_bounds__(RB) void k_rs_scatter(const K *kin, const V *vin, K *kout, V *vout, Cnt nc,
-                                                   int shift, const uint32_t *hscan, int nblocks, int iota) {
+                                                   int shift, const uint32_t *hist, const uint32_t *total,
+                                                   int nblocks, int iota) {
   constexpr int TILE = RB * IPT, WT = TILE / RW;  // keys per tile, per wave (IPT chunks of 64)
   const int64_t n = nc.get();
   if ((int64_t)blockIdx.x * TILE >= n) return;
   __shared__ uint32_t wcnt[RW][256];
-  __shared__ uint32_t dbase[256];
+  __shared__ uint32_t dbase[256], gbase[256];
   __shared__ uint32_t lw[RB / 64];
   __shared__ K skey[TILE];
   __shared__ V sval[TILE];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   for (int i = tid; i < RW * 256; i += RB) (&wcnt[0][0])[i] = 0;
+  // where this tile's keys of digit `tid` go: after all smaller digits and the same digit in earlier tiles
+  {
+    uint32_t all = 0, mine = 0;
+    if (nblocks <= RS_FEW) {
+#pragma unroll 8
+      for (int q = 0; q < nblocks; q++) {
+        const uint32_t c = hist[q * 256 + tid];
+        all += c;
+        if (q < (int)blockIdx.x) mine += c;
+      }
+    } else {
+      all = total[tid];
+      mine = hist[(int64_t)tid * nblocks + blockIdx.x];
+    }
+    gbase[tid] = block_excl_scan(all, lw, nullptr) + mine;
+  }
   __syncthreads();
   const int64_t tbase = (int64_t)blockIdx.x * TILE;
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -274,9 +333,102 @@ __global__ __launch_bounds__(RB) void k_rs_scatter(const K *kin, const V *vin, K
   for (int i = tid; i < valid_n; i += RB) {
     K k = skey[i];
     uint32_t d = (uint32_t)(k >> shift) & 255u;
-    int64_t g = (int64_t)hscan[(int64_t)d * nblocks + blockIdx.x] + (i - (int64_t)dbase[d]);
+    const int64_t g = (int64_t)gbase[d] + (i - (int64_t)dbase[d]);
     kout[g] = k;
     vout[g] = sval[i];
+  }
+}
+
+// A sort of up to RS_SMALL pairs in one workgroup, all passes in LDS: a wave
+// ranks 256 neighbouring keys, and the pairs move through LDS between passes.
+constexpr int RS_SMALL = 4096, SMB = 1024, SMW = SMB / 64, SMI = RS_SMALL / SMB;
+template <class K, class V>
+__global__ __launch_bounds__(SMB) void k_rs_small(const K *kin, const V *vin, K *kout, V *vout, Cnt nc, int begin_bit,
+                                                  int end_bit, int iota) {
+  __shared__ uint32_t wcnt[SMW][256];
+  __shared__ uint32_t dbase[256];
+  __shared__ uint32_t lw[4];
+  __shared__ K skey[RS_SMALL];
+  __shared__ V sval[RS_SMALL];
+  const int n = (int)nc.get();
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint64_t below = lanes_below((uint32_t)lane);
+  K key[SMI];
+  V val[SMI];
+#pragma unroll
+  for (int c = 0; c < SMI; c++) {
+    const int i = w * (64 * SMI) + c * 64 + lane;
+    key[c] = i < n ? kin[i] : K(0);
+    val[c] = i < n ? (iota ? iota_value<V>(i) : vin[i]) : V{};
+  }
+  for (int shift = begin_bit; shift < end_bit; shift += 8) {
+    for (int i = tid; i < SMW * 256; i += SMB) (&wcnt[0][0])[i] = 0;
+    __syncthreads();
+    uint32_t off[SMI], dig[SMI];
+#pragma unroll
+    for (int c = 0; c < SMI; c++) {
+      const bool valid = w * (64 * SMI) + c * 64 + lane < n;
+      const uint32_t d = (uint32_t)(key[c] >> shift) & 255u;
+      uint64_t peers = __ballot(valid);
+#pragma unroll
+      for (int b = 0; b < 8; b++) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t bb = __ballot(bit);
+        peers &= bit ? bb : ~bb;
+      }
+      const int leader = valid ? (__ffsll((unsigned long long)peers) - 1) : lane;
+      uint32_t old = 0;
+      if (valid && lane == leader) old = atomicAdd(&wcnt[w][d], (uint32_t)__popcll(peers));
+      old = __shfl(old, leader, 64);
+      dig[c] = valid ? d : 256u;
+      off[c] = old + (uint32_t)__popcll(peers & below);
+    }
+    __syncthreads();
+    uint32_t tot = 0, inc = 0;
+    if (tid < 256) {  // per digit: offsets of the waves; then the digits' own
+#pragma unroll
+      for (int q = 0; q < SMW; q++) {
+        const uint32_t t = wcnt[q][tid];
+        wcnt[q][tid] = tot;
+        tot += t;
+      }
+      inc = wave_incl_scan(tot, lane);
+      if (lane == 63) lw[w] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      uint32_t before = 0;
+#pragma unroll
+      for (int q = 0; q < 4; q++)
+        if (q < w) before += lw[q];
+      dbase[tid] = before + inc - tot;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < SMI; c++) {
+      if (dig[c] < 256u) {
+        const uint32_t p = dbase[dig[c]] + wcnt[w][dig[c]] + off[c];
+        skey[p] = key[c];
+        sval[p] = val[c];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < SMI; c++) {
+      const int i = w * (64 * SMI) + c * 64 + lane;
+      if (i < n) {
+        key[c] = skey[i];
+        val[c] = sval[i];
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < SMI; c++) {
+    const int i = w * (64 * SMI) + c * 64 + lane;
+    if (i < n) {
+      kout[i] = key[c];
+      vout[i] = val[c];
+    }
   }
 }
 
@@ -287,6 +439,7 @@ int radix_ipt(int64_t n) {
   int ipt = tuning().radix_ipt;
   if (ipt != 4 && ipt != 8 && ipt != 16) ipt = 8;
   if (ipt == 4 && n > (int64_t(1) << 24)) ipt = 8;
+  if (ipt == 8 && n <= (int64_t)RB * 4 * RS_FEW) ipt = 4;  // twice the workgroups where few tiles leave CUs idle
   return ipt;
 }
 
@@ -298,8 +451,8 @@ ce_status radix_passes(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int end
   if (nb64 > 0x7fffffff) return CE_EINVAL;
   const int nb = (int)nb64;
   size_t m = ws.mark();
-  uint32_t *hist = ws.alloc<uint32_t>((size_t)nb * 256 + 1);
-  uint32_t *hsc = ws.alloc<uint32_t>((size_t)nb * 256 + 1);
+  uint32_t *hist = ws.alloc<uint32_t>((size_t)nb * 256);
+  uint32_t *total = ws.alloc<uint32_t>(256);
   CE_WS_CHECK(ws);
   K *ki = k0, *ko = k1;
   V *vi = v0, *vo = v1;
@@ -309,9 +462,9 @@ ce_status radix_passes(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int end
   for (int shift = begin_bit; shift < end_bit; shift += 8) {
     CE_LAUNCH((k_rs_hist<K, IPT>), dim3((unsigned)nb), dim3(RB), 0, s, ki, n, shift, hist, nb);
     CE_HIP(hipGetLastError());
-    CE_TRY(scan_exclusive_u32(hist, hsc, Cnt((int64_t)nb * 256), ws, s));
+    if (nb > RS_FEW) CE_LAUNCH(k_rs_digits, dim3(256), dim3(DB), 0, s, hist, nb, total);
     CE_LAUNCH((k_rs_scatter<K, V, IPT>), dim3((unsigned)nb), dim3(RB), 0, s, ki, (const V *)vi, ko, vo, n,
-                       shift, hsc, nb, (first && iota_values) ? 1 : 0);
+                       shift, hist, total, nb, (first && iota_values) ? 1 : 0);
     CE_HIP(hipGetLastError());
     first = false;
     K *tk = ki; ki = ko; ko = tk;
@@ -327,9 +480,8 @@ ce_status radix_passes(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int end
 
 size_t radix_ws_bytes(int64_t n) {
   const int64_t tile = RB * (n > (int64_t(1) << 24) ? 8 : 4);  // the smallest tile a sort of n keys takes
-  int64_t nb = (n + tile - 1) / tile;
-  size_t h = (size_t)nb * 256;
-  return 2 * (((h + 1) * 4 + 255) & ~size_t(255)) + scan_ws_bytes((int64_t)h) + 512;
+  const int64_t nb = (n + tile - 1) / tile;
+  return (size_t)nb * 1024 + 1024 + 512;
 }
 
 template <class K, class V>
@@ -337,6 +489,15 @@ ce_status radix_sort_pairs(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int
                            bool *result_in_alt, Ws &ws, hipStream_t s) {
   *result_in_alt = false;
   if (n.v <= 0) return CE_OK;
+  if (n.v <= RS_SMALL) {  // the output goes where that many passes would have left it
+    if (end_bit <= begin_bit) end_bit = begin_bit + 1;
+    const bool alt = ((end_bit - begin_bit + 7) / 8) & 1;
+    CE_LAUNCH((k_rs_small<K, V>), dim3(1), dim3(SMB), 0, s, k0, (const V *)v0, alt ? k1 : k0, alt ? v1 : v0, n,
+              begin_bit, end_bit, iota_values ? 1 : 0);
+    CE_HIP(hipGetLastError());
+    *result_in_alt = alt;
+    return CE_OK;
+  }
   switch (radix_ipt(n.v)) {
     case 4:
       return radix_passes<K, V, 4>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
