@@ -129,7 +129,9 @@ struct Cnt {
   __host__ __device__ Cnt(int64_t x = 0) : p(nullptr), v(x), sh(0) {}
   __host__ __device__ Cnt(const uint64_t *q, int64_t bound, int shift = 0) : p(q), v(bound), sh(shift) {}
   __device__ inline int64_t get() const {
-    return p ? (int64_t)((*p + ((uint64_t(1) << sh) - 1)) >> sh) : v;
+    if (!p) return v;
+    const int64_t x = (int64_t)((*p + ((uint64_t(1) << sh) - 1)) >> sh);
+    return x < v ? x : v;  // (never more than the bound, unless the call failed)
   }
 };
 
@@ -265,13 +267,7 @@ __device__ inline uint64_t wave_min_u64(uint64_t v) {
   return v;
 }
 
-// Tile compaction: a 256-thread block keeps the elements of its tile
-// [tile_base, tile_base + 256*CT) for which keep[k] is set and appends
-// vals[k] to out[] with ONE atomic on the global counter per tile. Thread t
-// owns elements tile_base + k*256 + t (coalesced loads). The output keeps
-// element order inside the tile: per (k, wave) a ballot count, one 64-wide
-// exclusive scan over the (k, wave) counts, then popcount ranks within the
-// wave. Call from all threads of the block.
+// most items per thread of the aggregation kernels (LDS hash per tile)
 constexpr int CT = 16;
 // Linear probes an LDS aggregation hash tries before a key goes straight to
 // its global atomic: hot keys enter the table early, and a tile with many
@@ -294,15 +290,6 @@ struct TuningScope {
 };
 Tuning resolve_tuning(int64_t n, int64_t V, const ce_tuning *given);
 
-// Items per thread of a tile loop over n items, at most CT: all CT once the
-// launched grid is full, fewer when a short list (a small call, a late round)
-// would otherwise sit in a few workgroups whose threads take their items one
-// after another; then it spreads over the whole grid. Uniform over the grid.
-__device__ inline int tile_items(int64_t n) {
-  const int64_t span = (int64_t)blockDim.x * gridDim.x;
-  const int64_t per = (n + span - 1) / span;
-  return per < 1 ? 1 : (per > CT ? CT : (int)per);
-}
 // end of tile `tile` of `span` items in a list of n
 __device__ inline int64_t tile_end(int64_t n, int64_t tile, int64_t span) {
   const int64_t e = (tile + 1) * span;
@@ -315,37 +302,6 @@ inline int items_per_thread(int64_t n, int block) {
   const int64_t per = n / ((int64_t)block * 1024);
   return per < 1 ? 1 : (per > CT ? CT : (int)per);
 }
-// Output positions for the kept elements of a tile (order as described
-// above); pos[k] is valid where keep[k]. One atomic on `counter` per tile.
-__device__ inline void tile_positions(const bool (&keep)[CT], uint32_t (&pos)[CT], unsigned long long *counter) {
-  __shared__ uint32_t s_cnt[CT * 4];
-  __shared__ uint32_t s_base;
-  const uint32_t lane = wave_lane(), w = threadIdx.x >> 6;
-  uint64_t mask[CT];
-#pragma unroll
-  for (int k = 0; k < CT; k++) {
-    mask[k] = __ballot(keep[k]);
-    if (lane == 0) s_cnt[k * 4 + w] = (uint32_t)__popcll(mask[k]);
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) {  // CT * 4 == 64 counts in (k, wave) order
-    uint32_t x = s_cnt[threadIdx.x], inc = x;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      uint32_t y = __shfl_up(inc, d, 64);
-      if (threadIdx.x >= (uint32_t)d) inc += y;
-    }
-    uint32_t tot = __shfl(inc, 63, 64);
-    s_cnt[threadIdx.x] = inc - x;
-    if (threadIdx.x == 0) s_base = tot ? (uint32_t)atomicAdd(counter, (unsigned long long)tot) : 0u;
-  }
-  __syncthreads();
-  const uint64_t below = lanes_below(lane);
-#pragma unroll
-  for (int k = 0; k < CT; k++) pos[k] = s_base + s_cnt[k * 4 + w] + (uint32_t)__popcll(mask[k] & below);
-  __syncthreads();  // s_cnt / s_base may be reused by a later call
-}
-
 // List kernels (a pass that compacts a list): workgroups of LBK threads, up to
 // LCT elements per thread and tile, one counter update per tile. All
 // workgroups update one address, which takes about 15 ns each, so the tiles
@@ -355,7 +311,11 @@ __device__ inline int list_items(int64_t n) {
   const int64_t per = (n + (int64_t)LBK * 512 - 1) / ((int64_t)LBK * 512);
   return per < 1 ? 1 : (per > LCT ? LCT : (int)per);
 }
-// tile_positions for workgroups of LBK threads
+// Output positions for the kept elements of a tile [base, base + LBK * LCT):
+// thread t owns elements base + k * LBK + t (coalesced loads), pos[k] is valid
+// where keep[k], and the output keeps element order inside the tile: per (k,
+// wave) a ballot count, one 64-wide scan over the counts, then popcount ranks
+// in the wave. One atomic on `counter` per tile. Call from all threads.
 __device__ inline void list_positions(const bool (&keep)[LCT], uint32_t (&pos)[LCT], unsigned long long *counter) {
   constexpr int W = LBK / 64;
   static_assert(LCT * W == 64, "one wave scans the (k, wave) counts");
@@ -393,18 +353,12 @@ inline unsigned list_blocks(int64_t n) {
   return grid_for(n, LBK, cap < 1 ? 1 : cap);
 }
 
-__device__ inline void tile_append(const bool (&keep)[CT], const uint32_t (&vals)[CT], uint32_t *out,
-                                   unsigned long long *counter) {
-  uint32_t pos[CT];
-  tile_positions(keep, pos, counter);
-#pragma unroll
-  for (int k = 0; k < CT; k++)
-    if (keep[k]) out[pos[k]] = vals[k];
-}
-
 // ------------------------------------------------------------ primitives
-// Exclusive scan of n elements; out must hold n+1 (out[n] = total). In-place allowed.
-// With a device count (n.p), n.v is the capacity and out[*n.p] gets the total.
+// Exclusive scan of n elements; out must hold n+1 (out[n] = total). In-place allowed (32-bit elements).
+// With a device count (n.p), n.v is the capacity and out[*n.p] gets the total. Both arrays start at a workspace
+// region.
+template <class T>
+ce_status scan_exclusive(const T *in, uint32_t *out, Cnt n, Ws &ws, hipStream_t s);
 ce_status scan_exclusive_u32(const uint32_t *in, uint32_t *out, Cnt n, Ws &ws, hipStream_t s);
 size_t scan_ws_bytes(int64_t n);
 
@@ -510,7 +464,7 @@ ce_status stage_dendrogram(Bufs &b, bool cut, Ws &ws, hipStream_t s);
 ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, int64_t *hout);
 ce_status stage_graph_rows(Bufs &b, Ws &ws, hipStream_t s);
 size_t stage_graph_rows_scratch(int64_t n, int64_t G);
-ce_status stage_write_rows(Bufs &b, const ce_result *out, hipStream_t s);
+ce_status stage_write_rows(Bufs &b, const ce_result *out, hipStream_t s);  // and the dendrogram's own arrays
 
 size_t stage_sort_skeleton_scratch(int64_t n);
 // weight ranks of the first cnt skeleton slots from their raw weights (any mode)

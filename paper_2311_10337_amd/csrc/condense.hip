@@ -35,17 +35,46 @@ __device__ inline uint32_t node_size(uint32_t x, int64_t n, const uint32_t *ksiz
 __global__ __launch_bounds__(B) void k_fill32(uint32_t *p, int64_t n, uint32_t v) {
   for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) p[i] = v;
 }
-__global__ __launch_bounds__(B) void k_fill64(uint64_t *p, int64_t n, uint64_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) p[i] = v;
-}
-__global__ void k_set64(uint64_t *p, uint64_t v) { *p = v; }
 
-// big component roots per graph
-__global__ __launch_bounds__(B) void k_cd_bigroots(const uint32_t *kpar, const uint32_t *ksize, const uint32_t *rowg,
-                                                   Cnt mc, int64_t n, int64_t M, uint32_t *nbig) {
+// every array that starts at a constant: big roots, birth and label flags, sums, children, smallest members
+__global__ __launch_bounds__(B) void k_cd_init(int64_t n, int64_t m, int64_t G, int64_t R, uint32_t *nbig,
+                                               uint8_t *isbirth, uint8_t *fl, uint64_t *acc, uint32_t *nch,
+                                               uint32_t *ch, uint32_t *minmem) {
+  const int64_t step = (int64_t)gridDim.x * B, i0 = (int64_t)blockIdx.x * B + threadIdx.x;
+  for (int64_t i = i0; i < G + 1; i += step) nbig[i] = 0;
+  for (int64_t i = i0; i < (m + 3) / 4; i += step) ((uint32_t *)isbirth)[i] = 0;  // regions are 256-byte aligned
+  for (int64_t i = i0; i < (n + 3) / 4; i += step) ((uint32_t *)fl)[i] = 0;
+  for (int64_t i = i0; i < R; i += step) {
+    acc[3 * i] = 0;
+    acc[3 * i + 1] = 0;
+    acc[3 * i + 2] = 0;
+    nch[i] = 0;
+    ch[2 * i] = 0;
+    ch[2 * i + 1] = 0;
+    minmem[i] = NONE32;
+  }
+}
+
+// Per row: lambda, of its weight, or with thresholds (the discrete dendrogram
+// of Alg. 5) of its level's threshold, level = the first threshold the weight
+// does not exceed; and the big component roots per graph
+__global__ __launch_bounds__(B) void k_cd_lambda(const uint64_t *msf_w, const uint32_t *kpar, const uint32_t *ksize,
+                                                 const uint32_t *rowg, Cnt mc, int64_t n, int64_t M,
+                                                 const int64_t *thr, int q, uint64_t *rowL, uint32_t *level,
+                                                 uint32_t *nbig) {
   const int64_t m = mc.get();
-  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B)
+  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
     if (kpar[n + j] == NONE32 && ksize[j] >= (uint64_t)M) atomicAdd(&nbig[graph_at(rowg, j)], 1u);
+    const int64_t w = (int64_t)msf_w[j];
+    if (q == 0) {
+      rowL[j] = lambda_of(w);
+      continue;
+    }
+    int L = 0;
+    while (L < q - 1 && w > thr[L]) L++;  // rows above the last threshold were dropped before
+    rowL[j] = lambda_of(thr[L]);
+    level[j] = (uint32_t)L;
+  }
 }
 
 __global__ __launch_bounds__(B) void k_cd_birth(const uint32_t *kc_u, const uint32_t *kc_v, const uint32_t *ksize,
@@ -69,87 +98,76 @@ __global__ __launch_bounds__(B) void k_cd_birth(const uint32_t *kc_u, const uint
   }
 }
 
-// lambda of every row: of its weight, or with thresholds (the discrete
-// dendrogram of Alg. 5) of its level's threshold, level = the first threshold
-// the weight does not exceed
-__global__ __launch_bounds__(B) void k_row_lambda(const uint64_t *msf_w, Cnt mc, const int64_t *thr, int q,
-                                                  uint64_t *rowL, uint32_t *level) {
-  const int64_t m = mc.get();
-  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    const int64_t w = (int64_t)msf_w[j];
-    if (q == 0) {
-      rowL[j] = lambda_of(w);
-      continue;
-    }
-    int L = 0;
-    while (L < q - 1 && w > thr[L]) L++;  // rows above the last threshold were dropped before
-    rowL[j] = lambda_of(thr[L]);
-    level[j] = (uint32_t)L;
-  }
-}
+// Links climbed per pointer-jumping round: a round makes links HOPS + 1 times
+// as long, so a path of k rows takes log(k) / log(5) rounds; a launch costs
+// about as much as the four extra reads (19 rounds of one link each took 85 us
+// at 7e4 rows).
+constexpr int HOPS = 4;
 
 // Discrete dendrogram: a row's level top is its highest ancestor reached
 // through parents of the same level (the component that first appears at that
-// level, a D-node). First step: the parent if it has the same level.
-__global__ __launch_bounds__(B) void k_dd_top_init(const uint32_t *kpar, const uint32_t *level, Cnt mc, int64_t n,
-                                                   uint32_t *top) {
+// level, a D-node). First step: the parent if it has the same level; the list
+// gets the rows whose pointer moved.
+__global__ __launch_bounds__(LBK) void k_dd_top_init(const uint32_t *kpar, const uint32_t *level, Cnt mc, int64_t n,
+                                                     uint32_t *top, uint32_t *act, unsigned long long *nact) {
   const int64_t m = mc.get();
-  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    const uint32_t p = kpar[n + j];
-    top[j] = (p != NONE32 && level[p - n] == level[j]) ? p : (uint32_t)(n + j);
-  }
-}
-// rows whose level top is not known yet (their pointer is not a top)
-__global__ __launch_bounds__(B) void k_dd_top_active(const uint32_t *top, Cnt mc, int64_t n, uint32_t *act,
-                                                     unsigned long long *nact) {
-  const int64_t m = mc.get();
-  const int ct = tile_items(m);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < m; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(m, tile, B * ct);
+  const int ct = list_items(m);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < m; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(m, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t j = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t j = base + (int64_t)k * LBK;
       keep[k] = false;
-      vals[k] = (uint32_t)j;
       if (j >= end) continue;
-      const uint32_t t = top[j];
-      keep[k] = t != (uint32_t)(n + j) && top[t - n] != t;
+      const uint32_t p = kpar[n + j];
+      keep[k] = p != NONE32 && level[p - n] == level[j];
+      top[j] = keep[k] ? p : (uint32_t)(n + j);
     }
-    tile_append(keep, vals, act, nact);
+    list_positions(keep, pos, nact);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) act[pos[k]] = (uint32_t)(base + (int64_t)k * LBK);
   }
 }
-// one pointer-doubling round over the active rows, in place: a row only reads
-// pointers of rows above it, which stay valid ancestors of the same level
-__global__ __launch_bounds__(B) void k_dd_top_jump(const uint32_t *act, const uint64_t *nact_in, int64_t n,
-                                                   uint32_t *top, uint32_t *next, unsigned long long *nnext) {
+// one round over the active rows, in place: a row only reads pointers of rows
+// above it, which stay valid ancestors of the same level
+__global__ __launch_bounds__(LBK) void k_dd_top_jump(const uint32_t *act, const uint64_t *nact_in, int64_t n,
+                                                     uint32_t *top, uint32_t *next, unsigned long long *nnext) {
   const int64_t nact = (int64_t)*nact_in;
-  const int ct = tile_items(nact);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < nact; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(nact, tile, B * ct);
+  const int ct = list_items(nact);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nact; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t vals[LCT], pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nact, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t i = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
       keep[k] = false;
       vals[k] = 0;
       if (i >= end) continue;
-      const uint32_t j = act[i], t = top[j], tt = top[t - n];
-      if (tt == t) continue;  // t is a top
+      const uint32_t j = act[i];
+      uint32_t t = top[j], tt = top[t - n];
+      for (int hop = 1; hop < HOPS && tt != t; hop++) {
+        t = tt;
+        tt = top[t - n];
+      }
       top[j] = tt;
-      keep[k] = top[tt - n] != tt;
+      keep[k] = tt != t;  // tt may not be a top
       vals[k] = j;
     }
-    tile_append(keep, vals, next, nnext);
+    list_positions(keep, pos, nnext);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) next[pos[k]] = vals[k];
   }
 }
-// after the enqueued rounds every list must be empty (pointer doubling over
-// a tree of m rows ends within bits(m) + 1 rounds); if not, the call fails
+// after the enqueued rounds every list must be empty; if not, the call fails
 __global__ void k_loop_done(const uint64_t *cnt, uint64_t *hdr) {
   if (threadIdx.x == 0 && *cnt != 0) hdr[H_STATUS] |= 32;
 }
+
 // big children of every D-node: the level tops (rows that are their own top)
 // hanging below its block; records are never big (M >= 2)
 // big D-node children per D-node; a D-node can have millions of them, so the
@@ -217,20 +235,19 @@ __device__ inline bool j_terminal(uint32_t x, int64_t n, int64_t m, const uint8_
 
 // J[j] for big rows: self if birth, ROOT if a root, else the parent node.
 // Rows whose J is not yet a birth node or ROOT go to the active list.
-__global__ __launch_bounds__(B) void k_cd_jinit(const uint8_t *isbirth, const uint32_t *kpar, const uint32_t *ksize,
-                                                const uint32_t *rowg, Cnt mc, int64_t n, int64_t M, uint32_t *J,
-                                                uint32_t *act, unsigned long long *nact) {
+__global__ __launch_bounds__(LBK) void k_cd_jinit(const uint8_t *isbirth, const uint32_t *kpar, const uint32_t *ksize,
+                                                  const uint32_t *rowg, Cnt mc, int64_t n, int64_t M, uint32_t *J,
+                                                  uint32_t *act, unsigned long long *nact) {
   const int64_t m = mc.get();
-  const int ct = tile_items(m);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < m; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(m, tile, B * ct);
+  const int ct = list_items(m);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < m; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(m, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t j = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t j = base + (int64_t)k * LBK;
       keep[k] = false;
-      vals[k] = (uint32_t)j;
       if (j >= end) continue;
       uint32_t v = NONE32;
       if (ksize[j] >= (uint64_t)M) {
@@ -243,44 +260,47 @@ __global__ __launch_bounds__(B) void k_cd_jinit(const uint8_t *isbirth, const ui
       }
       J[j] = v;
     }
-    tile_append(keep, vals, act, nact);
+    list_positions(keep, pos, nact);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) act[pos[k]] = (uint32_t)(base + (int64_t)k * LBK);
   }
 }
 
-// one pointer-doubling round toward the nearest birth ancestor; finished rows
+// one pointer-jumping round toward the nearest birth ancestor; finished rows
 // leave the list (in place: J only moves up, so a pointer read while another
 // row updates it is still an ancestor on the way)
-__global__ __launch_bounds__(B) void k_cd_jstep(const uint32_t *act, const uint64_t *nact_in, uint32_t *J,
-                                                const uint8_t *isbirth, Cnt mc, int64_t n, uint32_t *out,
-                                                unsigned long long *nout) {
+__global__ __launch_bounds__(LBK) void k_cd_jstep(const uint32_t *act, const uint64_t *nact_in, uint32_t *J,
+                                                  const uint8_t *isbirth, Cnt mc, int64_t n, uint32_t *out,
+                                                  unsigned long long *nout) {
   const int64_t m = mc.get(), nact = (int64_t)*nact_in;
-  const int ct = tile_items(nact);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < nact; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(nact, tile, B * ct);
+  const int ct = list_items(nact);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nact; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t vals[LCT], pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nact, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t i = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
       keep[k] = false;
       vals[k] = 0;
       if (i >= end) continue;
       const uint32_t j = act[i];
-      const uint32_t x = J[j];
-      const uint32_t y = J[x - n];
-      J[j] = y;
-      if (!j_terminal(y, n, m, isbirth)) {
-        keep[k] = true;
-        vals[k] = j;
+      uint32_t x = J[J[j] - n];
+      bool done = j_terminal(x, n, m, isbirth);
+      for (int hop = 1; hop < HOPS && !done; hop++) {
+        x = J[x - n];
+        done = j_terminal(x, n, m, isbirth);
       }
+      J[j] = x;
+      keep[k] = !done;
+      vals[k] = j;
     }
-    tile_append(keep, vals, out, nout);
+    list_positions(keep, pos, nout);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) out[pos[k]] = vals[k];
   }
-}
-
-__global__ __launch_bounds__(B) void k_u8_to_u32(const uint8_t *a, Cnt nc, uint32_t *o) {
-  const int64_t n = nc.get();
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) o[i] = a[i];
 }
 
 __device__ inline uint32_t row_of(uint32_t c, int64_t n, int64_t m, const uint32_t *rowof, const uint32_t *rootrow) {
@@ -290,9 +310,18 @@ __device__ inline uint32_t row_of(uint32_t c, int64_t n, int64_t m, const uint32
 // cluster rows: node, size, birth lambda, parent row
 __global__ __launch_bounds__(B) void k_cd_rows(const uint8_t *isbirth, const uint32_t *rowof, const uint32_t *rootrow,
                                                const uint32_t *ksize, const uint64_t *birthL, const uint32_t *kpar,
-                                               const uint32_t *J, const uint32_t *rowg, Cnt mc, int64_t n,
-                                               uint32_t *cnode, uint32_t *csize, uint64_t *cbirth, uint32_t *cprow) {
+                                               const uint32_t *J, const uint32_t *rowg, const int64_t *eoff, int64_t G,
+                                               Cnt mc, int64_t n, uint32_t *cnode, uint32_t *csize, uint64_t *cbirth,
+                                               uint32_t *cprow) {
   const int64_t m = mc.get();
+  // one root row per graph: size = the graph's records, born at lambda 0, no parent
+  for (int64_t g = (int64_t)blockIdx.x * B + threadIdx.x; g < G; g += (int64_t)gridDim.x * B) {
+    const uint32_t r = rootrow[g];
+    cnode[r] = (uint32_t)(n + m + g);
+    csize[r] = (uint32_t)(eoff[g + 1] - eoff[g]);
+    cbirth[r] = 0;
+    cprow[r] = NONE32;
+  }
   for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
     if (!isbirth[j]) continue;
     uint32_t r = rowof[j];
@@ -302,20 +331,6 @@ __global__ __launch_bounds__(B) void k_cd_rows(const uint8_t *isbirth, const uin
     uint32_t par = kpar[n + j];
     uint32_t pc = par == NONE32 ? (uint32_t)(n + m + graph_at(rowg, j)) : J[par - n];
     cprow[r] = row_of(pc, n, m, rowof, rootrow);
-  }
-}
-
-// one root row per graph: size = the graph's records, born at lambda 0, no parent
-__global__ __launch_bounds__(B) void k_cd_rootrows(const uint32_t *rootrow, const int64_t *eoff, int64_t G, Cnt mc,
-                                                   int64_t n, uint32_t *cnode, uint32_t *csize, uint64_t *cbirth,
-                                                   uint32_t *cprow) {
-  const int64_t m = mc.get();
-  for (int64_t g = (int64_t)blockIdx.x * B + threadIdx.x; g < G; g += (int64_t)gridDim.x * B) {
-    const uint32_t r = rootrow[g];
-    cnode[r] = (uint32_t)(n + m + g);
-    csize[r] = (uint32_t)(eoff[g + 1] - eoff[g]);
-    cbirth[r] = 0;
-    cprow[r] = NONE32;
   }
 }
 
@@ -331,20 +346,24 @@ __global__ __launch_bounds__(B) void k_birth_list(const uint8_t *isbirth, const 
   }
 }
 // births and cluster rows from the scan of the birth flags (idx[m] = births);
-// more rows than the bound marks the call failed
-__global__ void k_cluster_counts(const uint32_t *idx, const uint64_t *m, int64_t G, int64_t R, uint64_t *hdr) {
+// more rows than the bound marks the call failed. One graph: its births are
+// rows 0..nb-1, its root the next.
+__global__ void k_cluster_counts(const uint32_t *idx, Cnt mc, int64_t G, int64_t R, uint32_t *bstart,
+                                 uint32_t *rootrow, uint64_t *hdr) {
   if (threadIdx.x != 0) return;
-  uint64_t nb = idx[*m];
+  uint64_t nb = idx[mc.get()];
   if ((int64_t)(nb + G) > R) {  // (cannot happen: every birth has at least M records) stay in bounds
     hdr[H_STATUS] |= 64;
     nb = 0;
   }
   hdr[H_NB] = nb;
   hdr[H_NROWS] = nb + (uint64_t)G;
-}
-// one graph: its births are rows 0..nb-1
-__global__ void k_bstart_one(uint32_t *bstart, const uint64_t *hdr) {
-  if (threadIdx.x == 0) { bstart[0] = 0; bstart[1] = (uint32_t)hdr[H_NB]; }
+  hdr[H_NEOM] = nb + (uint64_t)G;  // the excess-of-mass rows, unless virtual ones are added
+  if (G == 1) {
+    bstart[0] = 0;
+    bstart[1] = (uint32_t)nb;
+    rootrow[0] = (uint32_t)nb;
+  }
 }
 __global__ __launch_bounds__(B) void k_birth_rows(const uint32_t *sorted_j, const uint32_t *rowg, Cnt nbc,
                                                   uint32_t *rowof) {
@@ -377,15 +396,18 @@ __device__ inline void add_limbs(bool active, uint32_t row, uint64_t l0, uint64_
 
 constexpr int AHS = 512;  // LDS hash slots for per-cluster-row sums
 
+// Also one 8-byte word per row for the exit walk: (parent node, size) for a
+// small row, (cluster row of its cluster, size) for a big one.
+//
 // Point term of each cluster's stability: the records of a small child c of
 // a big row j all leave the cluster of j at lambda_j, so they add size(c) *
 // lambda_j; summed per cluster row in an LDS hash, then one atomic per limb,
 // row and tile.
 __global__ __launch_bounds__(B) void k_cd_point_terms(const uint32_t *kc_u, const uint32_t *kc_v,
                                                       const uint32_t *ksize, const uint32_t *J, const uint64_t *rowL,
-                                                      const uint32_t *rowof, const uint32_t *rootrow, Cnt mc,
-                                                      int64_t n, int64_t M, int kct,
-                                                      unsigned long long *acc) {
+                                                      const uint32_t *rowof, const uint32_t *rootrow,
+                                                      const uint32_t *kpar, Cnt mc, int64_t n, int64_t M, int kct,
+                                                      unsigned long long *acc, uint2 *wk) {
   __shared__ uint32_t hk[AHS];
   const int64_t m = mc.get();
   __shared__ unsigned long long h0[AHS], h1[AHS], h2[AHS];
@@ -396,11 +418,18 @@ __global__ __launch_bounds__(B) void k_cd_point_terms(const uint32_t *kc_u, cons
     const int64_t j = tbase + (int64_t)k * B + threadIdx.x;
     uint32_t cnt = 0, r = 0;
     uint64_t L = 0;
-    if (j < m && ksize[j] >= (uint64_t)M) {
-      L = rowL[j];
-      const uint32_t su = node_size(kc_u[j], n, ksize), sv = node_size(kc_v[j], n, ksize);
-      cnt = (su < (uint64_t)M ? su : 0u) + (sv < (uint64_t)M ? sv : 0u);
-      if (cnt && L) r = row_of(J[j], n, m, rowof, rootrow);
+    if (j < m) {
+      const uint32_t sz = ksize[j];
+      uint32_t up;
+      if (sz >= (uint64_t)M) {
+        L = rowL[j];
+        const uint32_t su = node_size(kc_u[j], n, ksize), sv = node_size(kc_v[j], n, ksize);
+        cnt = (su < (uint64_t)M ? su : 0u) + (sv < (uint64_t)M ? sv : 0u);
+        up = r = row_of(J[j], n, m, rowof, rootrow);
+      } else {
+        up = kpar[n + j];
+      }
+      wk[j] = make_uint2(up, sz);
     }
     const bool act = cnt != 0 && L != 0;
     const u128 prod = u128_mul64(cnt, L);
@@ -441,18 +470,6 @@ __global__ __launch_bounds__(B) void k_cd_point_terms(const uint32_t *kc_u, cons
   }
 }
 
-// One 8-byte word per row for the exit walk: (parent node, size) for a small
-// row, (cluster row of its cluster, size) for a big one.
-__global__ __launch_bounds__(B) void k_cd_walk_words(const uint32_t *kpar, const uint32_t *ksize, const uint32_t *J,
-                                                     const uint32_t *rowof, const uint32_t *rootrow, int64_t n,
-                                                     Cnt mc, int64_t M, uint2 *wk) {
-  const int64_t m = mc.get();
-  for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
-    const uint32_t sz = ksize[j];
-    wk[j] = make_uint2(sz < (uint64_t)M ? kpar[n + j] : row_of(J[j], n, m, rowof, rootrow), sz);
-  }
-}
-
 // Exit of every record, in input order: from its leaf, up through the small
 // subtrees (fewer than M records, so fewer than M steps) to the first big
 // row y; it leaves the cluster of y at lambda_y, or its graph's root at 0 when
@@ -480,9 +497,12 @@ __global__ __launch_bounds__(B) void k_cd_exit_ids(const uint32_t *kpar, const u
   }
 }
 
+// per cluster row with a parent: its term in the parent's sum, and (exact
+// dendrogram, list) its place among the parent's at most two children; root
+// rows are the rows without a parent
 __global__ __launch_bounds__(B) void k_cd_acc_children(const uint32_t *csize, const uint64_t *cbirth,
-                                                       const uint32_t *cprow, Cnt nrc,
-                                                       unsigned long long *acc) {
+                                                       const uint32_t *cprow, Cnt nrc, unsigned long long *acc,
+                                                       bool list, uint32_t *nch, uint32_t *ch) {
   const int64_t nrows = nrc.get();
   int64_t r = (int64_t)blockIdx.x * B + threadIdx.x;
   bool act = r < (int64_t)nrows && cprow[r] != NONE32;
@@ -491,34 +511,20 @@ __global__ __launch_bounds__(B) void k_cd_acc_children(const uint32_t *csize, co
   if (act) {
     pr = cprow[r];
     prod = u128_mul64(csize[r], cbirth[r]);
+    if (list && cprow[pr] != NONE32) {
+      const uint32_t k = atomicAdd(&nch[pr], 1u);
+      if (k < 2) ch[2 * (uint64_t)pr + k] = (uint32_t)r;
+    }
   }
   add_limbs(act, pr, prod.lo & 0xffffffffull, prod.lo >> 32, prod.hi, acc);
 }
 
 // S = sum - size * birth  (exact u128)
-__global__ __launch_bounds__(B) void k_cd_stab(const unsigned long long *acc, const uint32_t *csize,
-                                               const uint64_t *cbirth, Cnt nrc, uint64_t *shi, uint64_t *slo) {
-  const int64_t nrows = nrc.get();
-  for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * B) {
-    u128 t0{acc[3 * r], 0};
-    u128 t1 = u128_mul64(acc[3 * r + 1], uint64_t(1) << 32);
-    u128 t2{0, acc[3 * r + 2]};
-    u128 T = u128_add(u128_add(t0, t1), t2);
-    u128 S = u128_sub(T, u128_mul64(csize[r], cbirth[r]));
-    shi[r] = S.hi;
-    slo[r] = S.lo;
-  }
-}
-
-// root rows are the rows without a parent
-__global__ __launch_bounds__(B) void k_cd_children(const uint32_t *cprow, Cnt nrc, uint32_t *nch, uint32_t *ch) {
-  const int64_t nrows = nrc.get();
-  for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * B) {
-    uint32_t p = cprow[r];
-    if (p == NONE32 || cprow[p] == NONE32) continue;
-    uint32_t k = atomicAdd(&nch[p], 1u);
-    if (k < 2) ch[2 * (uint64_t)p + k] = (uint32_t)r;
-  }
+__device__ inline u128 stability(const unsigned long long *acc, uint32_t size, uint64_t birth, int64_t r) {
+  u128 t0{acc[3 * r], 0};
+  u128 t1 = u128_mul64(acc[3 * r + 1], uint64_t(1) << 32);
+  u128 t2{0, acc[3 * r + 2]};
+  return u128_sub(u128_add(u128_add(t0, t1), t2), u128_mul64(size, birth));
 }
 
 // More than two child clusters (discrete dendrogram): children listed per
@@ -560,7 +566,7 @@ __global__ __launch_bounds__(B) void k_cd_pairs(const uint32_t *nch, const uint3
 // one -> (L_{k-2}, L_{k-1}); its parent is the last p with vbase[p] <= v
 __global__ __launch_bounds__(B) void k_cd_virtual(const uint32_t *nch, const uint32_t *choff, const uint32_t *clist,
                                                   const uint32_t *vbase, Cnt nrc, Cnt nvc,
-                                                  uint32_t *ch, uint32_t *vnch, uint64_t *shi, uint64_t *slo) {
+                                                  uint32_t *ch, uint32_t *vnch) {
   const int64_t nrows = nrc.get(), nvirt = nvc.get();
   for (int64_t v = (int64_t)blockIdx.x * B + threadIdx.x; v < nvirt; v += (int64_t)gridDim.x * B) {
     int64_t lo = 0, hi = (int64_t)nrows - 1;
@@ -575,8 +581,6 @@ __global__ __launch_bounds__(B) void k_cd_virtual(const uint32_t *nch, const uin
     ch[2 * node] = L[i + 1];
     ch[2 * node + 1] = (i + 3 < k) ? (uint32_t)(node + 1) : L[k - 1];
     vnch[node] = 2;
-    shi[node] = 0;
-    slo[node] = 0;
   }
 }
 
@@ -598,35 +602,44 @@ __device__ inline void eom_store(const Eom &o, uint32_t r, uint8_t st, u128 v, u
   o.dep[r] = dep;
 }
 
-__global__ __launch_bounds__(B) void k_eom_init(const uint32_t *nch, const uint64_t *shi, const uint64_t *slo,
-                                                const uint32_t *cprow, Cnt nrc, Cnt nec, Eom e0,
-                                                Eom e1, uint32_t *act, unsigned long long *nact) {
+__global__ __launch_bounds__(LBK) void k_eom_init(const uint32_t *nch, const unsigned long long *acc,
+                                                  const uint32_t *csize, const uint64_t *cbirth, uint64_t *shi,
+                                                  uint64_t *slo, const uint32_t *cprow, Cnt nrc, Cnt nec, Eom e0,
+                                                  Eom e1, uint32_t *act, unsigned long long *nact) {
   const int64_t nreal = nrc.get(), nrows = nec.get();
-  const int ct = tile_items(nrows);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < nrows; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(nrows, tile, B * ct);
+  const int ct = list_items(nrows);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nrows; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nrows, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t r = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t r = base + (int64_t)k * LBK;
       keep[k] = false;
-      vals[k] = (uint32_t)r;
       if (r >= end) continue;
-      // rows from nreal on are virtual sum nodes, never leaves
-      bool leaf = r < nreal && (nch[r] == 0 || cprow[r] == NONE32);
-      u128 S{slo[r], shi[r]}, z{0, 0};
+      u128 S{0, 0}, z{0, 0};
+      bool leaf = false;  // rows from nreal on are virtual sum nodes, never leaves
+      if (r < nreal) {
+        S = stability(acc, csize[r], cbirth[r], r);
+        leaf = nch[r] == 0 || cprow[r] == NONE32;
+      }
+      shi[r] = S.hi;
+      slo[r] = S.lo;
       eom_store(e0, (uint32_t)r, leaf ? 2 : 0, S, z, z, NONE32);
       eom_store(e1, (uint32_t)r, leaf ? 2 : 0, S, z, z, NONE32);
       keep[k] = !leaf;
     }
-    tile_append(keep, vals, act, nact);
+    list_positions(keep, pos, nact);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) act[pos[k]] = (uint32_t)(base + (int64_t)k * LBK);
   }
 }
 
 // One round over the pending rows: rake (both children done), turn into a
-// unary f(x) = max(a, x + b) when one child is done, or compose along a chain
-// of unary rows (pointer jumping). Reads `in`, writes `out`. A row that
+// unary f(x) = max(a, x + b) when one child is done, and compose along a chain
+// of unary rows, HOPS links a round (so links grow fivefold a round instead of
+// twofold, and a spine of 8 000 clusters takes 8 rounds instead of 16). Reads `in`, writes `out`. A row that
 // finishes goes once more to the next list, flagged COPY, so that both state
 // buffers hold its final value; when the list is empty they agree everywhere.
 __device__ inline bool eom_step(uint32_t item, const Eom &in, const Eom &out, const uint32_t *ch,
@@ -653,12 +666,14 @@ __device__ inline bool eom_step(uint32_t item, const Eom &in, const Eom &out, co
       dep = pn;
       st = 1;
     }
-  } else if (st == 1) {
-    uint8_t ds = in.st[dep];
+  }
+  for (int hop = 0; st == 1 && hop < HOPS; hop++) {
+    const uint8_t ds = in.st[dep];
+    if (ds == 0) break;
     if (ds == 2) {
       v = u128_max(a, u128_add(u128{in.vlo[dep], in.vhi[dep]}, bb));
       st = 2;
-    } else if (ds == 1) {
+    } else {
       u128 ad{in.alo[dep], in.ahi[dep]}, bd{in.blo[dep], in.bhi[dep]};
       a = u128_max(a, u128_add(ad, bb));
       bb = u128_add(bd, bb);
@@ -670,23 +685,26 @@ __device__ inline bool eom_step(uint32_t item, const Eom &in, const Eom &out, co
   return true;
 }
 
-__global__ __launch_bounds__(B) void k_eom_round(const uint32_t *act, const uint64_t *nact_in, Eom in, Eom out,
-                                                 const uint32_t *ch, const uint64_t *shi, const uint64_t *slo,
-                                                 uint32_t *next, unsigned long long *nnext) {
+__global__ __launch_bounds__(LBK) void k_eom_round(const uint32_t *act, const uint64_t *nact_in, Eom in, Eom out,
+                                                   const uint32_t *ch, const uint64_t *shi, const uint64_t *slo,
+                                                   uint32_t *next, unsigned long long *nnext) {
   const int64_t nact = (int64_t)*nact_in;
-  const int ct = tile_items(nact);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < nact; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(nact, tile, B * ct);
-#pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t i = base + (int64_t)k * B;
+  const int ct = list_items(nact);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nact; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t vals[LCT], pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nact, tile, LBK * ct);
+#pragma unroll 1
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
       keep[k] = false;
       vals[k] = 0;
       if (i < end) keep[k] = eom_step(act[i], in, out, ch, shi, slo, &vals[k]);
     }
-    tile_append(keep, vals, next, nnext);
+    list_positions(keep, pos, nnext);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) next[pos[k]] = vals[k];
   }
 }
 
@@ -724,21 +742,20 @@ __global__ __launch_bounds__(TB) void k_eom_tail(uint32_t *l0, uint32_t *l1, con
 }
 
 // selection with ties kept by the parent; ROOT never selected
-__global__ __launch_bounds__(B) void k_eom_select(const uint32_t *nch, const uint32_t *ch, Eom e, const uint64_t *shi,
-                                                  const uint64_t *slo, Cnt nrc, uint32_t *top, uint32_t *nxt,
-                                                  uint32_t *top2, uint32_t *nxt2, const uint32_t *cprow, uint32_t *act,
-                                                  unsigned long long *nact) {
+__global__ __launch_bounds__(LBK) void k_eom_select(const uint32_t *nch, const uint32_t *ch, Eom e, const uint64_t *shi,
+                                                    const uint64_t *slo, Cnt nrc, uint32_t *top, uint32_t *nxt,
+                                                    uint32_t *top2, uint32_t *nxt2, const uint32_t *cprow,
+                                                    uint32_t *act, unsigned long long *nact) {
   const int64_t nrows = nrc.get();
-  const int ct = tile_items(nrows);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < nrows; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(nrows, tile, B * ct);
+  const int ct = list_items(nrows);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nrows; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nrows, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t r = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t r = base + (int64_t)k * LBK;
       keep[k] = false;
-      vals[k] = (uint32_t)r;
       if (r >= end) continue;
       bool sel;
       if (cprow[r] == NONE32) sel = false;
@@ -755,13 +772,17 @@ __global__ __launch_bounds__(B) void k_eom_select(const uint32_t *nch, const uin
       nxt[r] = nx; nxt2[r] = nx;
       keep[k] = nx != NONE32;
     }
-    tile_append(keep, vals, act, nact);
+    list_positions(keep, pos, nact);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) act[pos[k]] = (uint32_t)(base + (int64_t)k * LBK);
   }
 }
 
-// top[r] = highest selected row among r and its ancestors below ROOT
-// (pointer doubling over (top, nxt); a row that finishes goes once more to the
-// next list, flagged COPY, so both buffers agree when the list is empty)
+// top[r] = highest selected row among r and its ancestors below ROOT (pointer
+// jumping over (top, nxt), HOPS links a round; a row that finishes goes once
+// more to the next list, flagged COPY, so both buffers agree when the list is
+// empty)
 __device__ inline bool top_step(uint32_t item, const uint32_t *tin, const uint32_t *nin, uint32_t *tout,
                                 uint32_t *nout, uint32_t *val) {
   const uint32_t r = item & ~COPY;
@@ -771,32 +792,37 @@ __device__ inline bool top_step(uint32_t item, const uint32_t *tin, const uint32
     nout[r] = nx;
     return false;
   }
-  uint32_t tv = tin[nx];
-  if (tv != NONE32) t = tv;
-  nx = nin[nx];
+  for (int hop = 0; nx != NONE32 && hop < HOPS; hop++) {
+    const uint32_t tv = tin[nx];
+    if (tv != NONE32) t = tv;
+    nx = nin[nx];
+  }
   tout[r] = t;
   nout[r] = nx;
   *val = nx == NONE32 ? (r | COPY) : r;
   return true;
 }
 
-__global__ __launch_bounds__(B) void k_top_jump(const uint32_t *act, const uint64_t *nact_in, const uint32_t *tin,
-                                                const uint32_t *nin, uint32_t *tout, uint32_t *nout, uint32_t *next,
-                                                unsigned long long *nnext) {
+__global__ __launch_bounds__(LBK) void k_top_jump(const uint32_t *act, const uint64_t *nact_in, const uint32_t *tin,
+                                                  const uint32_t *nin, uint32_t *tout, uint32_t *nout, uint32_t *next,
+                                                  unsigned long long *nnext) {
   const int64_t nact = (int64_t)*nact_in;
-  const int ct = tile_items(nact);
-  for (int64_t tile = blockIdx.x; tile * (B * ct) < nact; tile += gridDim.x) {
-    bool keep[CT];
-    uint32_t vals[CT];
-    const int64_t base = tile * (B * ct) + threadIdx.x, end = tile_end(nact, tile, B * ct);
+  const int ct = list_items(nact);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nact; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t vals[LCT], pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nact, tile, LBK * ct);
 #pragma unroll
-    for (int k = 0; k < CT; k++) {
-      const int64_t i = base + (int64_t)k * B;
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
       keep[k] = false;
       vals[k] = 0;
       if (i < end) keep[k] = top_step(act[i], tin, nin, tout, nout, &vals[k]);
     }
-    tile_append(keep, vals, next, nnext);
+    list_positions(keep, pos, nnext);
+#pragma unroll
+    for (int k = 0; k < LCT; k++)
+      if (keep[k]) next[pos[k]] = vals[k];
   }
 }
 
@@ -840,7 +866,7 @@ __global__ __launch_bounds__(B) void k_lab_rows(const uint32_t *prow, const uint
 }
 
 __global__ __launch_bounds__(B) void k_lab_flags(const uint32_t *top, const uint32_t *minmem, Cnt nrc,
-                                                 uint32_t *flag) {
+                                                 uint8_t *flag) {
   const int64_t nrows = nrc.get();
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * B)
     if (top[r] == (uint32_t)r && minmem[r] != NONE32) flag[minmem[r]] = 1;
@@ -855,27 +881,22 @@ __device__ inline uint32_t local_node(uint32_t x, uint32_t g, int64_t n, int64_t
   return ng + (pos_at(rowpos, x - n) - moff[g]);
 }
 
-// per record, in input order: its exit row's node and label
-__global__ __launch_bounds__(B) void k_out_points(const uint32_t *prow, const uint32_t *rlocal, const int32_t *rlab,
-                                                  int64_t n, const uint64_t *hdr, uint32_t *pt_cluster,
-                                                  int32_t *labels) {
+// per record, in input order: its exit row's node and label; then the cluster rows
+__global__ __launch_bounds__(B) void k_out(const uint32_t *prow, const uint32_t *rlocal, const int32_t *rlab,
+                                           const uint32_t *cnode, const uint32_t *cprow, const uint32_t *csize,
+                                           const uint64_t *cbirth, const uint64_t *shi, const uint64_t *slo,
+                                           const uint32_t *top, const uint32_t *rowg, const int64_t *eoff,
+                                           const uint32_t *moff, const uint32_t *rowpos, int64_t n, Cnt mc, Cnt nrc,
+                                           const uint64_t *hdr, ce_result out) {
   if (hdr[H_STATUS] != 0) return;  // a data error: no output is written
-  for (int64_t id = (int64_t)blockIdx.x * B + threadIdx.x; id < n; id += (int64_t)gridDim.x * B) {
+  const int64_t step = (int64_t)gridDim.x * B, i0 = (int64_t)blockIdx.x * B + threadIdx.x;
+  for (int64_t id = i0; id < n; id += step) {
     const uint32_t r = prow[id];
-    if (pt_cluster) pt_cluster[id] = rlocal[r];
-    if (labels) labels[id] = rlab[r];
+    if (out.pt_cluster) out.pt_cluster[id] = rlocal[r];
+    if (out.labels) out.labels[id] = rlab[r];
   }
-}
-
-__global__ __launch_bounds__(B) void k_out_clusters(const uint32_t *cnode, const uint32_t *cprow,
-                                                    const uint32_t *csize, const uint64_t *cbirth,
-                                                    const uint64_t *shi, const uint64_t *slo, const uint32_t *top,
-                                                    const uint32_t *rowg, const int64_t *eoff, const uint32_t *moff,
-                                                    const uint32_t *rowpos, int64_t n, Cnt mc, Cnt nrc,
-                                                    const uint64_t *hdr, ce_result out) {
-  if (hdr[H_STATUS] != 0) return;
   const int64_t m = mc.get(), nrows = nrc.get();
-  for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * B) {
+  for (int64_t r = i0; r < nrows; r += step) {
     const uint32_t c = cnode[r];
     const uint32_t g = c >= (uint64_t)(n + m) ? (uint32_t)(c - n - m) : graph_at(rowg, c - n);
     if (out.cl_id) out.cl_id[r] = local_node(c, g, n, m, eoff, moff, rowpos);
@@ -921,30 +942,23 @@ __global__ __launch_bounds__(B) void k_row_point_vals(const uint32_t *cnode, con
   }
 }
 
-__global__ __launch_bounds__(B) void k_graph_labels(const uint32_t *fscan, const int64_t *eoff, int64_t G,
-                                                    uint32_t *nl) {
-  for (int64_t g = (int64_t)blockIdx.x * B + threadIdx.x; g < G; g += (int64_t)gridDim.x * B)
-    nl[g] = fscan[eoff[g + 1]] - fscan[eoff[g]];
-}
-
 // per-graph counts and offsets of the call (its header): total and per-graph
 // rows, cluster rows and labels, row and cluster offsets; the status from the
 // error bits. Cluster rows of graph g start at bstart[g] + g (births, then its root).
 __global__ __launch_bounds__(B) void k_header(const uint64_t *hdr, int64_t G, const uint32_t *moff,
-                                              const uint32_t *bstart, const uint32_t *nlab, int64_t *out) {
+                                              const uint32_t *bstart, const uint32_t *fscan, const int64_t *eoff,
+                                              int64_t *out) {
   for (int64_t g = (int64_t)blockIdx.x * B + threadIdx.x; g <= G; g += (int64_t)gridDim.x * B) {
     if (g == 0) {
-      uint64_t labels = 0;
-      for (int64_t k = 0; k < G; k++) labels += nlab[k];
       out[0] = status_of(hdr[H_STATUS]);
       out[1] = moff[G];
       out[2] = (int64_t)bstart[G] + G;
-      out[3] = (int64_t)labels;
+      out[3] = fscan[eoff[G]];
     }
     if (g < G) {
       out[4 + 3 * g] = (int64_t)moff[g + 1] - moff[g];
       out[4 + 3 * g + 1] = (int64_t)bstart[g + 1] - bstart[g] + 1;
-      out[4 + 3 * g + 2] = nlab[g];
+      out[4 + 3 * g + 2] = (int64_t)fscan[eoff[g + 1]] - fscan[eoff[g]];
     }
     out[4 + 3 * G + g] = moff[g];
     out[4 + 3 * G + (G + 1) + g] = (int64_t)bstart[g] + g;
@@ -963,31 +977,27 @@ __global__ void k_virtual_counts(const uint32_t *vbase, uint64_t *hdr, int64_t R
   hdr[H_NVIRT] = nv;
   hdr[H_NEOM] = nrows + nv;
 }
-__global__ void k_eom_count(uint64_t *hdr) {
-  if (threadIdx.x == 0) hdr[H_NEOM] = hdr[H_NROWS];
-}
 
 }  // namespace
 
-// Rounds of a pointer-doubling loop over a tree of up to k rows: bits(k) + 1
-// end it; one more is a margin.
-static int doubling_rounds(int64_t k) { return bits_for((uint64_t)k) + 2; }
+// Rounds of a pointer-jumping loop over a tree of up to k rows: links grow
+// fivefold a round, and 5^(bits / 2) > 2^bits; one more empties the list.
+static int jump_rounds(int64_t k) { return bits_for((uint64_t)k) / 2 + 2; }
 
-// level tops (pointer doubling over same-level parents) and big children per
+// level tops (pointer jumping over same-level parents) and big children per
 // D-node, then births; act and act2 hold m + 1 entries each, loop is the
 // counter words of the rounds
 static ce_status discrete_births(Bufs &b, Cnt m, const uint32_t *kpar, const uint32_t *level, const uint64_t *rowL,
                                  uint32_t *top, uint32_t *act, uint32_t *act2, uint64_t *loop, uint32_t *bigcnt,
                                  uint8_t *isbirth, uint64_t *birthL, hipStream_t s) {
   const int64_t n = b.n, M = b.M;
-  const unsigned g = grid_cap(m.v, B), tg = grid_cap(m.v, B, tuning().list_grid);
+  const unsigned g = grid_cap(m.v, B), tg = list_blocks(m.v);
   auto tiles = [](int64_t k, int per = CT) { return (unsigned)((k + (int64_t)B * per - 1) / ((int64_t)B * per)); };
-  CE_LAUNCH(k_dd_top_init, dim3(g), dim3(B), 0, s, kpar, level, m, n, top);
-  CE_LAUNCH(k_dd_top_active, dim3(tg), dim3(B), 0, s, top, m, n, act, (unsigned long long *)&loop[0]);
-  const int R = doubling_rounds(m.v);
+  CE_LAUNCH(k_dd_top_init, dim3(tg), dim3(LBK), 0, s, kpar, level, m, n, top, act, (unsigned long long *)&loop[0]);
+  const int R = jump_rounds(m.v);
   uint32_t *lists[2] = {act, act2};
   for (int r = 0; r < R; r++)
-    CE_LAUNCH(k_dd_top_jump, dim3(tg), dim3(B), 0, s, lists[r & 1], &loop[r], n, top, lists[1 - (r & 1)],
+    CE_LAUNCH(k_dd_top_jump, dim3(tg), dim3(LBK), 0, s, lists[r & 1], &loop[r], n, top, lists[1 - (r & 1)],
               (unsigned long long *)&loop[r + 1]);
   CE_LAUNCH(k_loop_done, dim3(1), dim3(64), 0, s, &loop[R], b.hdr);
   CE_LAUNCH(k_fill32, dim3(g), dim3(B), 0, s, bigcnt, m.v, 0u);
@@ -1007,9 +1017,9 @@ size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete) {
   w.alloc<uint8_t>(m + 4);       // isbirth
   w.alloc<uint64_t>(m + 1);      // birthL
   w.alloc<uint64_t>(m + 1);      // rowL (the discrete arrays reuse exc, exl, labrow and fl)
-  w.alloc<uint32_t>(m + 2); w.alloc<uint32_t>(m + 2); w.alloc<uint32_t>(m + 1);  // flags32, idx, rowof
+  w.alloc<uint32_t>(m + 2);  // idx
+  if (G > 1) w.alloc<uint32_t>(m + 1);  // rowof
   for (int k = 0; k < 3; k++) w.alloc<uint32_t>(G + 2);  // nbig, bstart, rootrow
-  w.alloc<uint32_t>(G + 1);  // labels per graph
   for (int k = 0; k < 4; k++) w.alloc<uint32_t>(R);  // birth sort keys/values
   w.alloc<uint32_t>(n); w.alloc<uint64_t>(n);  // exc exl
   w.alloc<uint32_t>(R); w.alloc<uint32_t>(R); w.alloc<uint64_t>(R); w.alloc<uint32_t>(R);  // cnode csize cbirth cprow
@@ -1027,20 +1037,22 @@ size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete) {
   w.alloc<uint32_t>(R);  // minmem
   w.alloc<uint32_t>(RE); w.alloc<uint32_t>(RE);  // row active lists
   w.alloc<uint32_t>(n);  // labrow
-  w.alloc<uint32_t>(n + 1);  // flag / scan
+  w.alloc<uint8_t>(n);       // label flags
+  w.alloc<uint32_t>(n + 1);  // their scan
   return w.off + scan_ws_bytes(n + 1) + scan_ws_bytes(m + 1) + scan_ws_bytes(G + 1) + scan_ws_bytes(R + 1) +
          radix_ws_bytes(R) + 4096;
 }
 
 // Grid rounds of the excess-of-mass and label pointer-jumping loops that the
 // host enqueues for R cluster rows; what is left after them runs in one
-// workgroup. Pointer doubling over a tree of R rows ends within bits(R) + 1
-// rounds; the excess-of-mass rounds also rake, and measured runs end within
-// about bits(R) + 2.
-static int eom_rounds(int64_t R) { return bits_for((uint64_t)R) + 4; }
-static int top_rounds(int64_t R) { return bits_for((uint64_t)R) + 2; }
+// workgroup. Links grow fivefold a round, so jumping over a tree of R rows
+// ends within bits(R) / 2 + 1 rounds; the excess-of-mass rounds also rake, one
+// level of a balanced tree a round. Small calls (where a launch costs as much
+// as a round of one workgroup) leave more of them to it.
+static int eom_rounds(int64_t R) { return R <= 2048 ? 1 : bits_for((uint64_t)R) / (R <= 65536 ? 2 : 1) + 2; }
+static int top_rounds(int64_t R) { return R <= 2048 ? 0 : bits_for((uint64_t)R) / 2 + 1; }
 // counter words of the bounded loops (from H_LOOP): level tops, J, excess of mass, label tops
-constexpr int LOOP_DD = 0, LOOP_J = 40, LOOP_EOM = 80, LOOP_TOP = 130, LOOP_END = H_LOOP_END - H_LOOP;
+constexpr int LOOP_DD = 0, LOOP_J = 24, LOOP_EOM = 48, LOOP_TOP = 90, LOOP_END = H_LOOP_END - H_LOOP;
 
 // Sizes: m rows (device word, bound n - 1), nb births and nrows = nb + G
 // cluster rows, nvirt virtual nodes (device words, bounds from R).
@@ -1056,10 +1068,9 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   uint8_t *isbirth = ws.alloc<uint8_t>(mb + 4);
   uint64_t *birthL = ws.alloc<uint64_t>(mb + 1);
   uint64_t *rowL = ws.alloc<uint64_t>(mb + 1);
-  uint32_t *flags32 = ws.alloc<uint32_t>(mb + 2), *idx = ws.alloc<uint32_t>(mb + 2), *rowof = ws.alloc<uint32_t>(mb + 1);
+  uint32_t *idx = ws.alloc<uint32_t>(mb + 2), *rowof = G > 1 ? ws.alloc<uint32_t>(mb + 1) : nullptr;
   uint32_t *nbig = ws.alloc<uint32_t>(G + 2), *bstart = ws.alloc<uint32_t>(G + 2);
   uint32_t *rootrow = ws.alloc<uint32_t>(G + 2);
-  uint32_t *nlab = ws.alloc<uint32_t>(G + 1);
   uint32_t *bkey = ws.alloc<uint32_t>(R), *bval = ws.alloc<uint32_t>(R);
   uint32_t *bkey2 = ws.alloc<uint32_t>(R), *bval2 = ws.alloc<uint32_t>(R);
   uint32_t *exc = ws.alloc<uint32_t>(n);
@@ -1093,7 +1104,8 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   uint32_t *minmem = ws.alloc<uint32_t>(R);
   uint32_t *ract = ws.alloc<uint32_t>(RE), *ract2 = ws.alloc<uint32_t>(RE);
   uint32_t *labrow = ws.alloc<uint32_t>(n);
-  uint32_t *fl = ws.alloc<uint32_t>(n + 1);
+  uint8_t *fl = ws.alloc<uint8_t>(n);
+  uint32_t *fscan = ws.alloc<uint32_t>(n + 1);
   CE_WS_CHECK(ws);
   // discrete dendrogram: level, level tops and big-child counts per row live only until the
   // births are known and the per-row discrete outputs written, before exits, labels and flags use these
@@ -1102,12 +1114,11 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   uint64_t *loop = b.hdr + H_LOOP;  // counters of the bounded loops, zero from the start of the call
 
   const unsigned gm = grid_cap(mb + 1, B), gG = grid_for(G + 1, B),
-                 gR = grid_cap(R, B), gRE = grid_cap(RE, B);
-  CE_LAUNCH(k_fill32, dim3(gG), dim3(B), 0, s, nbig, G + 1, 0u);
-  CE_LAUNCH(k_cd_bigroots, dim3(gm), dim3(B), 0, s, kpar, b.ksize, b.rowg, m, n, M, nbig);
-  CE_LAUNCH(k_fill32, dim3(grid_cap((mb + 4) / 4, B)), dim3(B), 0, s, (uint32_t *)isbirth, (mb + 4) / 4, 0u);
-  CE_HIP(hipGetLastError());
-  CE_LAUNCH(k_row_lambda, dim3(gm), dim3(B), 0, s, b.msf_key, m, b.thr, b.q, rowL, level);
+                 gR = grid_cap(R, B);
+  CE_LAUNCH(k_cd_init, dim3(grid_cap(n > R ? n : R, B)), dim3(B), 0, s, n, mb, G, R, nbig, isbirth, fl,
+            (uint64_t *)acc, nch, ch, minmem);
+  CE_LAUNCH(k_cd_lambda, dim3(gm), dim3(B), 0, s, b.msf_key, kpar, b.ksize, b.rowg, m, n, M, b.thr, b.q, rowL, level,
+            nbig);
   CE_LAUNCH(k_cd_birth, dim3(gm), dim3(B), 0, s, b.kc_u, b.kc_v, b.ksize, kpar, rowL, b.q > 0, m, n, M, nbig, b.rowg,
             isbirth, birthL);
   CE_HIP(hipGetLastError());
@@ -1118,27 +1129,25 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
                 out->dd_level, out->dd_top);
     CE_HIP(hipGetLastError());
   }
+  // the cluster of every big row: the nearest birth above or at it
   {
     uint64_t *jl = loop + LOOP_J;
-    const unsigned tg = grid_cap(mb, B, tuning().list_grid);
-    CE_LAUNCH(k_cd_jinit, dim3(tg), dim3(B), 0, s, isbirth, kpar, b.ksize, b.rowg, m, n, M, J, jact,
+    const unsigned tg = list_blocks(mb);
+    CE_LAUNCH(k_cd_jinit, dim3(tg), dim3(LBK), 0, s, isbirth, kpar, b.ksize, b.rowg, m, n, M, J, jact,
               (unsigned long long *)&jl[0]);
-    const int R = doubling_rounds(mb);
+    const int R = jump_rounds(mb);
     uint32_t *lists[2] = {jact, jact2};
     for (int r = 0; r < R; r++)
-      CE_LAUNCH(k_cd_jstep, dim3(tg), dim3(B), 0, s, lists[r & 1], &jl[r], J, isbirth, m, n, lists[1 - (r & 1)],
+      CE_LAUNCH(k_cd_jstep, dim3(tg), dim3(LBK), 0, s, lists[r & 1], &jl[r], J, isbirth, m, n, lists[1 - (r & 1)],
                 (unsigned long long *)&jl[r + 1]);
     CE_LAUNCH(k_loop_done, dim3(1), dim3(64), 0, s, &jl[R], b.hdr);
   }
   // cluster rows: births in (graph, node) order, each graph followed by its root row
-  CE_LAUNCH(k_u8_to_u32, dim3(gm), dim3(B), 0, s, isbirth, m, flags32);
   CE_HIP(hipGetLastError());
-  CE_TRY(scan_exclusive_u32(flags32, idx, m, ws, s));
-  CE_LAUNCH(k_cluster_counts, dim3(1), dim3(64), 0, s, idx, &b.hdr[H_M], G, R, b.hdr);
+  CE_TRY(scan_exclusive<uint8_t>(isbirth, idx, m, ws, s));
+  CE_LAUNCH(k_cluster_counts, dim3(1), dim3(64), 0, s, idx, m, G, R, bstart, rootrow, b.hdr);
   const uint32_t *rowmap = idx;  // one graph: a birth's row is its index among births
-  if (G == 1) {
-    CE_LAUNCH(k_bstart_one, dim3(1), dim3(64), 0, s, bstart, b.hdr);
-  } else {
+  if (G > 1) {
     CE_LAUNCH(k_birth_list, dim3(gm), dim3(B), 0, s, isbirth, idx, b.rowg, m, bkey, bval);
     CE_HIP(hipGetLastError());
     bool alt = false;
@@ -1146,27 +1155,22 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
                                                  &alt, ws, s)));
     CE_LAUNCH(k_birth_rows, dim3(gR), dim3(B), 0, s, alt ? bval2 : bval, b.rowg, nb, rowof);
     CE_TRY(segment_bounds_u32(alt ? bkey2 : bkey, nb, Cnt(G), bstart, s));
+    CE_LAUNCH(k_root_rows, dim3(gG), dim3(B), 0, s, bstart, G, rootrow);
     rowmap = rowof;
   }
   CE_HIP(hipGetLastError());
-  CE_LAUNCH(k_root_rows, dim3(gG), dim3(B), 0, s, bstart, G, rootrow);
-  CE_LAUNCH(k_cd_rows, dim3(gm), dim3(B), 0, s, isbirth, rowmap, rootrow, b.ksize, birthL, kpar, J, b.rowg, m, n,
-            cnode, csize, cbirth, cprow);
-  CE_LAUNCH(k_cd_rootrows, dim3(gG), dim3(B), 0, s, rootrow, b.eoff, G, m, n, cnode, csize, cbirth, cprow);
-  CE_LAUNCH(k_fill64, dim3(grid_cap(3 * R, B)), dim3(B), 0, s, (uint64_t *)acc, 3 * R, (uint64_t)0);
+  CE_LAUNCH(k_cd_rows, dim3(gm), dim3(B), 0, s, isbirth, rowmap, rootrow, b.ksize, birthL, kpar, J, b.rowg, b.eoff, G,
+            m, n, cnode, csize, cbirth, cprow);
   // point terms of the stabilities per big row; exits per record in input order
   const int kp = items_per_thread(mb, B);
-  CE_LAUNCH(k_cd_point_terms, dim3(tiles(mb, kp)), dim3(B), 0, s, b.kc_u, b.kc_v, b.ksize, J, rowL, rowmap, rootrow, m,
-            n, M, kp, acc);
   uint32_t *prow = labrow;
   uint2 *wk = (uint2 *)exl;  // m <= n words of 8 bytes
-  CE_LAUNCH(k_cd_walk_words, dim3(gm), dim3(B), 0, s, kpar, b.ksize, J, rowmap, rootrow, n, m, M, wk);
-  CE_LAUNCH(k_cd_exit_ids, dim3(grid_cap(n, B)), dim3(B), 0, s, kpar, wk, rowL, b.eoff, G, rootrow, n, M,
-            prow, b.hdr, out->pt_lambda);
-  CE_LAUNCH(k_cd_acc_children, dim3((unsigned)((R + B - 1) / B)), dim3(B), 0, s, csize, cbirth, cprow, nrows, acc);
-  CE_LAUNCH(k_cd_stab, dim3(gR), dim3(B), 0, s, acc, csize, cbirth, nrows, shi, slo);
-  CE_LAUNCH(k_fill32, dim3(gR), dim3(B), 0, s, nch, R, 0u);
-  CE_LAUNCH(k_fill32, dim3(grid_cap(2 * R, B)), dim3(B), 0, s, ch, 2 * R, 0u);
+  CE_LAUNCH(k_cd_point_terms, dim3(tiles(mb, kp)), dim3(B), 0, s, b.kc_u, b.kc_v, b.ksize, J, rowL, rowmap, rootrow,
+            kpar, m, n, M, kp, acc, wk);
+  CE_LAUNCH(k_cd_exit_ids, dim3(grid_cap(n, B)), dim3(B), 0, s, kpar, wk, rowL, b.eoff, G, rootrow, n, M, prow, b.hdr,
+            out->pt_lambda);
+  CE_LAUNCH(k_cd_acc_children, dim3((unsigned)((R + B - 1) / B)), dim3(B), 0, s, csize, cbirth, cprow, nrows, acc,
+            b.q == 0, nch, ch);
   if (b.q > 0) {
     // any number of child clusters: per-parent lists, then chains of virtual sum nodes
     CE_LAUNCH(k_cd_child_keys, dim3(gR), dim3(B), 0, s, cprow, nrows, ckey);
@@ -1182,17 +1186,14 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
     CE_TRY(scan_exclusive_u32(vbase, vbase, nrows, ws, s));
     CE_LAUNCH(k_virtual_counts, dim3(1), dim3(64), 0, s, vbase, b.hdr, RE);
     CE_LAUNCH(k_cd_pairs, dim3(gR), dim3(B), 0, s, nch, choff, clist, vbase, nrows, ch);
-    CE_LAUNCH(k_cd_virtual, dim3(gR), dim3(B), 0, s, nch, choff, clist, vbase, nrows, nvirt, ch, nch, shi, slo);
+    CE_LAUNCH(k_cd_virtual, dim3(gR), dim3(B), 0, s, nch, choff, clist, vbase, nrows, nvirt, ch, nch);
     CE_HIP(hipGetLastError());
-  } else {
-    CE_LAUNCH(k_cd_children, dim3(gR), dim3(B), 0, s, cprow, nrows, nch, ch);
-    CE_LAUNCH(k_eom_count, dim3(1), dim3(64), 0, s, b.hdr);
   }
   // excess of mass: enqueued rounds, then the rest in one workgroup
   uint64_t *el = loop + LOOP_EOM;
-  const unsigned tRE = grid_cap(RE, B, tuning().list_grid);
-  CE_LAUNCH(k_eom_init, dim3(tRE), dim3(B), 0, s, nch, shi, slo, cprow, nrows, neom, e[0], e[1], ract,
-            (unsigned long long *)&el[0]);
+  const unsigned tRE = list_blocks(RE);
+  CE_LAUNCH(k_eom_init, dim3(tRE), dim3(LBK), 0, s, nch, acc, csize, cbirth, shi, slo, cprow, nrows, neom, e[0], e[1],
+            ract, (unsigned long long *)&el[0]);
   CE_HIP(hipGetLastError());
   uint32_t *lists[2] = {ract, ract2};
   const int EOM_ROUNDS = eom_rounds(RE), TOP_ROUNDS = top_rounds(R);
@@ -1201,42 +1202,36 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
     return CE_EDEVICE;
   }
   for (int r = 0; r < EOM_ROUNDS; r++)
-    CE_LAUNCH(k_eom_round, dim3(tRE), dim3(B), 0, s, lists[r & 1], &el[r], e[r & 1], e[1 - (r & 1)], ch, shi, slo,
+    CE_LAUNCH(k_eom_round, dim3(tRE), dim3(LBK), 0, s, lists[r & 1], &el[r], e[r & 1], e[1 - (r & 1)], ch, shi, slo,
               lists[1 - (r & 1)], (unsigned long long *)&el[r + 1]);
   CE_LAUNCH(k_eom_tail, dim3(1), dim3(TB), 0, s, lists[0], lists[1], &el[EOM_ROUNDS], EOM_ROUNDS & 1, e[0], e[1],
             ch, shi, slo, b.hdr);
   CE_HIP(hipGetLastError());
   // the list is empty: both state buffers hold the final values
   uint64_t *tl = loop + LOOP_TOP;
-  CE_LAUNCH(k_eom_select, dim3(grid_cap(R, B, tuning().list_grid)), dim3(B), 0, s, nch, ch, e[0], shi, slo, nrows,
+  CE_LAUNCH(k_eom_select, dim3(list_blocks(R)), dim3(LBK), 0, s, nch, ch, e[0], shi, slo, nrows,
             top, nxt, top2, nxt2, cprow, ract, (unsigned long long *)&tl[0]);
   CE_HIP(hipGetLastError());
   uint32_t *tops[2] = {top, top2}, *nxts[2] = {nxt, nxt2};
   for (int r = 0; r < TOP_ROUNDS; r++)
-    CE_LAUNCH(k_top_jump, dim3(tRE), dim3(B), 0, s, lists[r & 1], &tl[r], tops[r & 1], nxts[r & 1],
+    CE_LAUNCH(k_top_jump, dim3(tRE), dim3(LBK), 0, s, lists[r & 1], &tl[r], tops[r & 1], nxts[r & 1],
               tops[1 - (r & 1)], nxts[1 - (r & 1)], lists[1 - (r & 1)], (unsigned long long *)&tl[r + 1]);
   CE_LAUNCH(k_top_tail, dim3(1), dim3(TB), 0, s, lists[0], lists[1], &tl[TOP_ROUNDS], TOP_ROUNDS & 1, top, nxt, top2,
             nxt2, b.hdr);
   CE_HIP(hipGetLastError());
-  CE_LAUNCH(k_fill32, dim3(gR), dim3(B), 0, s, minmem, R, NONE32);
   CE_LAUNCH(k_lab_rows, dim3(grid_cap(n, B)), dim3(B), 0, s, prow, top, cprow, n, minmem);
-  CE_LAUNCH(k_fill32, dim3(grid_cap(n + 1, B)), dim3(B), 0, s, fl, n + 1, 0u);
   CE_LAUNCH(k_lab_flags, dim3(gR), dim3(B), 0, s, top, minmem, nrows, fl);
   CE_HIP(hipGetLastError());
-  CE_TRY(scan_exclusive_u32(fl, fl, Cnt(n), ws, s));
+  CE_TRY(scan_exclusive<uint8_t>(fl, fscan, Cnt(n), ws, s));
   // per cluster row first (small arrays), then every record reads its row's values
   uint32_t *rlocal = nxt;
   int32_t *rlab = (int32_t *)nxt2;
-  CE_LAUNCH(k_row_point_vals, dim3(gR), dim3(B), 0, s, cnode, cprow, top, minmem, fl, b.rowg, b.eoff, b.moff,
+  CE_LAUNCH(k_row_point_vals, dim3(gR), dim3(B), 0, s, cnode, cprow, top, minmem, fscan, b.rowg, b.eoff, b.moff,
             b.rowpos, n, m, nrows, rlocal, rlab);
-  CE_LAUNCH(k_out_points, dim3(grid_cap(n, B)), dim3(B), 0, s, prow, rlocal, rlab, n, b.hdr, out->pt_cluster,
-            out->labels);
-  CE_LAUNCH(k_out_clusters, dim3(gR), dim3(B), 0, s, cnode, cprow, csize, cbirth, shi, slo, top, b.rowg, b.eoff,
-            b.moff, b.rowpos, n, m, nrows, b.hdr, *out);
-  CE_LAUNCH(k_graph_labels, dim3(gG), dim3(B), 0, s, fl, b.eoff, G, nlab);
-  CE_LAUNCH(k_header, dim3(gG), dim3(B), 0, s, b.hdr, G, b.moff, bstart, nlab, hout);
+  CE_LAUNCH(k_out, dim3(grid_cap(n, B)), dim3(B), 0, s, prow, rlocal, rlab, cnode, cprow, csize, cbirth, shi, slo, top,
+            b.rowg, b.eoff, b.moff, b.rowpos, n, m, nrows, b.hdr, *out);
+  CE_LAUNCH(k_header, dim3(gG), dim3(B), 0, s, b.hdr, G, b.moff, bstart, fscan, b.eoff, hout);
   CE_HIP(hipGetLastError());
-  (void)gRE;
   ws.release(m0);
   return CE_OK;
 }

@@ -44,61 +44,102 @@ __device__ inline uint32_t block_excl_scan(uint32_t x, uint32_t *lds_w /*[4]*/, 
   return before + inc - x;
 }
 
+// SIPT consecutive elements from position base (a multiple of SIPT; the arrays
+// start at 16-byte boundaries), zero past n
+__device__ inline void scan_load(const uint32_t *in, int64_t base, int64_t n, uint32_t (&v)[SIPT]) {
+  static_assert(SIPT == 8, "two 16-byte loads");
+  if (base + SIPT <= n) {
+    const uint4 a = *(const uint4 *)(in + base), b = *(const uint4 *)(in + base + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < SIPT; k++) v[k] = base + k < n ? in[base + k] : 0u;
+  }
+}
+__device__ inline void scan_load(const uint8_t *in, int64_t base, int64_t n, uint32_t (&v)[SIPT]) {
+  if (base + SIPT <= n) {
+    const uint2 a = *(const uint2 *)(in + base);
+#pragma unroll
+    for (int k = 0; k < SIPT; k++) v[k] = ((k < 4 ? a.x : a.y) >> (8 * (k & 3))) & 255u;
+  } else {
+#pragma unroll
+    for (int k = 0; k < SIPT; k++) v[k] = base + k < n ? in[base + k] : 0u;
+  }
+}
+
 // Tiles of STILE elements; a block takes tiles blockIdx.x, + gridDim.x, ...
 // up to the live count's tiles (the grid is capped, so a small or empty live
 // count costs little).
-__global__ __launch_bounds__(SB) void k_scan_reduce(const uint32_t *in, Cnt nc, uint32_t *sums) {
+template <class T>
+__global__ __launch_bounds__(SB) void k_scan_reduce(const T *in, Cnt nc, uint32_t *sums) {
   __shared__ uint32_t lw[SB / 64];
   const int64_t n = nc.get();
   const int64_t tiles = (n + STILE - 1) / STILE;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int64_t base = tile * STILE + (int64_t)threadIdx.x * SIPT;
-    uint32_t acc = 0;
+    uint32_t v[SIPT], acc = 0;
+    scan_load(in, tile * STILE + (int64_t)threadIdx.x * SIPT, n, v);
 #pragma unroll
-    for (int k = 0; k < SIPT; k++)
-      if (base + k < n) acc += in[base + k];
+    for (int k = 0; k < SIPT; k++) acc += v[k];
     uint32_t tot;
     block_excl_scan(acc, lw, &tot);
     if (threadIdx.x == 0) sums[tile] = tot;
   }
 }
 
-__global__ __launch_bounds__(SB) void k_scan_apply(const uint32_t *in, uint32_t *out, Cnt nc,
-                                                   const uint32_t *sums_scanned) {
+// Up to SDIRECT tiles (scanned false) a block adds up the sums before its
+// tile itself: at most SDIRECT / 256 reads a thread against one more launch.
+constexpr int64_t SDIRECT = 2048;
+template <class T>
+__global__ __launch_bounds__(SB) void k_scan_apply(const T *in, uint32_t *out, Cnt nc, const uint32_t *sums,
+                                                   bool scanned) {
   __shared__ uint32_t lw[SB / 64];
   const int64_t n = nc.get();
   const int64_t tiles = (n + STILE - 1) / STILE;
   for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int64_t base = tile * STILE + (int64_t)threadIdx.x * SIPT;
-    uint32_t v[SIPT];
-    uint32_t acc = 0;
-#pragma unroll
-    for (int k = 0; k < SIPT; k++) {
-      v[k] = (base + k < n) ? in[base + k] : 0u;
-      acc += v[k];
+    uint32_t v[SIPT], acc = 0, before;
+    if (scanned) {
+      before = sums[tile];
+    } else {
+      uint32_t part = 0;
+      for (int64_t q = threadIdx.x; q < tile; q += SB) part += sums[q];
+      block_excl_scan(part, lw, &before);
     }
-    uint32_t run = block_excl_scan(acc, lw, nullptr) + sums_scanned[tile];
+    scan_load(in, base, n, v);
+#pragma unroll
+    for (int k = 0; k < SIPT; k++) acc += v[k];
+    uint32_t run = block_excl_scan(acc, lw, nullptr) + before;
+    uint32_t o[SIPT];
 #pragma unroll
     for (int k = 0; k < SIPT; k++) {
-      if (base + k < n) out[base + k] = run;
+      o[k] = run;
       run += v[k];
     }
+    if (base + SIPT <= n) {
+      *(uint4 *)(out + base) = make_uint4(o[0], o[1], o[2], o[3]);
+      *(uint4 *)(out + base + 4) = make_uint4(o[4], o[5], o[6], o[7]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < SIPT; k++)
+        if (base + k < n) out[base + k] = o[k];
+    }
+    if (base < n && base + SIPT >= n) out[n] = run;  // the thread of the last element
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums_scanned[tiles];
+  if (tiles == 0 && blockIdx.x == 0 && threadIdx.x == 0) out[0] = 0;
 }
 
 // single-block exclusive scan for up to STILE elements; out[n] = total
-__global__ __launch_bounds__(SB) void k_scan_small(const uint32_t *in, uint32_t *out, Cnt nc) {
+template <class T>
+__global__ __launch_bounds__(SB) void k_scan_small(const T *in, uint32_t *out, Cnt nc) {
   __shared__ uint32_t lw[SB / 64];
   const int64_t n = nc.get();
   int64_t base = (int64_t)threadIdx.x * SIPT;
   uint32_t v[SIPT];
   uint32_t acc = 0;
+  scan_load(in, base, n, v);
 #pragma unroll
-  for (int k = 0; k < SIPT; k++) {
-    v[k] = (base + k < n) ? in[base + k] : 0u;
-    acc += v[k];
-  }
+  for (int k = 0; k < SIPT; k++) acc += v[k];
   uint32_t tot;
   uint32_t run = block_excl_scan(acc, lw, &tot);
 #pragma unroll
@@ -121,9 +162,10 @@ size_t scan_ws_bytes(int64_t n) {
   return b + 512;
 }
 
-ce_status scan_exclusive_u32(const uint32_t *in, uint32_t *out, Cnt n, Ws &ws, hipStream_t s) {
+template <class T>
+ce_status scan_exclusive(const T *in, uint32_t *out, Cnt n, Ws &ws, hipStream_t s) {
   if (n.v <= STILE) {
-    CE_LAUNCH(k_scan_small, dim3(1), dim3(SB), 0, s, in, out, n);
+    CE_LAUNCH(k_scan_small<T>, dim3(1), dim3(SB), 0, s, in, out, n);
     CE_HIP(hipGetLastError());
     return CE_OK;
   }
@@ -133,14 +175,19 @@ ce_status scan_exclusive_u32(const uint32_t *in, uint32_t *out, Cnt n, Ws &ws, h
   uint32_t *sums = ws.alloc<uint32_t>(nb + 1);
   uint32_t *sums_sc = ws.alloc<uint32_t>(nb + 1);
   CE_WS_CHECK(ws);
+  const bool direct = nb <= SDIRECT;
   const unsigned g = grid_for(nb, 1, 2048);
-  CE_LAUNCH(k_scan_reduce, dim3(g), dim3(SB), 0, s, in, n, sums);
+  CE_LAUNCH(k_scan_reduce<T>, dim3(g), dim3(SB), 0, s, in, n, sums);
   CE_HIP(hipGetLastError());
-  CE_TRY(scan_exclusive_u32(sums, sums_sc, n.p ? Cnt(n.p, nb, n.sh + 11) : Cnt(nb), ws, s));
-  CE_LAUNCH(k_scan_apply, dim3(g), dim3(SB), 0, s, in, out, n, sums_sc);
+  if (!direct) CE_TRY(scan_exclusive<uint32_t>(sums, sums_sc, n.p ? Cnt(n.p, nb, n.sh + 11) : Cnt(nb), ws, s));
+  CE_LAUNCH(k_scan_apply<T>, dim3(g), dim3(SB), 0, s, in, out, n, direct ? sums : sums_sc, !direct);
   CE_HIP(hipGetLastError());
   ws.release(m);
   return CE_OK;
+}
+template ce_status scan_exclusive<uint8_t>(const uint8_t *, uint32_t *, Cnt, Ws &, hipStream_t);
+ce_status scan_exclusive_u32(const uint32_t *in, uint32_t *out, Cnt n, Ws &ws, hipStream_t s) {
+  return scan_exclusive<uint32_t>(in, out, n, ws, s);
 }
 
 // ------------------------------------------------------------ segment bounds
