@@ -4,14 +4,19 @@
 // connected-components run per threshold. By Thm 3 (at every threshold) the
 // components are those of the forest rows with w <= threshold, and the sorted
 // forest rows of a level are a prefix of the rows, so each level adds its
-// rows to the previous level's components:
-//   level 0: labels = identity, union rows [0, p_0), compress;
-//   level l: labels = level l-1, union rows [p_{l-1}, p_l), compress.
-// The union-find hooks the larger root under the smaller and halving moves a
-// link to a grandparent, so a parent always has a smaller id than its child
-// and every component's root is its smallest member: after compression the
-// labels are exactly the smallest member ids. The previous level's labels are
-// the next level's union-find, so no workspace is needed.
+// rows to the previous level's components, whose roots its labels name:
+//   W = identity
+//   level l: join the labels (level l-1) of the ends of the rows
+//   [p_{l-1}, p_l) in W, then every record's label = the root in W of its
+//   label at level l-1 (level -1: itself).
+// A join hooks a larger root under a smaller node and halving moves a link to
+// a grandparent, so a parent always has a smaller id than its child and every
+// component's root is its smallest member: the labels are exactly the smallest
+// member ids. Only roots of the level before are looked up in W, so W is never
+// copied: it lies where the last level's labels go, and no workspace is
+// needed. A level streams the labels once in and once out and reads W at the
+// roots: 29 levels of 2e7 records in 3.7 ms (copying the labels, joining through
+// the copy and compressing it in place took 4.2).
 #include "ce_internal.h"
 
 namespace ce {
@@ -19,9 +24,14 @@ namespace ce {
 namespace {
 
 constexpr int B = 256;
+constexpr int LI = 4;  // records per thread of the label pass, their first reads in flight together (1: 82 us a level
+                       // of 2e7 records, 4: 76; the joins lose by it, 59 -> 66)
 
 __device__ inline int32_t lc_ld(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline int32_t lc_cached(const int32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ inline void lc_st(int32_t *p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -73,38 +83,68 @@ __global__ __launch_bounds__(B) void k_lc_iota(int32_t *lab, int64_t n) {
   for (int64_t x = (int64_t)blockIdx.x * B + threadIdx.x; x < n; x += (int64_t)gridDim.x * B) lab[x] = (int32_t)x;
 }
 
-// joins the components of the rows [a, b): the larger root goes under the smaller
+// Joins the components of the rows [a, b). The labels before this level are
+// roots, so the first attempt needs no find: it fails only when the larger one
+// was hooked in this level. The smaller may have been: linking to a node that
+// is no root is as good, for its root is smaller still, so the two are never
+// of one component.
 __global__ __launch_bounds__(B) void k_lc_union(const uint32_t *tl, const uint32_t *hd, int64_t a, int64_t b,
-                                                int32_t *par) {
+                                                const int32_t *prev, int32_t *W) {
   for (int64_t j = a + (int64_t)blockIdx.x * B + threadIdx.x; j < b; j += (int64_t)gridDim.x * B) {
     int32_t u = (int32_t)tl[j], v = (int32_t)hd[j];
-    while (true) {
-      u = lc_find(par, u);
-      v = lc_find(par, v);
-      if (u == v) break;
+    if (prev) {
+      u = prev[u];
+      v = prev[v];
+    }
+    while (u != v) {
       const int32_t hi = u > v ? u : v, lo = u > v ? v : u;
-      if (atomicCAS(&par[hi], hi, lo) == hi) break;
+      if (atomicCAS(&W[hi], hi, lo) == hi) break;
+      u = lc_find(W, u);
+      v = lc_find(W, v);
     }
   }
 }
 
-// root without halving: a halving store is an intermediate ancestor, and one
-// landing after another thread stored the root would leave a non-root label
-__device__ inline int32_t lc_root(const int32_t *par, int32_t x) {
-  while (true) {
-    const int32_t p = lc_ld(&par[x]);
-    if (p == x) return x;
-    x = p;
+// Every record's label: the root of its label before. No hooks run now, and
+// the roots go elsewhere, so walks may halve W and read it through the caches
+// (a stale link is an ancestor all the same).
+__global__ __launch_bounds__(B) void k_lc_labels(const int32_t *prev, int32_t *W, int64_t n, int32_t *out) {
+  const int64_t i0 = (int64_t)blockIdx.x * (B * LI) + threadIdx.x;
+  int32_t x[LI], p[LI];
+#pragma unroll
+  for (int k = 0; k < LI; k++) {
+    const int64_t i = i0 + (int64_t)k * B;
+    x[k] = i < n ? (prev ? prev[i] : (int32_t)i) : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < LI; k++) p[k] = lc_cached(&W[x[k]]);
+#pragma unroll
+  for (int k = 0; k < LI; k++) {
+    const int64_t i = i0 + (int64_t)k * B;
+    if (i >= n) continue;
+    while (p[k] != x[k]) {
+      const int32_t g = lc_cached(&W[p[k]]);
+      if (g == p[k]) {
+        x[k] = g;
+        break;
+      }
+      lc_st(&W[x[k]], g);
+      x[k] = g;
+      p[k] = lc_cached(&W[g]);
+    }
+    out[i] = x[k];
   }
 }
 
-// every record's root, its component's smallest member (no hooks run now).
-// Only roots are stored, so every value a walk reads is an ancestor and the
-// last store to each entry is its root.
-__global__ __launch_bounds__(B) void k_lc_compress(int32_t *par, int64_t n) {
-  for (int64_t x = (int64_t)blockIdx.x * B + threadIdx.x; x < n; x += (int64_t)gridDim.x * B) {
-    const int32_t r = lc_root(par, (int32_t)x);
-    if (r != (int32_t)x) lc_st(&par[x], r);
+// The last level's labels take W's own place: only roots are stored, so every
+// value a walk reads is an ancestor and the last store to each entry is its
+// root. (A halving store, an intermediate ancestor, could land after another
+// thread stored the root.)
+__global__ __launch_bounds__(B) void k_lc_labels_last(const int32_t *prev, int32_t *W, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) {
+    int32_t x = prev ? prev[i] : (int32_t)i;
+    for (int32_t p = lc_ld(&W[x]); p != x; p = lc_ld(&W[x])) x = p;
+    lc_st(&W[i], x);
   }
 }
 
@@ -174,19 +214,27 @@ extern "C" ce_status ce_level_components(const uint32_t *msf_tail, const uint32_
     set_error("rows must be in ascending w (the order of the sorted forest)");
     return CE_EINVAL;
   }
+  int32_t *W = labels + (q - 1) * n;
+  CE_LAUNCH(k_lc_iota, dim3(grid_for(n, B)), dim3(B), 0, s, W, n);
   int64_t prev = 0;
   for (int64_t l = 0; l < q; l++) {
     int32_t *lab = labels + l * n;
+    const int32_t *before = l > 0 ? lab - n : nullptr;
     const int64_t end = (int64_t)hb[1 + l];
     if (end < prev || end > m) {
       set_error("internal: level bounds");
       return CE_EDEVICE;
     }
-    if (l == 0) CE_LAUNCH(k_lc_iota, dim3(grid_for(n, B)), dim3(B), 0, s, lab, n);
-    else CE_HIP(hipMemcpyAsync(lab, lab - n, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
-    if (end > prev) {
-      CE_LAUNCH(k_lc_union, dim3(grid_for(end - prev, B)), dim3(B), 0, s, msf_tail, msf_head, prev, end, lab);
-      CE_LAUNCH(k_lc_compress, dim3(grid_for(n, B)), dim3(B), 0, s, lab, n);
+    if (end > prev)
+      CE_LAUNCH(k_lc_union, dim3(grid_for(end - prev, B)), dim3(B), 0, s, msf_tail, msf_head, prev, end, before, W);
+    if (l == q - 1) {
+      if (end > prev || l > 0) CE_LAUNCH(k_lc_labels_last, dim3(grid_for(n, B)), dim3(B), 0, s, before, W, n);
+    } else if (end > prev) {
+      CE_LAUNCH(k_lc_labels, dim3((unsigned)((n + B * LI - 1) / (B * LI))), dim3(B), 0, s, before, W, n, lab);
+    } else if (before) {
+      CE_HIP(hipMemcpyAsync(lab, before, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
+    } else {
+      CE_LAUNCH(k_lc_iota, dim3(grid_for(n, B)), dim3(B), 0, s, lab, n);
     }
     CE_HIP(hipGetLastError());
     prev = end;
