@@ -97,8 +97,7 @@ __global__ __launch_bounds__(B) void k_ties(const uint32_t *gf, const uint32_t *
     tie[i] = tv;
     if (tv > mx) mx = tv;
   }
-  mx = wave_max_u32(mx);
-  if (wave_lane() == 0 && mx) atomicMax(maxtie, mx);
+  block_atomic_max(mx, maxtie);
 }
 
 // Alg. 2 window of every out-entry as a run [a, a + cnt) of in-entry indices
@@ -287,7 +286,7 @@ ce_status stage_causal_skeleton(const int32_t *src, const int32_t *dst, const in
   CE_TRY(scan_exclusive_u32(gf, gx, n, ws, s));
   CE_LAUNCH(k_run_starts, dim3(grid_for(n, B)), dim3(B), 0, s, gf, gx, n, gstart);
   CE_LAUNCH(k_zero_u64, dim3(1), dim3(1), 0, s, &b.hdr[7]);
-  CE_LAUNCH(k_ties, dim3(grid_for(n, B)), dim3(B), 0, s, gf, gx, gstart, n, tie, (unsigned int *)&b.hdr[7]);
+  CE_LAUNCH(k_ties, dim3(grid_for(n, B, 1024)), dim3(B), 0, s, gf, gx, gstart, n, tie, (unsigned int *)&b.hdr[7]);
   CE_LAUNCH(k_windows, dim3(grid_for(n, B)), dim3(B), 0, s, sk, incount, inpos, outpos, n, wa, wcnt);
   CE_HIP(hipGetLastError());
   CE_TRY(scan_exclusive_u32(wcnt, eoff, n, ws, s));

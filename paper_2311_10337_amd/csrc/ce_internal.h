@@ -267,6 +267,44 @@ __device__ inline uint64_t wave_min_u64(uint64_t v) {
   return v;
 }
 
+// max over a workgroup (up to 16 waves), applied with one atomic; call from all threads
+__device__ inline void block_atomic_max(uint32_t v, unsigned int *to) {
+  __shared__ uint32_t s_max;
+  if (threadIdx.x == 0) s_max = 0;
+  __syncthreads();
+  v = wave_max_u32(v);
+  if (wave_lane() == 0 && v) atomicMax(&s_max, v);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_max) atomicMax(to, s_max);
+}
+// workgroups of VB threads that validate: smallest and largest (ordered) time
+// and the error bits they found, one update each
+constexpr int VB = 1024;
+__device__ inline void put_validation(uint64_t mn, uint64_t mx, uint32_t flag, uint64_t *hdr) {
+  __shared__ uint64_t smin[VB / 64], smax[VB / 64];
+  __shared__ uint32_t sflag;
+  if (threadIdx.x == 0) sflag = 0;
+  __syncthreads();
+  for (int d = 32; d >= 1; d >>= 1) {
+    uint64_t a = __shfl_xor(mn, d, 64), b = __shfl_xor(mx, d, 64);
+    mn = a < mn ? a : mn;
+    mx = b > mx ? b : mx;
+  }
+  if (flag) atomicOr(&sflag, flag);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (lane == 0) { smin[w] = mn; smax[w] = mx; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int q = 1; q < VB / 64; q++) {
+      mn = smin[q] < mn ? smin[q] : mn;
+      mx = smax[q] > mx ? smax[q] : mx;
+    }
+    if (sflag) atomicOr((unsigned long long *)&hdr[H_STATUS], (unsigned long long)sflag);
+    atomicMin((unsigned long long *)&hdr[H_TMIN], (unsigned long long)mn);
+    atomicMax((unsigned long long *)&hdr[H_TMAX], (unsigned long long)mx);
+  }
+}
+
 // most items per thread of the aggregation kernels (LDS hash per tile)
 constexpr int CT = 16;
 // Linear probes an LDS aggregation hash tries before a key goes straight to

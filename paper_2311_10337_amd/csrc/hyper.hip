@@ -31,16 +31,12 @@ constexpr int B = 256;
 __device__ inline uint64_t t_to_ord(int64_t t) { return (uint64_t)t ^ (uint64_t(1) << 63); }
 
 // hdr[0] |= 2 member out of range, 4 bad offsets; hdr[1] = min t, hdr[2] = max t (ordered)
-__global__ __launch_bounds__(B) void k_hvalidate(const int32_t *members, const int64_t *off, const int64_t *t,
-                                                 int64_t n, int64_t nnz, int64_t V, uint64_t *hdr) {
-  __shared__ uint64_t smin[B / 64], smax[B / 64];
-  __shared__ uint32_t sflag;
-  if (threadIdx.x == 0) sflag = 0;
-  __syncthreads();
+__global__ __launch_bounds__(VB) void k_hvalidate(const int32_t *members, const int64_t *off, const int64_t *t,
+                                                  int64_t n, int64_t nnz, int64_t V, uint64_t *hdr) {
   uint64_t mn = NONE64, mx = 0;
   uint32_t flag = 0;
   const int64_t N = n > nnz ? n : nnz;
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < N; i += (int64_t)gridDim.x * B) {
+  for (int64_t i = (int64_t)blockIdx.x * VB + threadIdx.x; i < N; i += (int64_t)gridDim.x * VB) {
     if (i < n) {
       if (off[i + 1] < off[i]) flag |= 4u;
       const uint64_t o = t_to_ord(t[i]);
@@ -53,24 +49,7 @@ __global__ __launch_bounds__(B) void k_hvalidate(const int32_t *members, const i
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && (off[0] != 0 || off[n] != nnz)) flag |= 4u;
-  for (int d = 32; d >= 1; d >>= 1) {
-    uint64_t a = __shfl_xor(mn, d, 64), b = __shfl_xor(mx, d, 64);
-    mn = a < mn ? a : mn;
-    mx = b > mx ? b : mx;
-  }
-  if (flag) atomicOr(&sflag, flag);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) { smin[w] = mn; smax[w] = mx; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int q = 1; q < B / 64; q++) {
-      mn = smin[q] < mn ? smin[q] : mn;
-      mx = smax[q] > mx ? smax[q] : mx;
-    }
-    if (sflag) atomicOr((unsigned long long *)&hdr[0], (unsigned long long)sflag);
-    atomicMin((unsigned long long *)&hdr[1], (unsigned long long)mn);
-    atomicMax((unsigned long long *)&hdr[2], (unsigned long long)mx);
-  }
+  put_validation(mn, mx, flag, hdr);
 }
 
 __global__ void k_hinit_hdr(uint64_t *hdr) {
@@ -146,8 +125,7 @@ __global__ __launch_bounds__(B) void k_hrun_max(const uint32_t *start, const uin
     const uint32_t len = start[q + 1] - start[q];
     if (len - 1 > mx) mx = len - 1;
   }
-  mx = wave_max_u32(mx);
-  if (wave_lane() == 0 && mx) atomicMax(maxtie, mx);
+  block_atomic_max(mx, maxtie);
 }
 
 __global__ __launch_bounds__(B) void k_hemit(const uint32_t *sk, const uint32_t *sv, const uint32_t *pos,
@@ -181,7 +159,7 @@ __global__ void k_hput_u64(uint64_t *p, uint64_t v) { *p = v; }
 ce_status stage_hyper_validate(const int32_t *members, const int64_t *offsets, const int64_t *t, int64_t nnz,
                                Bufs &b, hipStream_t s) {
   CE_LAUNCH(k_hinit_hdr, dim3(1), dim3(64), 0, s, b.hdr);
-  CE_LAUNCH(k_hvalidate, dim3(grid_for(b.n > nnz ? b.n : nnz, B, 4096)), dim3(B), 0, s, members, offsets, t, b.n,
+  CE_LAUNCH(k_hvalidate, dim3(grid_for(b.n > nnz ? b.n : nnz, VB, 512)), dim3(VB), 0, s, members, offsets, t, b.n,
             nnz, b.V, b.hdr);
   CE_HIP(hipGetLastError());
   return CE_OK;
@@ -273,7 +251,7 @@ ce_status stage_hyper_skeleton(const int32_t *members, const int64_t *offsets, c
   CE_TRY(scan_exclusive_u32(f, fx, n, ws, s));
   CE_LAUNCH(k_hzero, dim3(1), dim3(64), 0, s, &b.hdr[7]);
   CE_LAUNCH(k_hrun_starts, dim3(grid_for(n, B)), dim3(B), 0, s, f, fx, n, start);
-  CE_LAUNCH(k_hrun_max, dim3(grid_for(n, B)), dim3(B), 0, s, start, fx, n, (unsigned int *)&b.hdr[7]);
+  CE_LAUNCH(k_hrun_max, dim3(grid_for(n, B, 512)), dim3(B), 0, s, start, fx, n, (unsigned int *)&b.hdr[7]);
   CE_HIP(hipGetLastError());
   uint64_t h[2];
   {
