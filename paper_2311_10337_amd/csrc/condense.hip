@@ -396,8 +396,8 @@ __device__ inline void add_limbs(bool active, uint32_t row, uint64_t l0, uint64_
 
 constexpr int AHS = 512;  // LDS hash slots for per-cluster-row sums
 
-// Also one 8-byte word per row for the exit walk: (parent node, size) for a
-// small row, (cluster row of its cluster, size) for a big one.
+// Also 16 bytes per row for the exit walk: (parent node, size) for a small
+// row, (cluster row of its cluster, size, lambda) for a big one.
 //
 // Point term of each cluster's stability: the records of a small child c of
 // a big row j all leave the cluster of j at lambda_j, so they add size(c) *
@@ -407,7 +407,7 @@ __global__ __launch_bounds__(B) void k_cd_point_terms(const uint32_t *kc_u, cons
                                                       const uint32_t *ksize, const uint32_t *J, const uint64_t *rowL,
                                                       const uint32_t *rowof, const uint32_t *rootrow,
                                                       const uint32_t *kpar, Cnt mc, int64_t n, int64_t M, int kct,
-                                                      unsigned long long *acc, uint2 *wk) {
+                                                      unsigned long long *acc, uint4 *wk) {
   __shared__ uint32_t hk[AHS];
   const int64_t m = mc.get();
   __shared__ unsigned long long h0[AHS], h1[AHS], h2[AHS];
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(B) void k_cd_point_terms(const uint32_t *kc_u, cons
       } else {
         up = kpar[n + j];
       }
-      wk[j] = make_uint2(up, sz);
+      wk[j] = make_uint4(up, sz, (uint32_t)L, (uint32_t)(L >> 32));
     }
     const bool act = cnt != 0 && L != 0;
     const u128 prod = u128_mul64(cnt, L);
@@ -474,24 +474,25 @@ __global__ __launch_bounds__(B) void k_cd_point_terms(const uint32_t *kc_u, cons
 // subtrees (fewer than M records, so fewer than M steps) to the first big
 // row y; it leaves the cluster of y at lambda_y, or its graph's root at 0 when
 // no big row is above it. Writes the exit cluster row and the exit lambda.
-__global__ __launch_bounds__(B) void k_cd_exit_ids(const uint32_t *kpar, const uint2 *wk, const uint64_t *rowL,
-                                                   const int64_t *eoff, int64_t G, const uint32_t *rootrow, int64_t n,
-                                                   int64_t M, uint32_t *prow, const uint64_t *hdr,
-                                                   uint64_t *pt_lambda) {
+// Bound by the random reads, one a step; with lambda in an array of its own,
+// one more a record, the walks took 3.5 ms at 5e7 records, now 2.6.
+__global__ __launch_bounds__(B) void k_cd_exit_ids(const uint32_t *kpar, const uint4 *wk, const int64_t *eoff,
+                                                   int64_t G, const uint32_t *rootrow, int64_t n, int64_t M,
+                                                   uint32_t *prow, const uint64_t *hdr, uint64_t *pt_lambda) {
   if (hdr[H_STATUS] != 0) pt_lambda = nullptr;  // a data error: no output is written
   for (int64_t id = (int64_t)blockIdx.x * B + threadIdx.x; id < n; id += (int64_t)gridDim.x * B) {
     uint32_t y = kpar[id], r = NONE32;
+    uint64_t L = 0;
     while (y != NONE32) {
-      const uint2 e = wk[y - n];
+      const uint4 e = wk[y - n];
       if (e.y >= (uint64_t)M) {
         r = e.x;
+        L = (uint64_t)e.z | ((uint64_t)e.w << 32);
         break;
       }
       y = e.x;
     }
-    uint64_t L = 0;
     if (y == NONE32) r = rootrow[G > 1 ? graph_of(eoff, G, id) : 0u];
-    else L = rowL[y - n];
     prow[id] = r;
     if (pt_lambda) pt_lambda[id] = L;
   }
@@ -1015,13 +1016,12 @@ size_t stage_condense_scratch(int64_t n, int64_t M, int64_t G, bool discrete) {
   Ws w;
   w.alloc<uint32_t>(m + 1); w.alloc<uint32_t>(m + 1); w.alloc<uint32_t>(m + 1);  // J, active lists
   w.alloc<uint8_t>(m + 4);       // isbirth
-  w.alloc<uint64_t>(m + 1);      // birthL
-  w.alloc<uint64_t>(m + 1);      // rowL (the discrete arrays reuse exc, exl, labrow and fl)
+  w.alloc<uint64_t>(m + 1);      // rowL
   w.alloc<uint32_t>(m + 2);  // idx
   if (G > 1) w.alloc<uint32_t>(m + 1);  // rowof
   for (int k = 0; k < 3; k++) w.alloc<uint32_t>(G + 2);  // nbig, bstart, rootrow
   for (int k = 0; k < 4; k++) w.alloc<uint32_t>(R);  // birth sort keys/values
-  w.alloc<uint32_t>(n); w.alloc<uint64_t>(n);  // exc exl
+  w.alloc<uint32_t>(n); w.alloc<uint64_t>(2 * n + 2);  // level; births' lambdas and big children, then the exit walk
   w.alloc<uint32_t>(R); w.alloc<uint32_t>(R); w.alloc<uint64_t>(R); w.alloc<uint32_t>(R);  // cnode csize cbirth cprow
   w.alloc<uint64_t>(3 * R);  // acc
   w.alloc<uint64_t>(RE); w.alloc<uint64_t>(RE);  // shi slo (and virtual nodes)
@@ -1066,15 +1066,14 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   uint32_t *J = ws.alloc<uint32_t>(mb + 1);
   uint32_t *jact = ws.alloc<uint32_t>(mb + 1), *jact2 = ws.alloc<uint32_t>(mb + 1);
   uint8_t *isbirth = ws.alloc<uint8_t>(mb + 4);
-  uint64_t *birthL = ws.alloc<uint64_t>(mb + 1);
   uint64_t *rowL = ws.alloc<uint64_t>(mb + 1);
   uint32_t *idx = ws.alloc<uint32_t>(mb + 2), *rowof = G > 1 ? ws.alloc<uint32_t>(mb + 1) : nullptr;
   uint32_t *nbig = ws.alloc<uint32_t>(G + 2), *bstart = ws.alloc<uint32_t>(G + 2);
   uint32_t *rootrow = ws.alloc<uint32_t>(G + 2);
   uint32_t *bkey = ws.alloc<uint32_t>(R), *bval = ws.alloc<uint32_t>(R);
   uint32_t *bkey2 = ws.alloc<uint32_t>(R), *bval2 = ws.alloc<uint32_t>(R);
-  uint32_t *exc = ws.alloc<uint32_t>(n);
-  uint64_t *exl = ws.alloc<uint64_t>(n);
+  uint32_t *level = ws.alloc<uint32_t>(n);
+  uint64_t *birthL = ws.alloc<uint64_t>(2 * mb + 2);
   uint32_t *cnode = ws.alloc<uint32_t>(R), *csize = ws.alloc<uint32_t>(R);
   uint64_t *cbirth = ws.alloc<uint64_t>(R);
   uint32_t *cprow = ws.alloc<uint32_t>(R);
@@ -1109,7 +1108,7 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   CE_WS_CHECK(ws);
   // discrete dendrogram: level, level tops and big-child counts per row live only until the
   // births are known and the per-row discrete outputs written, before exits, labels and flags use these
-  uint32_t *level = exc, *dtop = labrow, *bigcnt = (uint32_t *)exl;
+  uint32_t *dtop = labrow, *bigcnt = (uint32_t *)(birthL + mb + 1);
   auto tiles = [](int64_t k, int per = CT) { return (unsigned)((k + (int64_t)B * per - 1) / ((int64_t)B * per)); };
   uint64_t *loop = b.hdr + H_LOOP;  // counters of the bounded loops, zero from the start of the call
 
@@ -1164,10 +1163,10 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   // point terms of the stabilities per big row; exits per record in input order
   const int kp = items_per_thread(mb, B);
   uint32_t *prow = labrow;
-  uint2 *wk = (uint2 *)exl;  // m <= n words of 8 bytes
+  uint4 *wk = (uint4 *)birthL;  // 16 bytes a row where the births' lambdas were
   CE_LAUNCH(k_cd_point_terms, dim3(tiles(mb, kp)), dim3(B), 0, s, b.kc_u, b.kc_v, b.ksize, J, rowL, rowmap, rootrow,
             kpar, m, n, M, kp, acc, wk);
-  CE_LAUNCH(k_cd_exit_ids, dim3(grid_cap(n, B)), dim3(B), 0, s, kpar, wk, rowL, b.eoff, G, rootrow, n, M, prow, b.hdr,
+  CE_LAUNCH(k_cd_exit_ids, dim3(grid_cap(n, B)), dim3(B), 0, s, kpar, wk, b.eoff, G, rootrow, n, M, prow, b.hdr,
             out->pt_lambda);
   CE_LAUNCH(k_cd_acc_children, dim3((unsigned)((R + B - 1) / B)), dim3(B), 0, s, csize, cbirth, cprow, nrows, acc,
             b.q == 0, nch, ch);
