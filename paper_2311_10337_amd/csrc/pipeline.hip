@@ -610,7 +610,7 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
 // per node, the minimum key over its live edges. A tile of up to LBK * CT edges
 // first takes per-node minima in an LDS hash (late rounds send most edges to
 // a few big components), then one atomicMin per node per tile.
-constexpr int MHS = 1024;
+constexpr int MHS = 512;  // (1024, as many as the nodes of a small tile, cost 1e6-record calls 2 %)
 __global__ __launch_bounds__(LBK) void k_bv_min(EdgeLists L, const uint64_t *bv, uint64_t *best) {
   if (bv[BV_ACT] != ACT_ROUND) return;
   const Live lv = live_list(L, bv);
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(LBK) void k_bv_min(EdgeLists L, const uint64_t *bv,
           if ((int)wave_lane() == leader) kmin = v;
         });
         if (upd) {
-          uint32_t sl = (c * 2654435761u) >> 22;  // 10 bits
+          uint32_t sl = (c * 2654435761u) >> 23;  // 9 bits
           bool placed = false;
           for (int probe = 0; probe < HASH_PROBES && !placed; probe++) {
             uint32_t old = atomicCAS(&hk[sl], NONE32, c);
