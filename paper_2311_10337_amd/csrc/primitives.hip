@@ -1,10 +1,11 @@
 // Device-wide primitives: exclusive scan and a stable LSD radix sort.
 //
 // The radix sort is a reduce-then-scan design tiled for 64-wide waves:
-// each 256-thread block owns a 2048-key tile; the scatter pass ranks keys
+// each block owns a tile of 1024 to 4096 keys; the scatter pass ranks keys
 // stably inside the tile with 8 ballots per 64-key chunk (lanes with equal
-// digits form a peer mask), stages the tile in LDS in digit order and then
-// writes it out in runs of consecutive addresses. Up to 4096 pairs are sorted
+// digits form a peer mask), stages the tile in LDS in digit order, keys
+// first and then values in the same space, and writes it out in runs of
+// consecutive addresses. Up to 4096 pairs are sorted
 // by one workgroup in one launch; up to 96 tiles a pass is two launches
 // (counts, scatter), beyond three.
 #include "ce_internal.h"
@@ -215,28 +216,41 @@ ce_status segment_bounds_u32(const uint32_t *sorted_keys, Cnt n, Cnt G, uint32_t
 // ------------------------------------------------------------ radix sort
 namespace {
 
-constexpr int RB = 256;              // block
-constexpr int RW = RB / 64;          // waves per block
+constexpr int RB = 256;              // block, but for the widest tiles
 // keys per thread (IPT): 4, 8 or 16 (a tuning choice); a tile is RB * IPT keys
 
 // Digit counts per tile. Up to RS_FEW tiles, tile-major: a scatter workgroup
 // adds up the rows before its own itself, 256 digits at a time. Beyond,
 // digit-major, and k_rs_digits turns each digit's row into tile offsets.
 constexpr int RS_FEW = 96;
-template <class K, int IPT>
+constexpr int RS_ROWS = 32;  // rows of counts in flight
+template <class K, int IPT, int RB>
 __global__ __launch_bounds__(RB) void k_rs_hist(const K *keys, Cnt nc, int shift, uint32_t *hist,
                                                 int nblocks) {
-  constexpr int TILE = RB * IPT;
+  constexpr int TILE = RB * IPT, RW = RB / 64;
   __shared__ uint32_t cnt[RW][256];
   const int64_t n = nc.get();  // tiles past a device count write zero counts
   const int w = threadIdx.x >> 6;
   for (int i = threadIdx.x; i < RW * 256; i += RB) (&cnt[0][0])[i] = 0;
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * TILE;
+  constexpr int VK = 16 / sizeof(K);  // keys per 16-byte load
+  if (base + TILE <= n && ((uintptr_t)keys & 15) == 0) {
+    struct alignas(16) Vec { K k[VK]; };
+    const Vec *p = (const Vec *)(keys + base);
+    Vec v[IPT / VK];
 #pragma unroll
-  for (int k = 0; k < IPT; k++) {
-    int64_t i = base + k * RB + threadIdx.x;
-    if (i < n) atomicAdd(&cnt[w][(uint32_t)(keys[i] >> shift) & 255u], 1u);
+    for (int k = 0; k < IPT / VK; k++) v[k] = p[k * RB + threadIdx.x];
+#pragma unroll
+    for (int k = 0; k < IPT / VK; k++)
+#pragma unroll
+      for (int q = 0; q < VK; q++) atomicAdd(&cnt[w][(uint32_t)(v[k].k[q] >> shift) & 255u], 1u);
+  } else {
+#pragma unroll
+    for (int k = 0; k < IPT; k++) {
+      int64_t i = base + k * RB + threadIdx.x;
+      if (i < n) atomicAdd(&cnt[w][(uint32_t)(keys[i] >> shift) & 255u], 1u);
+    }
   }
   __syncthreads();
   for (int d = threadIdx.x; d < 256; d += RB) {
@@ -288,36 +302,57 @@ __device__ inline V iota_value(int64_t i) { return V(i); }
 template <>
 __device__ inline uint4 iota_value<uint4>(int64_t i) { return make_uint4((uint32_t)i, 0u, 0u, 0u); }
 
-template <class K, class V, int IPT>
+// exclusive scan over the 256 digits, one a thread of the first four waves; call from all threads
+__device__ inline uint32_t digit_excl_scan(uint32_t x, uint32_t *lds_w /*[4]*/) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t inc = wave_incl_scan(x, lane);
+  if (lane == 63 && w < 4) lds_w[w] = inc;
+  __syncthreads();
+  uint32_t before = 0;
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+    if (i < w) before += lds_w[i];
+  __syncthreads();
+  return before + inc - x;
+}
+
+template <class K, class V, int IPT, int RB>
 __global__ __launch_bounds__(RB) void k_rs_scatter(const K *kin, const V *vin, K *kout, V *vout, Cnt nc,
                                                    int shift, const uint32_t *hist, const uint32_t *total,
                                                    int nblocks, int iota) {
-  constexpr int TILE = RB * IPT, WT = TILE / RW;  // keys per tile, per wave (IPT chunks of 64)
+  constexpr int TILE = RB * IPT, RW = RB / 64, WT = TILE / RW;  // keys per tile, per wave (IPT chunks of 64)
   const int64_t n = nc.get();
   if ((int64_t)blockIdx.x * TILE >= n) return;
   __shared__ uint32_t wcnt[RW][256];
   __shared__ uint32_t dbase[256], gbase[256];
-  __shared__ uint32_t lw[RB / 64];
-  __shared__ K skey[TILE];
-  __shared__ V sval[TILE];
+  __shared__ uint32_t lw[4];
+  // keys, then values, pass through the same LDS on their way out
+  __shared__ alignas(16) char stage[TILE * (sizeof(K) > sizeof(V) ? sizeof(K) : sizeof(V))];
+  K *skey = (K *)stage;
+  V *sval = (V *)stage;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   for (int i = tid; i < RW * 256; i += RB) (&wcnt[0][0])[i] = 0;
   // where this tile's keys of digit `tid` go: after all smaller digits and the same digit in earlier tiles
-  {
-    uint32_t all = 0, mine = 0;
+  uint32_t all = 0, mine = 0;
+  if (tid < 256) {
     if (nblocks <= RS_FEW) {
-#pragma unroll 8
-      for (int q = 0; q < nblocks; q++) {
-        const uint32_t c = hist[q * 256 + tid];
-        all += c;
-        if (q < (int)blockIdx.x) mine += c;
+      for (int q0 = 0; q0 < nblocks; q0 += RS_ROWS) {
+        uint32_t c[RS_ROWS];
+#pragma unroll
+        for (int k = 0; k < RS_ROWS; k++) c[k] = q0 + k < nblocks ? hist[(q0 + k) * 256 + tid] : 0u;
+#pragma unroll
+        for (int k = 0; k < RS_ROWS; k++) {
+          all += c[k];
+          if (q0 + k < (int)blockIdx.x) mine += c[k];
+        }
       }
     } else {
       all = total[tid];
       mine = hist[(int64_t)tid * nblocks + blockIdx.x];
     }
-    gbase[tid] = block_excl_scan(all, lw, nullptr) + mine;
   }
+  all = digit_excl_scan(all, lw);
+  if (tid < 256) gbase[tid] = all + mine;
   __syncthreads();
   const int64_t tbase = (int64_t)blockIdx.x * TILE;
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -351,8 +386,8 @@ __global__ __launch_bounds__(RB) void k_rs_scatter(const K *kin, const V *vin, K
   __syncthreads();
   // per digit: exclusive prefix over waves, then exclusive scan over digits
   uint32_t tot = 0;
-  {
-    const int d = tid;  // RB == 256 digits
+  if (tid < 256) {
+    const int d = tid;
     uint32_t run = 0;
 #pragma unroll
     for (int q = 0; q < RW; q++) {
@@ -363,26 +398,39 @@ __global__ __launch_bounds__(RB) void k_rs_scatter(const K *kin, const V *vin, K
     tot = run;
   }
   __syncthreads();
-  uint32_t ex = block_excl_scan(tot, lw, nullptr);
-  dbase[tid] = ex;
+  const uint32_t ex = digit_excl_scan(tot, lw);
+  if (tid < 256) dbase[tid] = ex;
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < IPT; c++) {
     if (dig[c] < 256u) {
-      uint32_t p = dbase[dig[c]] + wcnt[w][dig[c]] + off[c];
-      skey[p] = key[c];
-      sval[p] = val[c];
+      off[c] += dbase[dig[c]] + wcnt[w][dig[c]];
+      skey[off[c]] = key[c];
     }
   }
   __syncthreads();
   const int64_t rem = n - tbase;
   const int valid_n = rem < TILE ? (int)rem : TILE;
-  for (int i = tid; i < valid_n; i += RB) {
-    K k = skey[i];
-    uint32_t d = (uint32_t)(k >> shift) & 255u;
-    const int64_t g = (int64_t)gbase[d] + (i - (int64_t)dbase[d]);
-    kout[g] = k;
-    vout[g] = sval[i];
+  uint32_t to[IPT];
+#pragma unroll
+  for (int c = 0; c < IPT; c++) {
+    const int i = c * RB + tid;
+    if (i < valid_n) {
+      const K k = skey[i];
+      const uint32_t d = (uint32_t)(k >> shift) & 255u;
+      to[c] = gbase[d] + ((uint32_t)i - dbase[d]);
+      kout[to[c]] = k;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < IPT; c++)
+    if (dig[c] < 256u) sval[off[c]] = val[c];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < IPT; c++) {
+    const int i = c * RB + tid;
+    if (i < valid_n) vout[to[c]] = sval[i];
   }
 }
 
@@ -480,8 +528,17 @@ __global__ __launch_bounds__(SMB) void k_rs_small(const K *kin, const V *vin, K 
 }
 
 // Up to 2^24 keys a sort may take 4 keys per thread (its histogram is sized
-// for that); larger sorts take at least 8. A 16-key tile stages up to 24 B
-// pairs in LDS: 96 KiB of the 160 KiB a gfx950 workgroup may use.
+// for that); larger sorts take at least 8. A tile of 4096 keys stages up to
+// 16 bytes of each in LDS: 64 KiB of the 160 KiB a gfx950 workgroup may use.
+//
+// Eight keys a thread (the default) means 2048-key tiles of 256 threads up to
+// RS_WIDE keys and 4096-key tiles of 512 threads beyond: runs of 16 keys a
+// digit instead of 8, and half the digit counts, whose columns are strided. At
+// 5e7 records the sorts take 1.8 ms less so (2.5e8 incidences and more: 8.3 of
+// 226), at 1e6 records 0.03 of 2.84, and lines at 6e6 or 1.2e7 keys lost 0.3 to
+// 0.4 ms of 1e7-record calls. Tiles of 8192 keys leave one workgroup on a CU
+// (53.1 ms against 50.3), 16 keys a thread at 256 threads too few waves (51.6).
+constexpr int64_t RS_WIDE = int64_t(1) << 19;
 int radix_ipt(int64_t n) {
   int ipt = tuning().radix_ipt;
   if (ipt != 4 && ipt != 8 && ipt != 16) ipt = 8;
@@ -490,7 +547,7 @@ int radix_ipt(int64_t n) {
   return ipt;
 }
 
-template <class K, class V, int IPT>
+template <class K, class V, int IPT, int RB>
 ce_status radix_passes(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int end_bit, bool iota_values,
                        bool *result_in_alt, Ws &ws, hipStream_t s) {
   constexpr int TILE = RB * IPT;
@@ -507,10 +564,10 @@ ce_status radix_passes(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int end
   bool first = true;
   if (end_bit <= begin_bit) end_bit = begin_bit + 1;  // one stable pass still materialises identity values
   for (int shift = begin_bit; shift < end_bit; shift += 8) {
-    CE_LAUNCH((k_rs_hist<K, IPT>), dim3((unsigned)nb), dim3(RB), 0, s, ki, n, shift, hist, nb);
+    CE_LAUNCH((k_rs_hist<K, IPT, RB>), dim3((unsigned)nb), dim3(RB), 0, s, ki, n, shift, hist, nb);
     CE_HIP(hipGetLastError());
     if (nb > RS_FEW) CE_LAUNCH(k_rs_digits, dim3(256), dim3(DB), 0, s, hist, nb, total);
-    CE_LAUNCH((k_rs_scatter<K, V, IPT>), dim3((unsigned)nb), dim3(RB), 0, s, ki, (const V *)vi, ko, vo, n,
+    CE_LAUNCH((k_rs_scatter<K, V, IPT, RB>), dim3((unsigned)nb), dim3(RB), 0, s, ki, (const V *)vi, ko, vo, n,
                        shift, hist, total, nb, (first && iota_values) ? 1 : 0);
     CE_HIP(hipGetLastError());
     first = false;
@@ -547,11 +604,13 @@ ce_status radix_sort_pairs(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int
   }
   switch (radix_ipt(n.v)) {
     case 4:
-      return radix_passes<K, V, 4>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
+      return radix_passes<K, V, 4, RB>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
     case 16:
-      return radix_passes<K, V, 16>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
+      return radix_passes<K, V, 16, RB>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
     default:
-      return radix_passes<K, V, 8>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
+      if (n.v > RS_WIDE)
+        return radix_passes<K, V, 8, 2 * RB>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
+      return radix_passes<K, V, 8, RB>(k0, v0, k1, v1, n, begin_bit, end_bit, iota_values, result_in_alt, ws, s);
   }
 }
 
