@@ -70,11 +70,6 @@ __global__ __launch_bounds__(B) void k_rowg(const uint64_t *msf_val, const int64
   }
 }
 
-// one graph: its rows are all rows
-__global__ void k_moff_one(uint32_t *moff, const uint64_t *m) {
-  if (threadIdx.x == 0) { moff[0] = 0; moff[1] = (uint32_t)*m; }
-}
-
 __global__ __launch_bounds__(B) void k_rowpos(const uint32_t *sorted_j, Cnt mc, uint32_t *rowpos) {
   const int64_t m = mc.get();
   for (int64_t p = (int64_t)blockIdx.x * B + threadIdx.x; p < m; p += (int64_t)gridDim.x * B)
@@ -82,27 +77,42 @@ __global__ __launch_bounds__(B) void k_rowpos(const uint32_t *sorted_j, Cnt mc, 
 }
 
 // Row j is written at its position in the batch, with its graph's local ids.
-__global__ __launch_bounds__(B) void k_rows(const uint64_t *msf_w, const uint64_t *msf_val, const uint32_t *kc_u,
-                                            const uint32_t *kc_v, const uint32_t *ksize, const uint32_t *rowg,
-                                            const uint32_t *rowpos, const uint32_t *moff, const int64_t *eoff,
-                                            Cnt mc, int64_t n, bool one, ce_result out) {
+// One graph: rows stay in place, local ids are the internal ones, and the
+// row's children, size and parent come from its 16-byte node and go to their
+// arrays here too.
+__global__ __launch_bounds__(B) void k_rows(const uint64_t *msf_w, const uint64_t *msf_val, const uint4 *node,
+                                            uint32_t *kc_u, uint32_t *kc_v, uint32_t *ksize, uint32_t *kpar,
+                                            const uint32_t *rowg, const uint32_t *rowpos, uint32_t *moff,
+                                            const int64_t *eoff, Cnt mc, int64_t n, ce_result out) {
   const int64_t m = mc.get();
+  const bool one = node != nullptr;
+  if (one && blockIdx.x == 0 && threadIdx.x < 2) moff[threadIdx.x] = threadIdx.x ? (uint32_t)m : 0u;
   for (int64_t j = (int64_t)blockIdx.x * B + threadIdx.x; j < m; j += (int64_t)gridDim.x * B) {
     const uint64_t v = msf_val[j];
     const int64_t w = (int64_t)msf_w[j];
-    // one graph: rows stay in place and local ids are the internal ones
     const uint32_t g = one ? 0u : rowg[j], p = one ? (uint32_t)j : rowpos[j], m0 = one ? 0u : moff[g];
     const uint32_t e0 = one ? 0u : (uint32_t)eoff[g], ng = one ? (uint32_t)n : (uint32_t)(eoff[g + 1] - eoff[g]);
     if (out.msf_tail) out.msf_tail[p] = (uint32_t)v - e0;
     if (out.msf_head) out.msf_head[p] = (uint32_t)(v >> 32) - e0;
     if (out.msf_w) out.msf_w[p] = w;
-    const uint32_t a = kc_u[j], b = kc_v[j];
+    uint32_t a, b, size;
+    if (one) {
+      const uint4 x = node[j];
+      kc_u[j] = a = x.x;
+      kc_v[j] = b = x.y;
+      ksize[j] = size = x.z;
+      kpar[n + j] = x.w;
+    } else {
+      a = kc_u[j];
+      b = kc_v[j];
+      size = ksize[j];
+    }
     const uint32_t fa = one ? a : a < (uint64_t)n ? a - e0 : ng + (rowpos[a - n] - m0);
     const uint32_t fb = one ? b : b < (uint64_t)n ? b - e0 : ng + (rowpos[b - n] - m0);
     if (out.sl_left) out.sl_left[p] = fa < fb ? fa : fb;
     if (out.sl_right) out.sl_right[p] = fa < fb ? fb : fa;
     if (out.sl_w) out.sl_w[p] = w;
-    if (out.sl_size) out.sl_size[p] = ksize[j];
+    if (out.sl_size) out.sl_size[p] = size;
   }
 }
 
@@ -144,11 +154,7 @@ size_t stage_graph_rows_scratch(int64_t n, int64_t G) {
 ce_status stage_graph_rows(Bufs &b, Ws &ws, hipStream_t s) {
   const int64_t G = b.G, mb = b.n > 1 ? b.n - 1 : 1;
   const Cnt m(&b.hdr[H_M], mb);
-  if (G == 1) {
-    CE_LAUNCH(k_moff_one, dim3(1), dim3(64), 0, s, b.moff, &b.hdr[H_M]);
-    CE_HIP(hipGetLastError());
-    return CE_OK;
-  }
+  if (G == 1) return CE_OK;  // (its rows are all rows: moff is written with them)
   size_t m0 = ws.mark();
   uint32_t *key = ws.alloc<uint32_t>(mb), *val = ws.alloc<uint32_t>(mb);
   uint32_t *key2 = ws.alloc<uint32_t>(mb), *val2 = ws.alloc<uint32_t>(mb);
@@ -167,8 +173,8 @@ ce_status stage_graph_rows(Bufs &b, Ws &ws, hipStream_t s) {
 
 ce_status stage_write_rows(Bufs &b, const ce_result *out, hipStream_t s) {
   const int64_t mb = b.n > 1 ? b.n - 1 : 1;
-  CE_LAUNCH(k_rows, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_key, b.msf_val, b.kc_u, b.kc_v, b.ksize,
-            b.rowg, b.rowpos, b.moff, b.eoff, Cnt(&b.hdr[H_M], mb), b.n, b.G == 1, *out);
+  CE_LAUNCH(k_rows, dim3(grid_cap(mb, B)), dim3(B), 0, s, b.msf_key, b.msf_val, b.node, b.kc_u, b.kc_v,
+            b.ksize, b.kpar, b.rowg, b.rowpos, b.moff, b.eoff, Cnt(&b.hdr[H_M], mb), b.n, *out);
   CE_HIP(hipGetLastError());
   return CE_OK;
 }
@@ -420,9 +426,6 @@ struct ThrArg {
 __global__ void k_set_thresholds(int64_t *thr, ThrArg a, int q) {
   for (int i = threadIdx.x; i < q; i += blockDim.x) thr[i] = a.v[i];
 }
-__global__ void k_set_offsets_one(int64_t *eoff, int64_t *voff, int64_t n, int64_t V) {
-  if (threadIdx.x == 0) { eoff[0] = 0; eoff[1] = n; voff[0] = 0; voff[1] = V; }
-}
 __global__ __launch_bounds__(B) void k_copy_i64(int64_t *dst, const int64_t *src, int64_t k) {
   for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < k; i += (int64_t)gridDim.x * B) dst[i] = src[i];
 }
@@ -525,13 +528,13 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
   b.G = G;
   b.t = c.t;
   int64_t *hout = sync ? b.outhdr : hdr_out;
+  OneGraph og;
+  if (!c.eoff_d && G == 1) og = OneGraph{(int64_t *)b.eoff, (int64_t *)b.voff, n, V};
   // offsets and thresholds reach the device without host staging (a call may be captured in a graph)
   if (c.eoff_d) {
     CE_LAUNCH(k_copy_i64, dim3(grid_for(G + 1, B, 1024)), dim3(B), 0, s, (int64_t *)b.eoff, c.eoff_d, G + 1);
     CE_LAUNCH(k_copy_i64, dim3(grid_for(G + 1, B, 1024)), dim3(B), 0, s, (int64_t *)b.voff, c.voff_d, G + 1);
-  } else if (G == 1) {
-    CE_LAUNCH(k_set_offsets_one, dim3(1), dim3(64), 0, s, (int64_t *)b.eoff, (int64_t *)b.voff, n, V);
-  } else {
+  } else if (G > 1) {
     CE_HIP(hipMemcpyAsync((void *)b.eoff, c.eoff_h, sizeof(int64_t) * (G + 1), hipMemcpyHostToDevice, s));
     CE_HIP(hipMemcpyAsync((void *)b.voff, c.voff_h, sizeof(int64_t) * (G + 1), hipMemcpyHostToDevice, s));
   }
@@ -545,8 +548,8 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
     if (max_dt < 0 || max_dt > c.th.v[c.th.q - 1]) max_dt = c.th.v[c.th.q - 1];
   }
   CE_HIP(hipGetLastError());
-  if (hy) CE_TRY(stage_hyper_validate(hy->members, hy->offsets, c.t, nnz, b, s));
-  else CE_TRY(stage_validate(c.src, c.dst, c.t, b, s));
+  if (hy) CE_TRY(stage_hyper_validate(hy->members, hy->offsets, c.t, nnz, og, b, s));
+  else CE_TRY(stage_validate(c.src, c.dst, c.t, og, b, s));
   if (c.eoff_d)
     CE_LAUNCH(k_check_offsets, dim3(grid_for(G + 1, B, 1024)), dim3(B), 0, s, b.eoff, b.voff, G, n, V, b.hdr);
   CE_HIP(hipGetLastError());

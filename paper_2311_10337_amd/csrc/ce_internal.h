@@ -465,6 +465,7 @@ struct Bufs {
   // the dendrogram: node x < n is the record with input id x, node n + j row j
   uint32_t *kpar = nullptr;     // [2n] parent of each node, NONE without one
   uint32_t *kc_u = nullptr, *kc_v = nullptr, *ksize = nullptr; // [n] children and size of each row
+  const uint4 *node = nullptr;  // one graph: the same four of each row, for the kernel that writes the rows out
   // scratch arenas: A for grouping, skeleton and Boruvka (it may overlap the
   // MSF/dendrogram arrays, which are not live yet), T for Boruvka, M for sorting
   // the MSF and the dendrogram, B for condensing (it overlaps the dead skeleton arrays)
@@ -481,7 +482,20 @@ enum : uint8_t { MSF_EDGE = 1, MSF_FIRST = 2, MSF_HEAD = 4, MSF_TAIL = 8 };
 
 // Stages. Sizes that depend on the data (forest rows, births, list lengths)
 // are device words of the control block; the stages enqueue work only.
-ce_status stage_validate(const int32_t *src, const int32_t *dst, const int64_t *t, Bufs &b, hipStream_t s);
+// offsets of a call on one graph, written with the control block's first words (eoff null: they are there)
+struct OneGraph {
+  int64_t *eoff = nullptr, *voff = nullptr;
+  int64_t n = 0, V = 0;
+};
+__device__ inline void init_hdr(uint64_t *hdr, const OneGraph &og) {
+  for (int i = threadIdx.x; i < kHdrWords; i += blockDim.x) hdr[i] = i == H_TMIN ? NONE64 : 0;
+  if (og.eoff && threadIdx.x < 2) {
+    og.eoff[threadIdx.x] = threadIdx.x ? og.n : 0;
+    og.voff[threadIdx.x] = threadIdx.x ? og.V : 0;
+  }
+}
+ce_status stage_validate(const int32_t *src, const int32_t *dst, const int64_t *t, const OneGraph &og, Bufs &b,
+                         hipStream_t s);
 ce_status stage_check_span(Bufs &b, hipStream_t s);
 ce_status read_validation(Bufs &b, hipStream_t s, uint64_t *flags, int64_t *tmin, int64_t *tmax);
 ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int64_t *t, Bufs &b, Ws &ws,
@@ -520,7 +534,7 @@ ce_status stage_time_filter(Bufs &b, int64_t max_dt, hipStream_t s);
 size_t stage_boruvka_scratch(int64_t n, int64_t slots);
 // dynamic hypergraphs (Sec. 5.3): members/offsets CSR per hyperedge
 ce_status stage_hyper_validate(const int32_t *members, const int64_t *offsets, const int64_t *t, int64_t nnz,
-                               Bufs &b, hipStream_t s);
+                               const OneGraph &og, Bufs &b, hipStream_t s);
 ce_status stage_hyper_skeleton(const int32_t *members, const int64_t *offsets, const int64_t *t, int64_t nnz,
                                Bufs &b, Ws &ws, hipStream_t s);
 size_t stage_hyper_skeleton_scratch(int64_t n, int64_t nnz);

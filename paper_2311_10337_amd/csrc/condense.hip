@@ -164,10 +164,6 @@ __global__ __launch_bounds__(LBK) void k_dd_top_jump(const uint32_t *act, const 
   }
 }
 // after the enqueued rounds every list must be empty; if not, the call fails
-__global__ void k_loop_done(const uint64_t *cnt, uint64_t *hdr) {
-  if (threadIdx.x == 0 && *cnt != 0) hdr[H_STATUS] |= 32;
-}
-
 // big children of every D-node: the level tops (rows that are their own top)
 // hanging below its block; records are never big (M >= 2)
 // big D-node children per D-node; a D-node can have millions of them, so the
@@ -235,6 +231,26 @@ __device__ inline bool j_terminal(uint32_t x, int64_t n, int64_t m, const uint8_
 
 // J[j] for big rows: self if birth, ROOT if a root, else the parent node.
 // Rows whose J is not yet a birth node or ROOT go to the active list.
+__device__ inline uint32_t j_first(const uint8_t *isbirth, const uint32_t *kpar, const uint32_t *ksize,
+                                   const uint32_t *rowg, int64_t j, int64_t n, int64_t m, int64_t M, bool *open) {
+  *open = false;
+  if (ksize[j] < (uint64_t)M) return NONE32;
+  if (isbirth[j]) return (uint32_t)(n + j);
+  const uint32_t v = kpar[n + j];
+  if (v == NONE32) return (uint32_t)(n + m + graph_at(rowg, j));
+  *open = !j_terminal(v, n, m, isbirth);
+  return v;
+}
+// HOPS links up from x, no further than a terminal; true when there
+__device__ inline bool j_hops(uint32_t *x, const uint32_t *J, const uint8_t *isbirth, int64_t n, int64_t m) {
+  bool done = false;
+  for (int hop = 0; hop < HOPS && !done; hop++) {
+    *x = J[*x - n];
+    done = j_terminal(*x, n, m, isbirth);
+  }
+  return done;
+}
+
 __global__ __launch_bounds__(LBK) void k_cd_jinit(const uint8_t *isbirth, const uint32_t *kpar, const uint32_t *ksize,
                                                   const uint32_t *rowg, Cnt mc, int64_t n, int64_t M, uint32_t *J,
                                                   uint32_t *act, unsigned long long *nact) {
@@ -249,16 +265,7 @@ __global__ __launch_bounds__(LBK) void k_cd_jinit(const uint8_t *isbirth, const 
       const int64_t j = base + (int64_t)k * LBK;
       keep[k] = false;
       if (j >= end) continue;
-      uint32_t v = NONE32;
-      if (ksize[j] >= (uint64_t)M) {
-        if (isbirth[j]) v = (uint32_t)(n + j);
-        else if (kpar[n + j] == NONE32) v = (uint32_t)(n + m + graph_at(rowg, j));
-        else {
-          v = kpar[n + j];
-          keep[k] = !j_terminal(v, n, m, isbirth);
-        }
-      }
-      J[j] = v;
+      J[j] = j_first(isbirth, kpar, ksize, rowg, j, n, m, M, &keep[k]);
     }
     list_positions(keep, pos, nact);
 #pragma unroll
@@ -286,20 +293,48 @@ __global__ __launch_bounds__(LBK) void k_cd_jstep(const uint32_t *act, const uin
       vals[k] = 0;
       if (i >= end) continue;
       const uint32_t j = act[i];
-      uint32_t x = J[J[j] - n];
-      bool done = j_terminal(x, n, m, isbirth);
-      for (int hop = 1; hop < HOPS && !done; hop++) {
-        x = J[x - n];
-        done = j_terminal(x, n, m, isbirth);
-      }
+      uint32_t x = J[j];
+      keep[k] = !j_hops(&x, J, isbirth, n, m);
       J[j] = x;
-      keep[k] = !done;
       vals[k] = j;
     }
     list_positions(keep, pos, nout);
 #pragma unroll
     for (int k = 0; k < LCT; k++)
       if (keep[k]) out[pos[k]] = vals[k];
+  }
+}
+
+// Up to JSMALL rows: all of it in one workgroup, where a launch costs as much
+// as several rounds (eight launches, 20 us, at 1000 records).
+constexpr int JSB = 1024, JSMALL = 4096;
+__global__ __launch_bounds__(JSB) void k_cd_jsmall(const uint8_t *isbirth, const uint32_t *kpar, const uint32_t *ksize,
+                                                   const uint32_t *rowg, Cnt mc, int64_t n, int64_t M, uint32_t *J,
+                                                   uint64_t *hdr) {
+  const int64_t m = mc.get();
+  bool open[JSMALL / JSB], any = false;
+#pragma unroll
+  for (int k = 0; k < JSMALL / JSB; k++) {
+    const int64_t j = k * JSB + threadIdx.x;
+    open[k] = false;
+    if (j < m) J[j] = j_first(isbirth, kpar, ksize, rowg, j, n, m, M, &open[k]);
+    any |= open[k];
+  }
+  for (int round = 0; __syncthreads_or(any); round++) {
+    if (round > 8) {  // 5^6 > JSMALL: not a forest
+      if (threadIdx.x == 0) atomicOr((unsigned long long *)&hdr[H_STATUS], 32ull);
+      break;
+    }
+    any = false;
+#pragma unroll
+    for (int k = 0; k < JSMALL / JSB; k++) {
+      if (!open[k]) continue;
+      const int64_t j = k * JSB + threadIdx.x;
+      uint32_t x = J[j];
+      open[k] = !j_hops(&x, J, isbirth, n, m);
+      J[j] = x;
+      any |= open[k];
+    }
   }
 }
 
@@ -346,11 +381,13 @@ __global__ __launch_bounds__(B) void k_birth_list(const uint8_t *isbirth, const 
   }
 }
 // births and cluster rows from the scan of the birth flags (idx[m] = births);
-// more rows than the bound marks the call failed. One graph: its births are
+// more rows than the bound, or rows left over by the pointer jumping before
+// (left0, left1), mark the call failed. One graph: its births are
 // rows 0..nb-1, its root the next.
-__global__ void k_cluster_counts(const uint32_t *idx, Cnt mc, int64_t G, int64_t R, uint32_t *bstart,
-                                 uint32_t *rootrow, uint64_t *hdr) {
+__global__ void k_cluster_counts(const uint32_t *idx, Cnt mc, int64_t G, int64_t R, const uint64_t *left0,
+                                 const uint64_t *left1, uint32_t *bstart, uint32_t *rootrow, uint64_t *hdr) {
   if (threadIdx.x != 0) return;
+  if (*left0 != 0 || *left1 != 0) hdr[H_STATUS] |= 32;
   uint64_t nb = idx[mc.get()];
   if ((int64_t)(nb + G) > R) {  // (cannot happen: every birth has at least M records) stay in bounds
     hdr[H_STATUS] |= 64;
@@ -982,8 +1019,8 @@ __global__ void k_virtual_counts(const uint32_t *vbase, uint64_t *hdr, int64_t R
 }  // namespace
 
 // Rounds of a pointer-jumping loop over a tree of up to k rows: links grow
-// fivefold a round, and 5^(bits / 2) > 2^bits; one more empties the list.
-static int jump_rounds(int64_t k) { return bits_for((uint64_t)k) / 2 + 2; }
+// fivefold a round, and 5^(bits / 2.3) > 2^bits.
+static int jump_rounds(int64_t k) { return bits_for((uint64_t)k) * 10 / 23 + 1; }
 
 // level tops (pointer jumping over same-level parents) and big children per
 // D-node, then births; act and act2 hold m + 1 entries each, loop is the
@@ -1000,7 +1037,6 @@ static ce_status discrete_births(Bufs &b, Cnt m, const uint32_t *kpar, const uin
   for (int r = 0; r < R; r++)
     CE_LAUNCH(k_dd_top_jump, dim3(tg), dim3(LBK), 0, s, lists[r & 1], &loop[r], n, top, lists[1 - (r & 1)],
               (unsigned long long *)&loop[r + 1]);
-  CE_LAUNCH(k_loop_done, dim3(1), dim3(64), 0, s, &loop[R], b.hdr);
   CE_LAUNCH(k_fill32, dim3(g), dim3(B), 0, s, bigcnt, m.v, 0u);
   const int kb = items_per_thread(m.v, B);
   CE_LAUNCH(k_dd_bigcount, dim3(tiles(m.v, kb)), dim3(B), 0, s, kpar, b.ksize, top, m, n, M, kb, bigcnt);
@@ -1129,7 +1165,11 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
     CE_HIP(hipGetLastError());
   }
   // the cluster of every big row: the nearest birth above or at it
-  {
+  const uint64_t *jleft;
+  if (mb <= JSMALL) {
+    CE_LAUNCH(k_cd_jsmall, dim3(1), dim3(JSB), 0, s, isbirth, kpar, b.ksize, b.rowg, m, n, M, J, b.hdr);
+    jleft = loop + LOOP_J;  // (zero)
+  } else {
     uint64_t *jl = loop + LOOP_J;
     const unsigned tg = list_blocks(mb);
     CE_LAUNCH(k_cd_jinit, dim3(tg), dim3(LBK), 0, s, isbirth, kpar, b.ksize, b.rowg, m, n, M, J, jact,
@@ -1139,12 +1179,13 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
     for (int r = 0; r < R; r++)
       CE_LAUNCH(k_cd_jstep, dim3(tg), dim3(LBK), 0, s, lists[r & 1], &jl[r], J, isbirth, m, n, lists[1 - (r & 1)],
                 (unsigned long long *)&jl[r + 1]);
-    CE_LAUNCH(k_loop_done, dim3(1), dim3(64), 0, s, &jl[R], b.hdr);
+    jleft = &jl[R];
   }
   // cluster rows: births in (graph, node) order, each graph followed by its root row
   CE_HIP(hipGetLastError());
   CE_TRY(scan_exclusive<uint8_t>(isbirth, idx, m, ws, s));
-  CE_LAUNCH(k_cluster_counts, dim3(1), dim3(64), 0, s, idx, m, G, R, bstart, rootrow, b.hdr);
+  CE_LAUNCH(k_cluster_counts, dim3(1), dim3(64), 0, s, idx, m, G, R,
+            loop + LOOP_DD + (b.q > 0 ? jump_rounds(mb) : 0), jleft, bstart, rootrow, b.hdr);
   const uint32_t *rowmap = idx;  // one graph: a birth's row is its index among births
   if (G > 1) {
     CE_LAUNCH(k_birth_list, dim3(gm), dim3(B), 0, s, isbirth, idx, b.rowg, m, bkey, bval);

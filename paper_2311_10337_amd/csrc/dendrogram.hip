@@ -50,8 +50,12 @@ __global__ __launch_bounds__(B) void k_dn_init(uint32_t *kpar, int64_t n, uint32
   }
 }
 
-__global__ __launch_bounds__(LBK) void k_msf_list(const uint8_t *flag, int64_t n2, uint32_t *out,
-                                                  unsigned long long *cnt) {
+// The forest's slots. Every live edge must be gone by now (the bound on the
+// enqueued slots guarantees it); if not, the call fails instead of returning a
+// partial forest.
+__global__ __launch_bounds__(LBK) void k_msf_list(const uint8_t *flag, int64_t n2, uint32_t *out, uint64_t *hdr) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && hdr[H_BV] != 0) atomicOr((unsigned long long *)&hdr[H_STATUS], 32ull);
+  unsigned long long *cnt = (unsigned long long *)&hdr[H_M];
   const int ct = list_items(n2);
   for (int64_t tile = blockIdx.x; tile * (LBK * ct) < n2; tile += gridDim.x) {
     bool keep[LCT];
@@ -66,15 +70,6 @@ __global__ __launch_bounds__(LBK) void k_msf_list(const uint8_t *flag, int64_t n
 #pragma unroll
     for (int k = 0; k < LCT; k++)
       if (keep[k]) out[pos[k]] = (uint32_t)(base + (int64_t)k * LBK);
-  }
-}
-
-// a forest has at most n - 1 rows; more means the call failed (and the rows
-// are dropped, so that later kernels stay in bounds)
-__global__ void k_check_rows(uint64_t *hdr, int64_t n) {
-  if (threadIdx.x == 0 && (int64_t)hdr[H_M] > (n > 1 ? n - 1 : 0)) {
-    hdr[H_STATUS] |= 64;
-    hdr[H_M] = 0;
   }
 }
 
@@ -93,6 +88,9 @@ __global__ __launch_bounds__(B) void k_dn_gather(const uint32_t *list, Cnt mc, c
                                                  const uint64_t *best, const uint32_t *bpar, int64_t n, uint64_t *okey,
                                                  uint4 *rec, uint32_t *mate, uint64_t *hdr) {
   const int64_t m = mc.get();
+  // a forest has at most n - 1 rows; more means the call failed (row counts are clamped wherever they are read)
+  if (blockIdx.x == 0 && threadIdx.x == 0 && (int64_t)hdr[H_M] > n - 1)
+    atomicOr((unsigned long long *)&hdr[H_STATUS], 64ull);
   for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < m; i += (int64_t)gridDim.x * B) {
     const uint32_t e = list[i], f = flag[e];
     const uint64_t key = skel_key[e];
@@ -246,8 +244,7 @@ __global__ __launch_bounds__(TB) void k_dn_level_tail(const uint32_t *sc, const 
   for (int l = from; l <= L; l++) {
     dn_level(sc, sp, mate, n, (int64_t)hdr[H_LPOS + l - 1], (int64_t)hdr[H_LPOS + l], threadIdx.x >> 6, TB / 64, side,
              T);
-    __threadfence();
-    __syncthreads();
+    __syncthreads();  // (the sums are read and added to past the workgroup's caches)
   }
 }
 
@@ -349,10 +346,8 @@ ce_status stage_rows(Bufs &b, Ws &ws, hipStream_t s) {
   Chains c;
   CE_TRY(carve(b, ws, c));
   uint32_t *list = (uint32_t *)b.msf_val;  // written after the list is read
-  CE_LAUNCH(k_msf_list, dim3(list_blocks(n2)), dim3(LBK), 0, s, b.msf_flag, n2, list,
-            (unsigned long long *)&b.hdr[H_M]);
-  CE_LAUNCH(k_check_rows, dim3(1), dim3(64), 0, s, b.hdr, n);
-  const Cnt m(&b.hdr[H_M], mb);
+  CE_LAUNCH(k_msf_list, dim3(list_blocks(n2)), dim3(LBK), 0, s, b.msf_flag, n2, list, b.hdr);
+  const Cnt m(&b.hdr[H_M], mb < n - 1 ? mb : n - 1);
   // gather into the key buffer from which an odd or even number of radix
   // passes ends in msf_key, so no copy follows the sort
   const int passes = b.keybits > 8 ? (b.keybits + 7) / 8 : 1;
@@ -379,7 +374,7 @@ ce_status stage_rows(Bufs &b, Ws &ws, hipStream_t s) {
 ce_status stage_dendrogram(Bufs &b, bool cut, Ws &ws, hipStream_t s) {
   const int64_t n = b.n, mb = row_bound(n, b.slots);
   if (n <= 1) return CE_OK;
-  const Cnt m(&b.hdr[H_M], mb);
+  const Cnt m(&b.hdr[H_M], mb < n - 1 ? mb : n - 1);
   size_t m0 = ws.mark();
   Chains c;
   CE_TRY(carve(b, ws, c));
@@ -408,7 +403,8 @@ ce_status stage_dendrogram(Bufs &b, bool cut, Ws &ws, hipStream_t s) {
   CE_HIP(hipGetLastError());
   CE_TRY(scan_exclusive_u32(side, side, m, ws, s));
   CE_LAUNCH(k_dn_emit, dim3(g), dim3(B), 0, s, sc, sp, side, cstart, top, c.mate, c.up, n, m, node);
-  CE_LAUNCH(k_dn_unpack, dim3(g), dim3(B), 0, s, node, n, m, b.kc_u, b.kc_v, b.ksize, b.kpar);
+  if (b.G == 1) b.node = node;  // unpacked where the rows are written
+  else CE_LAUNCH(k_dn_unpack, dim3(g), dim3(B), 0, s, node, n, m, b.kc_u, b.kc_v, b.ksize, b.kpar);
   if (cut) CE_LAUNCH(k_dn_trim, dim3(grid_cap(n, B)), dim3(B), 0, s, b.kpar, n, m);
   CE_HIP(hipGetLastError());
   ws.release(m0);

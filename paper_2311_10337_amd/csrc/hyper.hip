@@ -52,9 +52,7 @@ __global__ __launch_bounds__(VB) void k_hvalidate(const int32_t *members, const 
   put_validation(mn, mx, flag, hdr);
 }
 
-__global__ void k_hinit_hdr(uint64_t *hdr) {
-  for (int i = threadIdx.x; i < kHdrWords; i += blockDim.x) hdr[i] = i == H_TMIN ? NONE64 : 0;
-}
+__global__ void k_hinit_hdr(uint64_t *hdr, OneGraph og) { init_hdr(hdr, og); }
 __global__ void k_hzero(uint64_t *p) {
   if (threadIdx.x == 0) *p = 0;
 }
@@ -157,8 +155,8 @@ __global__ void k_hput_u64(uint64_t *p, uint64_t v) { *p = v; }
 }  // namespace
 
 ce_status stage_hyper_validate(const int32_t *members, const int64_t *offsets, const int64_t *t, int64_t nnz,
-                               Bufs &b, hipStream_t s) {
-  CE_LAUNCH(k_hinit_hdr, dim3(1), dim3(64), 0, s, b.hdr);
+                               const OneGraph &og, Bufs &b, hipStream_t s) {
+  CE_LAUNCH(k_hinit_hdr, dim3(1), dim3(256), 0, s, b.hdr, og);
   CE_LAUNCH(k_hvalidate, dim3(grid_for(b.n > nnz ? b.n : nnz, VB, 512)), dim3(VB), 0, s, members, offsets, t, b.n,
             nnz, b.V, b.hdr);
   CE_HIP(hipGetLastError());

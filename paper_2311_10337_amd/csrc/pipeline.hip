@@ -50,9 +50,7 @@ __global__ __launch_bounds__(VB) void k_validate(const int32_t *src, const int32
   put_validation(mn, mx, flag, hdr);
 }
 
-__global__ void k_init_hdr(uint64_t *hdr) {
-  for (int i = threadIdx.x; i < kHdrWords; i += blockDim.x) hdr[i] = i == H_TMIN ? NONE64 : 0;
-}
+__global__ void k_init_hdr(uint64_t *hdr, OneGraph og) { init_hdr(hdr, og); }
 
 // After validation: a time span wider than the plan's tbits bits is an error too (the keys would not fit).
 __global__ void k_check_span(uint64_t *hdr, int64_t n, int tbits) {
@@ -116,13 +114,15 @@ __global__ __launch_bounds__(B) void k_incidence_packed(const uint64_t *keys, co
 // every incidence entry names its slot; the entry's predecessor in the same
 // vertex list is the tail of the skeleton edge stored there
 // (an input that failed validation gets an empty skeleton, so everything after
-// it runs on n isolated records and stays in bounds whatever the input held)
+// it runs on n isolated records and stays in bounds whatever the input held).
+// No record has a minimum yet.
 __global__ __launch_bounds__(B) void k_skel_tails(const uint32_t *ikey, const uint32_t *ival, int64_t n2,
-                                                  const uint64_t *hdr, uint32_t *skel_tail) {
+                                                  const uint64_t *hdr, uint32_t *skel_tail, uint64_t *best) {
   const bool bad = hdr[H_STATUS] != 0;
   for (int64_t k = (int64_t)blockIdx.x * B + threadIdx.x; k < n2; k += (int64_t)gridDim.x * B) {
     uint32_t slot = ival[k];
     skel_tail[slot] = (!bad && k > 0 && ikey[k - 1] == ikey[k]) ? (ival[k - 1] >> 1) : NONE32;
+    if (k < n2 / 2) best[k] = NONE64;
   }
 }
 
@@ -169,10 +169,6 @@ __global__ __launch_bounds__(B) void k_skel_keys(uint32_t *skel_tail, const uint
   }
 }
 
-__global__ __launch_bounds__(B) void k_fill_u64(uint64_t *p, int64_t n, uint64_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) p[i] = v;
-}
-
 // ---------------------------------------------------------------- Boruvka
 // Every component that ever exists is a node: the records are nodes 0..n-1,
 // and each round gives the components it forms the next free ids. best[x] is
@@ -206,6 +202,7 @@ __global__ __launch_bounds__(B) void k_fill_u64(uint64_t *p, int64_t n, uint64_t
 // Boruvka state, words H_BV + k of the control block
 enum : int {
   BV_ACT = 0,      // what this slot does: 0 nothing, 1 a round, 2 a filter split, 3 the heavy edges of the split
+                   // (the listing of the forest's rows looks at it too)
   BV_E = 1,        // live edges of the current list
   BV_IN = 2,       // the list: edge buffer 0 or 1, or 2 = the skeleton rows themselves
   BV_OFF = 3,      // its first entry in that buffer
@@ -579,6 +576,7 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
     bv[BV_LIGHT] = light;
     bv[BV_CNT1] = 0;
     bv[BV_CNT2] = 0;
+    bv[H_M - H_BV] = 0;  // the forest's rows, counted after the last slot
     s_split = split;
   }
   __threadfence_block();
@@ -726,20 +724,11 @@ __global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint
   }
 }
 
-// after the last enqueued slot every live edge must be gone (the slot bound
-// guarantees it); if not, the call fails instead of returning a partial
-// forest. Also clears the forest's row count for the listing that follows.
-__global__ void k_bv_check(const uint64_t *bv, uint64_t *hdr) {
-  if (threadIdx.x != 0) return;
-  if (bv[BV_ACT] != ACT_NONE) hdr[H_STATUS] |= 32;
-  hdr[H_M] = 0;
-}
-
 // rows with weight < limit (rows are sorted, so they are a prefix): one binary
 // search; the prefix becomes the forest (the row count shrinks in place)
-__global__ void k_prefix_below(const uint64_t *key, uint64_t *m, uint64_t limit) {
+__global__ void k_prefix_below(const uint64_t *key, Cnt mc, uint64_t *m, uint64_t limit) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int64_t lo = 0, hi = (int64_t)*m;
+  int64_t lo = 0, hi = mc.get();
   while (lo < hi) {
     const int64_t mid = lo + (hi - lo) / 2;
     if (key[mid] < limit) lo = mid + 1;
@@ -810,8 +799,9 @@ ce_status read_u64(const uint64_t *dev, uint64_t *host_out, int count, hipStream
 }
 
 // Enqueues validation: error bits, min and max time into the control block.
-ce_status stage_validate(const int32_t *src, const int32_t *dst, const int64_t *t, Bufs &b, hipStream_t s) {
-  CE_LAUNCH(k_init_hdr, dim3(1), dim3(64), 0, s, b.hdr);
+ce_status stage_validate(const int32_t *src, const int32_t *dst, const int64_t *t, const OneGraph &og, Bufs &b,
+                         hipStream_t s) {
+  CE_LAUNCH(k_init_hdr, dim3(1), dim3(256), 0, s, b.hdr, og);
   CE_HIP(hipGetLastError());
   if (b.n > 0) {
     CE_LAUNCH(k_validate, dim3(grid_for(b.n, VB, 512)), dim3(VB), 0, s, src, dst, t, b.n, b.eoff, b.voff, b.G,
@@ -966,8 +956,7 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
   const uint32_t *sk = alt ? ikey_alt : ikey;
   const uint32_t *sv = alt ? ival_alt : ival;
   // 3. skeleton: predecessor in the same vertex list, then packed keys
-  CE_LAUNCH(k_skel_tails, dim3(grid_for(n2, B)), dim3(B), 0, s, sk, sv, n2, b.hdr, b.skel_tail);
-  CE_LAUNCH(k_fill_u64, dim3(grid_for(n, B)), dim3(B), 0, s, b.best, n, NONE64);
+  CE_LAUNCH(k_skel_tails, dim3(grid_for(n2, B)), dim3(B), 0, s, sk, sv, n2, b.hdr, b.skel_tail, b.best);
   CE_HIP(hipGetLastError());
   CE_LAUNCH(k_skel_keys, dim3(grid_for(n, B)), dim3(B), 0, s, b.skel_tail, b.ts, b.perm, n, b.idbits, b.skel_key,
             b.best, wraw);
@@ -1080,7 +1069,6 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   }
   CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
   if (plan.tail) CE_LAUNCH(k_bv_tail, dim3(1), dim3(BTB), 0, s, L, bv, best, bpar, rootc, b.msf_flag, b.hdr);
-  CE_LAUNCH(k_bv_check, dim3(1), dim3(64), 0, s, bv, b.hdr);
   CE_HIP(hipGetLastError());
   ws.release(m0);
   return CE_OK;
@@ -1093,7 +1081,8 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
 ce_status stage_time_filter(Bufs &b, int64_t max_dt, hipStream_t s) {
   if (max_dt < 0) return CE_OK;
   // the sorted rows' weights ascend
-  CE_LAUNCH(k_prefix_below, dim3(1), dim3(64), 0, s, b.msf_key, &b.hdr[H_M], (uint64_t)max_dt + 1);
+  CE_LAUNCH(k_prefix_below, dim3(1), dim3(64), 0, s, b.msf_key, Cnt(&b.hdr[H_M], b.n > 1 ? b.n - 1 : 0), &b.hdr[H_M],
+            (uint64_t)max_dt + 1);
   CE_HIP(hipGetLastError());
   return CE_OK;
 }

@@ -436,15 +436,16 @@ __global__ __launch_bounds__(RB) void k_rs_scatter(const K *kin, const V *vin, K
 
 // A sort of up to RS_SMALL pairs in one workgroup, all passes in LDS: a wave
 // ranks 256 neighbouring keys, and the pairs move through LDS between passes.
-constexpr int RS_SMALL = 4096, SMB = 1024, SMW = SMB / 64, SMI = RS_SMALL / SMB;
-template <class K, class V>
+// (SMI chunks of 64 keys a wave: one chunk spreads up to 1024 keys over all waves)
+constexpr int RS_SMALL = 4096, SMB = 1024, SMW = SMB / 64;
+template <class K, class V, int SMI>
 __global__ __launch_bounds__(SMB) void k_rs_small(const K *kin, const V *vin, K *kout, V *vout, Cnt nc, int begin_bit,
                                                   int end_bit, int iota) {
   __shared__ uint32_t wcnt[SMW][256];
   __shared__ uint32_t dbase[256];
   __shared__ uint32_t lw[4];
-  __shared__ K skey[RS_SMALL];
-  __shared__ V sval[RS_SMALL];
+  __shared__ K skey[SMB * SMI];
+  __shared__ V sval[SMB * SMI];
   const int n = (int)nc.get();
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const uint64_t below = lanes_below((uint32_t)lane);
@@ -596,8 +597,14 @@ ce_status radix_sort_pairs(K *k0, V *v0, K *k1, V *v1, Cnt n, int begin_bit, int
   if (n.v <= RS_SMALL) {  // the output goes where that many passes would have left it
     if (end_bit <= begin_bit) end_bit = begin_bit + 1;
     const bool alt = ((end_bit - begin_bit + 7) / 8) & 1;
-    CE_LAUNCH((k_rs_small<K, V>), dim3(1), dim3(SMB), 0, s, k0, (const V *)v0, alt ? k1 : k0, alt ? v1 : v0, n,
-              begin_bit, end_bit, iota_values ? 1 : 0);
+    K *ko = alt ? k1 : k0;
+    V *vo = alt ? v1 : v0;
+    if (n.v <= SMB)
+      CE_LAUNCH((k_rs_small<K, V, 1>), dim3(1), dim3(SMB), 0, s, k0, (const V *)v0, ko, vo, n, begin_bit, end_bit,
+                iota_values ? 1 : 0);
+    else
+      CE_LAUNCH((k_rs_small<K, V, RS_SMALL / SMB>), dim3(1), dim3(SMB), 0, s, k0, (const V *)v0, ko, vo, n, begin_bit,
+                end_bit, iota_values ? 1 : 0);
     CE_HIP(hipGetLastError());
     *result_in_alt = alt;
     return CE_OK;
