@@ -111,37 +111,45 @@ __global__ __launch_bounds__(B) void k_incidence_packed(const uint64_t *keys, co
   }
 }
 
-// every incidence entry names its slot; the entry's predecessor in the same
-// vertex list is the tail of the skeleton edge stored there
+// every incidence entry names its slot; the entry's neighbours in the same
+// vertex list go there: before it the tail of its skeleton edge, after it the
+// head of the edge whose tail it is (NONE at the list's ends). A scattered
+// write costs a 32-byte transaction whatever its width.
 // (an input that failed validation gets an empty skeleton, so everything after
-// it runs on n isolated records and stays in bounds whatever the input held).
-// No record has a minimum yet.
-__global__ __launch_bounds__(B) void k_skel_tails(const uint32_t *ikey, const uint32_t *ival, int64_t n2,
-                                                  const uint64_t *hdr, uint32_t *skel_tail, uint64_t *best) {
+// it runs on n isolated records and stays in bounds whatever the input held)
+__global__ __launch_bounds__(B) void k_skel_links(const uint32_t *ikey, const uint32_t *ival, int64_t n2,
+                                                  const uint64_t *hdr, uint2 *link) {
   const bool bad = hdr[H_STATUS] != 0;
   for (int64_t k = (int64_t)blockIdx.x * B + threadIdx.x; k < n2; k += (int64_t)gridDim.x * B) {
-    uint32_t slot = ival[k];
-    skel_tail[slot] = (!bad && k > 0 && ikey[k - 1] == ikey[k]) ? (ival[k - 1] >> 1) : NONE32;
-    if (k < n2 / 2) best[k] = NONE64;
+    const uint32_t v = ikey[k];
+    uint2 l = make_uint2(NONE32, NONE32);
+    if (!bad && k > 0 && ikey[k - 1] == v) l.x = ival[k - 1] >> 1;
+    if (!bad && k + 1 < n2 && ikey[k + 1] == v) l.y = ival[k + 1] >> 1;
+    link[ival[k]] = l;
   }
 }
 
-// Also seeds the first Boruvka round: every record starts as its own
-// component, so each edge offers its key to both of its records.
+// Keys of a record's two skeleton edges as a head, and its first Boruvka
+// minimum: every record starts as its own component, and its edges are the
+// two it heads and the two it is the tail of.
 // The low bit orders the two edges of a head by descending tail id; it only
 // decides their order when they have the same weight (else w does), so the
-// tails' ids are read only then.
+// tails' ids are read only then. As a tail a record offers itself the key
+// with that bit zero: no other edge of its has the same weight and head, so
+// the choice is the same, and the first round compares without the bit.
+// (Each head offering its keys to its tails instead, two atomics a record, took
+// 3.84 ms at 5e7 records with burst-local tails and 15.8 at 2e8; reading the
+// heads' times and ids takes 2.3 and 14.2, the wider links 1.0 and 0.8 more.)
 // Weight ranks (wraw set): the keys get their tie bits only, the weights go
-// to wraw, and the seeding waits for the ranks.
-__global__ __launch_bounds__(B) void k_skel_keys(uint32_t *skel_tail, const uint64_t *ts, const uint32_t *perm,
-                                                 int64_t n, int idbits, uint64_t *skel_key, uint64_t *best,
+// to wraw, and the minima wait for the ranks.
+// The links lie where the keys go; a thread reads its own two first.
+__global__ __launch_bounds__(B) void k_skel_keys(const uint64_t *ts, const uint32_t *perm, int64_t n, int idbits,
+                                                 uint64_t *skel_key, uint2 *skel_tail, uint64_t *best,
                                                  uint64_t *wraw) {
   for (int64_t h = (int64_t)blockIdx.x * B + threadIdx.x; h < n; h += (int64_t)gridDim.x * B) {
-    uint32_t t0 = skel_tail[2 * h], t1 = skel_tail[2 * h + 1];
-    if (t0 != NONE32 && t0 == t1) {  // the same pair twice: one line-graph edge
-      t1 = NONE32;
-      skel_tail[2 * h + 1] = NONE32;
-    }
+    const uint4 l = ((const uint4 *)skel_key)[h];
+    const uint32_t t0 = l.x, t1 = l.z == l.x ? NONE32 : l.z;  // the same pair twice: one line-graph edge
+    skel_tail[h] = make_uint2(t0, t1);
     const uint64_t hid = perm[h];
     const uint64_t th = ts[h];
     const uint64_t w0 = t0 != NONE32 ? th - ts[t0] : 0, w1 = t1 != NONE32 ? th - ts[t1] : 0;
@@ -151,21 +159,29 @@ __global__ __launch_bounds__(B) void k_skel_keys(uint32_t *skel_tail, const uint
       b0 = i0 < i1 ? 1u : 0u;
       b1 = 1u - b0;
     }
+    ulonglong2 k;
     if (wraw) {
-      skel_key[2 * h] = t0 != NONE32 ? (hid << 1) | b0 : NONE64;
-      skel_key[2 * h + 1] = t1 != NONE32 ? (hid << 1) | b1 : NONE64;
+      k.x = t0 != NONE32 ? (hid << 1) | b0 : NONE64;
+      k.y = t1 != NONE32 ? (hid << 1) | b1 : NONE64;
+      ((ulonglong2 *)skel_key)[h] = k;
       wraw[2 * h] = w0;
       wraw[2 * h + 1] = w1;
+      best[h] = NONE64;
       continue;
     }
-    const uint64_t k0 = t0 != NONE32 ? (w0 << (idbits + 1)) | (hid << 1) | b0 : NONE64;
-    const uint64_t k1 = t1 != NONE32 ? (w1 << (idbits + 1)) | (hid << 1) | b1 : NONE64;
-    skel_key[2 * h] = k0;
-    skel_key[2 * h + 1] = k1;
-    uint64_t mine = k0 < k1 ? k0 : k1;
-    if (mine != NONE64) atomicMin((unsigned long long *)&best[h], (unsigned long long)mine);
-    if (t0 != NONE32) atomicMin((unsigned long long *)&best[t0], (unsigned long long)k0);
-    if (t1 != NONE32) atomicMin((unsigned long long *)&best[t1], (unsigned long long)k1);
+    k.x = t0 != NONE32 ? (w0 << (idbits + 1)) | (hid << 1) | b0 : NONE64;
+    k.y = t1 != NONE32 ? (w1 << (idbits + 1)) | (hid << 1) | b1 : NONE64;
+    ((ulonglong2 *)skel_key)[h] = k;
+    uint64_t mine = k.x < k.y ? k.x : k.y;
+    if (l.y != NONE32) {
+      const uint64_t f = ((ts[l.y] - th) << (idbits + 1)) | ((uint64_t)perm[l.y] << 1);
+      mine = f < mine ? f : mine;
+    }
+    if (l.w != NONE32) {
+      const uint64_t f = ((ts[l.w] - th) << (idbits + 1)) | ((uint64_t)perm[l.w] << 1);
+      mine = f < mine ? f : mine;
+    }
+    best[h] = mine;
   }
 }
 
@@ -278,7 +294,7 @@ __global__ __launch_bounds__(B) void k_bv_start(int64_t n, int64_t slots, bool f
 // and a rank for every input id 0.8 more.
 __device__ inline uint8_t hook_first(uint64_t k, uint32_t t, uint32_t h, uint64_t bh, uint64_t bt, uint32_t *bpar) {
   if (k == NONE64) return 0;
-  const bool ph = bh == k, pt = bt == k;
+  const bool ph = bh == k, pt = (bt ^ k) < 2;  // (a tail's minimum may lack the key's low bit)
   if (ph) bpar[h] = t;
   else if (pt) bpar[t] = h;
   else return 0;
@@ -955,11 +971,11 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
   CE_TRY((radix_sort_pairs<uint32_t, uint32_t>(ikey, ival, ikey_alt, ival_alt, n2, 0, b.vbits, true, &alt, ws, s)));
   const uint32_t *sk = alt ? ikey_alt : ikey;
   const uint32_t *sv = alt ? ival_alt : ival;
-  // 3. skeleton: predecessor in the same vertex list, then packed keys
-  CE_LAUNCH(k_skel_tails, dim3(grid_for(n2, B)), dim3(B), 0, s, sk, sv, n2, b.hdr, b.skel_tail, b.best);
+  // 3. skeleton: neighbours in the same vertex list, then packed keys and first minima
+  CE_LAUNCH(k_skel_links, dim3(grid_for(n2, B)), dim3(B), 0, s, sk, sv, n2, b.hdr, (uint2 *)b.skel_key);
   CE_HIP(hipGetLastError());
-  CE_LAUNCH(k_skel_keys, dim3(grid_for(n, B)), dim3(B), 0, s, b.skel_tail, b.ts, b.perm, n, b.idbits, b.skel_key,
-            b.best, wraw);
+  CE_LAUNCH(k_skel_keys, dim3(grid_for(n, B)), dim3(B), 0, s, b.ts, b.perm, n, b.idbits, b.skel_key,
+            (uint2 *)b.skel_tail, b.best, wraw);
   CE_HIP(hipGetLastError());
   ws.release(m1);
   if (b.rank) CE_TRY(stage_rank_weights(b, wraw, n2, ws, s));
