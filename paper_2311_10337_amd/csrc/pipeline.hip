@@ -675,21 +675,62 @@ __global__ __launch_bounds__(LBK) void k_bv_min(EdgeLists L, const uint64_t *bv,
   }
 }
 
-// The rounds left after the enqueued slots of a small call, in one workgroup:
-// the same five steps with barriers between them. Components at least halve
-// per round, so 32 rounds end any call; past them the call fails.
+// What the enqueued slots of a small call leave, in one workgroup: rounds of
+// the same five steps with barriers between them, and after the light edges of
+// a split its heavy ones. (A split decided for the slot after the last is not
+// made: the list is whole.) Components at least halve per round, so the tree's
+// levels (H_LEV holds 96) end any call; past them the call fails.
 constexpr int BTB = 1024;
 __global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint64_t *best, uint32_t *bpar,
                                                  uint32_t *rootc, uint8_t *msf_flag, uint64_t *hdr) {
-  if (bv[BV_ACT] != ACT_ROUND) return;
+  const uint64_t act = bv[BV_ACT];
+  if (act == ACT_NONE) return;
   __shared__ uint32_t s_nb, s_cnt;
   Live lv = live_list(L, bv);
   int ob = out_buffer(bv);
   int64_t lo = (int64_t)bv[BV_LO], hi = (int64_t)bv[BV_HI];
-  if (threadIdx.x == 0) s_nb = (uint32_t)hi;
+  const int hb = (int)bv[BV_HB];
+  const int64_t slo = (int64_t)bv[BV_SLO], EH = (int64_t)bv[BV_EH];
+  bool light = bv[BV_LIGHT] != 0 || act == ACT_HEAVY, marked = bv[BV_MARK] != 0;
+  int level = (int)bv[H_BV_NLEV - H_BV];
   const int tid = threadIdx.x;
-  for (int round = 0; lv.E > 0 && round < 40; round++) {
-    if (tid == 0) s_cnt = 0;
+  if (act == ACT_HEAVY) lv.E = 0;
+  __syncthreads();  // (bv is written below)
+  while (true) {
+    if (tid == 0) {
+      s_nb = (uint32_t)hi;
+      s_cnt = 0;
+    }
+    if (lv.E == 0) {
+      if (!light) break;
+      // the heavy edges, from the back of the buffer of the split, by the tops of their nodes
+      light = false;
+      marked = true;
+      lo = slo;
+      for (int64_t c = lo + tid; c < hi; c += BTB) {
+        uint32_t x = (uint32_t)c;
+        for (uint32_t q = bpar[x]; q != x; q = bpar[x]) x = q;
+        rootc[c - lo] = x;
+      }
+      __syncthreads();
+      const int64_t off = L.cap - EH;
+      ob = 1 - hb;
+      for (int64_t i = tid; i < EH; i += BTB) {
+        const uint32_t fu = rootc[L.u[hb][off + i] - lo], fv = rootc[L.v[hb][off + i] - lo];
+        if (fu == fv) continue;
+        const uint32_t p = atomicAdd(&s_cnt, 1u);
+        L.key[ob][p] = L.key[hb][off + i];
+        L.u[ob][p] = fu;
+        L.v[ob][p] = fv;
+        L.s[ob][p] = L.s[hb][off + i];
+      }
+      __syncthreads();
+      lv = Live{L.key[ob], L.u[ob], L.v[ob], L.s[ob], (int64_t)s_cnt};
+      ob = 1 - ob;
+      __syncthreads();
+      continue;
+    }
+    if (level >= H_LPOS - H_LEV - 1) break;
     for (int64_t i = tid; i < lv.E; i += BTB) {
       const unsigned long long k = lv.key[i];
       const uint32_t u = lv.u[i], v = lv.v[i];
@@ -702,7 +743,7 @@ __global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint
     __syncthreads();
     for (int64_t c = lo + tid; c < hi; c += BTB) {
       uint32_t r = NONE32;
-      if (best[c] != NONE64) {
+      if (!(marked && rootc[c - lo] != c) && best[c] != NONE64) {
         r = bv_root(bpar, (uint32_t)c, hdr);
         if (r == (uint32_t)c) r = atomicAdd(&s_nb, 1u);
       }
@@ -727,6 +768,8 @@ __global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint
     }
     __syncthreads();
     if (tid == 0) bv_level(bv, (uint64_t)nb);
+    level++;
+    marked = false;
     lv = Live{L.key[ob], L.u[ob], L.v[ob], L.s[ob], (int64_t)s_cnt};
     ob = 1 - ob;
     lo = hi;
@@ -1012,17 +1055,20 @@ static int boruvka_rounds(int64_t n, bool split_possible) {
   return split_possible ? 2 * r + 3 : r;
 }
 
-// Up to 2^20 skeleton slots, a call without a split enqueues fewer slots and
-// leaves the rest to one workgroup: an idle slot costs six launches of about
-// 2 us, a round of one workgroup about 10 us plus 0.5 us per 1024 edges and
-// step. Larger calls enqueue the full bound.
+// Up to 2^22 skeleton slots a call enqueues fewer slots than the bound (half
+// a round per bit of n, and if it may split, one) and leaves the rest, if any,
+// to one workgroup: an idle slot costs six launches of about 2 us and its level
+// of the dendrogram one more, a round of one workgroup about 10 us plus 0.5 us
+// per 1024 edges and step. (1e6 records with a split use 17 slots of a bound of
+// 45: 2.77 ms with all of them, 2.47 so.) Larger calls enqueue the full bound:
+// one workgroup could be left with too many edges.
 BvPlan boruvka_plan(int64_t n, int64_t slots) {
   BvPlan p;
   p.split_possible = slots >= split_min_edges();
-  p.tail = !p.split_possible && slots <= (int64_t(1) << 20);
+  p.tail = slots <= (int64_t(1) << 22);
   p.slots = boruvka_rounds(n, p.split_possible);
   if (p.tail) {
-    const int few = slots <= 8192 ? 0 : bits_for((uint64_t)n) / 2 + 1;
+    const int few = p.split_possible ? bits_for((uint64_t)n) : slots <= 8192 ? 0 : bits_for((uint64_t)n) / 2 + 1;
     if (few < p.slots) p.slots = few;
   }
   return p;
