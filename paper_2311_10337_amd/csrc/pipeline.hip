@@ -233,6 +233,7 @@ enum : int {
   BV_HB = 12,      // buffer holding the heavy edges at its back
   BV_EH = 13,      // heavy edges
   BV_CNT1 = 14, BV_CNT2 = 15,  // list counters
+  BV_FIRST = 16,   // the first contraction splits its list at the pivot
   BV_WORDS = 24
 };
 enum : int { ACT_NONE = 0, ACT_ROUND = 1, ACT_SPLIT = 2, ACT_HEAVY = 3 };
@@ -422,32 +423,37 @@ __global__ __launch_bounds__(B) void k_bv_link(const uint64_t *bv, const uint32_
   }
 }
 
-// first contraction: skeleton slots between different components, endpoints renamed to nodes
+// first contraction: skeleton slots between different components, endpoints
+// renamed to nodes; with a pivot, split as below
 __global__ __launch_bounds__(LBK) void k_contract_first(int64_t n, const uint64_t *skel_key, const uint32_t *skel_tail,
                                                         const uint32_t *bpar, EdgeLists L, uint64_t *bv) {
   const int64_t n2 = 2 * n;
   const int ct = list_items(n2);
+  const bool split = bv[BV_FIRST] != 0;
+  const uint64_t pivot = split ? bv[BV_PIVOT] : NONE64;
   for (int64_t tile = blockIdx.x; tile * (LBK * ct) < n2; tile += gridDim.x) {
-    bool keep[LCT];
-    uint32_t pos[LCT], nu[LCT], nv[LCT];
+    bool keep[LCT], heavy[LCT];
+    uint32_t pos[LCT], hpos[LCT], nu[LCT], nv[LCT];
     uint64_t kk[LCT];
     const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(n2, tile, LBK * ct);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
       const int64_t e = base + (int64_t)k * LBK;
-      keep[k] = false;
+      keep[k] = heavy[k] = false;
       kk[k] = e < end ? skel_key[e] : NONE64;
       nu[k] = nv[k] = 0;
       if (kk[k] == NONE64) continue;
       nu[k] = bpar[skel_tail[e]];
       nv[k] = bpar[e >> 1];
-      keep[k] = nu[k] != nv[k];
+      keep[k] = nu[k] != nv[k] && kk[k] < pivot;
+      heavy[k] = nu[k] != nv[k] && kk[k] >= pivot;
     }
     list_positions(keep, pos, (unsigned long long *)&bv[BV_CNT1]);
+    if (split) list_positions(heavy, hpos, (unsigned long long *)&bv[BV_CNT2]);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
-      if (!keep[k]) continue;
-      const uint32_t p = pos[k];
+      if (!keep[k] && !heavy[k]) continue;
+      const int64_t p = keep[k] ? (int64_t)pos[k] : L.cap - 1 - (int64_t)hpos[k];
       L.key[0][p] = kk[k];
       L.u[0][p] = nu[k];
       L.v[0][p] = nv[k];
@@ -462,7 +468,7 @@ __global__ __launch_bounds__(LBK) void k_contract_first(int64_t n, const uint64_
 // the pivot go to the front of the output buffer, the others to its back,
 // counted down from cap (light and heavy together are E <= cap entries, so
 // later contractions of the light part, which only shrink it, never reach the
-// heavy part).
+// heavy part). The first contraction may split its list on the way.
 __global__ __launch_bounds__(LBK) void k_contract(EdgeLists L, uint64_t *bv, const uint32_t *bpar,
                                                   const uint32_t *rootc) {
   const uint64_t act = bv[BV_ACT];
@@ -507,27 +513,34 @@ __global__ __launch_bounds__(LBK) void k_contract(EdgeLists L, uint64_t *bv, con
     }
     return;
   }
+  const bool split = bv[BV_FIRST] != 0;
+  const uint64_t pivot = split ? bv[BV_PIVOT] : NONE64;
   for (int64_t tile = blockIdx.x; tile * (LBK * ct) < E; tile += gridDim.x) {
-    bool keep[LCT];
-    uint32_t pos[LCT], nu[LCT], nv[LCT];
+    bool keep[LCT], hv[LCT];
+    uint32_t pos[LCT], hpos[LCT], nu[LCT], nv[LCT];
     const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(E, tile, LBK * ct);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
       const int64_t i = base + (int64_t)k * LBK;
-      keep[k] = false;
+      keep[k] = hv[k] = false;
       nu[k] = nv[k] = 0;
       if (i >= end) continue;
       const uint32_t fu = up[eu[i] - ulo], fv = up[ev[i] - ulo];
       keep[k] = fu != fv;
+      if (split && keep[k] && key[i] >= pivot) {
+        hv[k] = true;
+        keep[k] = false;
+      }
       nu[k] = fu;
       nv[k] = fv;
     }
     list_positions(keep, pos, cnt);
+    if (split) list_positions(hv, hpos, cnt2);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
-      if (!keep[k]) continue;
+      if (!keep[k] && !hv[k]) continue;
       const int64_t i = base + (int64_t)k * LBK;
-      const uint32_t p = pos[k];
+      const int64_t p = keep[k] ? (int64_t)pos[k] : L.cap - 1 - (int64_t)hpos[k];
       L.key[ob][p] = key[i];
       L.u[ob][p] = nu[k];
       L.v[ob][p] = nv[k];
@@ -543,6 +556,45 @@ __global__ __launch_bounds__(LBK) void k_contract(EdgeLists L, uint64_t *bv, con
 // when live edges are at least `split_min` and more than twice the
 // components; the pivot is the key of rank ~C*S/E among S evenly spaced
 // samples of the list (sorted in LDS), so about one light edge per component.
+//
+// Before the first contraction, k_bv_first decides the same from samples of
+// the skeleton's slots alone (how many are live, and their keys), so that the
+// contraction itself splits: a 5e7-record call 50.5 -> 49.0 ms, 4e6 hypergraph
+// records 9.0 -> 8.7.
+template <int S>
+__device__ inline void sort_keys(uint64_t (&sk)[S], int i) {  // bitonic, ascending; S threads
+  for (int k = 2; k <= S; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      const int p = i ^ j;
+      if (p > i) {
+        const uint64_t a = sk[i], b2 = sk[p];
+        const bool up = (i & k) == 0;
+        if ((a > b2) == up) { sk[i] = b2; sk[p] = a; }
+      }
+      __syncthreads();
+    }
+  }
+}
+constexpr int FIRST_SAMPLES = 1024;
+__global__ __launch_bounds__(FIRST_SAMPLES) void k_bv_first(EdgeLists L, bool flat, int64_t slots, const uint32_t *bpar,
+                                                            uint64_t *bv, int64_t split_min) {
+  __shared__ uint64_t sk[FIRST_SAMPLES];
+  const int64_t rows = flat ? (int64_t)bv[BV_E] : slots;
+  if (rows <= 0) return;
+  const int i = threadIdx.x;
+  const int64_t e = (int64_t)((unsigned __int128)i * (uint64_t)rows / FIRST_SAMPLES);
+  uint64_t k = L.key[2][e];
+  if (k != NONE64 && bpar[L.u[2][e]] == bpar[flat ? L.v[2][e] : (uint32_t)(e >> 1)]) k = NONE64;
+  sk[i] = k;
+  const int live = __syncthreads_count(k != NONE64);
+  sort_keys(sk, i);
+  if (i != 0) return;
+  const uint64_t C = bv[BV_NB] - bv[BV_HI];  // the nodes that the round made
+  const uint64_t E = (uint64_t)((unsigned __int128)live * (uint64_t)rows / FIRST_SAMPLES);
+  if ((int64_t)E < split_min || E <= 2 * C) return;
+  bv[BV_PIVOT] = sk[(int64_t)((unsigned __int128)FIRST_SAMPLES * C / (uint64_t)rows)];  // below live / 2
+  bv[BV_FIRST] = 1;
+}
 constexpr int SPLIT_SAMPLES = 256;
 __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t *bv, int64_t split_min) {
   __shared__ uint64_t sk[SPLIT_SAMPLES];
@@ -558,7 +610,10 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
       lo = hi;
       hi = bv[BV_NB];
       bv_level(bv, hi);
-    } else if (act == ACT_SPLIT) {
+    }
+    const bool first = bv[BV_FIRST] != 0;
+    bv[BV_FIRST] = 0;
+    if (act == ACT_SPLIT || first) {
       bv[BV_IN] = ob;
       bv[BV_SPLITDONE] = 1;
       if (c1 > 0) {  // light rounds first
@@ -602,17 +657,7 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
   const int i = threadIdx.x;
   sk[i] = lv.key[(int64_t)((unsigned __int128)i * (uint64_t)lv.E / SPLIT_SAMPLES)];
   __syncthreads();
-  for (int k = 2; k <= SPLIT_SAMPLES; k <<= 1) {  // bitonic sort, ascending
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const int p = i ^ j;
-      if (p > i) {
-        const uint64_t a = sk[i], b2 = sk[p];
-        const bool up = (i & k) == 0;
-        if ((a > b2) == up) { sk[i] = b2; sk[p] = a; }
-      }
-      __syncthreads();
-    }
-  }
+  sort_keys(sk, i);
   if (i == 0) {
     const uint64_t C = bv[BV_HI] - bv[BV_LO];
     int64_t q = (int64_t)((unsigned __int128)SPLIT_SAMPLES * C / (uint64_t)lv.E);
@@ -1104,6 +1149,10 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
               (const uint2 *)b.skel_tail, bpar, (uchar2 *)b.msf_flag);
   CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
   CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
+  const int64_t split_min = split_min_edges();
+  const BvPlan plan = boruvka_plan(n, n2);
+  if (plan.split_possible)
+    CE_LAUNCH(k_bv_first, dim3(1), dim3(FIRST_SAMPLES), 0, s, L, b.flat, n2, bpar, bv, split_min);
   if (b.flat)
     CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar, rootc);
   else
@@ -1118,8 +1167,6 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   // is the largest on a cycle of light edges, and contracting the light forest
   // keeps every heavy edge's cycles. The heavy edges wait, with the nodes they
   // had at the split, at the back of the buffer the split wrote.
-  const int64_t split_min = split_min_edges();
-  const BvPlan plan = boruvka_plan(n, n2);
   for (int r = 0; r < plan.slots; r++) {
     CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
     CE_LAUNCH(k_bv_min, dim3(lE), dim3(LBK), 0, s, L, bv, best);
