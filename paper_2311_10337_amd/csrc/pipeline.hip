@@ -227,7 +227,7 @@ enum : int {
   BV_NB = 6,       // next free node id (a counter while a round runs)
   BV_MARK = 7,     // the range holds merged nodes too (marked NONE in rootc)
   BV_LIGHT = 8,    // rounds run on the light edges of a split
-  BV_SPLITDONE = 9,  // at most one split per call (it bounds the slots)
+  BV_SPLITDONE = 9,  // splits so far, MAX_SPLITS at most
   BV_PIVOT = 10,
   BV_SLO = 11,     // LO at the split
   BV_HB = 12,      // buffer holding the heavy edges at its back
@@ -556,6 +556,12 @@ __global__ __launch_bounds__(LBK) void k_contract(EdgeLists L, uint64_t *bv, con
 // when live edges are at least `split_min` and more than twice the
 // components; the pivot is the key of rank ~C*S/E among S evenly spaced
 // samples of the list (sorted in LDS), so about one light edge per component.
+// After a split, another where a plain round still left more than three
+// quarters of the edges (parallel edges between few components), if enough
+// slots are left for it: 4e6 hypergraph records 8.8 -> 8.4 ms, 1024 graphs 77.6
+// -> 76; below split_min, or without the round in between, it lost at 1e6
+// records (2.45 -> 2.52 ms) or 5e7 (49.0 -> 49.6).
+constexpr int MAX_SPLITS = 3;
 //
 // Before the first contraction, k_bv_first decides the same from samples of
 // the skeleton's slots alone (how many are live, and their keys), so that the
@@ -596,12 +602,14 @@ __global__ __launch_bounds__(FIRST_SAMPLES) void k_bv_first(EdgeLists L, bool fl
   bv[BV_FIRST] = 1;
 }
 constexpr int SPLIT_SAMPLES = 256;
-__global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t *bv, int64_t split_min) {
+__global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t *bv, int64_t split_min,
+                                                          int left) {
   __shared__ uint64_t sk[SPLIT_SAMPLES];
   __shared__ int s_split;
   if (threadIdx.x == 0) {
     const uint64_t act = bv[BV_ACT], c1 = bv[BV_CNT1], c2 = bv[BV_CNT2], ob = (uint64_t)out_buffer(bv);
     uint64_t E = bv[BV_E], lo = bv[BV_LO], hi = bv[BV_HI], light = bv[BV_LIGHT];
+    const uint64_t before = E;
     if (act == ACT_ROUND) {
       E = c1;
       bv[BV_IN] = ob;
@@ -615,7 +623,7 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
     bv[BV_FIRST] = 0;
     if (act == ACT_SPLIT || first) {
       bv[BV_IN] = ob;
-      bv[BV_SPLITDONE] = 1;
+      bv[BV_SPLITDONE]++;
       if (c1 > 0) {  // light rounds first
         light = 1;
         E = c1;
@@ -638,8 +646,11 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
     }
     uint64_t next = E > 0 ? ACT_ROUND : ACT_NONE;
     if (light && E == 0) next = ACT_HEAVY;  // light edges used up: the heavy ones are contracted next
-    const bool split = next == ACT_ROUND && !light && act == ACT_ROUND && !bv[BV_SPLITDONE] &&
-                       (int64_t)E >= split_min && E > 2 * (hi - lo);
+    const uint64_t C = hi - lo;
+    const bool again = bv[BV_SPLITDONE] > 0;
+    const bool split = next == ACT_ROUND && !light && act == ACT_ROUND && (int64_t)E >= split_min && E > 2 * C &&
+                       (!again || (bv[BV_SPLITDONE] < MAX_SPLITS && 4 * E > 3 * before &&
+                                   left >= 2 * (64 - __clzll((long long)C)) + 4));
     bv[BV_ACT] = split ? (uint64_t)ACT_SPLIT : next;
     bv[BV_E] = E;
     bv[BV_LO] = lo;
@@ -1090,7 +1101,8 @@ static int64_t split_min_edges() { return tuning().split_min_edges; }
 
 // Slots the host enqueues after the first round: in every round the
 // components that still have live edges at least halve, so bits(n) + 1 rounds
-// end a run of plain rounds. With the (single) split, plain rounds before it
+// end a run of plain rounds. With one split (a further one is made only where
+// its slots are left), plain rounds before it
 // and the light rounds together halve the components at least once per
 // round, and so do the light rounds and the plain rounds after them:
 // 2 (bits(n) + 1) + 1 rounds cover both, and two more slots split and
@@ -1168,7 +1180,9 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   // keeps every heavy edge's cycles. The heavy edges wait, with the nodes they
   // had at the split, at the back of the buffer the split wrote.
   for (int r = 0; r < plan.slots; r++) {
-    CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
+    // slots a further split may count on: where one workgroup takes the rest, any number, but not at the very end
+    const int slots_left = plan.slots - r, left = !plan.tail ? slots_left : slots_left >= 10 ? 128 : 0;
+    CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min, left);
     CE_LAUNCH(k_bv_min, dim3(lE), dim3(LBK), 0, s, L, bv, best);
     CE_LAUNCH(k_bv_hook, dim3(gE), dim3(B), 0, s, L, bv, best, bpar, b.msf_flag);
     CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
@@ -1176,7 +1190,7 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
     CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar, rootc);
     CE_HIP(hipGetLastError());
   }
-  CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min);
+  CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min, 0);
   if (plan.tail) CE_LAUNCH(k_bv_tail, dim3(1), dim3(BTB), 0, s, L, bv, best, bpar, rootc, b.msf_flag, b.hdr);
   CE_HIP(hipGetLastError());
   ws.release(m0);
