@@ -527,6 +527,7 @@ static ce_status run_call(const Call &c, const ce_result *out, ce_counts *counts
   b.M = c.M;
   b.G = G;
   b.t = c.t;
+  b.sync = sync;
   int64_t *hout = sync ? b.outhdr : hdr_out;
   OneGraph og;
   if (!c.eoff_d && G == 1) og = OneGraph{(int64_t *)b.eoff, (int64_t *)b.voff, n, V};

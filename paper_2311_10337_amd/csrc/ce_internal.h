@@ -448,6 +448,8 @@ struct Bufs {
   const int64_t *thr = nullptr;
   int q = 0;
   const int64_t *t = nullptr;   // the input times
+  bool sync = false;  // a synchronous call: the host may read the device's state on the way
+  int levels = 0;     // levels of the Boruvka tree, where the host knows them
   // persistent
   uint64_t *hdr = nullptr;      // [kHdrWords] the call's control block (H_* words)
   int64_t *outhdr = nullptr;    // [CE_HDR_WORDS(G)] the call's header (read back by synchronous calls)

@@ -394,7 +394,7 @@ ce_status stage_dendrogram(Bufs &b, bool cut, Ws &ws, hipStream_t s) {
   CE_HIP(hipGetLastError());
   const BvPlan plan = boruvka_plan(n, b.slots);
   const unsigned gl = grid_for(mb, B, 2048);
-  const int levels = plan.slots + 1;  // the first round and the enqueued ones
+  const int levels = b.levels > 0 ? b.levels : plan.slots + 1;  // the first round and the enqueued ones
   for (int l = 1; l <= levels && !(plan.tail && plan.slots == 0); l++)
     CE_LAUNCH(k_dn_level, dim3(gl), dim3(B), 0, s, sc, sp, c.mate, n, l, b.hdr, side, T);
   if (plan.tail)

@@ -52,3 +52,10 @@ def test_around_the_line(n):
     V = n // 30
     src, dst, t = synth.chung_lu_bursts(n, V, n)
     undirected.assert_parity(src, dst, t, V, 5, "n=%d" % n)
+
+
+@pytest.mark.parametrize("split", [0, 1 << 20])
+def test_many_rounds_past_the_line(split, monkeypatch):
+    # 22 rounds: a synchronous call looks for the end after 12 slots and every 4 from there
+    monkeypatch.setenv("CE_SPLIT_MIN_EDGES", str(split))
+    undirected.assert_parity(*nested_path(22), 3, "nested path 2^22, split %d" % split)
