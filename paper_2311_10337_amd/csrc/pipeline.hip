@@ -76,11 +76,13 @@ __global__ __launch_bounds__(B) void k_tkeys(const int64_t *t, const int32_t *sr
 }
 
 // incidence entries in rank order: key = vertex, value (implicit) = 2r+side
-__global__ __launch_bounds__(B) void k_incidence(const uint4 *vals, int64_t n, uint32_t *perm,
+// (times of up to 32 bits: the id joins them, as in the packed sort)
+__global__ __launch_bounds__(B) void k_incidence(const uint4 *vals, int64_t n, bool pack, uint64_t *ts, uint32_t *perm,
                                                  uint32_t *ikey) {
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) {
     const uint4 v = vals[r];
     perm[r] = v.x;
+    if (pack) ts[r] = (ts[r] << 32) | v.x;
     ikey[2 * r] = v.y;
     ikey[2 * r + 1] = v.z;
   }
@@ -99,12 +101,12 @@ __global__ __launch_bounds__(B) void k_tkeys_packed(const int64_t *t, const int3
   }
 }
 
-// incidence entries from the packed sort; also t - tmin by rank (keys may be ts itself)
+// incidence entries from the packed sort; its keys stay as they are, in ts (keys may be ts itself)
 __global__ __launch_bounds__(B) void k_incidence_packed(const uint64_t *keys, const uint64_t *vals, int64_t n,
                                                         uint64_t *ts, uint32_t *perm, uint32_t *ikey) {
   for (int64_t r = (int64_t)blockIdx.x * B + threadIdx.x; r < n; r += (int64_t)gridDim.x * B) {
     const uint64_t k = keys[r], v = vals[r];
-    ts[r] = k >> 32;
+    if (ts != keys) ts[r] = k;
     perm[r] = (uint32_t)k;
     ikey[2 * r] = (uint32_t)v;
     ikey[2 * r + 1] = (uint32_t)(v >> 32);
@@ -138,24 +140,29 @@ __global__ __launch_bounds__(B) void k_skel_links(const uint32_t *ikey, const ui
 // with that bit zero: no other edge of its has the same weight and head, so
 // the choice is the same, and the first round compares without the bit.
 // (Each head offering its keys to its tails instead, two atomics a record, took
-// 3.84 ms at 5e7 records with burst-local tails and 15.8 at 2e8; reading the
-// heads' times and ids takes 2.3 and 14.2, the wider links 1.0 and 0.8 more.)
+// 3.84 ms at 5e7 records with burst-local tails, 15.8 at 2e8 and 88 at 2^30;
+// reading the heads' times and ids takes 1.7, 9.2 and 77, and the wider links
+// 1.0, 0.8 and 1.5 more.)
+// PACKED: time and id of a rank in one word, time << 32 | id (times of up to 32
+// bits), one random read a neighbour; with ids from perm it is 2.3, 14.2 and 112.
 // Weight ranks (wraw set): the keys get their tie bits only, the weights go
 // to wraw, and the minima wait for the ranks.
 // The links lie where the keys go; a thread reads its own two first.
+template <bool PACKED>
 __global__ __launch_bounds__(B) void k_skel_keys(const uint64_t *ts, const uint32_t *perm, int64_t n, int idbits,
                                                  uint64_t *skel_key, uint2 *skel_tail, uint64_t *best,
                                                  uint64_t *wraw) {
+  constexpr int TS = PACKED ? 32 : 0;
   for (int64_t h = (int64_t)blockIdx.x * B + threadIdx.x; h < n; h += (int64_t)gridDim.x * B) {
     const uint4 l = ((const uint4 *)skel_key)[h];
     const uint32_t t0 = l.x, t1 = l.z == l.x ? NONE32 : l.z;  // the same pair twice: one line-graph edge
     skel_tail[h] = make_uint2(t0, t1);
-    const uint64_t hid = perm[h];
-    const uint64_t th = ts[h];
-    const uint64_t w0 = t0 != NONE32 ? th - ts[t0] : 0, w1 = t1 != NONE32 ? th - ts[t1] : 0;
+    const uint64_t xh = ts[h], th = xh >> TS, hid = PACKED ? (uint32_t)xh : perm[h];
+    const uint64_t x0 = t0 != NONE32 ? ts[t0] : 0, x1 = t1 != NONE32 ? ts[t1] : 0;
+    const uint64_t w0 = t0 != NONE32 ? th - (x0 >> TS) : 0, w1 = t1 != NONE32 ? th - (x1 >> TS) : 0;
     uint64_t b0 = 0, b1 = 0;
     if (t0 != NONE32 && t1 != NONE32 && w0 == w1) {
-      const uint32_t i0 = perm[t0], i1 = perm[t1];
+      const uint32_t i0 = PACKED ? (uint32_t)x0 : perm[t0], i1 = PACKED ? (uint32_t)x1 : perm[t1];
       b0 = i0 < i1 ? 1u : 0u;
       b1 = 1u - b0;
     }
@@ -173,12 +180,12 @@ __global__ __launch_bounds__(B) void k_skel_keys(const uint64_t *ts, const uint3
     k.y = t1 != NONE32 ? (w1 << (idbits + 1)) | (hid << 1) | b1 : NONE64;
     ((ulonglong2 *)skel_key)[h] = k;
     uint64_t mine = k.x < k.y ? k.x : k.y;
-    if (l.y != NONE32) {
-      const uint64_t f = ((ts[l.y] - th) << (idbits + 1)) | ((uint64_t)perm[l.y] << 1);
-      mine = f < mine ? f : mine;
-    }
-    if (l.w != NONE32) {
-      const uint64_t f = ((ts[l.w] - th) << (idbits + 1)) | ((uint64_t)perm[l.w] << 1);
+#pragma unroll
+    for (int side = 0; side < 2; side++) {
+      const uint32_t x = side ? l.w : l.y;  // the head of an edge whose tail h is
+      if (x == NONE32 || (side && l.w == l.y)) continue;
+      const uint64_t y = ts[x];
+      const uint64_t f = (((y >> TS) - th) << (idbits + 1)) | ((uint64_t)(PACKED ? (uint32_t)y : perm[x]) << 1);
       mine = f < mine ? f : mine;
     }
     best[h] = mine;
@@ -1050,11 +1057,12 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
   uint32_t *ikey_alt = ws.alloc<uint32_t>(n2);
   uint32_t *ival_alt = ws.alloc<uint32_t>(n2);
   CE_WS_CHECK(ws);
+  const bool packed = b.tbits <= 32;  // b.ts ends up as time << 32 | id by rank, else as the time alone
   // 1. records by (t, id)
   // 2. incidence entries (vertex, 2*rank+side) in rank order, perm by rank
   {
     size_t m2 = ws.mark();
-    if (b.G == 1 && b.tbits <= 32) {
+    if (b.G == 1 && packed) {
       uint64_t *kalt = ws.alloc<uint64_t>(n), *v0 = ws.alloc<uint64_t>(n), *v1 = ws.alloc<uint64_t>(n);
       CE_WS_CHECK(ws);
       CE_LAUNCH(k_tkeys_packed, dim3(grid_for(n, B)), dim3(B), 0, s, t, src, dst, n, b.hdr, b.ts, v0);
@@ -1066,7 +1074,7 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
     } else {
       const uint4 *vals = nullptr;
       CE_TRY(sort_records_by_time(src, dst, t, b, ws, s, &vals));
-      CE_LAUNCH(k_incidence, dim3(grid_for(n, B)), dim3(B), 0, s, vals, n, b.perm, ikey);
+      CE_LAUNCH(k_incidence, dim3(grid_for(n, B)), dim3(B), 0, s, vals, n, packed, b.ts, b.perm, ikey);
     }
     CE_HIP(hipGetLastError());
     ws.release(m2);
@@ -1079,8 +1087,12 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
   // 3. skeleton: neighbours in the same vertex list, then packed keys and first minima
   CE_LAUNCH(k_skel_links, dim3(grid_for(n2, B)), dim3(B), 0, s, sk, sv, n2, b.hdr, (uint2 *)b.skel_key);
   CE_HIP(hipGetLastError());
-  CE_LAUNCH(k_skel_keys, dim3(grid_for(n, B)), dim3(B), 0, s, b.ts, b.perm, n, b.idbits, b.skel_key,
-            (uint2 *)b.skel_tail, b.best, wraw);
+  if (packed)
+    CE_LAUNCH(k_skel_keys<true>, dim3(grid_for(n, B)), dim3(B), 0, s, b.ts, b.perm, n, b.idbits, b.skel_key,
+              (uint2 *)b.skel_tail, b.best, wraw);
+  else
+    CE_LAUNCH(k_skel_keys<false>, dim3(grid_for(n, B)), dim3(B), 0, s, b.ts, b.perm, n, b.idbits, b.skel_key,
+              (uint2 *)b.skel_tail, b.best, wraw);
   CE_HIP(hipGetLastError());
   ws.release(m1);
   if (b.rank) CE_TRY(stage_rank_weights(b, wraw, n2, ws, s));
