@@ -453,7 +453,7 @@ struct Bufs {
   // persistent
   uint64_t *hdr = nullptr;      // [kHdrWords] the call's control block (H_* words)
   int64_t *outhdr = nullptr;    // [CE_HDR_WORDS(G)] the call's header (read back by synchronous calls)
-  uint64_t *ts = nullptr;       // [n] t - tmin by rank (undirected, up to 32 bits: << 32 | input id)
+  uint64_t *ts = nullptr;       // [n] t - tmin by rank (records of two vertices, up to 32 bits: << 32 | input id)
   uint32_t *perm = nullptr;     // [n] rank -> input id
   uint64_t *skel_key = nullptr; // [slots] slot 2h+s: key of the skeleton edge whose head is rank h
   uint32_t *skel_tail = nullptr;// [slots] tail rank of that edge or NONE
