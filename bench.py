@@ -123,26 +123,19 @@ def compare_numpy(got, ref, fields=FIELDS):
 
 
 # ---------------------------------------------------------------------------------------------- roofline
-def roofline_line(ce, profiling, kernel, kms, kcnt, w, m, steps, tag, level_bits=0):
-    """Roofline of the dominant kernel against the path's algorithmic bytes: the dendrogram stage's share of
-    the per-edge model (bytes of the dendrogram rows per MSF row) spread over the kernel's launches, divided by
-    its average launch time. The kernel's own access model and the counter traffic are given beside it."""
-    per_row = profiling.STAGE_BYTES["dendrogram"]
-    per_launch = per_row * m * steps / kcnt
+def roofline_line(profiling, kernel, kms, kcnt, w, m, steps, tag, causal):
+    """Roofline of the dominant kernel: the bytes that its launches must move in a step, over their time; the counter
+    traffic is given beside it."""
+    unit, per_step = profiling.algorithmic_bytes_per_step(kernel, w.n, m, w.num_vertices, int(w.t.max() - w.t.min()),
+                                                          causal)
+    per_launch = per_step * steps / kcnt
     avg_s = kms / kcnt * 1e-3
     achieved = per_launch / avg_s / 1e9
-    unit, model_per_unit, model_units = profiling.algorithmic_bytes_per_step(kernel, w.n, m, level_bits)
-    model_per_launch = model_per_unit * model_units * steps / kcnt
     traffic = profiling.load_traffic(kernel, os.path.join(ROOT, "profiles", "%s_%s_pmc.md" % (kernel, tag)))
     return {"bound": "hbm", "achieved": achieved, "peak": profiling.HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / profiling.HBM_PEAK_GBS, "traffic": traffic, "kernel": kernel,
             "algorithmic_bytes_per_launch": per_launch, "launches": kcnt, "avg_launch_us": 1e6 * avg_s,
-            "unit_of_work": "MSF row (dendrogram rows: %d B per row, all of the stage given to this kernel)" % per_row,
-            "amplification": traffic / per_launch if traffic else None,
-            "kernel_model": {"unit": unit, "bytes_per_unit": model_per_unit, "bytes_per_launch": model_per_launch,
-                             "achieved": model_per_launch / avg_s / 1e9,
-                             "frac": model_per_launch / avg_s / 1e9 / profiling.HBM_PEAK_GBS,
-                             "amplification": traffic / model_per_launch if traffic else None}}
+            "unit_of_work": unit, "amplification": traffic / per_launch if traffic else None}
 
 
 # --------------------------------------------------------------------------------------------- workloads
@@ -732,7 +725,7 @@ def make_parser():
                     help="also time the dynamic-hypergraph workload (2e7 multi-recipient messages)")
     ap.add_argument("--no-batch", action="store_true",
                     help="skip the batched-vs-one-graph-per-call measurement on the 4096-graph batch")
-    ap.add_argument("--roofline-kernel", default="k_krt_union",
+    ap.add_argument("--roofline-kernel", default="k_rs_scatter",
                     help="dominant kernel: its launches are timed with HIP events on its stream for the roofline")
     ap.add_argument("--timing-steps", type=int, default=3,
                     help="steps after the timed ones in which the roofline kernel's launches are timed (0: none)")
@@ -805,8 +798,7 @@ def main():
     if args.roofline_kernel and kcnt:
         log("kernel %s: %d launches in %d steps of their own, %.3f ms total, %.1f us avg"
             % (args.roofline_kernel, kcnt, ksteps, kms, 1e3 * kms / kcnt))
-        roof = roofline_line(ce, profiling, args.roofline_kernel, kms, kcnt, w, r.m, ksteps, tag,
-                             (knobs or {}).get("krt_level_bits", 0))
+        roof = roofline_line(profiling, args.roofline_kernel, kms, kcnt, w, r.m, ksteps, tag, causal)
         roof["timed_in"] = "%d steps after the timed ones (events in the kernel's own dispatches)" % ksteps
     value = w.n * args.steps / el
     # whole path: HBM traffic per step from the committed counter summary (calibrated FETCH_SIZE +

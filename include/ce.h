@@ -358,7 +358,7 @@ ce_status ce_cluster_batch_async(const int32_t *src, const int32_t *dst, const i
  * allocates nothing. Every GPU the library runs on holds its own copy of the
  * array until the process ends. Calls whose workspace (ce_workspace_bytes)
  * exceeds it return CE_ENOMEM (with the default M = 5 and V = n/20, about
- * 650 000 records fit). All calls on one GPU share its array: calls that
+ * 730 000 records fit). All calls on one GPU share its array: calls that
  * overlap on one GPU (other streams, other threads) race and must be
  * serialised by the caller; the array keeps the last call's contents, and the
  * pipeline initialises everything it reads. Inputs, outputs and hdr as for

@@ -216,11 +216,11 @@ __global__ __launch_bounds__(B) void k_skel_keys(const uint64_t *ts, const uint3
 // (With the state advanced by the last workgroup of the contraction, found by
 // a ticket, and one counter update per 256-edge tile, 4096 workgroups queued
 // at two addresses for about 15 ns each: a round of 1e6 edges took 145 us in
-// its contraction alone, now 14. A 1e6-record call went from 7.5 to 4.65 ms, a
-// 2e5-record call from 2.74 to 2.04 ms, 5e7 records from 89.6 to 84.4 ms.)
-// Every kernel reads the state when it starts; the
-// host enqueues a fixed number of slots, and those after the forest is
-// complete return at once.
+// its contraction alone, now 14. With that step alone a 1e6-record call went
+// from 7.5 to 4.65 ms, a 2e5-record call from 2.74 to 2.04 ms, 5e7 records from
+// 89.6 to 84.4 ms.) Every kernel reads the state when it starts; the host
+// enqueues a number of slots that depends on sizes alone, and those after the
+// forest is complete return at once.
 
 // Boruvka state, words H_BV + k of the control block
 enum : int {
@@ -232,7 +232,7 @@ enum : int {
   BV_LO = 4,       // nodes of this round: [LO, HI)
   BV_HI = 5,
   BV_NB = 6,       // next free node id (a counter while a round runs)
-  BV_MARK = 7,     // the range holds merged nodes too (marked NONE in rootc)
+  BV_MARK = 7,     // the range holds merged nodes too (rootc names another node for them)
   BV_LIGHT = 8,    // rounds run on the light edges of a split
   BV_SPLITDONE = 9,  // splits so far, MAX_SPLITS at most
   BV_PIVOT = 10,
@@ -1120,9 +1120,8 @@ static int64_t split_min_edges() { return tuning().split_min_edges; }
 // Slots the host enqueues after the first round: in every round the
 // components that still have live edges at least halve, so bits(n) + 1 rounds
 // end a run of plain rounds. With one split (a further one is made only where
-// its slots are left), plain rounds before it
-// and the light rounds together halve the components at least once per
-// round, and so do the light rounds and the plain rounds after them:
+// its slots are left), plain rounds before it and the light rounds together
+// halve the components at least once per round, and so do the light rounds and the plain rounds after them:
 // 2 (bits(n) + 1) + 1 rounds cover both, and two more slots split and
 // contract the heavy edges.
 static int boruvka_rounds(int64_t n, bool split_possible) {

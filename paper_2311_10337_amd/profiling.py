@@ -19,49 +19,33 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 
 
-def dendrogram_levels(m: int, lds_bits: int = 9, level_bits: int = 0) -> int:
-    """Global levels of the rank-interval dendrogram for m rows, as the library plans them: level_bits (a
-    tuning choice) when given, else the level count of least modelled time (a pass of random accesses per
-    level, about 0.4 ns per row, against 20 us per sub-interval and 15 us per level)."""
-    if m <= 1:
-        return 0
-    gbits = (m - 1).bit_length() - lds_bits
-    if gbits <= 0:
-        return 0
-    if level_bits:
-        return -(-gbits // level_bits)
-    best, kbest = None, gbits
-    for nlev in range(1, gbits + 1):
-        hi, lo, nhi = -(-gbits // nlev), gbits // nlev, gbits % nlev
-        if hi > 12:
-            continue
-        steps = nhi * 2 ** hi + (nlev - nhi) * 2 ** lo
-        t = nlev * (0.4e-9 * m + 15e-6) + steps * 20e-6
-        if best is None or t < best:
-            best, kbest = t, hi
-    return -(-gbits // kbest)
+def _bits(x: int) -> int:
+    """Bits of a sort key that holds the values 0..x, as the library counts them (at least one)."""
+    return max(1, int(x).bit_length())
 
 
-# kernel -> (unit, algorithmic bytes per unit, units per step as a function of the run)
-def algorithmic_bytes_per_step(kernel: str, n: int, m: int, level_bits: int = 0) -> tuple:
-    """(unit description, bytes per unit, units per step) for a kernel of the pipeline."""
-    if kernel == "k_krt_accum":
-        # per row and global level: hooked root id (4), its size (4), the parent of that root (4),
-        # the row id it offers (4); the per-root atomics are combined in LDS
-        return ("MSF row x global level", 16, dendrogram_levels(m, level_bits=level_bits) * m)
-    if kernel == "k_krt_union":
-        # per row and global level: two labels read (8), the two root entries read (2 x 16), the new labels
-        # and sizes written (16), one 8-byte CAS (8), the hooked root written (4)
-        return ("MSF row x global level", 68, dendrogram_levels(m, level_bits=level_bits) * m)
-    if kernel == "k_krt_relabel":
-        # per row and level: two labels (8) read and rewritten (8), two sizes rewritten (8), two roots
-        # written (8), two root entries read (2 x 12)
-        return ("MSF row x global level", 56, dendrogram_levels(m, level_bits=level_bits) * m)
-    if kernel == "k_krt_lds":
-        # per row: two labels and two sizes read (16), two children and the size written (12)
-        return ("MSF row", 28, m)
+def sorts(n: int, m: int, num_vertices: int, span: int, causal: bool = False) -> list:
+    """The radix sorts of one call on one graph, as the library makes them: (elements, key bytes, value bytes,
+    passes, whether the values are implicit in the first pass). span = max t - min t; a causal key's tie field
+    is taken as one bit."""
+    tb, idb = _bits(span), _bits(n - 1)
+    packed = tb <= 32 and not causal
+    passes = lambda bits: -(-bits // 8)
+    return [(n, 8, 8 if packed else 16, passes(tb), False),
+            (2 * n, 4, 4, passes(_bits(num_vertices - 1)), not causal),
+            (m, 8, 4, passes(tb + idb + 1), True),
+            (m, 4, 8, passes(_bits(n - 1)), False)]
+
+
+def algorithmic_bytes_per_step(kernel: str, n: int, m: int, num_vertices: int, span: int,
+                               causal: bool = False) -> tuple:
+    """(unit description, bytes per step): what the launches of a kernel must move in one call."""
     if kernel == "k_rs_scatter":
-        return ("element x pass (u64 key + u64 value)", 32, None)
+        # per element and pass: key and value read and written (the first pass of an implicit value reads the key)
+        total = sum(k * (2 * (kb + vb) * p - (vb if iota else 0))
+                    for k, kb, vb, p, iota in sorts(n, m, num_vertices, span, causal))
+        return ("element x pass: key and value read and written (records by time, incidences by vertex, rows by "
+                "key, rows by chain)", total)
     raise KeyError(kernel)
 
 
