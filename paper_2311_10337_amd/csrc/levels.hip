@@ -15,7 +15,7 @@
 // member ids. Only roots of the level before are looked up in W, so W is never
 // copied: it lies where the last level's labels go, and no workspace is
 // needed. A level streams the labels once in and once out and reads W at the
-// roots: 29 levels of 2e7 records in 3.7 ms (copying the labels, joining through
+// roots: 29 levels of 2e7 records in 3.5 ms (copying the labels, joining through
 // the copy and compressing it in place took 4.2).
 #include "ce_internal.h"
 
@@ -24,8 +24,10 @@ namespace ce {
 namespace {
 
 constexpr int B = 256;
-constexpr int LI = 4;  // records per thread of the label pass, their first reads in flight together (1: 82 us a level
-                       // of 2e7 records, 4: 76; the joins lose by it, 59 -> 66)
+// Records per thread of the label pass, their first reads in flight together: 4
+// from LI_FROM records on (82 -> 76 us a level of 2e7 records; the joins lose by
+// it, 59 -> 66), 1 below, where four would leave CUs idle.
+constexpr int64_t LI_FROM = int64_t(1) << 21;
 
 __device__ inline int32_t lc_ld(const int32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -87,7 +89,8 @@ __global__ __launch_bounds__(B) void k_lc_iota(int32_t *lab, int64_t n) {
 // roots, so the first attempt needs no find: it fails only when the larger one
 // was hooked in this level. The smaller may have been: linking to a node that
 // is no root is as good, for its root is smaller still, so the two are never
-// of one component.
+// of one component. (Finding both roots first: 4.1 ms instead of 3.5 for 29
+// levels of 2e7 records.)
 __global__ __launch_bounds__(B) void k_lc_union(const uint32_t *tl, const uint32_t *hd, int64_t a, int64_t b,
                                                 const int32_t *prev, int32_t *W) {
   for (int64_t j = a + (int64_t)blockIdx.x * B + threadIdx.x; j < b; j += (int64_t)gridDim.x * B) {
@@ -106,8 +109,14 @@ __global__ __launch_bounds__(B) void k_lc_union(const uint32_t *tl, const uint32
 }
 
 // Every record's label: the root of its label before. No hooks run now, and
-// the roots go elsewhere, so walks may halve W and read it through the caches
-// (a stale link is an ancestor all the same).
+// the roots go elsewhere, so walks may shorten W and read it through the caches
+// (a stale link is an ancestor all the same). Only long walks do: the stores
+// of short ones go to the few nodes above everything, one after another (4e5
+// records at 8 levels: 0.52 ms with halving from the first or the eighth step,
+// 0.19 without). A path of 1e6 rows in one level takes 0.7 ms this way and 144
+// with walks that never shorten.
+constexpr int LONG_WALK = 64;
+template <int LI>
 __global__ __launch_bounds__(B) void k_lc_labels(const int32_t *prev, int32_t *W, int64_t n, int32_t *out) {
   const int64_t i0 = (int64_t)blockIdx.x * (B * LI) + threadIdx.x;
   int32_t x[LI], p[LI];
@@ -122,16 +131,18 @@ __global__ __launch_bounds__(B) void k_lc_labels(const int32_t *prev, int32_t *W
   for (int k = 0; k < LI; k++) {
     const int64_t i = i0 + (int64_t)k * B;
     if (i >= n) continue;
-    while (p[k] != x[k]) {
-      const int32_t g = lc_cached(&W[p[k]]);
-      if (g == p[k]) {
-        x[k] = g;
-        break;
+    const int32_t x0 = x[k];
+    int steps = 0;
+    for (; p[k] != x[k]; steps++) {
+      if (steps >= LONG_WALK) {
+        const int32_t g = lc_cached(&W[p[k]]);
+        if (g != p[k]) lc_st(&W[x[k]], g);
+        p[k] = g;
       }
-      lc_st(&W[x[k]], g);
-      x[k] = g;
-      p[k] = lc_cached(&W[g]);
+      x[k] = p[k];
+      p[k] = lc_cached(&W[x[k]]);
     }
+    if (steps > LONG_WALK) lc_st(&W[x0], x[k]);
     out[i] = x[k];
   }
 }
@@ -230,7 +241,10 @@ extern "C" ce_status ce_level_components(const uint32_t *msf_tail, const uint32_
     if (l == q - 1) {
       if (end > prev || l > 0) CE_LAUNCH(k_lc_labels_last, dim3(grid_for(n, B)), dim3(B), 0, s, before, W, n);
     } else if (end > prev) {
-      CE_LAUNCH(k_lc_labels, dim3((unsigned)((n + B * LI - 1) / (B * LI))), dim3(B), 0, s, before, W, n, lab);
+      if (n >= LI_FROM)
+        CE_LAUNCH(k_lc_labels<4>, dim3((unsigned)((n + B * 4 - 1) / (B * 4))), dim3(B), 0, s, before, W, n, lab);
+      else
+        CE_LAUNCH(k_lc_labels<1>, dim3((unsigned)((n + B - 1) / B)), dim3(B), 0, s, before, W, n, lab);
     } else if (before) {
       CE_HIP(hipMemcpyAsync(lab, before, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
     } else {
