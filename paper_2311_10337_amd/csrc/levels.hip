@@ -81,8 +81,12 @@ __global__ void k_lc_zero(uint64_t *p, int64_t k) {
   for (int64_t i = threadIdx.x; i < k; i += blockDim.x) p[i] = 0;
 }
 
-__global__ __launch_bounds__(B) void k_lc_iota(int32_t *lab, int64_t n) {
-  for (int64_t x = (int64_t)blockIdx.x * B + threadIdx.x; x < n; x += (int64_t)gridDim.x * B) lab[x] = (int32_t)x;
+// every record its own root, and its own label at a first level without rows
+__global__ __launch_bounds__(B) void k_lc_iota(int32_t *W, int32_t *lab, int64_t n) {
+  for (int64_t x = (int64_t)blockIdx.x * B + threadIdx.x; x < n; x += (int64_t)gridDim.x * B) {
+    W[x] = (int32_t)x;
+    if (lab) lab[x] = (int32_t)x;
+  }
 }
 
 // Joins the components of the rows [a, b). The labels before this level are
@@ -226,7 +230,7 @@ extern "C" ce_status ce_level_components(const uint32_t *msf_tail, const uint32_
     return CE_EINVAL;
   }
   int32_t *W = labels + (q - 1) * n;
-  CE_LAUNCH(k_lc_iota, dim3(grid_for(n, B)), dim3(B), 0, s, W, n);
+  CE_LAUNCH(k_lc_iota, dim3(grid_for(n, B)), dim3(B), 0, s, W, q > 1 && hb[1] == 0 ? labels : nullptr, n);
   int64_t prev = 0;
   for (int64_t l = 0; l < q; l++) {
     int32_t *lab = labels + l * n;
@@ -247,8 +251,6 @@ extern "C" ce_status ce_level_components(const uint32_t *msf_tail, const uint32_
         CE_LAUNCH(k_lc_labels<1>, dim3((unsigned)((n + B - 1) / B)), dim3(B), 0, s, before, W, n, lab);
     } else if (before) {
       CE_HIP(hipMemcpyAsync(lab, before, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
-    } else {
-      CE_LAUNCH(k_lc_iota, dim3(grid_for(n, B)), dim3(B), 0, s, lab, n);
     }
     CE_HIP(hipGetLastError());
     prev = end;
