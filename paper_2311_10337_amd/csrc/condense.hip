@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "ce_internal.h"
+#include "rounds.h"
 
 namespace ce {
 
@@ -98,12 +99,6 @@ __global__ __launch_bounds__(B) void k_cd_birth(const uint32_t *kc_u, const uint
   }
 }
 
-// Links climbed per pointer-jumping round: a round makes links HOPS + 1 times
-// as long, so a path of k rows takes log(k) / log(5) rounds; a launch costs
-// about as much as the four extra reads (19 rounds of one link each took 85 us
-// at 7e4 rows).
-constexpr int HOPS = 4;
-
 // Discrete dendrogram: a row's level top is its highest ancestor reached
 // through parents of the same level (the component that first appears at that
 // level, a D-node). First step: the parent if it has the same level; the list
@@ -163,11 +158,10 @@ __global__ __launch_bounds__(LBK) void k_dd_top_jump(const uint32_t *act, const 
       if (keep[k]) next[pos[k]] = vals[k];
   }
 }
-// after the enqueued rounds every list must be empty; if not, the call fails
-// big children of every D-node: the level tops (rows that are their own top)
-// hanging below its block; records are never big (M >= 2)
-// big D-node children per D-node; a D-node can have millions of them, so the
-// counts are combined per wave and per tile (LDS hash) before the atomics
+// Big children of every D-node: the level tops (rows that are their own top)
+// hanging below its block; records are never big (M >= 2). A D-node can have
+// millions of them, so the counts are combined per wave and per tile (LDS
+// hash) before the atomics.
 constexpr int DHS = 512;
 __global__ __launch_bounds__(B) void k_dd_bigcount(const uint32_t *kpar, const uint32_t *ksize, const uint32_t *top,
                                                    Cnt mc, int64_t n, int64_t M, int kct, uint32_t *bigcnt) {
@@ -381,8 +375,9 @@ __global__ __launch_bounds__(B) void k_birth_list(const uint8_t *isbirth, const 
   }
 }
 // births and cluster rows from the scan of the birth flags (idx[m] = births);
-// more rows than the bound, or rows left over by the pointer jumping before
-// (left0, left1), mark the call failed. One graph: its births are
+// more rows than the bound, or rows left on a list after the enqueued rounds of
+// pointer jumping (left0, left1; there are enough rounds for any tree), mark
+// the call failed. One graph: its births are
 // rows 0..nb-1, its root the next.
 __global__ void k_cluster_counts(const uint32_t *idx, Cnt mc, int64_t G, int64_t R, const uint64_t *left0,
                                  const uint64_t *left1, uint32_t *bstart, uint32_t *rootrow, uint64_t *hdr) {
@@ -1018,9 +1013,12 @@ __global__ void k_virtual_counts(const uint32_t *vbase, uint64_t *hdr, int64_t R
 
 }  // namespace
 
-// Rounds of a pointer-jumping loop over a tree of up to k rows: links grow
-// fivefold a round, and 5^(bits / 2.3) > 2^bits.
-static int jump_rounds(int64_t k) { return bits_for((uint64_t)k) * 10 / 23 + 1; }
+// Rounds of the two pointer-jumping loops over up to k rows. The deepest tree
+// is one path: its first row is k - 1 links below the level top, and k links
+// below the virtual root. The two end differently (rounds.h): a row stays on
+// the list of level tops until it has seen its top point to itself.
+static int level_top_rounds(int64_t k) { return rounds_to_confirm(k - 1); }
+static int birth_rounds(int64_t k) { return rounds_to_arrive(k); }
 
 // level tops (pointer jumping over same-level parents) and big children per
 // D-node, then births; act and act2 hold m + 1 entries each, loop is the
@@ -1032,7 +1030,7 @@ static ce_status discrete_births(Bufs &b, Cnt m, const uint32_t *kpar, const uin
   const unsigned g = grid_cap(m.v, B), tg = list_blocks(m.v);
   auto tiles = [](int64_t k, int per = CT) { return (unsigned)((k + (int64_t)B * per - 1) / ((int64_t)B * per)); };
   CE_LAUNCH(k_dd_top_init, dim3(tg), dim3(LBK), 0, s, kpar, level, m, n, top, act, (unsigned long long *)&loop[0]);
-  const int R = jump_rounds(m.v);
+  const int R = level_top_rounds(m.v);
   uint32_t *lists[2] = {act, act2};
   for (int r = 0; r < R; r++)
     CE_LAUNCH(k_dd_top_jump, dim3(tg), dim3(LBK), 0, s, lists[r & 1], &loop[r], n, top, lists[1 - (r & 1)],
@@ -1174,7 +1172,7 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
     const unsigned tg = list_blocks(mb);
     CE_LAUNCH(k_cd_jinit, dim3(tg), dim3(LBK), 0, s, isbirth, kpar, b.ksize, b.rowg, m, n, M, J, jact,
               (unsigned long long *)&jl[0]);
-    const int R = jump_rounds(mb);
+    const int R = birth_rounds(mb);
     uint32_t *lists[2] = {jact, jact2};
     for (int r = 0; r < R; r++)
       CE_LAUNCH(k_cd_jstep, dim3(tg), dim3(LBK), 0, s, lists[r & 1], &jl[r], J, isbirth, m, n, lists[1 - (r & 1)],
@@ -1185,7 +1183,7 @@ ce_status stage_condense(Bufs &b, const ce_result *out, Ws &ws, hipStream_t s, i
   CE_HIP(hipGetLastError());
   CE_TRY(scan_exclusive<uint8_t>(isbirth, idx, m, ws, s));
   CE_LAUNCH(k_cluster_counts, dim3(1), dim3(64), 0, s, idx, m, G, R,
-            loop + LOOP_DD + (b.q > 0 ? jump_rounds(mb) : 0), jleft, bstart, rootrow, b.hdr);
+            loop + LOOP_DD + (b.q > 0 ? level_top_rounds(mb) : 0), jleft, bstart, rootrow, b.hdr);
   const uint32_t *rowmap = idx;  // one graph: a birth's row is its index among births
   if (G > 1) {
     CE_LAUNCH(k_birth_list, dim3(gm), dim3(B), 0, s, isbirth, idx, b.rowg, m, bkey, bval);
