@@ -346,21 +346,25 @@ __global__ __launch_bounds__(B) void k_bv_hook(EdgeLists L, const uint64_t *bv, 
   }
 }
 
-// The root of node c's hooks. The walk halves the path it follows (each store
-// moves a link to a grandparent), so long hook chains shrink as in pointer
-// jumping; a stale link is still an ancestor, so every walk ends at the root
-// (hooks form a forest: keys are unique, and of a mutual pair only one side
-// hooks). The root goes to an array of its own, which no halving store
+// The root of the hooks above node x. The walk halves the path it follows (each
+// store moves a link to a grandparent), so long hook chains shrink as in
+// pointer jumping; a stale link is still an ancestor, so every walk ends at the
+// root (hooks form a forest: keys are unique, and of a mutual pair only one
+// side hooks). The root goes to an array of its own, which no halving store
 // touches. A walk longer than any forest allows marks the call failed.
 constexpr uint32_t MAX_WALK = 1u << 26;
-__device__ inline uint32_t bv_root(uint32_t *bpar, uint32_t c, uint64_t *hdr) {
-  uint32_t x = __hip_atomic_load(&bpar[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (x == c) return c;
+__device__ inline uint32_t link_ld(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void link_st(uint32_t *p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline uint32_t bv_root(uint32_t *bpar, uint32_t x, uint64_t *hdr) {
   for (uint32_t steps = 0;; steps++) {
-    const uint32_t p = __hip_atomic_load(&bpar[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t p = link_ld(&bpar[x]);
     if (p == x) return x;
-    const uint32_t gp = __hip_atomic_load(&bpar[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (gp != p) __hip_atomic_store(&bpar[x], gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t gp = link_ld(&bpar[p]);
+    if (gp != p) link_st(&bpar[x], gp);
     x = gp;
     if (steps > MAX_WALK) {
       atomicOr((unsigned long long *)&hdr[H_STATUS], 16ull);
@@ -375,10 +379,24 @@ __device__ inline uint32_t bv_root(uint32_t *bpar, uint32_t c, uint64_t *hdr) {
 // edges are contracted, every node's top: several heavy edges end in one node,
 // so a climb per node and one read per end take 0.9 ms of a 5e7-record call
 // where climbing from each end took 2.0 (and 6.7 ms less of a 2e8-record one).
+//
+// Records at regular intervals hook into one chain of neighbours, millions of
+// links long. A tile first jumps along the links inside it, in LDS, so that a
+// chain crosses a tile of up to 4096 nodes in one step: 2e6 such records of one
+// vertex took 9.2 ms with walks alone, now 1.8. That holds while all tiles are
+// in flight together; else a walk comes to tiles that have not been started
+// (8e6 such records: 3.3 s, or 14.6 with hooks towards later ones). So past as
+// many nodes as 512 tiles hold, which two workgroups a CU cover, the links of
+// all tiles are shortened by a launch of its own before the walks: 4.6 and 7.1
+// ms. Up to 2^18 nodes, one a thread, the walks do alone: a chain of all of them
+// costs 0.05 ms, while the barriers took 2 % of any 7e4-record call. Other
+// inputs take the same time either way.
+enum : int { CP_LINKS = 1, CP_WALK = 2 };
+template <int DO>
 __global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_t *best, uint32_t *bpar,
                                                      uint32_t *rootc, uint64_t *hdr) {
   const uint64_t act = bv[BV_ACT];
-  if (act == ACT_HEAVY) {  // the heavy edges' way up, which also marks the next round's range
+  if ((DO & CP_WALK) && act == ACT_HEAVY) {  // the heavy edges' way up, which also marks the next round's range
     const int64_t lo = (int64_t)bv[BV_SLO], hi = (int64_t)bv[BV_NB];
     for (int64_t c = lo + (int64_t)blockIdx.x * LBK + threadIdx.x; c < hi; c += (int64_t)gridDim.x * LBK) {
       uint32_t x = (uint32_t)c;  // as many steps as light rounds at most
@@ -391,32 +409,69 @@ __global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_
   const int64_t lo = (int64_t)bv[BV_LO], nc = (int64_t)bv[BV_HI] - lo;
   const bool marked = bv[BV_MARK] != 0;
   const int ct = list_items(nc);
+  __shared__ uint32_t s_link[(DO & CP_LINKS) ? LBK * LCT : 1];
   for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nc; tile += gridDim.x) {
-    bool keep[LCT];
-    uint32_t pos[LCT];
+    bool keep[LCT], live[LCT];
+    uint32_t pos[LCT], link[LCT];
     const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nc, tile, LBK * ct);
+    const uint32_t c0 = (uint32_t)(lo + base - threadIdx.x), len = (uint32_t)(end - base + threadIdx.x);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
       const int64_t i = base + (int64_t)k * LBK;
-      keep[k] = false;
+      keep[k] = live[k] = false;
+      link[k] = NONE32;
       if (i >= end) continue;
       const uint32_t c = (uint32_t)(lo + i);
-      uint32_t r = NONE32;
-      if (marked && rootc[i] != c) {  // merged in an earlier round
-        rootc[i] = r;
-        continue;
+      live[k] = !(marked && rootc[i] != c) && best[c] != NONE64;  // (marked: some were merged in an earlier round)
+      link[k] = live[k] ? link_ld(&bpar[c]) : c;
+      if (DO & CP_LINKS) s_link[c - c0] = link[k];
+    }
+    if (DO & CP_LINKS) {
+      uint32_t changed = 0;
+      bool moved = true;
+      for (int round = 0; __syncthreads_or(moved) && round < 32; round++) {  // 12 rounds end any path of a tile
+        moved = false;
+#pragma unroll
+        for (int k = 0; k < LCT; k++) {
+          if (!live[k] || link[k] - c0 >= len) continue;
+          const uint32_t up = s_link[link[k] - c0];
+          if (up == link[k]) continue;
+          s_link[threadIdx.x + k * LBK] = link[k] = up;
+          changed |= 1u << k;
+          moved = true;
+        }
       }
-      if (best[c] != NONE64) {
-        r = bv_root(bpar, c, hdr);
-        keep[k] = r == c;
-      }
-      if (!keep[k]) rootc[i] = r;
+#pragma unroll
+      for (int k = 0; k < LCT; k++)
+        if (changed >> k & 1u) link_st(&bpar[lo + base + (int64_t)k * LBK], link[k]);
+    }
+    if (!(DO & CP_WALK)) {
+      __syncthreads();  // (the links' LDS is used again)
+      continue;
+    }
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
+      if (i >= end) continue;
+      const uint32_t c = (uint32_t)(lo + i);
+      keep[k] = live[k] && link[k] == c;
+      if (!keep[k]) rootc[i] = live[k] ? bv_root(bpar, link[k], hdr) : NONE32;
     }
     list_positions(keep, pos, (unsigned long long *)&bv[BV_NB]);
 #pragma unroll
     for (int k = 0; k < LCT; k++)
       if (keep[k]) rootc[base + (int64_t)k * LBK] = pos[k];
   }
+}
+// in a round of (about) nc nodes at most
+void bv_compress(int64_t nc, unsigned grid, uint64_t *bv, const uint64_t *best, uint32_t *bpar, uint32_t *rootc,
+                 uint64_t *hdr, hipStream_t s) {
+  const int64_t flight = grid < 512 ? (int64_t)LBK * grid : (int64_t)LBK * LCT * 512;  // (see list_items)
+  if (nc > flight) CE_LAUNCH(k_bv_compress<CP_LINKS>, dim3(grid), dim3(LBK), 0, s, bv, best, bpar, rootc, hdr);
+  if (nc > flight || nc <= (int64_t)LBK * 512)
+    CE_LAUNCH(k_bv_compress<CP_WALK>, dim3(grid), dim3(LBK), 0, s, bv, best, bpar, rootc, hdr);
+  else
+    CE_LAUNCH(k_bv_compress<CP_LINKS | CP_WALK>, dim3(grid), dim3(LBK), 0, s, bv, best, bpar, rootc, hdr);
 }
 
 // node c -> the new node of its component; new nodes start without a minimum
@@ -1183,7 +1238,7 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   else
     CE_LAUNCH(k_bv_hook_first, dim3(gN), dim3(B), 0, s, n, best, (const ulonglong2 *)b.skel_key,
               (const uint2 *)b.skel_tail, bpar, (uchar2 *)b.msf_flag);
-  CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
+  bv_compress(n, lN, bv, best, bpar, rootc, b.hdr, s);
   CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
   const int64_t split_min = split_min_edges();
   const BvPlan plan = boruvka_plan(n, n2);
@@ -1217,7 +1272,7 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
     }
     CE_LAUNCH(k_bv_min, dim3(lE), dim3(LBK), 0, s, L, bv, best);
     CE_LAUNCH(k_bv_hook, dim3(gE), dim3(B), 0, s, L, bv, best, bpar, b.msf_flag);
-    CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
+    bv_compress(r < 62 ? n >> (r + 1) : 0, lN, bv, best, bpar, rootc, b.hdr, s);  // (a round halves its nodes)
     CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
     CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar, rootc);
     CE_HIP(hipGetLastError());
