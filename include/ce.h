@@ -45,7 +45,8 @@
  *   CE_KRT_LEVEL_BITS   1..12: largest number of row-index bits one global
  *                       dendrogram level takes
  *   CE_SPLIT_MIN_EDGES  live-edge count from which Boruvka splits its edges
- *                       at a pivot key (default 2^20; 0 = never)
+ *                       at a pivot key (default 2^20; 0 = never), in calls
+ *                       that may have twice as many
  *   CE_RADIX_IPT        keys per thread of the radix sorts (4, 8, 16)
  *   CE_LIST_GRID        workgroups of the passes over live lists
  *   CE_TUNE_FILE        the autotuner's tuning file (per-bucket choices)
@@ -110,8 +111,9 @@ typedef struct {
                                      where those are of 512 threads */
   int32_t krt_level_bits;         /* taken (0..12) and reported, without effect: the dendrogram has no level
                                      width to choose */
-  int64_t split_min_edges;        /* Boruvka's filter split runs from this many live edges (default 2^20);
-                                     < 0: never */
+  int64_t split_min_edges;        /* Boruvka's filter split runs from this many live edges (default 2^20) in
+                                     calls of at least twice as many skeleton slots (2n, or nnz of a
+                                     hypergraph); < 0: never */
 } ce_tuning;
 
 typedef struct {

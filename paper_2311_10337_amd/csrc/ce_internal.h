@@ -504,12 +504,12 @@ ce_status stage_sort_skeleton(const int32_t *src, const int32_t *dst, const int6
                               hipStream_t s);
 ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s);
 // how a call runs Boruvka after its first round: enqueued slots, whether one may split, whether one workgroup
-// finishes what they leave
+// finishes what they leave, whether that may be thinned before
 struct BvPlan {
   int slots;
-  bool split_possible, tail;
+  bool split_possible, tail, thin;
 };
-BvPlan boruvka_plan(int64_t n, int64_t slots);
+BvPlan boruvka_plan(int64_t n, int64_t slots, bool sync);
 // the forest's rows sorted by key, with their weights and the chains of the dendrogram; then (after a cutoff) the
 // dendrogram itself
 ce_status stage_rows(Bufs &b, Ws &ws, hipStream_t s);

@@ -392,7 +392,7 @@ ce_status stage_dendrogram(Bufs &b, bool cut, Ws &ws, hipStream_t s) {
   const unsigned g = grid_cap(mb, B);
   CE_LAUNCH(k_dn_chains, dim3(g), dim3(B), 0, s, sc, sp, m, n, cstart, top, T, b.hdr);
   CE_HIP(hipGetLastError());
-  const BvPlan plan = boruvka_plan(n, b.slots);
+  const BvPlan plan = boruvka_plan(n, b.slots, b.sync);
   const unsigned gl = grid_for(mb, B, 2048);
   const int levels = b.levels > 0 ? b.levels : plan.slots + 1;  // the first round and the enqueued ones
   for (int l = 1; l <= levels && !(plan.tail && plan.slots == 0); l++)

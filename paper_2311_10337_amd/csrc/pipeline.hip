@@ -669,9 +669,15 @@ __global__ __launch_bounds__(FIRST_SAMPLES) void k_bv_first(EdgeLists L, bool fl
   bv[BV_PIVOT] = sk[(int64_t)((unsigned __int128)FIRST_SAMPLES * C / (uint64_t)rows)];  // below live / 2
   bv[BV_FIRST] = 1;
 }
+// whether the list that the last slot leaves is thinned (see k_bv_thin)
+constexpr int64_t THIN_MIN = 16384;
+__device__ inline bool bv_thins(const uint64_t *bv, int64_t n) {
+  const uint64_t C = bv[BV_HI] - bv[BV_LO];
+  return bv[BV_ACT] == ACT_ROUND && (int64_t)bv[BV_E] >= THIN_MIN && C * C <= (uint64_t)n / 2;
+}
 constexpr int SPLIT_SAMPLES = 256;
 __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t *bv, int64_t split_min,
-                                                          int left) {
+                                                          int left, int64_t n, uint64_t *pairs) {
   __shared__ uint64_t sk[SPLIT_SAMPLES];
   __shared__ int s_split;
   if (threadIdx.x == 0) {
@@ -731,6 +737,10 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
   }
   __threadfence_block();
   __syncthreads();
+  if (pairs && bv_thins(bv, n)) {
+    const uint64_t C = bv[BV_HI] - bv[BV_LO];
+    for (uint64_t p = threadIdx.x; p < C * C; p += SPLIT_SAMPLES) pairs[p] = NONE64;
+  }
   if (!s_split) return;
   const Live lv = live_list(L, bv);
   const int i = threadIdx.x;
@@ -799,62 +809,75 @@ __global__ __launch_bounds__(LBK) void k_bv_min(EdgeLists L, const uint64_t *bv,
   }
 }
 
-// What the enqueued slots of a small call leave, in one workgroup: rounds of
-// the same five steps with barriers between them, and after the light edges of
-// a split its heavy ones. (A split decided for the slot after the last is not
-// made: the list is whole.) Components at least halve per round, so the tree's
-// levels (H_LEV holds 96) end any call; past them the call fails.
+// One workgroup takes about 0.5 us per 1024 edges and step, and rounds that
+// only halve the components keep their parallel edges: 4e5 records of a nested
+// path with random second vertices left it 3e5 edges between 200 nodes, and
+// the call took 6.2 ms. So a long list is thinned first, on the grid, to the
+// smallest edge of each pair of nodes: 1.9 ms. The slots before leave at most
+// 2^(ceil(bits(n) / 2) - 2) nodes (each round halves those with edges), so a
+// table of all pairs fits where rootc lies; it is cleared by the last k_bv_ctl.
+__device__ inline uint64_t pair_at(uint32_t u, uint32_t v, const uint64_t *bv) {
+  const uint64_t lo = bv[BV_LO], C = bv[BV_HI] - lo;
+  return ((u < v ? u : v) - lo) * C + ((u < v ? v : u) - lo);
+}
+__global__ __launch_bounds__(B) void k_bv_pairs(EdgeLists L, const uint64_t *bv, int64_t n, uint64_t *pairs) {
+  if (!bv_thins(bv, n)) return;
+  const Live lv = live_list(L, bv);
+  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < lv.E; i += (int64_t)gridDim.x * B) {
+    const uint64_t k = lv.key[i], p = pair_at(lv.u[i], lv.v[i], bv);
+    if (k < pairs[p]) atomicMin((unsigned long long *)&pairs[p], (unsigned long long)k);
+  }
+}
+__global__ __launch_bounds__(LBK) void k_bv_thin(EdgeLists L, uint64_t *bv, int64_t n, const uint64_t *pairs) {
+  if (!bv_thins(bv, n)) return;
+  const Live lv = live_list(L, bv);
+  const int ob = out_buffer(bv), ct = list_items(lv.E);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < lv.E; tile += gridDim.x) {
+    bool keep[LCT];
+    uint32_t pos[LCT];
+    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(lv.E, tile, LBK * ct);
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = base + (int64_t)k * LBK;
+      keep[k] = i < end && pairs[pair_at(lv.u[i], lv.v[i], bv)] == lv.key[i];
+    }
+    list_positions(keep, pos, (unsigned long long *)&bv[BV_CNT1]);
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      if (!keep[k]) continue;
+      const int64_t i = base + (int64_t)k * LBK;
+      L.key[ob][pos[k]] = lv.key[i];
+      L.u[ob][pos[k]] = lv.u[i];
+      L.v[ob][pos[k]] = lv.v[i];
+      L.s[ob][pos[k]] = lv.s ? lv.s[i] : (uint32_t)i;
+    }
+  }
+}
+
+// What the enqueued slots of a small call leave (it does not split), in one
+// workgroup: rounds of the same five steps with barriers between them.
+// Components at least halve per round, so the tree's levels (H_LEV holds 96)
+// end any call; past them the call fails.
 constexpr int BTB = 1024;
-__global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint64_t *best, uint32_t *bpar,
-                                                 uint32_t *rootc, uint8_t *msf_flag, uint64_t *hdr) {
-  const uint64_t act = bv[BV_ACT];
-  if (act == ACT_NONE) return;
+__global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, int64_t n, bool thin, uint64_t *best,
+                                                 uint32_t *bpar, uint32_t *rootc, uint8_t *msf_flag, uint64_t *hdr) {
+  if (bv[BV_ACT] == ACT_NONE) return;
   __shared__ uint32_t s_nb, s_cnt;
   Live lv = live_list(L, bv);
   int ob = out_buffer(bv);
   int64_t lo = (int64_t)bv[BV_LO], hi = (int64_t)bv[BV_HI];
-  const int hb = (int)bv[BV_HB];
-  const int64_t slo = (int64_t)bv[BV_SLO], EH = (int64_t)bv[BV_EH];
-  bool light = bv[BV_LIGHT] != 0 || act == ACT_HEAVY, marked = bv[BV_MARK] != 0;
+  if (thin && bv_thins(bv, n)) {
+    lv = Live{L.key[ob], L.u[ob], L.v[ob], L.s[ob], (int64_t)bv[BV_CNT1]};
+    ob = 1 - ob;
+  }
   int level = (int)bv[H_BV_NLEV - H_BV];
   const int tid = threadIdx.x;
-  if (act == ACT_HEAVY) lv.E = 0;
   __syncthreads();  // (bv is written below)
-  while (true) {
+  while (lv.E > 0 && level < H_LPOS - H_LEV - 1) {
     if (tid == 0) {
       s_nb = (uint32_t)hi;
       s_cnt = 0;
     }
-    if (lv.E == 0) {
-      if (!light) break;
-      // the heavy edges, from the back of the buffer of the split, by the tops of their nodes
-      light = false;
-      marked = true;
-      lo = slo;
-      for (int64_t c = lo + tid; c < hi; c += BTB) {
-        uint32_t x = (uint32_t)c;
-        for (uint32_t q = bpar[x]; q != x; q = bpar[x]) x = q;
-        rootc[c - lo] = x;
-      }
-      __syncthreads();
-      const int64_t off = L.cap - EH;
-      ob = 1 - hb;
-      for (int64_t i = tid; i < EH; i += BTB) {
-        const uint32_t fu = rootc[L.u[hb][off + i] - lo], fv = rootc[L.v[hb][off + i] - lo];
-        if (fu == fv) continue;
-        const uint32_t p = atomicAdd(&s_cnt, 1u);
-        L.key[ob][p] = L.key[hb][off + i];
-        L.u[ob][p] = fu;
-        L.v[ob][p] = fv;
-        L.s[ob][p] = L.s[hb][off + i];
-      }
-      __syncthreads();
-      lv = Live{L.key[ob], L.u[ob], L.v[ob], L.s[ob], (int64_t)s_cnt};
-      ob = 1 - ob;
-      __syncthreads();
-      continue;
-    }
-    if (level >= H_LPOS - H_LEV - 1) break;
     for (int64_t i = tid; i < lv.E; i += BTB) {
       const unsigned long long k = lv.key[i];
       const uint32_t u = lv.u[i], v = lv.v[i];
@@ -867,7 +890,7 @@ __global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint
     __syncthreads();
     for (int64_t c = lo + tid; c < hi; c += BTB) {
       uint32_t r = NONE32;
-      if (!(marked && rootc[c - lo] != c) && best[c] != NONE64) {
+      if (best[c] != NONE64) {
         r = bv_root(bpar, (uint32_t)c, hdr);
         if (r == (uint32_t)c) r = atomicAdd(&s_nb, 1u);
       }
@@ -893,7 +916,6 @@ __global__ __launch_bounds__(BTB) void k_bv_tail(EdgeLists L, uint64_t *bv, uint
     __syncthreads();
     if (tid == 0) bv_level(bv, (uint64_t)nb);
     level++;
-    marked = false;
     lv = Live{L.key[ob], L.u[ob], L.v[ob], L.s[ob], (int64_t)s_cnt};
     ob = 1 - ob;
     lo = hi;
@@ -1170,8 +1192,6 @@ size_t stage_boruvka_scratch(int64_t n, int64_t slots) {
 // The filter split runs when the live edges number at least 2^20 and more
 // than twice the components. A call's tuning (ce_tuning.split_min_edges,
 // CE_SPLIT_MIN_EDGES) overrides the 2^20 or turns the split off.
-static int64_t split_min_edges() { return tuning().split_min_edges; }
-
 // Slots the host enqueues after the first round: in every round the
 // components that still have live edges at least halve, so bits(n) + 1 rounds
 // end a run of plain rounds. With one split (a further one is made only where
@@ -1184,26 +1204,38 @@ static int boruvka_rounds(int64_t n, bool split_possible) {
   return split_possible ? 2 * r + 3 : r;
 }
 
-// Up to 2^22 skeleton slots a call enqueues fewer slots than the bound (half
-// a round per bit of n, and if it may split, one) and leaves the rest, if any,
-// to one workgroup: an idle slot costs six launches of about 2 us and its level
-// of the dendrogram one more, a round of one workgroup about 10 us plus 0.5 us
-// per 1024 edges and step. (1e6 records with a split use 17 slots of a bound of
-// 45: 2.77 ms with all of them, 2.47 so.) Larger calls enqueue the full bound:
-// one workgroup could be left with too many edges.
-BvPlan boruvka_plan(int64_t n, int64_t slots) {
+// A call may split if it has at least twice as many skeleton slots as the live
+// edges from which lists are split (of a call's slots about half are live after
+// the first round), unless it is an asynchronous one of up to 2^22 slots under
+// the built-in choice: that would enqueue all the slots of the bound, idle or
+// not (1.1e6 and 2e6 records: 2.39 and 2.90 ms, without a split 1.96 and 2.73).
+//
+// A call of up to 2^22 slots that does not split enqueues half a round per bit
+// of n and leaves the rest, if any, to one workgroup: an idle slot costs six
+// launches of about 2 us and its level of the dendrogram one more. The rest is
+// little: few components are left after so many rounds, and from 2^18 slots on
+// (an idle pair of launches more) a long list is thinned before. Calls that
+// split enqueue the full bound, as light rounds may leave any number of heavy
+// edges between any number of components; with fewer slots, 1e6 records of two
+// nested paths left 4e5 edges to the one workgroup and took 14.0 ms, now 2.3.
+// (Synchronous calls with and without a split: 5e5 to 8e5 records 1.62 and 1.49
+// ms, 1e6 2.02 and 1.83 or, of sparser graphs, 1.72 and 1.83, 2e6 2.48 and 2.60.)
+BvPlan boruvka_plan(int64_t n, int64_t slots, bool sync) {
+  constexpr int64_t SMALL = int64_t(1) << 22;
+  const int64_t split_min = tuning().split_min_edges;
   BvPlan p;
-  p.split_possible = slots >= split_min_edges();
-  p.tail = slots <= (int64_t(1) << 22);
+  p.split_possible = slots / 2 >= split_min && (sync || slots > SMALL || split_min < Tuning().split_min_edges);
+  p.tail = !p.split_possible && slots <= SMALL;
+  p.thin = p.tail && slots > (int64_t(1) << 18);
   p.slots = boruvka_rounds(n, p.split_possible);
   if (p.tail) {
-    const int few = p.split_possible ? bits_for((uint64_t)n) : slots <= 8192 ? 0 : bits_for((uint64_t)n) / 2 + 1;
+    const int few = slots <= 8192 ? 0 : bits_for((uint64_t)n) / 2 + 1;
     if (few < p.slots) p.slots = few;
   }
   return p;
 }
 
-// A synchronous call of more slots looks whether the forest is complete, after
+// A synchronous call of the full bound looks whether the forest is complete, after
 // LOOK_FROM slots and every LOOK_EVERY from there: a look is a round trip of
 // about 25 us, an idle slot with its level of the dendrogram 15 to 30, and a
 // call uses 12 to 17 slots of a bound of 49 to 61. 8e6 causal records 10.35 ->
@@ -1240,8 +1272,8 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
               (const uint2 *)b.skel_tail, bpar, (uchar2 *)b.msf_flag);
   bv_compress(n, lN, bv, best, bpar, rootc, b.hdr, s);
   CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
-  const int64_t split_min = split_min_edges();
-  const BvPlan plan = boruvka_plan(n, n2);
+  const BvPlan plan = boruvka_plan(n, n2, b.sync);
+  const int64_t split_min = plan.split_possible ? tuning().split_min_edges : INT64_MAX;
   if (plan.split_possible)
     CE_LAUNCH(k_bv_first, dim3(1), dim3(FIRST_SAMPLES), 0, s, L, b.flat, n2, bpar, bv, split_min);
   if (b.flat)
@@ -1259,9 +1291,7 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   // keeps every heavy edge's cycles. The heavy edges wait, with the nodes they
   // had at the split, at the back of the buffer the split wrote.
   for (int r = 0; r < plan.slots; r++) {
-    // slots a further split may count on: where one workgroup takes the rest, any number, but not at the very end
-    const int slots_left = plan.slots - r, left = !plan.tail ? slots_left : slots_left >= 10 ? 128 : 0;
-    CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min, left);
+    CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min, plan.slots - r, n, (uint64_t *)nullptr);
     if (b.sync && !plan.tail && r >= LOOK_FROM && r % LOOK_EVERY == 0) {
       uint64_t st[H_BV_NLEV - H_BV + 1];
       CE_TRY(read_u64(bv, st, H_BV_NLEV - H_BV + 1, s));
@@ -1277,8 +1307,14 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
     CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar, rootc);
     CE_HIP(hipGetLastError());
   }
-  CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min, 0);
-  if (plan.tail) CE_LAUNCH(k_bv_tail, dim3(1), dim3(BTB), 0, s, L, bv, best, bpar, rootc, b.msf_flag, b.hdr);
+  uint64_t *pairs = plan.thin ? (uint64_t *)rootc : nullptr;
+  CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min, 0, n, pairs);
+  if (plan.thin) {
+    CE_LAUNCH(k_bv_pairs, dim3(gE), dim3(B), 0, s, L, bv, n, pairs);
+    CE_LAUNCH(k_bv_thin, dim3(lE), dim3(LBK), 0, s, L, bv, n, pairs);
+  }
+  if (plan.tail)
+    CE_LAUNCH(k_bv_tail, dim3(1), dim3(BTB), 0, s, L, bv, n, plan.thin, best, bpar, rootc, b.msf_flag, b.hdr);
   CE_HIP(hipGetLastError());
   ws.release(m0);
   return CE_OK;
