@@ -39,14 +39,39 @@ __device__ inline void lc_st(int32_t *p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The root above x. Short walks halve the path that they follow. Rows of
+// records at regular intervals hook each record to the one before, all at once,
+// and a row that comes later walks that whole chain by itself, one read after
+// another (1e6 links: 267 ms by halving; 141 when every row looked for its
+// roots before it hooked, as the chain was then still being made). So a longer
+// walk reads the links of LOOK neighbouring nodes at a time, through the caches
+// (a stale link is an ancestor; a root is read again), follows them as far as
+// they go, and leaves a link across STRIDE such windows behind it: 32 ms.
+constexpr int FIND_STEPS = 16, LOOK = 16, STRIDE = 4;
 __device__ inline int32_t lc_find(int32_t *par, int32_t x) {
-  while (true) {
+  for (int steps = 0; steps < FIND_STEPS; steps++) {
     const int32_t p = lc_ld(&par[x]);
     if (p == x) return x;
     const int32_t g = lc_ld(&par[p]);
     if (g == p) return p;
     lc_st(&par[x], g);
     x = g;
+  }
+  while (true) {
+    const int32_t from = x;
+    for (int w = 0; w < STRIDE; w++) {
+      int32_t link[LOOK];
+#pragma unroll
+      for (int k = 0; k < LOOK; k++) link[k] = lc_cached(&par[x > k ? x - k : 0]);
+      const int32_t top = x;
+#pragma unroll
+      for (int k = 0; k < LOOK; k++)  // parents are smaller: the nodes of the window are met in this order
+        if (x == top - k) x = link[k];
+      const int32_t p = lc_ld(&par[x]);
+      if (p == x) return x;
+      x = p;
+    }
+    lc_st(&par[from], x);
   }
 }
 
@@ -117,8 +142,8 @@ __global__ __launch_bounds__(B) void k_lc_union(const uint32_t *tl, const uint32
 // (a stale link is an ancestor all the same). Only long walks do: the stores
 // of short ones go to the few nodes above everything, one after another (4e5
 // records at 8 levels: 0.52 ms with halving from the first or the eighth step,
-// 0.19 without). A path of 1e6 rows in one level takes 0.7 ms this way and 144
-// with walks that never shorten.
+// 0.19 without). A path of 1e6 rows in one level takes 0.28 ms this way, of 2e7
+// 31.5.
 constexpr int LONG_WALK = 64;
 template <int LI>
 __global__ __launch_bounds__(B) void k_lc_labels(const int32_t *prev, int32_t *W, int64_t n, int32_t *out) {
@@ -154,7 +179,11 @@ __global__ __launch_bounds__(B) void k_lc_labels(const int32_t *prev, int32_t *W
 // The last level's labels take W's own place: only roots are stored, so every
 // value a walk reads is an ancestor and the last store to each entry is its
 // root. (A halving store, an intermediate ancestor, could land after another
-// thread stored the root.)
+// thread stored the root.) The roots shorten the walks behind them: workgroups
+// start in the order of the records, parents are smaller, so a walk goes no
+// further than the records in flight. A path of 1e6 rows takes 0.72 ms, of 2e7
+// 10.6 (with shortening by atomicMin, which no stale store could undo, 3.1 at
+// 1e6).
 __global__ __launch_bounds__(B) void k_lc_labels_last(const int32_t *prev, int32_t *W, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < n; i += (int64_t)gridDim.x * B) {
     int32_t x = prev ? prev[i] : (int32_t)i;
