@@ -755,57 +755,67 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
   }
 }
 
-// per node, the minimum key over its live edges. A tile of up to LBK * CT edges
-// first takes per-node minima in an LDS hash (late rounds send most edges to
-// a few big components), then one atomicMin per node per tile.
+// Minima per index, of the keys that the threads of a workgroup offer: first in
+// an LDS hash (late rounds send most edges to a few big components), then one
+// atomicMin per index. Call from all threads of a wave; min_flush ends a tile.
 constexpr int MHS = 512;  // (1024, as many as the nodes of a small tile, cost 1e6-record calls 2 %)
+struct MinHash {
+  uint32_t k[MHS];
+  unsigned long long v[MHS];
+};
+__device__ inline void min_clear(MinHash &h) {
+  for (int i = threadIdx.x; i < MHS; i += blockDim.x) { h.k[i] = NONE32; h.v[i] = NONE64; }
+  __syncthreads();
+}
+__device__ inline void min_offer(MinHash &h, bool act, uint32_t c, unsigned long long kv, uint64_t *best) {
+  unsigned long long kmin = kv;
+  const bool upd = wave_combine_first(act, c, [&](bool mine, int leader) {
+    const unsigned long long v = wave_min_u64(mine ? kv : NONE64);
+    if ((int)wave_lane() == leader) kmin = v;
+  });
+  if (!upd) return;
+  uint32_t sl = (c * 2654435761u) >> 23;  // 9 bits
+  bool placed = false;
+  for (int probe = 0; probe < HASH_PROBES && !placed; probe++) {
+    uint32_t old = atomicCAS(&h.k[sl], NONE32, c);
+    if (old == NONE32 || old == c) {
+      if (kmin < h.v[sl]) atomicMin(&h.v[sl], kmin);
+      placed = true;
+    } else {
+      sl = (sl + 1) & (MHS - 1);
+    }
+  }
+  if (!placed && kmin < best[c]) atomicMin((unsigned long long *)&best[c], kmin);
+}
+__device__ inline void min_flush(MinHash &h, uint64_t *best) {
+  __syncthreads();
+  for (int i = threadIdx.x; i < MHS; i += blockDim.x) {
+    const uint32_t c = h.k[i];
+    if (c == NONE32) continue;
+    const unsigned long long v = h.v[i];
+    if (v < best[c]) atomicMin((unsigned long long *)&best[c], v);
+  }
+  __syncthreads();
+}
+
+// per node, the minimum key over its live edges, in tiles of up to LBK * LCT edges
 __global__ __launch_bounds__(LBK) void k_bv_min(EdgeLists L, const uint64_t *bv, uint64_t *best) {
   if (bv[BV_ACT] != ACT_ROUND) return;
   const Live lv = live_list(L, bv);
-  __shared__ uint32_t hk[MHS];
-  __shared__ unsigned long long hv[MHS];
+  __shared__ MinHash h;
   const int ct = list_items(lv.E);
   for (int64_t tile = blockIdx.x; tile * (LBK * ct) < lv.E; tile += gridDim.x) {
-    for (int i = threadIdx.x; i < MHS; i += LBK) { hk[i] = NONE32; hv[i] = NONE64; }
-    __syncthreads();
+    min_clear(h);
     const int64_t tbase = tile * (LBK * ct);
     for (int k = 0; k < ct; k++) {
       const int64_t i = tbase + (int64_t)k * LBK + threadIdx.x;
       const bool act = i < lv.E;
       const unsigned long long kv = act ? lv.key[i] : NONE64;
       const uint32_t cu = act ? lv.u[i] : 0u, cv = act ? lv.v[i] : 0u;
-#pragma unroll
-      for (int side = 0; side < 2; side++) {
-        const uint32_t c = side ? cv : cu;
-        unsigned long long kmin = kv;
-        const bool upd = wave_combine_first(act, c, [&](bool mine, int leader) {
-          const unsigned long long v = wave_min_u64(mine ? kv : NONE64);
-          if ((int)wave_lane() == leader) kmin = v;
-        });
-        if (upd) {
-          uint32_t sl = (c * 2654435761u) >> 23;  // 9 bits
-          bool placed = false;
-          for (int probe = 0; probe < HASH_PROBES && !placed; probe++) {
-            uint32_t old = atomicCAS(&hk[sl], NONE32, c);
-            if (old == NONE32 || old == c) {
-              if (kmin < hv[sl]) atomicMin(&hv[sl], kmin);
-              placed = true;
-            } else {
-              sl = (sl + 1) & (MHS - 1);
-            }
-          }
-          if (!placed && kmin < best[c]) atomicMin((unsigned long long *)&best[c], kmin);
-        }
-      }
+      min_offer(h, act, cu, kv, best);
+      min_offer(h, act, cv, kv, best);
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < MHS; i += LBK) {
-      const uint32_t c = hk[i];
-      if (c == NONE32) continue;
-      const unsigned long long v = hv[i];
-      if (v < best[c]) atomicMin((unsigned long long *)&best[c], v);
-    }
-    __syncthreads();
+    min_flush(h, best);
   }
 }
 
@@ -820,12 +830,19 @@ __device__ inline uint64_t pair_at(uint32_t u, uint32_t v, const uint64_t *bv) {
   const uint64_t lo = bv[BV_LO], C = bv[BV_HI] - lo;
   return ((u < v ? u : v) - lo) * C + ((u < v ? v : u) - lo);
 }
-__global__ __launch_bounds__(B) void k_bv_pairs(EdgeLists L, const uint64_t *bv, int64_t n, uint64_t *pairs) {
+__global__ __launch_bounds__(LBK) void k_bv_pairs(EdgeLists L, const uint64_t *bv, int64_t n, uint64_t *pairs) {
   if (!bv_thins(bv, n)) return;
   const Live lv = live_list(L, bv);
-  for (int64_t i = (int64_t)blockIdx.x * B + threadIdx.x; i < lv.E; i += (int64_t)gridDim.x * B) {
-    const uint64_t k = lv.key[i], p = pair_at(lv.u[i], lv.v[i], bv);
-    if (k < pairs[p]) atomicMin((unsigned long long *)&pairs[p], (unsigned long long)k);
+  __shared__ MinHash h;
+  const int ct = list_items(lv.E);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < lv.E; tile += gridDim.x) {
+    min_clear(h);
+    for (int k = 0; k < ct; k++) {
+      const int64_t i = tile * (LBK * ct) + (int64_t)k * LBK + threadIdx.x;
+      const bool act = i < lv.E;
+      min_offer(h, act, act ? (uint32_t)pair_at(lv.u[i], lv.v[i], bv) : 0u, act ? lv.key[i] : NONE64, pairs);
+    }
+    min_flush(h, pairs);
   }
 }
 __global__ __launch_bounds__(LBK) void k_bv_thin(EdgeLists L, uint64_t *bv, int64_t n, const uint64_t *pairs) {
@@ -1310,7 +1327,7 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   uint64_t *pairs = plan.thin ? (uint64_t *)rootc : nullptr;
   CE_LAUNCH(k_bv_ctl, dim3(1), dim3(SPLIT_SAMPLES), 0, s, L, bv, split_min, 0, n, pairs);
   if (plan.thin) {
-    CE_LAUNCH(k_bv_pairs, dim3(gE), dim3(B), 0, s, L, bv, n, pairs);
+    CE_LAUNCH(k_bv_pairs, dim3(lE), dim3(LBK), 0, s, L, bv, n, pairs);
     CE_LAUNCH(k_bv_thin, dim3(lE), dim3(LBK), 0, s, L, bv, n, pairs);
   }
   if (plan.tail)
