@@ -422,7 +422,8 @@ __global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_
       link[k] = NONE32;
       if (i >= end) continue;
       const uint32_t c = (uint32_t)(lo + i);
-      live[k] = !(marked && rootc[i] != c) && best[c] != NONE64;  // (marked: some were merged in an earlier round)
+      // (marked: some were merged in an earlier round; a node without an edge points to itself)
+      live[k] = !(marked && rootc[i] != c) && (!(DO & CP_WALK) || best[c] != NONE64);
       link[k] = live[k] ? link_ld(&bpar[c]) : c;
       if (DO & CP_LINKS) s_link[c - c0] = link[k];
     }
