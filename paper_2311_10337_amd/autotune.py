@@ -5,7 +5,7 @@ Boruvka splits its edge list at a pivot key (``split_min_edges``), the size of
 the passes over live lists (``list_grid``), and the keys per thread of every
 radix sort (``radix_keys_per_thread``, the sort tile). None of them changes an
 output. (``krt_level_bits`` is read and written with the others, but has no
-effect any more, so it is not swept.)
+effect: it is not swept by default, and a sweep told to try it never keeps it.)
 
 A sweep is coordinate descent over the knobs in that order, starting from the
 built-in choices: each candidate is timed as the median wall time of ``reps``
@@ -40,6 +40,7 @@ CANDIDATES: Dict[str, Tuple[int, ...]] = {
     "radix_keys_per_thread": (4, 16),
 }
 ORDER = ("krt_level_bits", "split_min_edges", "list_grid", "radix_keys_per_thread")
+WITHOUT_EFFECT = ("krt_level_bits",)
 PACKAGE_FILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning", "mi355x.tune")
 HEADER = "# n_bits V_bits maxdeg_bits radix list_grid krt_bits split default_ms tuned_ms\n"
 
@@ -118,7 +119,7 @@ def sweep(run: Callable[[], object], digest: Callable[[object], tuple], reps: in
             trials.append((k, ms))
             if log:
                 log("%s: %.3f ms" % (k, ms))
-            if ms < best_ms * 0.98:
+            if ms < best_ms * 0.98 and knob not in WITHOUT_EFFECT:
                 best, best_ms = k, ms
     # the choice against the built-in one, timed again side by side
     if best:
