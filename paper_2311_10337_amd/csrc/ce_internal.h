@@ -149,16 +149,11 @@ enum : int {
                  // the plan's key allows; every stage after validation treats the input as empty when set
   H_TMIN = 1,    // min t as an order-preserving u64
   H_TMAX = 2,    // max t likewise
-  H_CNT = 4,     // list counters of the current stage
-  H_CNT2 = 5,
   H_M = 6,       // rows of the spanning forest
-  H_C7 = 7,      // stage-local counters
-  H_C8 = 8,
-  H_C9 = 9,
+  H_C7 = 7,      // stage-local counter
   H_NB = 10,     // cluster births
   H_NROWS = 11,  // cluster rows (births + one root per graph)
   H_NVIRT = 12,  // virtual sum nodes of the discrete condensing
-  H_KEYW = 13,   // key layout of the flat skeletons: wshift | hshift << 8 | keybits << 16
   H_NEOM = 14,   // rows of the excess-of-mass tree (cluster rows + virtual nodes)
   H_BV = 16,     // Boruvka state (24 words)
   H_BV_NLEV = 40,  // levels of the Boruvka tree (rounds that made nodes)
@@ -183,7 +178,6 @@ __host__ __device__ inline int64_t status_of(uint64_t bits) {
 struct u128 {
   uint64_t lo, hi;
 };
-__host__ __device__ inline u128 u128_make(uint64_t hi, uint64_t lo) { return u128{lo, hi}; }
 __host__ __device__ inline u128 u128_add(u128 a, u128 b) {
   u128 r;
   r.lo = a.lo + b.lo;
@@ -317,7 +311,7 @@ constexpr int HASH_PROBES = 4;
 struct Tuning {
   int radix_ipt = 8;
   int list_grid = 4096;
-  int krt_level_bits = 0;  // 0: the rule of the row count
+  int krt_level_bits = 0;  // taken and reported, without effect
   int64_t split_min_edges = int64_t(1) << 20;  // INT64_MAX: no split
 };
 const Tuning &tuning();

@@ -61,8 +61,8 @@ __global__ void k_check_span(uint64_t *hdr, int64_t n, int tbits) {
 
 __device__ inline int64_t tmin_of(const uint64_t *hdr) { return (int64_t)(hdr[H_TMIN] ^ (uint64_t(1) << 63)); }
 
-// the time sort carries (id, src, dst, graph) along, so grouping needs no
-// gathers; vertex ids become global (graph offset + local id)
+// the time sort carries (id, src, dst) along, so grouping needs no gathers;
+// vertex ids become global (graph offset + local id)
 __global__ __launch_bounds__(B) void k_tkeys(const int64_t *t, const int32_t *src, const int32_t *dst, int64_t n,
                                              const int64_t *eoff, const int64_t *voff, int64_t G,
                                              const uint64_t *hdr, uint64_t *keys, uint4 *vals) {
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(B) void k_tkeys(const int64_t *t, const int32_t *sr
     const uint32_t g = G > 1 ? graph_of(eoff, G, i) : 0u;
     const uint32_t vb = (uint32_t)voff[g];
     keys[i] = (uint64_t)(t[i] - tmin);
-    vals[i] = make_uint4((uint32_t)i, vb + (uint32_t)src[i], vb + (uint32_t)dst[i], g);
+    vals[i] = make_uint4((uint32_t)i, vb + (uint32_t)src[i], vb + (uint32_t)dst[i], 0u);
   }
 }
 
@@ -1123,7 +1123,7 @@ size_t stage_sort_skeleton_scratch(int64_t n) {
 }
 
 // Records by (t, id): stable radix sort on t - tmin carrying (id, global src,
-// global dst, graph). b.ts receives the sorted times; *vals points at the
+// global dst). b.ts receives the sorted times; *vals points at the
 // sorted payload inside ws (the caller releases it).
 ce_status sort_records_by_time(const int32_t *src, const int32_t *dst, const int64_t *t, Bufs &b, Ws &ws,
                                hipStream_t s, const uint4 **vals) {
