@@ -209,6 +209,7 @@ __global__ __launch_bounds__(B) void k_skel_keys(const uint64_t *ts, const uint3
 //   k_bv_min       minimum key per node over the live edges
 //   k_bv_hook      every edge that is its endpoint's minimum hooks it
 //   k_bv_compress  every node to the root of its hooks; roots get new ids
+//                  (where nodes are many, after k_bv_links)
 //   k_bv_link      bpar of every node = the new id of its root
 //   k_contract     edges between different components, renamed
 // preceded by k_bv_ctl, one workgroup that advances the state (live edges E,
@@ -391,12 +392,62 @@ __device__ inline uint32_t bv_root(uint32_t *bpar, uint32_t x, uint64_t *hdr) {
 // ms. Up to 2^18 nodes, one a thread, the walks do alone: a chain of all of them
 // costs 0.05 ms, while the barriers took 2 % of any 7e4-record call. Other
 // inputs take the same time either way.
-enum : int { CP_LINKS = 1, CP_WALK = 2 };
-template <int DO>
+constexpr int64_t BV_WALKS = (int64_t)LBK * 512;
+// nodes whose tiles are in flight together (see list_items for the 512)
+__host__ __device__ inline int64_t bv_flight(unsigned grid) {
+  return grid < 512 ? (int64_t)LBK * grid : (int64_t)LBK * LCT * 512;
+}
+// jumps along the links inside [c0, c0 + len); a thread has the nodes
+// threadIdx.x + k * LBK of it. Stores the links that have moved.
+__device__ inline void tile_links(uint32_t c0, uint32_t len, const bool (&live)[LCT], uint32_t (&link)[LCT],
+                                  uint32_t *s_link, uint32_t *bpar) {
+#pragma unroll
+  for (int k = 0; k < LCT; k++)
+    if (threadIdx.x + k * LBK < len) s_link[threadIdx.x + k * LBK] = link[k];
+  uint32_t changed = 0;
+  bool moved = true;
+  for (int round = 0; __syncthreads_or(moved) && round < 32; round++) {  // 12 rounds end any path of a tile
+    moved = false;
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      if (!live[k] || link[k] - c0 >= len) continue;
+      const uint32_t up = s_link[link[k] - c0];
+      if (up == link[k]) continue;
+      s_link[threadIdx.x + k * LBK] = link[k] = up;
+      changed |= 1u << k;
+      moved = true;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < LCT; k++)
+    if (changed >> k & 1u) link_st(&bpar[c0 + threadIdx.x + k * LBK], link[k]);
+}
+// (merged nodes of a marked range keep their parents; a node without an edge points to itself)
+__global__ __launch_bounds__(LBK) void k_bv_links(const uint64_t *bv, uint32_t *bpar, const uint32_t *rootc) {
+  const int64_t lo = (int64_t)bv[BV_LO], nc = (int64_t)bv[BV_HI] - lo;
+  if (bv[BV_ACT] != ACT_ROUND || nc <= bv_flight(gridDim.x)) return;
+  __shared__ uint32_t s_link[LBK * LCT];
+  const bool marked = bv[BV_MARK] != 0;
+  const int ct = list_items(nc);
+  for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nc; tile += gridDim.x) {
+    bool live[LCT];
+    uint32_t link[LCT];
+    const int64_t t0 = tile * (LBK * ct), end = tile_end(nc, tile, LBK * ct);
+#pragma unroll
+    for (int k = 0; k < LCT; k++) {
+      const int64_t i = t0 + threadIdx.x + (int64_t)k * LBK;
+      const uint32_t c = (uint32_t)(lo + i);
+      live[k] = i < end && !(marked && rootc[i] != c);
+      link[k] = live[k] ? link_ld(&bpar[c]) : c;
+    }
+    tile_links((uint32_t)(lo + t0), (uint32_t)(end - t0), live, link, s_link, bpar);
+    __syncthreads();  // (the links' LDS is used again)
+  }
+}
 __global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_t *best, uint32_t *bpar,
                                                      uint32_t *rootc, uint64_t *hdr) {
   const uint64_t act = bv[BV_ACT];
-  if ((DO & CP_WALK) && act == ACT_HEAVY) {  // the heavy edges' way up, which also marks the next round's range
+  if (act == ACT_HEAVY) {  // the heavy edges' way up, which also marks the next round's range
     const int64_t lo = (int64_t)bv[BV_SLO], hi = (int64_t)bv[BV_NB];
     for (int64_t c = lo + (int64_t)blockIdx.x * LBK + threadIdx.x; c < hi; c += (int64_t)gridDim.x * LBK) {
       uint32_t x = (uint32_t)c;  // as many steps as light rounds at most
@@ -407,72 +458,32 @@ __global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_
   }
   if (act != ACT_ROUND) return;
   const int64_t lo = (int64_t)bv[BV_LO], nc = (int64_t)bv[BV_HI] - lo;
-  const bool marked = bv[BV_MARK] != 0;
+  const bool marked = bv[BV_MARK] != 0, jump = nc > BV_WALKS && nc <= bv_flight(gridDim.x);
   const int ct = list_items(nc);
-  __shared__ uint32_t s_link[(DO & CP_LINKS) ? LBK * LCT : 1];
+  __shared__ uint32_t s_link[LBK * LCT];
   for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nc; tile += gridDim.x) {
     bool keep[LCT], live[LCT];
     uint32_t pos[LCT], link[LCT];
-    const int64_t base = tile * (LBK * ct) + threadIdx.x, end = tile_end(nc, tile, LBK * ct);
-    const uint32_t c0 = (uint32_t)(lo + base - threadIdx.x), len = (uint32_t)(end - base + threadIdx.x);
+    const int64_t t0 = tile * (LBK * ct), end = tile_end(nc, tile, LBK * ct);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
-      const int64_t i = base + (int64_t)k * LBK;
-      keep[k] = live[k] = false;
-      link[k] = NONE32;
-      if (i >= end) continue;
+      const int64_t i = t0 + threadIdx.x + (int64_t)k * LBK;
       const uint32_t c = (uint32_t)(lo + i);
-      // (marked: some were merged in an earlier round; a node without an edge points to itself)
-      live[k] = !(marked && rootc[i] != c) && (!(DO & CP_WALK) || best[c] != NONE64);
+      live[k] = i < end && !(marked && rootc[i] != c) && best[c] != NONE64;  // (marked: some were merged before)
       link[k] = live[k] ? link_ld(&bpar[c]) : c;
-      if (DO & CP_LINKS) s_link[c - c0] = link[k];
     }
-    if (DO & CP_LINKS) {
-      uint32_t changed = 0;
-      bool moved = true;
-      for (int round = 0; __syncthreads_or(moved) && round < 32; round++) {  // 12 rounds end any path of a tile
-        moved = false;
-#pragma unroll
-        for (int k = 0; k < LCT; k++) {
-          if (!live[k] || link[k] - c0 >= len) continue;
-          const uint32_t up = s_link[link[k] - c0];
-          if (up == link[k]) continue;
-          s_link[threadIdx.x + k * LBK] = link[k] = up;
-          changed |= 1u << k;
-          moved = true;
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < LCT; k++)
-        if (changed >> k & 1u) link_st(&bpar[lo + base + (int64_t)k * LBK], link[k]);
-    }
-    if (!(DO & CP_WALK)) {
-      __syncthreads();  // (the links' LDS is used again)
-      continue;
-    }
+    if (jump) tile_links((uint32_t)(lo + t0), (uint32_t)(end - t0), live, link, s_link, bpar);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
-      const int64_t i = base + (int64_t)k * LBK;
-      if (i >= end) continue;
-      const uint32_t c = (uint32_t)(lo + i);
-      keep[k] = live[k] && link[k] == c;
-      if (!keep[k]) rootc[i] = live[k] ? bv_root(bpar, link[k], hdr) : NONE32;
+      const int64_t i = t0 + threadIdx.x + (int64_t)k * LBK;
+      keep[k] = live[k] && link[k] == (uint32_t)(lo + i);
+      if (i < end && !keep[k]) rootc[i] = live[k] ? bv_root(bpar, link[k], hdr) : NONE32;
     }
     list_positions(keep, pos, (unsigned long long *)&bv[BV_NB]);
 #pragma unroll
     for (int k = 0; k < LCT; k++)
-      if (keep[k]) rootc[base + (int64_t)k * LBK] = pos[k];
+      if (keep[k]) rootc[t0 + threadIdx.x + (int64_t)k * LBK] = pos[k];
   }
-}
-// in a round of (about) nc nodes at most
-void bv_compress(int64_t nc, unsigned grid, uint64_t *bv, const uint64_t *best, uint32_t *bpar, uint32_t *rootc,
-                 uint64_t *hdr, hipStream_t s) {
-  const int64_t flight = grid < 512 ? (int64_t)LBK * grid : (int64_t)LBK * LCT * 512;  // (see list_items)
-  if (nc > flight) CE_LAUNCH(k_bv_compress<CP_LINKS>, dim3(grid), dim3(LBK), 0, s, bv, best, bpar, rootc, hdr);
-  if (nc > flight || nc <= (int64_t)LBK * 512)
-    CE_LAUNCH(k_bv_compress<CP_WALK>, dim3(grid), dim3(LBK), 0, s, bv, best, bpar, rootc, hdr);
-  else
-    CE_LAUNCH(k_bv_compress<CP_LINKS | CP_WALK>, dim3(grid), dim3(LBK), 0, s, bv, best, bpar, rootc, hdr);
 }
 
 // node c -> the new node of its component; new nodes start without a minimum
@@ -1288,7 +1299,10 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   else
     CE_LAUNCH(k_bv_hook_first, dim3(gN), dim3(B), 0, s, n, best, (const ulonglong2 *)b.skel_key,
               (const uint2 *)b.skel_tail, bpar, (uchar2 *)b.msf_flag);
-  bv_compress(n, lN, bv, best, bpar, rootc, b.hdr, s);
+  // (a round halves its nodes; after a split, up to half of all may be left in any slot, among the light rounds' own)
+  const int64_t flight = bv_flight(lN);
+  if (n > flight) CE_LAUNCH(k_bv_links, dim3(lN), dim3(LBK), 0, s, bv, bpar, rootc);
+  CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
   CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
   const BvPlan plan = boruvka_plan(n, n2, b.sync);
   const int64_t split_min = plan.split_possible ? tuning().split_min_edges : INT64_MAX;
@@ -1320,7 +1334,9 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
     }
     CE_LAUNCH(k_bv_min, dim3(lE), dim3(LBK), 0, s, L, bv, best);
     CE_LAUNCH(k_bv_hook, dim3(gE), dim3(B), 0, s, L, bv, best, bpar, b.msf_flag);
-    bv_compress(r < 62 ? n >> (r + 1) : 0, lN, bv, best, bpar, rootc, b.hdr, s);  // (a round halves its nodes)
+    if (n >> (plan.split_possible ? 1 : r < 62 ? r + 1 : 63) > flight)
+      CE_LAUNCH(k_bv_links, dim3(lN), dim3(LBK), 0, s, bv, bpar, rootc);
+    CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
     CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
     CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar, rootc);
     CE_HIP(hipGetLastError());

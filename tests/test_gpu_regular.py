@@ -55,3 +55,45 @@ def test_time_of_a_chain(n):
             ms[shape] = (time.perf_counter() - t0) * 1e3
         print("[gpu-regular] n=%d %s %.2f ms" % (n, shape, ms[shape]), flush=True)
         assert ms[shape] < 10 * ms["random"], shape
+
+
+def light_and_heavy(n, shape):
+    """Pairs of records, two halves: the first at regular gaps, smaller than any of the second, with second vertices in a
+    few classes, so that a split takes its edges alone; the second half is one chain among the heavy edges."""
+    h = n // 2
+    k = torch.arange(h, dtype=torch.int64, device="cuda")
+    j = torch.arange(h // 2, dtype=torch.int64, device="cuda")
+    gaps = 11000 + (j if shape == "growing" else h // 2 - j)
+    tb = (torch.cumsum(gaps, 0) - gaps)[:, None] + torch.tensor([0, 1000], device="cuda")
+    t = torch.cat([10 * (k // 2) + k % 2, 10 * h + 1000000 + tb.reshape(-1)])
+    cl = k // 2 % 3 * 2 + k % 2
+    src = torch.zeros(2 * h, dtype=torch.int32, device="cuda")
+    src[h:] = 1
+    return src, torch.cat([2 + cl, 8 + cl]).int(), t, 14
+
+
+@pytest.mark.parametrize("shape", ["growing", "shrinking"])
+@pytest.mark.parametrize("grid, split", [(256, 1000), (256, 50000), (4096, 1000)])
+def test_chain_among_heavy_edges(grid, split, shape, monkeypatch):
+    monkeypatch.setenv("CE_LIST_GRID", str(grid))
+    monkeypatch.setenv("CE_SPLIT_MIN_EDGES", str(split))
+    s, d, t, V = light_and_heavy(300_000, shape)
+    chains.check(s.cpu().numpy(), d.cpu().numpy(), t.cpu().numpy(), V, 3, "light and heavy, " + shape)
+
+
+def test_time_of_a_chain_among_heavy_edges():
+    import paper_2311_10337_amd as ce
+    n = 16_000_000
+    outs = ce.Outputs(n, 5, torch.device("cuda:0"))
+    ws = torch.empty(ce.workspace_bytes(n, 14, 5), dtype=torch.uint8, device="cuda")
+    ms = {}
+    for shape in ("growing", "shrinking"):
+        s, d, t, V = light_and_heavy(n, shape)
+        for rep in range(2):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            ce.cluster_edges(s, d, t, 5, V, outputs=outs, workspace=ws)
+            torch.cuda.synchronize()
+            ms[shape] = (time.perf_counter() - t0) * 1e3
+    print("[gpu-regular] light and heavy %s" % ms, flush=True)
+    assert ms["shrinking"] < 2 * ms["growing"]
