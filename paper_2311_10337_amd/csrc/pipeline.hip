@@ -444,6 +444,8 @@ __global__ __launch_bounds__(LBK) void k_bv_links(const uint64_t *bv, uint32_t *
     __syncthreads();  // (the links' LDS is used again)
   }
 }
+// (SMALL: at most BV_WALKS nodes in any round)
+template <bool SMALL>
 __global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_t *best, uint32_t *bpar,
                                                      uint32_t *rootc, uint64_t *hdr) {
   const uint64_t act = bv[BV_ACT];
@@ -458,26 +460,33 @@ __global__ __launch_bounds__(LBK) void k_bv_compress(uint64_t *bv, const uint64_
   }
   if (act != ACT_ROUND) return;
   const int64_t lo = (int64_t)bv[BV_LO], nc = (int64_t)bv[BV_HI] - lo;
-  const bool marked = bv[BV_MARK] != 0, jump = nc > BV_WALKS && nc <= bv_flight(gridDim.x);
+  const bool marked = bv[BV_MARK] != 0, jump = !SMALL && nc > BV_WALKS && nc <= bv_flight(gridDim.x);
   const int ct = list_items(nc);
-  __shared__ uint32_t s_link[LBK * LCT];
+  __shared__ uint32_t s_link[SMALL ? 1 : LBK * LCT];
   for (int64_t tile = blockIdx.x; tile * (LBK * ct) < nc; tile += gridDim.x) {
     bool keep[LCT], live[LCT];
     uint32_t pos[LCT], link[LCT];
     const int64_t t0 = tile * (LBK * ct), end = tile_end(nc, tile, LBK * ct);
+    auto root = [&](int k, int64_t i) {
+      keep[k] = live[k] && link[k] == (uint32_t)(lo + i);
+      if (!keep[k]) rootc[i] = live[k] ? bv_root(bpar, link[k], hdr) : NONE32;
+    };
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
       const int64_t i = t0 + threadIdx.x + (int64_t)k * LBK;
       const uint32_t c = (uint32_t)(lo + i);
-      live[k] = i < end && !(marked && rootc[i] != c) && best[c] != NONE64;  // (marked: some were merged before)
-      link[k] = live[k] ? link_ld(&bpar[c]) : c;
+      keep[k] = live[k] = false;
+      link[k] = c;
+      if (i >= end) continue;
+      live[k] = !(marked && rootc[i] != c) && best[c] != NONE64;  // (marked: some were merged before)
+      if (live[k]) link[k] = link_ld(&bpar[c]);
+      if (SMALL) root(k, i);
     }
     if (jump) tile_links((uint32_t)(lo + t0), (uint32_t)(end - t0), live, link, s_link, bpar);
 #pragma unroll
     for (int k = 0; k < LCT; k++) {
       const int64_t i = t0 + threadIdx.x + (int64_t)k * LBK;
-      keep[k] = live[k] && link[k] == (uint32_t)(lo + i);
-      if (i < end && !keep[k]) rootc[i] = live[k] ? bv_root(bpar, link[k], hdr) : NONE32;
+      if (!SMALL && i < end) root(k, i);
     }
     list_positions(keep, pos, (unsigned long long *)&bv[BV_NB]);
 #pragma unroll
@@ -769,14 +778,15 @@ __global__ __launch_bounds__(SPLIT_SAMPLES) void k_bv_ctl(EdgeLists L, uint64_t 
 
 // Minima per index, of the keys that the threads of a workgroup offer: first in
 // an LDS hash (late rounds send most edges to a few big components), then one
-// atomicMin per index. Call from all threads of a wave; min_flush ends a tile.
+// atomicMin per index. For workgroups of LBK threads; call from all of them.
+// min_flush ends a tile.
 constexpr int MHS = 512;  // (1024, as many as the nodes of a small tile, cost 1e6-record calls 2 %)
 struct MinHash {
   uint32_t k[MHS];
   unsigned long long v[MHS];
 };
 __device__ inline void min_clear(MinHash &h) {
-  for (int i = threadIdx.x; i < MHS; i += blockDim.x) { h.k[i] = NONE32; h.v[i] = NONE64; }
+  for (int i = threadIdx.x; i < MHS; i += LBK) { h.k[i] = NONE32; h.v[i] = NONE64; }
   __syncthreads();
 }
 __device__ inline void min_offer(MinHash &h, bool act, uint32_t c, unsigned long long kv, uint64_t *best) {
@@ -801,7 +811,7 @@ __device__ inline void min_offer(MinHash &h, bool act, uint32_t c, unsigned long
 }
 __device__ inline void min_flush(MinHash &h, uint64_t *best) {
   __syncthreads();
-  for (int i = threadIdx.x; i < MHS; i += blockDim.x) {
+  for (int i = threadIdx.x; i < MHS; i += LBK) {
     const uint32_t c = h.k[i];
     if (c == NONE32) continue;
     const unsigned long long v = h.v[i];
@@ -1302,7 +1312,8 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
   // (a round halves its nodes; after a split, up to half of all may be left in any slot, among the light rounds' own)
   const int64_t flight = bv_flight(lN);
   if (n > flight) CE_LAUNCH(k_bv_links, dim3(lN), dim3(LBK), 0, s, bv, bpar, rootc);
-  CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
+  const auto k_bv_compress_ = n <= BV_WALKS ? k_bv_compress<true> : k_bv_compress<false>;
+  CE_LAUNCH(k_bv_compress_, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
   CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
   const BvPlan plan = boruvka_plan(n, n2, b.sync);
   const int64_t split_min = plan.split_possible ? tuning().split_min_edges : INT64_MAX;
@@ -1336,7 +1347,7 @@ ce_status stage_boruvka(Bufs &b, Ws &ws, hipStream_t s) {
     CE_LAUNCH(k_bv_hook, dim3(gE), dim3(B), 0, s, L, bv, best, bpar, b.msf_flag);
     if (n >> (plan.split_possible ? 1 : r < 62 ? r + 1 : 63) > flight)
       CE_LAUNCH(k_bv_links, dim3(lN), dim3(LBK), 0, s, bv, bpar, rootc);
-    CE_LAUNCH(k_bv_compress, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
+    CE_LAUNCH(k_bv_compress_, dim3(lN), dim3(LBK), 0, s, bv, best, bpar, rootc, b.hdr);
     CE_LAUNCH(k_bv_link, dim3(gN), dim3(B), 0, s, bv, rootc, bpar, best);
     CE_LAUNCH(k_contract, dim3(lE), dim3(LBK), 0, s, L, bv, bpar, rootc);
     CE_HIP(hipGetLastError());
