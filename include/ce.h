@@ -113,7 +113,8 @@ typedef struct {
                                      width to choose */
   int64_t split_min_edges;        /* Boruvka's filter split runs from this many live edges (default 2^20) in
                                      calls of at least twice as many skeleton slots (2n, or nnz of a
-                                     hypergraph); < 0: never */
+                                     hypergraph), in asynchronous ones of up to 2^22 slots only if set
+                                     below 2^20; < 0: never */
 } ce_tuning;
 
 typedef struct {
