@@ -1228,9 +1228,6 @@ size_t stage_boruvka_scratch(int64_t n, int64_t slots) {
   return w.off + 1024;
 }
 
-// The filter split runs when the live edges number at least 2^20 and more
-// than twice the components. A call's tuning (ce_tuning.split_min_edges,
-// CE_SPLIT_MIN_EDGES) overrides the 2^20 or turns the split off.
 // Slots the host enqueues after the first round: in every round the
 // components that still have live edges at least halve, so bits(n) + 1 rounds
 // end a run of plain rounds. With one split (a further one is made only where
@@ -1243,9 +1240,11 @@ static int boruvka_rounds(int64_t n, bool split_possible) {
   return split_possible ? 2 * r + 3 : r;
 }
 
-// A call may split if it has at least twice as many skeleton slots as the live
-// edges from which lists are split (of a call's slots about half are live after
-// the first round), unless it is an asynchronous one of up to 2^22 slots under
+// Lists are split from 2^20 live edges on, if they are more than twice the
+// components; a call's tuning (ce_tuning.split_min_edges, CE_SPLIT_MIN_EDGES)
+// overrides the 2^20 or turns the split off. A call may split if it has at least
+// twice as many skeleton slots as that (of a call's slots about half are live
+// after the first round), unless it is an asynchronous one of up to 2^22 slots under
 // the built-in choice: that would enqueue all the slots of the bound, idle or
 // not (1.1e6 and 2e6 records: 2.39 and 2.90 ms, without a split 1.96 and 2.73).
 //
